@@ -58,6 +58,38 @@ __device__ __forceinline__ void swap_halves(float x, float &a, float &b)
     b = __uint_as_float(r[1]);
 }
 
+// One query row the plain way, by a whole wavefront: scores of keys 0 .. t only, one key per lane, in fp32.  The matrix
+// path multiplies the zero probability of a future key with that key's value, which is not a number when the value is
+// infinite or not a number; rows that come out as such are worked again here, from the keys they may see.
+template <int DT>
+__device__ __attribute__((noinline)) void attention_row(const uint16_t *base, uint16_t *out, int ld, int d, int d_head, int t, float scale)
+{
+    const int lane = threadIdx.x & 63;
+    auto score = [&](int j) {
+        const uint16_t *q = base + (size_t)t * ld, *k = base + (size_t)j * ld + d;
+        float s = 0.0f;
+        for (int c = 0; c < d_head; ++c) s += Prec<DT>::a2acc(q[c]) * Prec<DT>::a2acc(k[c]);
+        return s * scale;
+    };
+    float mx = -INFINITY;
+    for (int j = lane; j <= t; j += 64) mx = __builtin_fmaxf(mx, score(j));
+    for (int o = 32; o > 0; o >>= 1) mx = __builtin_fmaxf(mx, __shfl_xor(mx, o, 64));
+    float sum = 0.0f, a0 = 0.0f, a1 = 0.0f;                        // channels lane, lane + 64
+    for (int j0 = 0; j0 <= t; j0 += 64) {
+        const float p = j0 + lane <= t ? __expf(score(j0 + lane) - mx) : 0.0f;
+        sum += p;
+        for (int i = 0; i < 64 && j0 + i <= t; ++i) {
+            const float pi = __shfl(p, i, 64);
+            const uint16_t *v = base + (size_t)(j0 + i) * ld + 2 * d;
+            if (lane < d_head) a0 += pi * Prec<DT>::a2acc(v[lane]);
+            if (lane + 64 < d_head) a1 += pi * Prec<DT>::a2acc(v[lane + 64]);
+        }
+    }
+    sum = wave_sum(sum);
+    if (lane < d_head) out[lane] = Prec<DT>::acc2a(a0 / sum);
+    if (lane + 64 < d_head) out[lane + 64] = Prec<DT>::acc2a(a1 / sum);
+}
+
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // native vector: stays in registers across the loop
 
@@ -65,17 +97,29 @@ template <int DT, int DH>
 __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(const uint16_t *__restrict__ qkv, uint16_t *__restrict__ out, int seq,
                                                         int n_heads, int n_seq)
 {
-    constexpr int CH = DH / 8;            // 16-byte chunks per K / V row
-    constexpr int KS = DH / 16, CT = DH / 32;   // contraction steps of K Q^T, channel tiles of O^T
+    constexpr int KS = DH / 16, CT = (DH + 31) / 32;   // contraction steps of K Q^T, channel tiles of O^T
+    constexpr int CHD = DH / 8;           // 16-byte chunks per K / V row in memory
+    // 16-byte chunks per K / V row in LDS: whole channel tiles, so that the row pitch is 128, 192 or 256 bytes.  The
+    // chunks past a row's end hold its chunk two (of four) places before over again: the last channel tile of O^T then
+    // multiplies finite data, and what comes out in the channels past DH is not stored.
+    constexpr int CH = 4 * CT;
     constexpr int TILE = BKV * CH;        // 16-byte chunks per K / V tile
+    // Probabilities of the head sizes that the plain kernel served before this one stay 32-bit quantities: they enter the
+    // P V product as the sum of two 16-bit numbers (p rounded, and what the rounding left), two multiplies instead of
+    // one.  Without the second the error against 64 bits was 2.1e-3 instead of 1.6e-3 (bf16, 2048 keys).
+    constexpr bool SPLIT = DH != 64 && DH != 128;
+    constexpr int KR = KS % 4 == 0 ? 4 : KS;   // depth of the K fragment ring (it divides KS: a fragment's slot is the same in every unit)
     // K and V tiles, both [key][channel] as they sit in memory, 16-byte chunks XOR-swizzled per key so that
     // the MFMA fragment reads of K (32 keys, one chunk) and the transposing reads of V (4 keys x 32 bytes
     // per 16 lanes) are free of conflicts on the 64-bank LDS.
     // Three K and two V buffers: tiles arrive (global memory straight into LDS) while earlier ones are multiplied.
     __shared__ u32x4 ks3[3][TILE];
     __shared__ u32x4 vs2[2][TILE];
-    auto kswz = [](int r) { return DH == 128 ? (r & 15) : ((r >> 1) & 7); };
-    auto vswz = [](int r) { return DH == 128 ? ((r & 3) << 2) : (((r >> 1) & 1) << 2); };
+    // (pitch 192 bytes: 4 consecutive rows start on 4 different quarters of the 64 banks, which is all the reads of V
+    // need; K's 16 rows per read are told apart by the row bits above)
+    auto kswz = [](int r) { return CH == 16 ? (r & 15) : CH == 12 ? ((r >> 2) & 3) : ((r >> 1) & 7); };
+    auto vswz = [](int r) { return CH == 16 ? ((r & 3) << 2) : CH == 12 ? 0 : (((r >> 1) & 1) << 2); };
+    auto in_row = [](int chunk) { return chunk < CHD ? chunk : chunk - 2; };
 
     const int d = n_heads * DH, ld = 3 * d;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -105,8 +149,8 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
         const int pidx = 64 * (NLD * wave + i) + lane, r = pidx / CH, slot = pidx % CH;
-        kgo[i] = (uint32_t)(r * ld + d + (slot ^ kswz(r)) * 8) * 2u;
-        vgo[i] = (uint32_t)(r * ld + 2 * d + (slot ^ vswz(r)) * 8) * 2u;
+        kgo[i] = (uint32_t)(r * ld + d + in_row(slot ^ kswz(r)) * 8) * 2u;
+        vgo[i] = (uint32_t)(r * ld + 2 * d + in_row(slot ^ vswz(r)) * 8) * 2u;
     }
     const uint32_t ks_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)&ks3[0][0];
     const uint32_t vs_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)&vs2[0][0];
@@ -126,7 +170,7 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
             for (int i = 0; i < NLD; ++i) {
                 const int pidx = 64 * (NLD * wave + i) + lane, r = pidx / CH, slot = pidx % CH;
                 const int kr = k0 + r < seq ? k0 + r : seq - 1;
-                const int chunk = which ? (slot ^ vswz(r)) : (slot ^ kswz(r));
+                const int chunk = in_row(which ? (slot ^ vswz(r)) : (slot ^ kswz(r)));
                 dma16(gbase0, (uint32_t)(kr * ld + (which ? 2 * d : d) + chunk * 8) * 2u, dst + i * 1024u);
             }
         }
@@ -163,7 +207,7 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
     //               keys done in phase A, then the rest)     |  maximum (and causal mask) of S(s+1)
     // A vector instruction issued right after a matrix instruction of the same wave runs beside it, so a step
     // costs about its 16 matrix instructions when the vector work (4 to 5 instructions per slot) fits under
-    // them.  K fragments run through a ring of four that is refilled as it drains and runs on into the next unit;
+    // them.  K fragments run through a ring that is refilled as it drains and runs on into the next unit;
     // V^T fragments are read one 16-key step ahead.  The sched_barriers pin the order written here.
     //
     // Tiles in LDS: K of tiles T, T+1 and the arriving T+2 (the pipeline reads K one unit ahead of V), V of tiles
@@ -182,9 +226,10 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
     };
 
     f32x16 S[2];                                     // raw scores: S[s & 1] of unit s, the other of unit s + 1
-    u32x4 kf[4];                                     // K fragment ring
+    u32x4 kf[KR];                                    // K fragment ring
     v4i16 vf[CT][2];                                 // V^T fragments of one 16-key step
     uint4 pf[2];                                     // probabilities of the unit's two 16-key steps, packed
+    uint4 pl[SPLIT ? 2 : 1];                         // what rounding left of them
     float tmax;                                      // this lane's maximum over S of the unit about to be exponentiated
     auto k_frag = [&](int buf, int half, int f) { return ks3[buf][half * 32 * CH + koff[f]]; };
     auto unit_max = [&](const f32x16 &x) {
@@ -209,10 +254,10 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
                 const f32x16 zero = {};
                 dst = mfma32<DT>(__builtin_bit_cast(uint4, kf[0]), qf[0], zero);
             } else {
-                dst = mfma32<DT>(__builtin_bit_cast(uint4, kf[i % 4]), qf[i], dst);
+                dst = mfma32<DT>(__builtin_bit_cast(uint4, kf[i % KR]), qf[i], dst);
             }
             __builtin_amdgcn_sched_barrier(0);       // the refill goes out after the multiply that frees its slot
-            kf[i % 4] = i + 4 < KS ? k_frag(buf, half, i + 4) : k_frag(nbuf, nhalf, i + 4 - KS);
+            kf[i % KR] = i + KR < KS ? k_frag(buf, half, i + KR) : k_frag(nbuf, nhalf, i + KR - KS);
             between(i);
         }
     };
@@ -251,12 +296,16 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
         };
         auto cvt = [&](int e) {                      // after elements e - 1 and e (e odd) are done
             const uint32_t w = pack2<DT>(Sc[e - 1], Sc[e]);
-            uint4 &dst = pf[e >> 3];
             const int r = (e & 7) >> 1;
-            if (r == 0) dst.x = w;
-            else if (r == 1) dst.y = w;
-            else if (r == 2) dst.z = w;
-            else dst.w = w;
+            auto put = [r](uint4 &dst, uint32_t v) {
+                if (r == 0) dst.x = v;
+                else if (r == 1) dst.y = v;
+                else if (r == 2) dst.z = v;
+                else dst.w = v;
+            };
+            put(pf[e >> 3], w);
+            if constexpr (SPLIT)
+                put(pl[e >> 3], pack2<DT>(Sc[e - 1] - Prec<DT>::a2acc((uint16_t)(w & 0xffffu)), Sc[e] - Prec<DT>::a2acc((uint16_t)(w >> 16))));
         };
         __builtin_amdgcn_sched_barrier(0);
         // phase A.  K of unit s + 1: H = 0: tile T, second half; H = 1: tile T + 1, first half.  Unit s + 2 is
@@ -267,15 +316,15 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
                 vf[i][1] = vt_frag(vs2[(s >> 1) & 1], 32 * H + 8, i);
             }
             __builtin_amdgcn_sched_barrier(0);
-            constexpr int PER = 8 / KS;              // elements of each 16-key step per slot
+            // a KS-th of the elements of each 16-key step per slot
 #pragma unroll
-            for (int e = i * PER; e < (i + 1) * PER; ++e) {
+            for (int e = 8 * i / KS; e < 8 * (i + 1) / KS; ++e) {
                 pre(e);
                 ex(e);
                 if (e & 1) cvt(e);
             }
 #pragma unroll
-            for (int e = 8 + i * PER; e < 8 + (i + 1) * PER; ++e) pre(e);
+            for (int e = 8 + 8 * i / KS; e < 8 + 8 * (i + 1) / KS; ++e) pre(e);
             __builtin_amdgcn_sched_barrier(0);
         });
         // phase B
@@ -284,15 +333,15 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
             const int kstep = j / CT, c = j % CT;
             const uint2 lo2 = __builtin_bit_cast(uint2, vf[c][0]), hi2 = __builtin_bit_cast(uint2, vf[c][1]);
             oacc[c] = mfma32<DT>(uint4{lo2.x, lo2.y, hi2.x, hi2.y}, pf[kstep], oacc[c]);
+            if constexpr (SPLIT) oacc[c] = mfma32<DT>(uint4{lo2.x, lo2.y, hi2.x, hi2.y}, pl[kstep], oacc[c]);
             if (kstep == 0) {                        // the slot's fragments are in the matrix pipe: read the next step's
                 vf[c][0] = vt_frag(vs2[(s >> 1) & 1], 32 * H + 16, c);
                 vf[c][1] = vt_frag(vs2[(s >> 1) & 1], 32 * H + 24, c);
             }
             __builtin_amdgcn_sched_barrier(0);
             if (kstep == 0) {
-                constexpr int PER = 8 / CT;
 #pragma unroll
-                for (int e = 8 + c * PER; e < 8 + (c + 1) * PER; ++e) {
+                for (int e = 8 + 8 * c / CT; e < 8 + 8 * (c + 1) / CT; ++e) {
                     ex(e);
                     if (e & 1) cvt(e);
                 }
@@ -365,7 +414,7 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
 
         // prologue: scores of unit 0, nothing to overlap them with
     #pragma unroll
-        for (int r = 0; r < 4; ++r) kf[r] = k_frag(0, 0, r);
+        for (int r = 0; r < KR; ++r) kf[r] = k_frag(0, 0, r);
         qk_unit(S[0], 0, 0, 0, 1, [](int) { __builtin_amdgcn_sched_barrier(0); });
         if (u_last == 0) causal_mask(S[0], 0);
         tmax = unit_max(S[0]);
@@ -382,6 +431,19 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
                 sync_tile(T + 1);
             }
         }
+        auto store_row = [&](float inv) {
+            uint16_t *o = out + ((size_t)sq * seq + qrow) * d + head * DH;
+#pragma unroll
+            for (int c = 0; c < CT; ++c)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    if (c * 32 + 8 * g >= DH) continue;          // the padding of the last channel tile
+                    uint2 v;
+                    v.x = pack2<DT>(oacc[c][4 * g] * inv, oacc[c][4 * g + 1] * inv);
+                    v.y = pack2<DT>(oacc[c][4 * g + 2] * inv, oacc[c][4 * g + 3] * inv);
+                    *(uint2 *)(o + c * 32 + 8 * g + 4 * fh) = v;
+                }
+        };
         float l_run;
         {
             float ha, hb;
@@ -389,32 +451,49 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
             l_run = ha + hb;
         }
 
-        if (qrow < seq) {
-            const float inv = 1.0f / l_run;
-            uint16_t *o = out + ((size_t)sq * seq + qrow) * d + head * DH;
-    #pragma unroll
-            for (int c = 0; c < DH / 32; ++c)
-    #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    uint2 v;
-                    v.x = pack2<DT>(oacc[c][4 * g] * inv, oacc[c][4 * g + 1] * inv);
-                    v.y = pack2<DT>(oacc[c][4 * g + 2] * inv, oacc[c][4 * g + 3] * inv);
-                    *(uint2 *)(o + c * 32 + 8 * g + 4 * fh) = v;
+        // Head sizes that ran on the plain kernel before this one took them keep its answer where a later token's value
+        // is not finite (64 and 128 have always multiplied it with zero here): 20 instructions per work item.
+        if constexpr (DH != 64 && DH != 128) {
+            float probe = 0.0f;                                  // x times 0 is 0 for every finite x
+#pragma unroll
+            for (int c = 0; c < CT; ++c)
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    if (c * 32 + 8 * (i >> 2) < DH) probe = __builtin_fmaf(oacc[c][i], 0.0f, probe);
+            uint64_t bad = __builtin_amdgcn_ballot_w64(qrow < seq && !(probe == 0.0f));
+            if (bad != 0) {
+                // the rows' other results go out first: a lane that stored garbage over a recomputed row would race with it
+                uint32_t rows = (uint32_t)bad | (uint32_t)(bad >> 32);
+                const bool mine = (rows >> fr) & 1u;
+                if (qrow < seq && !mine) store_row(1.0f / l_run);
+                while (rows) {
+                    const int r = __builtin_ctz(rows);
+                    rows &= rows - 1;
+                    attention_row<DT>(base, out + ((size_t)sq * seq + q0 + r) * d + head * DH, ld, d, DH, q0 + r, 1.0f / __builtin_sqrtf((float)DH));
                 }
+                continue;
+            }
         }
+        if (qrow < seq) store_row(1.0f / l_run);
     }
 }
-
 }  // namespace
 
-bool mfma_attention_supported(int seq, int d_head) { return seq >= 1 && (d_head == 64 || d_head == 128); }
+// Head sizes from 64 to 128 in steps of the matrix instruction's contraction (16).  Smaller heads (the test models'),
+// odd multiples of 8 and buffers that are not 16-byte aligned take the plain kernel.  Measured at 4 x 2048 tokens, 32
+// heads of 80, bf16: 12.7 ms on the plain kernel (a workgroup per query row, K and V re-read per row), 0.165 ms here
+// (0.130 with probabilities rounded to 16 bits).
+bool mfma_attention_supported(int seq, int n_heads, int d_head)
+{
+    return seq >= 1 && d_head >= 64 && d_head <= 128 && d_head % 16 == 0 && 3LL * seq * n_heads * d_head < 0x7fffffffLL;
+}
 
 hipError_t launch_attention_mfma(const void *qkv, void *out, int dtype, int n_seq, int seq, int n_heads, int d_head,
                                  hipStream_t s)
 {
-    if (!mfma_attention_supported(seq, d_head) || (dtype != kBF16 && dtype != kFP16)) return hipErrorInvalidValue;
+    if (!mfma_attention_supported(seq, n_heads, d_head) || (dtype != kBF16 && dtype != kFP16)) return hipErrorInvalidValue;
     if (n_heads < 1 || n_seq < 1) return hipErrorInvalidValue;
-    // persistent workgroups: as many as are resident at once (2 per CU at d_head 128, 3 at 64; the CU count is
+    // persistent workgroups: as many as are resident at once (2 per CU, 3 at d_head 64; the CU count is
     // rounded down to whole XCDs' worth), fewer when there are fewer work items
     static int n_cu = 0;
     if (n_cu == 0) {
@@ -431,13 +510,16 @@ hipError_t launch_attention_mfma(const void *qkv, void *out, int dtype, int n_se
     const dim3 grid((unsigned)(8 * (items_xcd < slots_max ? items_xcd : slots_max))), block(256);
     const uint16_t *q = (const uint16_t *)qkv;
     uint16_t *o = (uint16_t *)out;
-    if (dtype == kBF16) {
-        if (d_head == 64) attn_mfma_kernel<kBF16, 64><<<grid, block, 0, s>>>(q, o, seq, n_heads, n_seq);
-        else attn_mfma_kernel<kBF16, 128><<<grid, block, 0, s>>>(q, o, seq, n_heads, n_seq);
-    } else {
-        if (d_head == 64) attn_mfma_kernel<kFP16, 64><<<grid, block, 0, s>>>(q, o, seq, n_heads, n_seq);
-        else attn_mfma_kernel<kFP16, 128><<<grid, block, 0, s>>>(q, o, seq, n_heads, n_seq);
+#define ZO_ATTN(DH)                                                                                       \
+    case DH:                                                                                              \
+        if (dtype == kBF16) attn_mfma_kernel<kBF16, DH><<<grid, block, 0, s>>>(q, o, seq, n_heads, n_seq); \
+        else attn_mfma_kernel<kFP16, DH><<<grid, block, 0, s>>>(q, o, seq, n_heads, n_seq);                \
+        break;
+    switch (d_head) {
+    ZO_ATTN(64) ZO_ATTN(80) ZO_ATTN(96) ZO_ATTN(112) ZO_ATTN(128)
+    default: return hipErrorInvalidValue;
     }
+#undef ZO_ATTN
     return hipGetLastError();
 }
 

@@ -86,7 +86,7 @@ hipError_t launch_linear_mfma(const void *x, const void *wt_p, const void *wt_m,
 int mfma_ce_partials(int n_sign, int m_half, int n, int k);
 hipError_t launch_ce_finish(const void *partials, int n_partial, const float *target_logit, const int32_t *target,
                             double *row_loss, int rows, hipStream_t s);
-bool mfma_attention_supported(int seq, int d_head);
+bool mfma_attention_supported(int seq, int n_heads, int d_head);
 hipError_t launch_attention_mfma(const void *qkv, void *out, int dtype, int n_seq, int seq, int n_heads,
                                  int d_head, hipStream_t s);
 

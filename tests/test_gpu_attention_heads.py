@@ -1,0 +1,79 @@
+"""Causal attention on the matrix path for the head sizes between 64 and 128 whose last channel tile is padded or whose
+number of contraction steps is odd (80, 96, 112), against the oracle: edges of the 32-key units, the 64-key tiles and the
+128-row work items; every key weighed exactly once; values that are not finite behind a row's last visible key."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2507_03211_amd as zo_amd
+import zo_inputs as zi
+from oracle import zo_oracle as zo
+from gpu_util import DEV
+
+pytestmark = pytest.mark.gpu
+
+TDT = {zi.BF16: torch.bfloat16, zi.FP16: torch.float16}
+ULP = {zi.BF16: 2.0**-8, zi.FP16: 2.0**-11}
+
+
+def _qkv(n_seq, seq, heads, dh, dtype, seed):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    return torch.randn(n_seq * seq, 3 * heads * dh, device=DEV, generator=g).to(TDT[dtype])
+
+
+def _run(qkv, n_seq, seq, heads, dh, dtype):
+    out = torch.full((n_seq * seq, heads * dh), 7.0, device=DEV, dtype=TDT[dtype])
+    zo_amd.zo_kernel_attention(qkv, out, dtype, n_seq, seq, heads, dh)
+    return out.double().cpu().numpy().reshape(n_seq, seq, heads, dh)
+
+
+def _oracle(qkv, n_seq, seq, heads, dh):
+    h = qkv.double().cpu().numpy().reshape(n_seq, seq, 3, heads * dh)
+    return zo.causal_attention(h[:, :, 0], h[:, :, 1], h[:, :, 2], heads).reshape(n_seq, seq, heads, dh)
+
+
+@pytest.mark.parametrize("dtype", [zi.BF16, zi.FP16])
+@pytest.mark.parametrize("dh", [80, 96, 112])
+@pytest.mark.parametrize("n_seq,seq,heads", [(1, 1, 1), (2, 31, 3), (1, 33, 2), (2, 64, 1), (1, 65, 9), (1, 128, 2), (3, 129, 1), (1, 331, 4)])
+def test_head_sizes_against_the_oracle(dtype, dh, n_seq, seq, heads):
+    qkv = _qkv(n_seq, seq, heads, dh, dtype, seq + dh)
+    got, want = _run(qkv, n_seq, seq, heads, dh, dtype), _oracle(qkv, n_seq, seq, heads, dh)
+    # three roundings (probabilities, values' product, output) on the output's scale, as for heads of 64 and 128
+    assert np.max(np.abs(got - want)) < 3 * ULP[dtype] * (1 + np.abs(want).max())
+
+
+@pytest.mark.parametrize("dh", [80, 96, 112])
+def test_every_key_counts_once(dh):
+    n_seq, seq, heads = 2, 700, 2
+    qkv = torch.zeros(n_seq, seq, 3, heads, dh, device=DEV, dtype=torch.bfloat16)
+    qkv[:, :, 1] = _qkv(n_seq, seq, heads, dh, zi.BF16, 3).reshape(n_seq, seq, 3, heads, dh)[:, :, 1]
+    qkv[:, :, 2] = torch.nn.functional.one_hot(torch.arange(seq, device=DEV) % dh, dh).to(torch.bfloat16)[None, :, None]
+    got = _run(qkv.contiguous(), n_seq, seq, heads, dh, zi.BF16)
+    t, j = np.arange(seq)[:, None], np.arange(dh)[None, :]
+    want = ((t >= j) * ((t - j) // dh + 1) / (t + 1.0))[None, :, None, :]
+    assert np.all(np.abs(got - want) <= ULP[zi.BF16] * want + 1e-30)       # one rounding of the output
+
+
+@pytest.mark.parametrize("dtype", [zi.BF16, zi.FP16])
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan")])
+def test_values_behind_the_last_visible_key_do_not_matter(dtype, value):
+    n_seq, seq, heads, dh, at = 1, 150, 2, 80, 70
+    qkv = _qkv(n_seq, seq, heads, dh, dtype, 11)
+    want = _oracle(qkv, n_seq, seq, heads, dh)
+    bad = qkv.clone().reshape(n_seq, seq, 3, heads, dh)
+    bad[0, at, 1:, 0] = value                       # key and value of one token, head 0
+    got = _run(bad.reshape(qkv.shape).contiguous(), n_seq, seq, heads, dh, dtype)
+    tol = 3 * ULP[dtype] * (1 + np.abs(want).max())
+    assert np.max(np.abs(got[:, :at] - want[:, :at])) < tol and np.max(np.abs(got[:, :, 1] - want[:, :, 1])) < tol
+    assert np.all(np.isnan(got[0, at, 0]))          # the token sees itself
+
+
+def test_unaligned_buffers_still_run():
+    n_seq, seq, heads, dh = 1, 40, 2, 80
+    flat = _qkv(n_seq, seq + 1, heads, dh, zi.BF16, 5).reshape(-1)
+    n = n_seq * seq * 3 * heads * dh
+    qkv = flat[1:1 + n].reshape(n_seq * seq, 3 * heads * dh)               # 2 bytes past a 16-byte boundary
+    want = _oracle(qkv, n_seq, seq, heads, dh)
+    got = _run(qkv, n_seq, seq, heads, dh, zi.BF16)
+    assert np.max(np.abs(got - want)) < 3 * ULP[zi.BF16] * (1 + np.abs(want).max())
