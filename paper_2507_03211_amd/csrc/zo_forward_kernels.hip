@@ -184,6 +184,7 @@ __global__ __launch_bounds__(256) void layernorm_block_kernel(const float *__res
 }
 
 // ------------------------------------------------------------------ plain linear layer
+// (16-bit types whose k is not a multiple of 64, fp32 whose k is not a multiple of 4 or whose buffers are unaligned)
 // y[row, n] = sum_k x[row, k] wt[n, k] (+ bias).  64 x 64 output tile, 16-deep LDS slabs,
 // 4 x 4 outputs per thread.  blockIdx.z selects the sign.
 template <int DT, int EPI>
@@ -242,6 +243,80 @@ __global__ __launch_bounds__(256) void linear_plain_kernel(const void *x, const 
             if constexpr (EPI == 2) ((typename P::R *)y)[row * n + c] += (typename P::R)v;
             if constexpr (EPI == 3) ((Acc *)y)[row * n + c] = v;
         }
+    }
+}
+
+// ------------------------------------------------------------------ fp64 linear layer on the matrix cores
+// The fp32-parameter precision (fp64 activations, fp64 sums).  Its models are tiny, so what a launch costs is the length
+// of its dependent chain, not its work: a workgroup owns one 16 TB x 16 TB output tile, its four waves take every fourth
+// 16-deep piece of the contraction straight from memory into v_mfma_f64_16x16x4 operands (no LDS slabs, no barrier in
+// the loop), and the four partial sums meet once, in LDS, in a fixed order.  In a piece lane group g (16 lanes) holds
+// k = 4 g .. 4 g + 3 of its row, which makes every load 16 or 32 contiguous bytes; the four multiplies of a piece take
+// element 0, 1, 2, 3 of both operands.  Needs k % 4 == 0 and 16-byte aligned x and weights; other shapes stay on the
+// plain kernel.  Both signs of m_half x n x k, plain kernel / here: 64 x 64 x 256 52 / 5.1 us, 64 x 192 x 64 16.6 / 5.0,
+// 256 x 128 x 512 100 / 5.3, 512 x 768 x 768 202 / 33, 8192 x 768 x 768 985 / 430 (45 TFLOP/s; what bounds it there is
+// L2 traffic, 5.3 flop a byte).
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+template <int EPI, int TB>
+__global__ __launch_bounds__(256) void linear_f64_mfma_kernel(const double *__restrict__ x, const float *__restrict__ wt_p,
+                                                              const float *__restrict__ wt_m, const float *__restrict__ b_p,
+                                                              const float *__restrict__ b_m, double *__restrict__ y, int m_half, int n,
+                                                              int k)
+{
+    constexpr int BT = 16 * TB;
+    __shared__ double part[4][BT][BT + 1];
+    const int sign = blockIdx.z;
+    const double *xa = x + (size_t)sign * m_half * k;
+    const float *wt = sign ? wt_m : wt_p;
+    const float *bias = sign ? b_m : b_p;
+    const int m0 = blockIdx.y * BT, n0 = blockIdx.x * BT;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r16 = lane & 15, g = lane >> 4;
+    const double *xr[TB];
+    const float *wr[TB];
+#pragma unroll
+    for (int t = 0; t < TB; ++t) {
+        const int xi = m0 + 16 * t + r16, wi = n0 + 16 * t + r16;          // clamped: never stored
+        xr[t] = xa + (size_t)(xi < m_half ? xi : m_half - 1) * k + 4 * g;
+        wr[t] = wt + (size_t)(wi < n ? wi : n - 1) * k + 4 * g;
+    }
+    f64x4 acc[TB][TB] = {};
+#pragma unroll 4
+    for (int k0 = 16 * wave; k0 < k; k0 += 64) {
+        f64x4 xv[TB], wv[TB];
+        const bool in = k0 + 4 * g < k;                                    // k % 4 == 0: a lane's four are all in or all out
+#pragma unroll
+        for (int t = 0; t < TB; ++t) {
+            const double2 a = in ? *(const double2 *)(xr[t] + k0) : double2{0.0, 0.0};
+            const double2 b = in ? *(const double2 *)(xr[t] + k0 + 2) : double2{0.0, 0.0};
+            const float4 w = in ? *(const float4 *)(wr[t] + k0) : float4{0.0f, 0.0f, 0.0f, 0.0f};
+            xv[t] = f64x4{a.x, a.y, b.x, b.y};
+            wv[t] = f64x4{(double)w.x, (double)w.y, (double)w.z, (double)w.w};
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int i = 0; i < TB; ++i)
+#pragma unroll
+                for (int j = 0; j < TB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(xv[i][e], wv[j][e], acc[i][j], 0, 0, 0);
+    }
+    // element e of a lane's result: row 4 e + lane / 16, column lane % 16 of the 16 x 16 block
+#pragma unroll
+    for (int i = 0; i < TB; ++i)
+#pragma unroll
+        for (int j = 0; j < TB; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) part[wave][16 * i + 4 * e + g][16 * j + r16] = acc[i][j][e];
+    __syncthreads();
+#pragma unroll
+    for (int o = threadIdx.x; o < BT * BT; o += 256) {
+        const int r = o / BT, c = o % BT;
+        if (m0 + r >= m_half || n0 + c >= n) continue;
+        double v = (part[0][r][c] + part[1][r][c]) + (part[2][r][c] + part[3][r][c]);
+        if constexpr (EPI != 3) v += (double)bias[n0 + c];
+        if constexpr (EPI == 1) v = v > 0.0 ? v : 0.0;
+        double *p = y + ((size_t)sign * m_half + m0 + r) * n + n0 + c;
+        if constexpr (EPI == 2) v += *p;
+        *p = v;
     }
 }
 
@@ -421,11 +496,36 @@ static void linear_plain_launch(const void *x, const void *wt_p, const void *wt_
     }
 }
 
+template <int TB>
+static void linear_f64_launch(const void *x, const void *wt_p, const void *wt_m, const void *b_p, const void *b_m, void *y, int n_sign,
+                              int m_half, int n, int k, int epi, hipStream_t s)
+{
+    const dim3 grid((n + 16 * TB - 1) / (16 * TB), (m_half + 16 * TB - 1) / (16 * TB), n_sign), block(256);
+#define ZO_F64(E)                                                                                                       \
+    linear_f64_mfma_kernel<E, TB><<<grid, block, 0, s>>>((const double *)x, (const float *)wt_p, (const float *)wt_m,   \
+                                                         (const float *)b_p, (const float *)b_m, (double *)y, m_half, n, k)
+    switch (epi) {
+    case 0: ZO_F64(0); break;
+    case 1: ZO_F64(1); break;
+    case 2: ZO_F64(2); break;
+    default: ZO_F64(3); break;
+    }
+#undef ZO_F64
+}
+
 hipError_t launch_linear(const void *x, const void *wt_p, const void *wt_m, const void *b_p, const void *b_m, void *y,
                          int dtype, int n_sign, int m_half, int n, int k, int epilogue, bool allow_mfma, hipStream_t s)
 {
     if (allow_mfma && dtype != kFP32 && mfma_linear_supported(m_half, n, k))
         return launch_linear_mfma(x, wt_p, wt_m, b_p, b_m, y, dtype, n_sign, m_half, n, k, epilogue, s);
+    if (dtype == kFP32 && k % 4 == 0 && (uintptr_t)x % 16 == 0 && (uintptr_t)wt_p % 16 == 0 && (uintptr_t)wt_m % 16 == 0) {
+        // 32 x 32 tiles once they give every CU two workgroups, else 16 x 16 (times in us, both tilings): 256 x 384 x 128
+        // (192 tiles) 5.0 / 5.3, 256 x 128 x 512 (64) 5.3 / 11.8, 512 x 768 x 768 (768) 50 / 33, 2048 x 768 x 3072 753 / 417
+        const long tiles32 = (long)n_sign * ((m_half + 31) / 32) * ((n + 31) / 32);
+        if (tiles32 >= 512) linear_f64_launch<2>(x, wt_p, wt_m, b_p, b_m, y, n_sign, m_half, n, k, epilogue, s);
+        else linear_f64_launch<1>(x, wt_p, wt_m, b_p, b_m, y, n_sign, m_half, n, k, epilogue, s);
+        return hipGetLastError();
+    }
     ZO_DISPATCH_DT(dtype, (linear_plain_launch<DT>(x, wt_p, wt_m, b_p, b_m, y, n_sign, m_half, n, k, epilogue, s)));
     return hipGetLastError();
 }
