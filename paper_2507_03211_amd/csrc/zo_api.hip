@@ -403,26 +403,32 @@ int lmhead_ce(zo_model *prof, hipStream_t s, const void *x, const void *e_p, con
         }
         return ZO_OK;
     }
+    // `row` .. of x against `wt_p` (and as many rows of the second sign against `wt_m` when signs == 2)
+    auto chunk = [&](size_t row, int signs, int nr, const void *wt_p, const void *wt_m) {
+        const char *xa = (const char *)x + row * d * ab;
+        const int rows = signs * nr;
+        if (prof) {
+            ZO_PROF(prof, K_LINEAR, 2.0 * rows * (double)vocab * d, launch_linear(xa, wt_p, wt_m, nullptr, nullptr, logits, dtype, signs, nr, vocab, d, 3, use_mfma, s));
+            ZO_PROF(prof, K_CE, (double)rows * vocab * acc_bytes(dtype), launch_ce_rows(logits, target + row, row_loss + row, dtype, rows, vocab, s));
+        } else {
+            ZO_HIP(launch_linear(xa, wt_p, wt_m, nullptr, nullptr, logits, dtype, signs, nr, vocab, d, 3, use_mfma, s));
+            ZO_HIP(launch_ce_rows(logits, target + row, row_loss + row, dtype, rows, vocab, s));
+        }
+        return (int)ZO_OK;
+    };
+    // small models: both signs' logits fit, two launches (of 4.5 us at least) instead of four
+    if (n_sign == 2 && 2 * (long)m_half <= logits_rows) return chunk(0, 2, m_half, e_p, e_m);
     for (int sign = 0; sign < n_sign; ++sign) {
         const void *wt = sign ? e_m : e_p;
-        for (int r0 = 0; r0 < m_half; r0 += logits_rows) {
-            const int nr = m_half - r0 < logits_rows ? m_half - r0 : logits_rows;
-            const size_t row = (size_t)sign * m_half + r0;
-            const char *xa = (const char *)x + row * d * ab;
-            if (prof) {
-                ZO_PROF(prof, K_LINEAR, 2.0 * nr * (double)vocab * d, launch_linear(xa, wt, wt, nullptr, nullptr, logits, dtype, 1, nr, vocab, d, 3, use_mfma, s));
-                ZO_PROF(prof, K_CE, (double)nr * vocab * acc_bytes(dtype), launch_ce_rows(logits, target + row, row_loss + row, dtype, nr, vocab, s));
-            } else {
-                ZO_HIP(launch_linear(xa, wt, wt, nullptr, nullptr, logits, dtype, 1, nr, vocab, d, 3, use_mfma, s));
-                ZO_HIP(launch_ce_rows(logits, target + row, row_loss + row, dtype, nr, vocab, s));
-            }
-        }
+        for (int r0 = 0; r0 < m_half; r0 += logits_rows)
+            ZO_TRY(chunk((size_t)sign * m_half + r0, 1, m_half - r0 < logits_rows ? m_half - r0 : logits_rows, wt, wt));
     }
     return ZO_OK;
 }
 
+// `gs`: both signs' losses are followed by g and the step scalar in the same launch (n_sign == 2)
 int head_and_loss(zo_model *m, int n_sign, int batch, int seq, const void *e_p, const void *e_m, const void *lnf_p,
-                  const void *lnf_m, double *loss_out)
+                  const void *lnf_m, double *loss_out, const GScalar *gs = nullptr)
 {
     const zo_config &c = m->cfg;
     const size_t e = elem_bytes(c.dtype);
@@ -435,7 +441,7 @@ int head_and_loss(zo_model *m, int n_sign, int batch, int seq, const void *e_p, 
                              c.ln_eps, m->compute));
     ZO_TRY(lmhead_ce(m, m->compute, x, e_p, e_m, target, row_loss, m->ws + m->wsp.logits, m->wsp.logits_rows, c.dtype, n_sign, m_half, d,
                      c.vocab, m->use_mfma));
-    ZO_PROF(m, K_OTHER, 8.0 * n_sign * m_half, launch_loss_reduce(row_loss, n_sign, m_half, batch * (seq - 1), loss_out, m->compute));
+    ZO_PROF(m, K_OTHER, 8.0 * n_sign * m_half, launch_loss_reduce(row_loss, n_sign, m_half, batch * (seq - 1), loss_out, gs, m->compute));
     return ZO_OK;
 }
 
@@ -449,7 +455,7 @@ int embed(zo_model *m, const int32_t *tokens, int n_sign, int batch, int seq, co
 }
 
 // Both signs in one batched pass over staged W+-; theta untouched.
-int forward_fused_resident(zo_model *m, const int32_t *tokens, int batch, int seq, uint64_t seed, float eps)
+int forward_fused_resident(zo_model *m, const int32_t *tokens, int batch, int seq, uint64_t seed, float eps, const GScalar *gs)
 {
     const zo_config &c = m->cfg;
     // a pending update (deferred mode) rides on this step's staging passes: every parameter is read here anyway
@@ -462,7 +468,7 @@ int forward_fused_resident(zo_model *m, const int32_t *tokens, int batch, int se
         ZO_TRY(block_forward(m, 2, batch, seq));
     }
     m->pend_n = 0;
-    return head_and_loss(m, 2, batch, seq, ep, em, m->ws + m->wsp.lnf_pm[0], m->ws + m->wsp.lnf_pm[1], m->loss_pm);
+    return head_and_loss(m, 2, batch, seq, ep, em, m->ws + m->wsp.lnf_pm[0], m->ws + m->wsp.lnf_pm[1], m->loss_pm, gs);
 }
 
 // One forward of theta as it stands (literal mode), loss into loss_pm[slot].
@@ -627,10 +633,11 @@ int stream_end(zo_model *m, float lr)
 {
     if (!m->step_open) return fail(ZO_ESTATE, "no streamed step is open");
     if (m->next_block != m->cfg.n_layers) return fail(ZO_ESTATE, "only %d of %d blocks were computed", m->next_block, m->cfg.n_layers);
+    const int pend = m->pend_n >= m->wb_interval ? 0 : m->pend_n;      // 0: this step's uploads took them all and were written back
+    const GScalar gs{m->step_eps, lr, m->g, m->s_pend + pend, m->flags};
     ZO_TRY(head_and_loss(m, 2, m->step_batch, m->step_seq, m->ws + m->wsp.e_pm[0], m->ws + m->wsp.e_pm[1], m->ws + m->wsp.lnf_pm[0],
-                         m->ws + m->wsp.lnf_pm[1], m->loss_pm));
-    if (m->pend_n >= m->wb_interval) m->pend_n = 0;       // this step's uploads took them all and were written back
-    ZO_HIP(launch_g_scalar(m->loss_pm, m->step_eps, lr, m->g, m->s_pend + m->pend_n, m->flags, m->compute));
+                         m->ws + m->wsp.lnf_pm[1], m->loss_pm, &gs));
+    m->pend_n = pend;
     m->pend_seed[m->pend_n++] = m->step_seed;
     m->resident_pending = true;
     m->step_open = false;
@@ -827,8 +834,9 @@ extern "C" int zo_perturb(zo_model *m, uint64_t seed, float scale, int first_ten
     return axpy_range(m, first_tensor, n_tensors, seed, scale, nullptr);
 }
 
-extern "C" int zo_dual_forward(zo_model *m, const int32_t *tokens, int batch, int seq, uint64_t seed, float eps, int mode,
-                               double *dev_loss_pm, double *host_loss_pm)
+// zo_dual_forward, and with `gs` the step's g and scalar right behind the losses
+static int dual_forward(zo_model *m, const int32_t *tokens, int batch, int seq, uint64_t seed, float eps, int mode,
+                        double *dev_loss_pm, double *host_loss_pm, const GScalar *gs)
 {
     if (!m) return fail(ZO_EINVAL, "model is NULL");
     ZO_TRY(check_batch(m, tokens, batch, seq));
@@ -836,7 +844,7 @@ extern "C" int zo_dual_forward(zo_model *m, const int32_t *tokens, int batch, in
     if (!(eps > 0.0f)) return fail(ZO_EINVAL, "eps must be positive");
     if (m->cfg.residency == ZO_STREAMED) return fail(ZO_ESTATE, "a streamed model runs its forward inside zo_step / zo_stream_*");
     if (mode == ZO_MODE_FUSED) {
-        ZO_TRY(forward_fused_resident(m, tokens, batch, seq, seed, eps));
+        ZO_TRY(forward_fused_resident(m, tokens, batch, seq, seed, eps, gs));
     } else {
         ZO_TRY(apply_pending_resident(m));
         ZO_TRY(axpy_range(m, 0, m->n_tensors, seed, eps, nullptr));
@@ -844,6 +852,7 @@ extern "C" int zo_dual_forward(zo_model *m, const int32_t *tokens, int batch, in
         ZO_TRY(axpy_range(m, 0, m->n_tensors, seed, -2.0f * eps, nullptr));
         ZO_TRY(forward_single(m, tokens, batch, seq, 1));
         ZO_TRY(axpy_range(m, 0, m->n_tensors, seed, eps, nullptr));
+        if (gs) ZO_HIP(launch_g_scalar(m->loss_pm, *gs, m->compute));
     }
     if (dev_loss_pm) ZO_HIP(hipMemcpyAsync(dev_loss_pm, m->loss_pm, 2 * sizeof(double), hipMemcpyDeviceToDevice, m->compute));
     if (host_loss_pm) {
@@ -853,6 +862,12 @@ extern "C" int zo_dual_forward(zo_model *m, const int32_t *tokens, int batch, in
     return ZO_OK;
 }
 
+extern "C" int zo_dual_forward(zo_model *m, const int32_t *tokens, int batch, int seq, uint64_t seed, float eps, int mode,
+                               double *dev_loss_pm, double *host_loss_pm)
+{
+    return dual_forward(m, tokens, batch, seq, seed, eps, mode, dev_loss_pm, host_loss_pm, nullptr);
+}
+
 extern "C" int zo_step(zo_model *m, const int32_t *tokens, int batch, int seq, uint64_t seed, float eps, float lr, int mode,
                        double *host_g, double *host_loss_pm)
 {
@@ -860,14 +875,14 @@ extern "C" int zo_step(zo_model *m, const int32_t *tokens, int batch, int seq, u
     ZO_TRY(check_batch(m, tokens, batch, seq));
     if (!(eps > 0.0f)) return fail(ZO_EINVAL, "eps must be positive");
     if (m->cfg.residency == ZO_RESIDENT) {
-        ZO_TRY(zo_dual_forward(m, tokens, batch, seq, seed, eps, mode, nullptr, nullptr));
-        if (m->deferred && mode == ZO_MODE_FUSED) {       // Alg. 2: the update waits for the next pass over theta
-            ZO_HIP(launch_g_scalar(m->loss_pm, eps, lr, m->g, m->s_pend, m->flags, m->compute));
+        const bool defer = m->deferred && mode == ZO_MODE_FUSED;       // Alg. 2: the update waits for the next pass over theta
+        const GScalar gs{eps, lr, m->g, defer ? m->s_pend : m->s_cur, m->flags};
+        ZO_TRY(dual_forward(m, tokens, batch, seq, seed, eps, mode, nullptr, nullptr, &gs));
+        if (defer) {
             m->pend_seed[0] = seed;
             m->pend_round = m->update_rounding;
             m->pend_n = 1;
         } else {
-            ZO_HIP(launch_g_scalar(m->loss_pm, eps, lr, m->g, m->s_cur, m->flags, m->compute));
             ZO_TRY(axpy_range(m, 0, m->n_tensors, seed, 0.0f, m->s_cur, true));
         }
         return read_back(m, host_g, host_loss_pm);
@@ -1160,7 +1175,8 @@ extern "C" int zo_kernel_attention(const void *qkv, void *out, int dtype, int n_
     return ZO_OK;
 }
 
-static int lmhead_rows(int m_half) { return m_half < 2048 ? m_half : 2048; }
+// rows of logits that a scratch region of zo_kernel_lmhead_scratch_bytes holds (lmhead_region_bytes)
+static int lmhead_rows(int m_half) { return m_half < 1024 ? 2 * m_half : 2048; }
 
 static int check_lmhead_args(const void *x, const void *e_plus, const void *e_minus, const int32_t *target, double *row_loss, int dtype,
                              int m_half, int d, int vocab)

@@ -409,28 +409,42 @@ __global__ __launch_bounds__(256) void ce_finish_kernel(const float2 *__restrict
     if (lane == 0) row_loss[r] = tg >= 0 ? (log(s) + (double)mx - (double)target_logit[r]) : (double)__builtin_nan("");
 }
 
-// L+- = sum of the sign's row losses / count, in a fixed order (deterministic).
-__global__ __launch_bounds__(1024) void loss_reduce_kernel(const double *__restrict__ row_loss, int m_half, int count,
-                                                           double *__restrict__ loss_pm)
+// Eq. 1 and the scalar of Eq. 2: g = (l+ - l-) / (2 eps), s = -(lr g) rounded once to fp32.
+__device__ __forceinline__ void g_and_scalar(double lp, double lm, const GScalar &gs)
 {
-    __shared__ double red[16];
-    const int sign = blockIdx.x;
-    const double *r = row_loss + (size_t)sign * m_half;
-    double s = 0;
-    for (int i = threadIdx.x; i < m_half; i += blockDim.x) s += r[i];
-    s = block_sum(s, red);
-    if (threadIdx.x == 0) loss_pm[sign] = s / (double)count;
+    const double g = (lp - lm) / (2.0 * (double)gs.eps);
+    float s = (float)(-((double)gs.lr * g));
+    if (!(g == g) || g - g != 0.0) { s = 0.0f; atomicOr(gs.flags, 1u); }
+    *gs.g = g;
+    *gs.s = s;
 }
 
-// Eq. 1 and the scalar of Eq. 2: g = (l+ - l-) / (2 eps), s = -(lr g) rounded once to fp32.
-__global__ void g_scalar_kernel(const double *loss_pm, float eps, float lr, double *g_out, float *s_out, uint32_t *flags)
+// L+- = sum of the sign's row losses / count, in a fixed order (deterministic); 512 threads per sign.  One workgroup for
+// both signs, so that g can follow in the same launch: a launch of its own costs 4.5 us for one thread's work.
+__global__ __launch_bounds__(1024) void loss_reduce_kernel(const double *__restrict__ row_loss, int n_sign, int m_half, int count,
+                                                           double *__restrict__ loss_pm, bool with_g, GScalar gs)
 {
-    const double g = (loss_pm[0] - loss_pm[1]) / (2.0 * (double)eps);
-    float s = (float)(-((double)lr * g));
-    if (!(g == g) || g - g != 0.0) { s = 0.0f; atomicOr(flags, 1u); }
-    *g_out = g;
-    *s_out = s;
+    __shared__ double red[16];
+    const int sign = threadIdx.x >> 9, t = threadIdx.x & 511;
+    double s = 0;
+    if (sign < n_sign) {
+        const double *r = row_loss + (size_t)sign * m_half;
+        for (int i = t; i < m_half; i += 512) s += r[i];
+    }
+    s = wave_sum(s);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    double l[2] = {0.0, 0.0};
+    for (int k = 0; k < n_sign; ++k) {
+        for (int w = 0; w < 8; ++w) l[k] += red[8 * k + w];
+        l[k] /= (double)count;
+        loss_pm[k] = l[k];
+    }
+    if (with_g) g_and_scalar(l[0], l[1], gs);
 }
+
+__global__ void g_scalar_kernel(const double *loss_pm, GScalar gs) { g_and_scalar(loss_pm[0], loss_pm[1], gs); }
 
 // ------------------------------------------------------------------ launchers
 #define ZO_DISPATCH_DT(dtype, CALL)                  \
@@ -562,16 +576,16 @@ hipError_t launch_ce_finish(const void *partials, int n_partial, const float *ta
 }
 
 hipError_t launch_loss_reduce(const double *row_loss, int n_sign, int m_half, int count_per_sign, double *loss_pm,
-                              hipStream_t s)
+                              const GScalar *gs, hipStream_t s)
 {
-    loss_reduce_kernel<<<dim3(n_sign), dim3(1024), 0, s>>>(row_loss, m_half, count_per_sign, loss_pm);
+    if (n_sign < 1 || n_sign > 2 || (gs && n_sign != 2)) return hipErrorInvalidValue;
+    loss_reduce_kernel<<<dim3(1), dim3(1024), 0, s>>>(row_loss, n_sign, m_half, count_per_sign, loss_pm, gs != nullptr, gs ? *gs : GScalar{});
     return hipGetLastError();
 }
 
-hipError_t launch_g_scalar(const double *loss_pm, float eps, float lr, double *g_out, float *s_out, uint32_t *flags,
-                           hipStream_t s)
+hipError_t launch_g_scalar(const double *loss_pm, const GScalar &gs, hipStream_t s)
 {
-    g_scalar_kernel<<<dim3(1), dim3(1), 0, s>>>(loss_pm, eps, lr, g_out, s_out, flags);
+    g_scalar_kernel<<<dim3(1), dim3(1), 0, s>>>(loss_pm, gs);
     return hipGetLastError();
 }
 
