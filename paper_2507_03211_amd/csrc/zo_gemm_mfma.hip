@@ -11,16 +11,16 @@
 // activation tile the B operand, so a lane's 16 accumulators are 4 runs of 4 consecutive n of
 // one output row, which makes the epilogue 8/16-byte stores.
 //
-// Two tilings:
-//  * 256 x 256 x 64, 4 waves of 128 x 128 (4 x 4 MFMA tiles, 256 accumulator registers), one persistent
-//    workgroup per CU that walks its XCD's share of the tile list.  Operand tiles go from global memory
-//    straight into LDS (global_load_lds_dwordx4, no register staging), whole 128-byte lines per tile row; the
-//    160 KiB of LDS hold three stages of the activation tile and two of the weight tile, and the pipeline
-//    runs on from one tile into the next.  16-byte chunks are XOR-swizzled on the global side so that
-//    fragment reads are free of bank conflicts.  Tiles are numbered so that each XCD (its own L2) owns a
+// Two kernels:
+//  * linear_mfma_pipe_kernel, for K of some slabs and more: one persistent workgroup of 2 x 2 waves per CU that walks its
+//    XCD's share of the tile list, tiles of 256 x 256 down to 128 x 128 with slabs of 64 k.  Operand tiles go from global
+//    memory straight into LDS (global_load_lds_dwordx4, no register staging), whole 128-byte lines per tile row, several
+//    slabs ahead, and the pipeline runs on from one tile into the next.  16-byte chunks are XOR-swizzled on the global
+//    side so that fragment reads are free of bank conflicts.  Tiles are numbered so that each XCD (its own L2) owns a
 //    contiguous band of 8 tile-rows and walks it column by column.  Outputs leave through LDS as whole rows.
-//  * 128 x 128 x 64, 4 waves of 64 x 64, register-staged double buffer: for shapes with fewer than 128
-//    256-tiles, K below three slabs, and ragged small cases.
+//  * linear_mfma_small_kernel, 64 x 64 tiles, one workgroup per tile and two of them per CU: any K, and shapes so small
+//    that what counts is how many CUs take part.
+// pick_tile() at the end chooses between the tile shapes.
 #include "zo_kernels.h"
 #include "zo_types.hip.h"
 
@@ -37,8 +37,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 namespace {
 
-constexpr int BM = 128, BN = 128, BK = 64;
-constexpr int kChunksPerRow = BK / 8;       // 16-byte chunks per tile row
+constexpr int BK = 64;                      // contraction slab; k is a multiple of it
 
 template <int DT> __device__ __forceinline__ f32x16 mfma32(const uint4 &a, const uint4 &b, const f32x16 &c)
 {
@@ -46,38 +45,6 @@ template <int DT> __device__ __forceinline__ f32x16 mfma32(const uint4 &a, const
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
     else
         return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
-}
-
-
-// One lane's run of 4 consecutive n of one output row.
-template <int DT, int EPI>
-__device__ __forceinline__ void epilogue_store(float (&v)[4], const uint16_t *__restrict__ bias, void *__restrict__ y, size_t row,
-                                               int n, int nc)
-{
-    if constexpr (EPI != 3) {
-        const uint2 braw = *(const uint2 *)(bias + nc);
-        const uint16_t bb[4] = {(uint16_t)(braw.x & 0xffff), (uint16_t)(braw.x >> 16), (uint16_t)(braw.y & 0xffff),
-                                (uint16_t)(braw.y >> 16)};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] += Prec<DT>::w2f(bb[e]);
-    }
-    if constexpr (EPI == 0 || EPI == 1) {
-        if constexpr (EPI == 1) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.0f ? v[e] : 0.0f;
-        }
-        uint2 o;
-        o.x = (uint32_t)Prec<DT>::acc2a(v[0]) | ((uint32_t)Prec<DT>::acc2a(v[1]) << 16);
-        o.y = (uint32_t)Prec<DT>::acc2a(v[2]) | ((uint32_t)Prec<DT>::acc2a(v[3]) << 16);
-        *(uint2 *)((uint16_t *)y + row * n + nc) = o;
-    } else if constexpr (EPI == 2) {
-        float4 *p = (float4 *)((float *)y + row * n + nc);
-        float4 h = *p;
-        h.x += v[0]; h.y += v[1]; h.z += v[2]; h.w += v[3];
-        *p = h;
-    } else {
-        *(float4 *)((float *)y + row * n + nc) = float4{v[0], v[1], v[2], v[3]};
-    }
 }
 
 
@@ -147,126 +114,6 @@ __device__ __forceinline__ void ce_partial_row(const f32x16 (&a)[TN], int col0, 
     if (live && fh == 0) *partial_slot = float2{m2, s2};
 }
 
-// LDS tile: [rows][8 chunks] of uint4, chunk c of row r stored at c ^ ((r >> 1) & 7): the LDS has 64
-// four-byte banks, so 16 lanes (16 consecutive rows, one logical chunk) must land on 16 distinct 16-byte
-// positions of a 256-byte window, i.e. on distinct (row parity, slot) pairs.
-__device__ __forceinline__ int lds_slot(int r, int c) { return r * kChunksPerRow + (c ^ ((r >> 1) & 7)); }
-
-template <int DT, int EPI>
-__global__ __launch_bounds__(256) void linear_mfma_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ wt_p,
-                                                          const uint16_t *__restrict__ wt_m, const uint16_t *__restrict__ b_p,
-                                                          const uint16_t *__restrict__ b_m, void *__restrict__ y,
-                                                          int m_half, int n, int k)
-{
-    __shared__ u32x4 xs[2][BM * kChunksPerRow];
-    __shared__ u32x4 ws[2][BN * kChunksPerRow];
-    const int sign = blockIdx.z;
-    const uint16_t *xa = x + (size_t)sign * m_half * k;
-    const uint16_t *wt = sign ? wt_m : wt_p;
-    const uint16_t *bias = sign ? b_m : b_p;
-    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-
-    // global -> LDS assignment: chunk c = tid % 8 of rows tid/8 + 32 i
-    const int lc = tid & 7, lr = tid >> 3;
-    const uint16_t *xg[4], *wg[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        int xr = m0 + lr + 32 * i; xr = xr < m_half ? xr : m_half - 1;     // clamp: masked at the store
-        int wr = n0 + lr + 32 * i; wr = wr < n ? wr : n - 1;
-        xg[i] = xa + (size_t)xr * k + lc * 8;
-        wg[i] = wt + (size_t)wr * k + lc * 8;
-    }
-    u32x4 xreg[4], wreg[4];
-    auto load_global = [&](int k0) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            xreg[i] = *(const u32x4 *)(xg[i] + k0);
-            wreg[i] = *(const u32x4 *)(wg[i] + k0);
-        }
-    };
-    auto store_lds = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            xs[buf][lds_slot(lr + 32 * i, lc)] = xreg[i];
-            ws[buf][lds_slot(lr + 32 * i, lc)] = wreg[i];
-        }
-    };
-
-    f32x16 acc[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.0f;
-
-    const int nk = k / BK;
-    load_global(0);
-    store_lds(0);
-    __syncthreads();
-    const int fr = lane & 31, fh = lane >> 5;     // fragment row, k half
-    for (int kt = 0; kt < nk; ++kt) {
-        const int buf = kt & 1;
-        if (kt + 1 < nk) load_global((kt + 1) * BK);
-#pragma unroll
-        for (int ks = 0; ks < BK / 16; ++ks) {
-            uint4 wf[2], xf[2];
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                wf[t] = __builtin_bit_cast(uint4, ws[buf][lds_slot(wn * 64 + t * 32 + fr, ks * 2 + fh)]);
-                xf[t] = __builtin_bit_cast(uint4, xs[buf][lds_slot(wm * 64 + t * 32 + fr, ks * 2 + fh)]);
-            }
-#pragma unroll
-            for (int tn = 0; tn < 2; ++tn)
-#pragma unroll
-                for (int tm = 0; tm < 2; ++tm) acc[tn][tm] = mfma32<DT>(wf[tn], xf[tm], acc[tn][tm]);
-        }
-        if (kt + 1 < nk) store_lds(buf ^ 1);
-        __syncthreads();
-    }
-
-    // epilogue: lane holds, for each (tn, tm), row m = .. + lane%32 and n = .. + 8 g + 4 (lane/32) + 0..3
-    if constexpr (EPI == 4) {
-        const int n_partial = 2 * (int)gridDim.x;
-#pragma unroll
-        for (int tm = 0; tm < 2; ++tm) {
-            const int mr = m0 + wm * 64 + tm * 32 + fr;
-            const size_t row = (size_t)sign * m_half + (mr < m_half ? mr : m_half - 1);
-            const f32x16 a[2] = {acc[0][tm], acc[1][tm]};
-            ce_partial_row<2>(a, n0 + wn * 64, fh, n, mr < m_half, ((const int32_t *)b_p)[row], (float *)b_m + row,
-                              (float2 *)y + row * n_partial + (blockIdx.x * 2 + wn));
-        }
-        return;
-    }
-#pragma unroll
-    for (int tm = 0; tm < 2; ++tm) {
-        const int mr = m0 + wm * 64 + tm * 32 + fr;
-        if (mr >= m_half) continue;
-        const size_t row = (size_t)sign * m_half + mr;
-#pragma unroll
-        for (int tn = 0; tn < 2; ++tn) {
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int nc = n0 + wn * 64 + tn * 32 + 8 * g + 4 * fh;
-                if (nc >= n) continue;
-                float v[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = acc[tn][tm][4 * g + e];
-                epilogue_store<DT, EPI>(v, bias, y, row, n, nc);
-            }
-        }
-    }
-}
-
-// ------------------------------------------------------------------ 256 x 256 x 64 tiling
-namespace big {
-
-constexpr int BM = 256, BN = 256, BK = 64;
-constexpr int STX = 3, STW = 2;                 // LDS stages of the activation tile / of the weight tile
-constexpr int kTileU4 = BM * (BK / 8);          // uint4 per operand tile (2048 = 32 KiB)
-constexpr int kLdsBytes = (STX + STW) * kTileU4 * 16;   // 160 KiB: all of a CU's LDS
 constexpr int kGroupM = 8;                      // tile-rows per band
 
 // 16 bytes per lane from global memory straight into LDS: lane L lands at lds_off + 16 L.
@@ -284,12 +131,213 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v)
     return ((uint64_t)hi << 32) | lo;
 }
 
-template <int DT, int EPI>
-__global__ __launch_bounds__(256) void linear_mfma256_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ wt_p,
+// Tile `lin` of the list -> sign, first row, tile column.  The list runs through the signs, in each through bands of 8
+// tile-rows, in a band column by column: what an XCD works on at one time shares operand slabs in its L2, and a band
+// never mixes the two signs, which share no weights.
+__device__ __forceinline__ void tile_at(int lin, int tiles_m, int tiles_n, int &sign, int &trow, int &tcol)
+{
+    const int per_sign = tiles_m * tiles_n;
+    sign = lin / per_sign;
+    const int in_sign = lin % per_sign, band = in_sign / (kGroupM * tiles_n), rem = in_sign % (kGroupM * tiles_n);
+    const int band_rows = tiles_m - band * kGroupM < kGroupM ? tiles_m - band * kGroupM : kGroupM;
+    trow = band * kGroupM + rem % band_rows;
+    tcol = rem / band_rows;
+}
+
+// Epilogues 0 - 3 of a wave's 32 TM x 32 TN outputs (rows m0 + wm 32 TM .., columns n0 + wn 32 TN .. of sign `sign`).
+// `stage`: kTileStageBytes<TN> bytes of LDS that are this wave's alone.
+template <int TN> constexpr int kTileStageBytes = (TN & (TN - 1)) ? 2048 * TN + 512 : 2048 * TN;
+template <int DT, int EPI, int TM, int TN>
+__device__ __forceinline__ void store_tile(const f32x16 (&acc)[TN][TM], char *stage, const uint16_t *__restrict__ bias, void *__restrict__ y,
+                                           int sign, int m_half, int n, int m0, int n0, int wm, int wn, int lane)
+{
+    const int fr = lane & 31, fh = lane >> 5;
+    // Output through LDS so that global stores are whole rows: in the MFMA layout a lane holds runs of 4
+    // consecutive columns of ONE row and a wave instruction would touch 32 rows with 16 or 32 bytes each.
+    // A wave stages 2 KiB x TN at a time (32 rows of two-byte columns, or 16 rows of fp32).  No workgroup barrier.  The
+    // run-wise writes and the row-wise 16-byte reads are free of bank conflicts: rows whose length is a power of two
+    // are XOR-swizzled by the row, others have 16 bytes of padding.
+    constexpr bool kOut16 = (EPI == 0 || EPI == 1);              // 2-byte outputs; else fp32
+    constexpr int RP = kOut16 ? 32 : 16;                         // rows per pass
+    constexpr int NPASS = 32 * TM / RP;
+    constexpr int RB = (kOut16 ? 64 : 128) * TN;                 // bytes per row
+    constexpr bool kXor = (TN & (TN - 1)) == 0;
+    constexpr int PITCH = kXor ? RB : RB + 16;
+    constexpr int NRUN = 8 * TN, LPR = RB / 16;                  // runs of 4 columns, 16-byte pieces per row
+    constexpr int NIO = RP * LPR / 64;                           // pieces per lane and pass
+    static_assert(RP * PITCH <= kTileStageBytes<TN>, "a pass fits the wave's staging area");
+    const int ncol0 = n0 + wn * 32 * TN;
+    // Bias: 2-byte outputs take it before the rounding, so per run of the MFMA layout (the same 16 runs
+    // for every row block); fp32 outputs take it after the LDS pass, where a lane always holds the same
+    // 4 columns.
+    // They come through the scalar cache (a wave-uniform address in the constant address space: 16 bytes
+    // = the 8 columns of a run pair, of which the lane half keeps its 4): a vector load here would make
+    // the compiler wait for every outstanding vector memory operation, the next tile's loads included.
+    float bvals[kOut16 ? TN : 1][4][4];
+    if constexpr (kOut16) {
+        typedef const __attribute__((address_space(4))) u32x4 *cptr;
+        const uint64_t bbase = uniform64((uint64_t)(uintptr_t)bias);
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                int c8 = ncol0 + tn * 32 + 8 * g;               // wave-uniform; clamped: columns >= n are never stored
+                c8 = c8 + 8 <= n ? c8 : n - 8;
+                const u32x4 raw = *(cptr)(uintptr_t)(bbase + 2u * (uint32_t)c8);
+                const uint32_t lo = fh ? raw.z : raw.x, hi = fh ? raw.w : raw.y;
+                bvals[tn][g][0] = Prec<DT>::w2f((uint16_t)(lo & 0xffff));
+                bvals[tn][g][1] = Prec<DT>::w2f((uint16_t)(lo >> 16));
+                bvals[tn][g][2] = Prec<DT>::w2f((uint16_t)(hi & 0xffff));
+                bvals[tn][g][3] = Prec<DT>::w2f((uint16_t)(hi >> 16));
+            }
+    }
+    // Residual epilogue: the 8 reads of the running sum that a pass needs are all issued one pass ahead
+    // (a load may not overtake an earlier store that the compiler cannot tell apart from it).  Reading
+    // further ahead (two passes, which is what the registers allow) changes nothing: what the tile waits
+    // for is the bandwidth of all workgroups' read-modify-write bursts arriving together, not one latency.
+    float4 hres[2][EPI == 2 ? NIO : 1];
+    auto load_res = [&](int pass, float4 (&h)[EPI == 2 ? NIO : 1]) {
+#pragma unroll
+        for (int i = 0; i < NIO; ++i) {
+            const int r = (64 * i + lane) / LPR, c = (64 * i + lane) % LPR;
+            const int mr = m0 + wm * 32 * TM + pass * 16 + r, nc = ncol0 + c * 4;
+            h[i] = float4{0.f, 0.f, 0.f, 0.f};
+            if (mr < m_half && nc < n) {
+                // read once, written once: neither the running sum nor any output is worth an L2 line that
+                // an operand slab could keep (non-temporal loads and stores)
+                const f32x4 t = __builtin_nontemporal_load((const f32x4 *)((const float *)y + ((size_t)sign * m_half + mr) * n + nc));
+                h[i] = float4{t.x, t.y, t.z, t.w};
+            }
+        }
+    };
+    // a lane's columns are the same in every piece when a row's pieces divide the wave, else they repeat after 3
+    constexpr int NBV = 64 % LPR == 0 ? 1 : 3;
+    static_assert(NBV == 1 || (192 % LPR == 0), "a lane's columns repeat after three pieces");
+    float bias4[EPI == 2 ? NBV : 1][4] = {};
+    if constexpr (EPI == 2) {
+        load_res(0, hres[0]);
+#pragma unroll
+        for (int v = 0; v < NBV; ++v) {
+            const int nc = ncol0 + (64 * v + lane) % LPR * 4;
+            if (nc < n) {
+                const uint2 braw = *(const uint2 *)(bias + nc);
+                bias4[v][0] = Prec<DT>::w2f((uint16_t)(braw.x & 0xffff));
+                bias4[v][1] = Prec<DT>::w2f((uint16_t)(braw.x >> 16));
+                bias4[v][2] = Prec<DT>::w2f((uint16_t)(braw.y & 0xffff));
+                bias4[v][3] = Prec<DT>::w2f((uint16_t)(braw.y >> 16));
+            }
+        }
+    }
+#pragma unroll
+    for (int pass = 0; pass < NPASS; ++pass) {
+        const int tm = pass * RP / 32;                          // MFMA row block of this pass
+        if constexpr (EPI == 2) {
+            if (pass + 1 < NPASS) load_res(pass + 1, hres[(pass + 1) & 1]);
+        }
+        // fp32: the pass covers rows 16 (pass % 2) .. + 15 of the block, held by the lanes with that fr / 16
+        if (kOut16 || (fr >> 4) == (pass & 1)) {
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    float v[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        v[e] = acc[tn][tm][4 * g + e];
+                        if constexpr (kOut16) v[e] += bvals[tn][g][e];
+                        if constexpr (EPI == 1) v[e] = v[e] > 0.0f ? v[e] : 0.0f;
+                    }
+                    const int run = tn * 8 + 2 * g + fh;         // which run of 4 columns of the row
+                    if constexpr (kOut16) {
+                        // two outputs per conversion instruction (round to nearest even, as the single one does)
+                        auto pack2 = [](float lo, float hi) {
+                            const f32x2 pr = {lo, hi};
+                            if constexpr (DT == kBF16) return __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, bf16x2));
+                            else return __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, f16x2));
+                        };
+                        uint2 o;
+                        o.x = pack2(v[0], v[1]);
+                        o.y = pack2(v[2], v[3]);
+                        *(uint2 *)(stage + fr * PITCH + ((kXor ? run ^ (fr & (NRUN - 1)) : run) << 3)) = o;      // 8-byte slots
+                    } else {
+                        *(float4 *)(stage + (fr & 15) * PITCH + ((kXor ? run ^ (fr & 15 & (NRUN - 1)) : run) << 4)) = float4{v[0], v[1], v[2], v[3]};
+                    }
+                }
+        }
+        const int mbase = m0 + wm * 32 * TM + pass * RP;
+        asm volatile("" ::: "memory");      // the wave's LDS operations execute in order; keep the compiler to it too
+#pragma unroll
+        for (int i = 0; i < NIO; ++i) {
+            const int r = (64 * i + lane) / LPR, c = (64 * i + lane) % LPR, mr = mbase + r;
+            if constexpr (kOut16) {
+                uint4 q = *(const uint4 *)(stage + r * PITCH + ((kXor ? c ^ ((r & (NRUN - 1)) >> 1) : c) << 4));
+                if (kXor && (r & 1)) q = uint4{q.z, q.w, q.x, q.y};          // odd rows hold the two runs swapped
+                const int nc = ncol0 + c * 8;
+                if (mr < m_half && nc < n) __builtin_nontemporal_store(__builtin_bit_cast(u32x4, q), (u32x4 *)((uint16_t *)y + ((size_t)sign * m_half + mr) * n + nc));
+            } else {
+                const float4 q = *(const float4 *)(stage + r * PITCH + ((kXor ? c ^ (r & (NRUN - 1)) : c) << 4));
+                const int nc = ncol0 + c * 4;
+                if (mr < m_half && nc < n) {
+                    float4 *p = (float4 *)((float *)y + ((size_t)sign * m_half + mr) * n + nc);
+                    if constexpr (EPI == 2) {
+                        float4 h = hres[pass & 1][i];
+                        const float *b4 = bias4[i % NBV];
+                        h.x += q.x + b4[0]; h.y += q.y + b4[1]; h.z += q.z + b4[2]; h.w += q.w + b4[3];
+                        __builtin_nontemporal_store(f32x4{h.x, h.y, h.z, h.w}, (f32x4 *)p);
+                    } else {
+                        *p = q;
+                    }
+                }
+            }
+        }
+        asm volatile("" ::: "memory");
+    }
+}
+
+// ------------------------------------------------------------------ pipelined tiles
+// What a tile shape is made of: 2 x 2 waves, each with TM x TN matrix tiles of 32 x 32; loads run A slabs ahead.
+template <int TM_, int TN_, int A_> struct Shape {
+    static constexpr int TM = TM_, TN = TN_, A = A_;
+    static constexpr int BM = 64 * TM, BN = 64 * TN;
+    static constexpr int STX = A + 1, STW = A;                   // LDS stages of the activation tile / of the weight tile
+    static constexpr int XU4 = BM * (BK / 8), WU4 = BN * (BK / 8);   // uint4 per stage
+    // the epilogue passes a wave's rows through its own slice of an activation stage where that is large enough, else
+    // through an area of its own
+    static constexpr bool kOwnArea = kTileStageBytes<TN> > 2048 * TM;
+    static constexpr int lds_bytes(int epi) { return (STX * XU4 + STW * WU4) * 16 + (kOwnArea && epi != 4 ? 4 * kTileStageBytes<TN> : 0); }
+    static constexpr int LX = 2 * TM, LW = 2 * TN, NM = TM * TN, R = TM + TN;   // loads per wave and slab; multiplies and fragments per quarter
+    static_assert(NM % 2 == 0 && R <= NM, "the schedules below");
+    // Fragment reads that have gone out before multiply j of quarter q, for the quarter after it.
+    static constexpr int reads(int q, int j)
+    {
+        const int c = q == 3 ? j : q == 2 ? (NM >= 8 ? 2 : 4) * j : NM == 2 * R ? j / 2 : (R * j + NM - 2) / (NM - 1);
+        return c > R ? R : c;
+    }
+    // Activation loads that have gone out before slot s of the 2 NM + NM / 2 multiplies ahead of the barrier; weight loads
+    // before slot s of the NM / 2 + NM behind it.
+    static constexpr int xloads(int s)
+    {
+        if (TM == 4 && TN == 4) return s <= 0 ? 0 : s <= 6 ? 1 : s <= 12 ? 2 : s <= 16 ? 3 : s <= 22 ? 4 : s <= 28 ? 5 : s <= 36 ? 6 : s <= 38 ? 7 : 8;
+        const int P = 2 * NM + NM / 2, c = (LX * s + P - 1) / P;
+        return c > LX ? LX : c;
+    }
+    static constexpr int wloads(int s)
+    {
+        const int P = NM / 2 + NM, c = (LW * s + P - 1) / P;
+        return c > LW ? LW : c;
+    }
+    // everything goes out exactly once, and the last fragments of a slab ahead of its barrier
+    static_assert(reads(0, 0) == 0 && reads(0, NM) == R && reads(2, 0) == 0 && reads(2, NM / 2) == R && reads(3, 0) == 0 && reads(3, NM) == R, "");
+    static_assert(xloads(0) == 0 && xloads(2 * NM + NM / 2) == LX && wloads(0) == 0 && wloads(NM / 2 + NM) == LW, "");
+};
+
+template <int DT, int EPI, class SH>
+__global__ __launch_bounds__(256) void linear_mfma_pipe_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ wt_p,
                                                              const uint16_t *__restrict__ wt_m, const uint16_t *__restrict__ b_p,
                                                              const uint16_t *__restrict__ b_m, void *__restrict__ y, int m_half,
-                                                             int n, int k, int n_sign, int tiles_m, int tiles_n, int total)
+                                                             int n, int k, int tiles_m, int tiles_n, int total)
 {
+    constexpr int TM = SH::TM, TN = SH::TN, A = SH::A, BM = SH::BM, BN = SH::BN, LX = SH::LX, LW = SH::LW, NM = SH::NM;
     extern __shared__ __attribute__((aligned(16))) uint4 smem[];
     // Persistent workgroups, one per CU: the hardware deals consecutive workgroup ids round-robin to the 8 XCDs,
     // so workgroup b sits on XCD b % 8 and is that XCD's slot b / 8; it walks the XCD's contiguous share of the
@@ -305,129 +353,137 @@ __global__ __launch_bounds__(256) void linear_mfma256_kernel(const uint16_t *__r
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
-    const int rows_total = n_sign * tiles_m;            // tile-rows over both signs
 
     // Load assignment: one wave instruction moves 8 tile rows x 128 bytes (whole cache lines); wave w,
-    // instruction i covers rows (8 w + i) * 8 .. + 7; lane -> (row, 16-byte slot).  The slot holds logical
+    // instruction i of n covers rows (n w + i) * 8 .. + 7; lane -> (row, 16-byte slot).  The slot holds logical
     // chunk slot ^ (row / 2 mod 8): 16 consecutive rows of one logical chunk then sit on 16 distinct
     // 16-byte positions of the 64-bank (256-byte wide) LDS, so fragment reads are conflict-free.
     const int lrow = lane >> 3, lslot = lane & 7;
     struct Tile {
         int sign, m0, n0, tcol;
         uint64_t xbase, wbase;          // first row of the tile in x / in the sign's weights (wave-uniform)
-        uint32_t xg[8], wg[8];          // byte offsets of this lane's 8 + 8 loads from those (clamped at ragged edges)
+        uint32_t xg[LX], wg[LW];        // byte offsets of this lane's loads from those (clamped at ragged edges)
     };
     auto setup = [&](int lin, Tile &t) {
-        const int band = lin / (kGroupM * tiles_n), rem = lin % (kGroupM * tiles_n);
-        const int band_rows = rows_total - band * kGroupM < kGroupM ? rows_total - band * kGroupM : kGroupM;
-        const int trow = band * kGroupM + rem % band_rows;
-        t.tcol = rem / band_rows;
-        t.sign = trow / tiles_m;
-        t.m0 = (trow % tiles_m) * BM;
+        int trow;
+        tile_at(lin, tiles_m, tiles_n, t.sign, trow, t.tcol);
+        t.m0 = trow * BM;
         t.n0 = t.tcol * BN;
         const uint16_t *xa = x + (size_t)t.sign * m_half * k;
         const uint16_t *wt = t.sign ? wt_m : wt_p;
         t.xbase = uniform64((uint64_t)(uintptr_t)(xa + (size_t)t.m0 * k));
         t.wbase = uniform64((uint64_t)(uintptr_t)(wt + (size_t)t.n0 * k));
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int row = (wave * 8 + i) * 8 + lrow;
-            const int chunk = lslot ^ ((row >> 1) & 7);
+        for (int i = 0; i < LX; ++i) {
+            const int row = (wave * LX + i) * 8 + lrow;
             int xr = t.m0 + row; xr = xr < m_half ? xr : m_half - 1;       // clamp: masked at the store
+            t.xg[i] = ((uint32_t)(xr - t.m0) * (uint32_t)k + (lslot ^ ((row >> 1) & 7)) * 8) * 2u;
+        }
+#pragma unroll
+        for (int i = 0; i < LW; ++i) {
+            const int row = (wave * LW + i) * 8 + lrow;
             int wr = t.n0 + row; wr = wr < n ? wr : n - 1;
-            t.xg[i] = ((uint32_t)(xr - t.m0) * (uint32_t)k + chunk * 8) * 2u;
-            t.wg[i] = ((uint32_t)(wr - t.n0) * (uint32_t)k + chunk * 8) * 2u;
+            t.wg[i] = ((uint32_t)(wr - t.n0) * (uint32_t)k + (lslot ^ ((row >> 1) & 7)) * 8) * 2u;
         }
     };
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint4 *)smem;
-    const int nk = k / BK;                              // >= 3 (the launcher sees to it)
-    // Slabs are numbered through all the tiles of this workgroup.  x slab g lives in x stage g % 3, w slab g in w
-    // stage g % 2 (after the three x stages); the stages of slabs g, g+1, g+2 are kept as rotating scalars (uint4
-    // index into smem) instead of being worked out from g every time.
-    constexpr uint32_t kStage = kTileU4;                 // uint4 per stage
-    uint32_t xs0 = 0, xs1 = kStage, xs2 = 2 * kStage;    // x stages of slabs g, g+1, g+2
-    uint32_t ws0 = STX * kStage, ws1 = (STX + 1) * kStage;   // w stages of slabs g (and g+2), g+1
-    auto lds_of = [&](uint32_t stage) { return lds_base + stage * 16u + (uint32_t)wave * 8192u; };   // this wave's slice
+    const int nk = k / BK;                              // > A (the launcher sees to it)
+    // Slabs are numbered through all the tiles of this workgroup.  x slab g lives in x stage g % (A + 1), w slab g in w
+    // stage g % A (after the x stages).  Kept as rotating scalars (uint4 index into smem): the stages of slabs g and
+    // g + 1, and the x stage of slab g - 1, which x slab g + A will go into.
+    constexpr uint32_t kXEnd = SH::STX * SH::XU4, kWEnd = kXEnd + SH::STW * SH::WU4;
+    auto next_x = [](uint32_t st) { st += SH::XU4; return st == kXEnd ? 0u : st; };
+    auto next_w = [](uint32_t st) { st += SH::WU4; return st == kWEnd ? kXEnd : st; };
+    uint32_t xs0 = 0, xs1 = next_x(0), xfree = kXEnd - SH::XU4;
+    uint32_t ws0 = kXEnd, ws1 = next_w(kXEnd);
+    auto lds_x = [&](uint32_t stage) { return lds_base + stage * 16u + (uint32_t)(wave * LX) * 1024u; };   // this wave's slice
+    auto lds_w = [&](uint32_t stage) { return lds_base + stage * 16u + (uint32_t)(wave * LW) * 1024u; };
 
-    f32x16 acc[4][4];
+    f32x16 acc[TN][TM];
     const int fr = lane & 31, fh = lane >> 5, sw = (fr >> 1) & 7;
-    const int xrow = (wm * 128 + fr) * 8, wrow = (wn * 128 + fr) * 8;     // uint4 index of the lane's first rows
-    uint4 wfa[4], xfa[4], wfb[4], xfb[4];                                 // two fragment sets: one multiplies while one loads
+    const int xrow = (wm * 32 * TM + fr) * 8, wrow = (wn * 32 * TN + fr) * 8;     // uint4 index of the lane's first rows
+    uint4 wfa[TN], xfa[TM], wfb[TN], xfb[TM];                             // two fragment sets: one multiplies while one loads
     // One fragment of set (wf, xf) for k-step ks of the slab in stages (xst, wst), in the order the multiplies need them:
-    // wf0, xf0, xf1, xf2, xf3, wf1, wf2, wf3.
-    auto frag1 = [&](uint32_t xst, uint32_t wst, int ks, int idx, uint4 (&wf)[4], uint4 (&xf)[4]) {
+    // wf0, xf0 .. , wf1 ..
+    auto frag1 = [&](uint32_t xst, uint32_t wst, int ks, int idx, uint4 (&wf)[TN], uint4 (&xf)[TM]) {
         const uint4 *xs = smem + xst;
         const uint4 *ws = smem + wst;
         const int slot = (2 * ks + fh) ^ sw;
         if (idx == 0) wf[0] = ws[wrow + slot];
-        else if (idx <= 4) xf[idx - 1] = xs[xrow + (idx - 1) * 256 + slot];
-        else wf[idx - 4] = ws[wrow + (idx - 4) * 256 + slot];
+        else if (idx <= TM) xf[idx - 1] = xs[xrow + (idx - 1) * 256 + slot];
+        else wf[idx - TM] = ws[wrow + (idx - TM) * 256 + slot];
     };
-    // Multiplies j0 .. j1-1 of the 4 x 4 fragment product of set (wf, xf).  Before multiply j:
-    //  * fragments rper (j - rj0) / revery .. + rper - 1 of set (nwf, nxf) are read for k-step nks of the slab in
-    //    stages (nxst, nwst), when that divides;
-    //  * load lfirst + (j - lj0) / levery (lane offsets `offs` from the scalar base `gbase`) goes out into LDS at
-    //    `st`, when that divides, `nload` in all.
+    // Multiplies j0 .. j1-1 of the TM x TN fragment product of set (wf, xf), quarter q of the slab.  Before multiply j go
+    // out: the fragment reads that SH::reads has due there, of set (nwf, nxf) for k-step nks of the slab in stages (nxst,
+    // nwst); the global->LDS load that SH::xloads / SH::wloads has due at slot s0 + j, into LDS at `st`.
     //  `first`: the product starts the accumulators (first quarter of a tile's first slab) instead of adding to them.
-    auto mma_rl = [&](const uint4 (&wf)[4], const uint4 (&xf)[4], int j0, int j1, uint4 (&nwf)[4], uint4 (&nxf)[4], uint32_t nxst,
-                      uint32_t nwst, int nks, int rj0, int revery, int rper, const uint32_t (&offs)[8], uint64_t gbase, uint32_t st,
-                      int lfirst, int nload, int lj0, int levery, bool first = false) {
+    auto mma_rl = [&](const uint4 (&wf)[TN], const uint4 (&xf)[TM], int q, int j0, int j1, uint4 (&nwf)[TN], uint4 (&nxf)[TM],
+                      uint32_t nxst, uint32_t nwst, int nks, const auto &offs, uint64_t gbase, uint32_t st, bool is_x, int s0,
+                      bool first = false) {
 #pragma unroll
         for (int j = j0; j < j1; ++j) {
-            if (j >= rj0 && (j - rj0) % revery == 0 && (j - rj0) / revery * rper < 8) {
+            const int r0 = SH::reads(q, j), r1 = SH::reads(q, j + 1);
+            if (r1 > r0) {
 #pragma unroll
-                for (int r = 0; r < rper; ++r) frag1(nxst, nwst, nks, (j - rj0) / revery * rper + r, nwf, nxf);
+                for (int r = r0; r < r1; ++r) frag1(nxst, nwst, nks, r, nwf, nxf);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if (j >= lj0 && (j - lj0) % levery == 0 && (j - lj0) / levery < nload) {
-                const int q = lfirst + (j - lj0) / levery;
-                gload_lds16(gbase, offs[q], st + q * 1024u);
+            const int l0 = is_x ? SH::xloads(s0 + j) : SH::wloads(s0 + j), l1 = is_x ? SH::xloads(s0 + j + 1) : SH::wloads(s0 + j + 1);
+            if (l1 > l0) {
+#pragma unroll
+                for (int l = l0; l < l1; ++l) gload_lds16(gbase, offs[l], st + l * 1024u);
                 __builtin_amdgcn_sched_barrier(0);
             }
             // back and forth over the activation fragments, so that one operand changes from one multiply to
             // the next, not both (a little less switching on a chip whose clock is set by its power)
-            const int xi = ((j >> 2) & 1) ? 3 - (j & 3) : (j & 3);
+            const int wi = j / TM, xi = (wi & 1) ? TM - 1 - j % TM : j % TM;
             if (first) {
                 f32x16 zero;
 #pragma unroll
                 for (int i = 0; i < 16; ++i) zero[i] = 0.0f;
-                acc[j >> 2][xi] = mfma32<DT>(wf[j >> 2], xf[xi], zero);
+                acc[wi][xi] = mfma32<DT>(wf[wi], xf[xi], zero);
             } else {
-                acc[j >> 2][xi] = mfma32<DT>(wf[j >> 2], xf[xi], acc[j >> 2][xi]);
+                acc[wi][xi] = mfma32<DT>(wf[wi], xf[xi], acc[wi][xi]);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    // Software pipeline.  The 160 KiB of LDS hold three stages of the activation tile and two of the weight
-    // tile, so half of every slab's loads are issued two slab-times ahead and only the other half one ahead:
-    // with a single slab of lookahead for everything the multiplies wait on memory latency.  One wave per SIMD
+    // Software pipeline (in brackets: the 256 x 256 tile).  The LDS holds A + 1 [3] stages of the activation tile and A [2]
+    // of the weight tile, so the activation half of every slab's loads is issued A slab-times ahead and the weight half
+    // nearly so: with a single slab of lookahead for everything the multiplies wait on memory latency.  One wave per SIMD
     // means nothing else hides an instruction that is slow to issue, so neither the global->LDS loads nor the
     // LDS fragment reads come in bursts: each sits alone between two multiplies and issues while the matrix
-    // pipe works on the one before.  The fragments of a quarter slab (16 multiplies) are read during the quarter
+    // pipe works on the one before.  The fragments of a quarter slab (TM TN [16] multiplies) are read during the quarter
     // before it, into the set of registers the quarter before that used.  The barrier sits in the middle of
     // the third quarter, once this wave's last LDS reads of slab g are in registers.
     // sched_barrier(0) pins the order (the compiler would sink each LDS read down to its first use).
     //
-    // One slab: multiplies slab g (fragment set A holds its first quarter), loads slab g + 2 from (xb, wb) with
-    // the lane offsets (xo, wo).  x(g+2) goes into the activation stage that slab g-1 left at the previous barrier:
-    // its 8 loads sit under the 40 multiplies before this slab's barrier; w(g+2) can only follow the barrier: its
-    // 8 loads sit under the 24 multiplies after it.
-    auto slab = [&](uint64_t xb, uint64_t wb, const uint32_t (&xo)[8], const uint32_t (&wo)[8], bool first) {
-        const uint32_t stx = lds_of(xs2), stw = lds_of(ws0);
-        mma_rl(wfa, xfa, 0, 16, wfb, xfb, xs0, ws0, 1, 1, 2, 1, xo, xb, stx, 0, 3, 0, 6, first);
-        mma_rl(wfb, xfb, 0, 16, wfa, xfa, xs0, ws0, 2, 1, 2, 1, xo, xb, stx, 3, 3, 0, 6);
-        // the last fragments of slab g, two reads at a time, so that they have landed when the barrier's wait comes
-        mma_rl(wfa, xfa, 0, 8, wfb, xfb, xs0, ws0, 3, 0, 1, 2, xo, xb, stx, 6, 2, 4, 2);
-        // slab g+1 landed (only x(g+2), the 8 newest loads, may still be out); slab g fully in registers
-        asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");
+    // One slab: multiplies slab g (fragment set A holds its first quarter), loads slab g + A from (xb, wb) with
+    // the lane offsets (xo, wo).  x(g+A) goes into the activation stage that slab g-1 left at the previous barrier:
+    // its loads sit under the multiplies before this slab's barrier; w(g+A) can only follow the barrier: its
+    // loads sit under the multiplies after it.
+    auto slab = [&](uint64_t xb, uint64_t wb, const uint32_t (&xo)[LX], const uint32_t (&wo)[LW], bool first) {
+        const uint32_t stx = lds_x(xfree), stw = lds_w(ws0);
+        constexpr int NB = NM / 2;
+        mma_rl(wfa, xfa, 0, 0, NM, wfb, xfb, xs0, ws0, 1, xo, xb, stx, true, 0, first);
+        mma_rl(wfb, xfb, 1, 0, NM, wfa, xfa, xs0, ws0, 2, xo, xb, stx, true, NM);
+        // the last fragments of slab g, several reads at a time, so that they have landed when the barrier's wait comes
+        mma_rl(wfa, xfa, 2, 0, NB, wfb, xfb, xs0, ws0, 3, xo, xb, stx, true, 2 * NM);
+        // slab g+1 landed (what was loaded after it may still be out); slab g fully in registers
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((A - 1) * LX + (A - 2) * LW) : "memory");
         __builtin_amdgcn_s_barrier();
-        mma_rl(wfa, xfa, 8, 16, wfb, xfb, xs0, ws0, 3, 99, 1, 1, wo, wb, stw, 0, 3, 8, 3);
+        mma_rl(wfa, xfa, 2, NB, NM, wfb, xfb, xs0, ws0, 3, wo, wb, stw, false, -NB);
         // the first fragments of slab g+1 early in the quarter: the loop's back edge waits for all LDS reads
-        mma_rl(wfb, xfb, 0, 16, wfa, xfa, xs1, ws1, 0, 0, 1, 1, wo, wb, stw, 3, 5, 0, 3);
-        // on to the next slab: the stage this one leaves is the one that slab g+3 will be loaded into
-        const uint32_t tx = xs0, tw = ws0;
-        xs0 = xs1; xs1 = xs2; xs2 = tx;
-        ws0 = ws1; ws1 = tw;
+        mma_rl(wfb, xfb, 3, 0, NM, wfa, xfa, xs1, ws1, 0, wo, wb, stw, false, NM - NB);
+        if constexpr (A == 2) {                 // three and two stages: moves alone
+            const uint32_t tx = xfree, tw = ws0;
+            xfree = xs0; xs0 = xs1; xs1 = tx;
+            ws0 = ws1; ws1 = tw;
+        } else {
+            xfree = xs0;
+            xs0 = xs1; xs1 = next_x(xs1);
+            ws0 = ws1; ws1 = next_w(ws1);
+        }
     };
 
     Tile cur, nxt;
@@ -435,19 +491,22 @@ __global__ __launch_bounds__(256) void linear_mfma256_kernel(const uint16_t *__r
     if (lin < 0) return;
     setup(lin, cur);
     int it = 0;                                         // tile number of this workgroup
-    // prologue of the first tile only: slabs 0 and 1, fragments of the first quarter
+    // prologue of the first tile only: slabs 0 .. A - 1, fragments of the first quarter
+    {
+        uint32_t px = xs0, pw = ws0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) gload_lds16(cur.xbase, cur.xg[i], lds_of(xs0) + i * 1024u);
+        for (int g = 0; g < A; ++g) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) gload_lds16(cur.wbase, cur.wg[i], lds_of(ws0) + i * 1024u);
+            for (int i = 0; i < LX; ++i) gload_lds16(cur.xbase + 2u * (uint32_t)(g * BK), cur.xg[i], lds_x(px) + i * 1024u);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) gload_lds16(cur.xbase + 2u * BK, cur.xg[i], lds_of(xs1) + i * 1024u);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) gload_lds16(cur.wbase + 2u * BK, cur.wg[i], lds_of(ws1) + i * 1024u);
-    asm volatile("s_waitcnt vmcnt(16)" ::: "memory");               // slab 0 landed
+            for (int i = 0; i < LW; ++i) gload_lds16(cur.wbase + 2u * (uint32_t)(g * BK), cur.wg[i], lds_w(pw) + i * 1024u);
+            px = next_x(px); pw = next_w(pw);
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((A - 1) * (LX + LW)) : "memory");               // slab 0 landed
     __builtin_amdgcn_s_barrier();
 #pragma unroll
-    for (int idx = 0; idx < 8; ++idx) frag1(xs0, ws0, 0, idx, wfa, xfa);
+    for (int idx = 0; idx < SH::R; ++idx) frag1(xs0, ws0, 0, idx, wfa, xfa);
 
     for (;;) {
         const int lin_next = tile_lin(it + 1);
@@ -455,18 +514,19 @@ __global__ __launch_bounds__(256) void linear_mfma256_kernel(const uint16_t *__r
         if (has_next) {
             setup(lin_next, nxt);
         } else {
-            // no successor: the two slabs loaded ahead are this tile's last two over again, which nothing reads
+            // no successor: the A slabs loaded ahead are this tile's last over again, which nothing reads
             nxt = cur;
-            nxt.xbase += 2u * (uint32_t)((nk - 2) * BK);
-            nxt.wbase += 2u * (uint32_t)((nk - 2) * BK);
+            nxt.xbase += 2u * (uint32_t)((nk - A) * BK);
+            nxt.wbase += 2u * (uint32_t)((nk - A) * BK);
         }
-        // all slabs but the last two load two slabs ahead in this tile; the first one starts the accumulators
-        slab(cur.xbase + 2u * (uint32_t)(2 * BK), cur.wbase + 2u * (uint32_t)(2 * BK), cur.xg, cur.wg, true);
-        for (int kt = 1; kt < nk - 2; ++kt)
-            slab(cur.xbase + 2u * (uint32_t)((kt + 2) * BK), cur.wbase + 2u * (uint32_t)((kt + 2) * BK), cur.xg, cur.wg, false);
-        // the last two load the first two slabs of the next tile
-        slab(nxt.xbase, nxt.wbase, nxt.xg, nxt.wg, false);
-        slab(nxt.xbase + 2u * BK, nxt.wbase + 2u * BK, nxt.xg, nxt.wg, false);
+        // all slabs but the last A load A slabs ahead in this tile; the first one starts the accumulators
+        slab(cur.xbase + 2u * (uint32_t)(A * BK), cur.wbase + 2u * (uint32_t)(A * BK), cur.xg, cur.wg, true);
+        for (int kt = 1; kt < nk - A; ++kt)
+            slab(cur.xbase + 2u * (uint32_t)((kt + A) * BK), cur.wbase + 2u * (uint32_t)((kt + A) * BK), cur.xg, cur.wg, false);
+        // the last A load the first A slabs of the next tile
+#pragma unroll
+        for (int g = 0; g < A; ++g)
+            slab(nxt.xbase + 2u * (uint32_t)(g * BK), nxt.wbase + 2u * (uint32_t)(g * BK), nxt.xg, nxt.wg, false);
 
         // ---- epilogue of tile `cur`
         const int sign = cur.sign, m0 = cur.m0, n0 = cur.n0;
@@ -474,148 +534,21 @@ __global__ __launch_bounds__(256) void linear_mfma256_kernel(const uint16_t *__r
         if constexpr (EPI == 4) {
             const int n_partial = 2 * tiles_n;
 #pragma unroll
-            for (int tm = 0; tm < 4; ++tm) {
-                const int mr = m0 + wm * 128 + tm * 32 + fr;
+            for (int tm = 0; tm < TM; ++tm) {
+                const int mr = m0 + wm * 32 * TM + tm * 32 + fr;
                 const size_t row = (size_t)sign * m_half + (mr < m_half ? mr : m_half - 1);
-                const f32x16 a[4] = {acc[0][tm], acc[1][tm], acc[2][tm], acc[3][tm]};
-                ce_partial_row<4>(a, n0 + wn * 128, fh, n, mr < m_half, ((const int32_t *)b_p)[row], (float *)b_m + row,
+                f32x16 a[TN];
+#pragma unroll
+                for (int t = 0; t < TN; ++t) a[t] = acc[t][tm];
+                ce_partial_row<TN>(a, n0 + wn * 32 * TN, fh, n, mr < m_half, ((const int32_t *)b_p)[row], (float *)b_m + row,
                                   (float2 *)y + row * n_partial + (cur.tcol * 2 + wn));
             }
         } else {
-            // Output through LDS so that global stores are whole rows: in the MFMA layout a lane holds runs of 4
-            // consecutive columns of ONE row and a wave instruction would touch 32 rows with 16 or 32 bytes each.
-            // A wave stages 8 KiB at a time (32 rows x 128 two-byte columns, or 16 rows of fp32) in its own slice
-            // of the activation stage that the tile's last slab has just left: every wave finished reading that
-            // stage before the slab's barrier, and the next loads into the slice are this wave's own, issued after
-            // the epilogue.  No workgroup barrier.  XOR-swizzled so that both the run-wise writes and the row-wise
-            // 16-byte reads are free of bank conflicts.
-            constexpr bool kOut16 = (EPI == 0 || EPI == 1);              // 2-byte outputs; else fp32
-            constexpr int RP = kOut16 ? 32 : 16;                         // rows per pass
-            constexpr int NPASS = 128 / RP;
-            char *stage = (char *)(smem + xs2) + wave * 8192;        // xs2: the stage the tile's last slab has just left
-            const int ncol0 = n0 + wn * 128;
-            // Bias: 2-byte outputs take it before the rounding, so per run of the MFMA layout (the same 16 runs
-            // for every row block); fp32 outputs take it after the LDS pass, where a lane always holds the same
-            // 4 columns.
-            // They come through the scalar cache (a wave-uniform address in the constant address space: 16 bytes
-            // = the 8 columns of a run pair, of which the lane half keeps its 4): a vector load here would make
-            // the compiler wait for every outstanding vector memory operation, the next tile's loads included.
-            float bvals[kOut16 ? 4 : 1][4][4];
-            if constexpr (kOut16) {
-                typedef const __attribute__((address_space(4))) u32x4 *cptr;
-                const uint64_t bbase = uniform64((uint64_t)(uintptr_t)bias);
-#pragma unroll
-                for (int tn = 0; tn < 4; ++tn)
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        int c8 = ncol0 + tn * 32 + 8 * g;               // wave-uniform; clamped: columns >= n are never stored
-                        c8 = c8 + 8 <= n ? c8 : n - 8;
-                        const u32x4 raw = *(cptr)(uintptr_t)(bbase + 2u * (uint32_t)c8);
-                        const uint32_t lo = fh ? raw.z : raw.x, hi = fh ? raw.w : raw.y;
-                        bvals[tn][g][0] = Prec<DT>::w2f((uint16_t)(lo & 0xffff));
-                        bvals[tn][g][1] = Prec<DT>::w2f((uint16_t)(lo >> 16));
-                        bvals[tn][g][2] = Prec<DT>::w2f((uint16_t)(hi & 0xffff));
-                        bvals[tn][g][3] = Prec<DT>::w2f((uint16_t)(hi >> 16));
-                    }
-            }
-            // Residual epilogue: the 8 reads of the running sum that a pass needs are all issued one pass ahead
-            // (a load may not overtake an earlier store that the compiler cannot tell apart from it).  Reading
-            // further ahead (two passes, which is what the registers allow) changes nothing: what the tile waits
-            // for is the bandwidth of all workgroups' read-modify-write bursts arriving together, not one latency.
-            float4 hres[2][8];
-            auto load_res = [&](int pass, float4 (&h)[8]) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const int r = 2 * i + (lane >> 5), c = lane & 31;
-                    const int mr = m0 + wm * 128 + pass * 16 + r, nc = ncol0 + c * 4;
-                    h[i] = float4{0.f, 0.f, 0.f, 0.f};
-                    if (mr < m_half && nc < n) {
-                        // read once, written once: neither the running sum nor any output is worth an L2 line that
-                        // an operand slab could keep (non-temporal loads and stores)
-                        const f32x4 t = __builtin_nontemporal_load((const f32x4 *)((const float *)y + ((size_t)sign * m_half + mr) * n + nc));
-                        h[i] = float4{t.x, t.y, t.z, t.w};
-                    }
-                }
-            };
-            float bias4[4] = {0.f, 0.f, 0.f, 0.f};
-            if constexpr (EPI == 2) {
-                load_res(0, hres[0]);
-                const int nc = ncol0 + (lane & 31) * 4;
-                if (nc < n) {
-                    const uint2 braw = *(const uint2 *)(bias + nc);
-                    bias4[0] = Prec<DT>::w2f((uint16_t)(braw.x & 0xffff));
-                    bias4[1] = Prec<DT>::w2f((uint16_t)(braw.x >> 16));
-                    bias4[2] = Prec<DT>::w2f((uint16_t)(braw.y & 0xffff));
-                    bias4[3] = Prec<DT>::w2f((uint16_t)(braw.y >> 16));
-                }
-            }
-#pragma unroll
-            for (int pass = 0; pass < NPASS; ++pass) {
-                const int tm = pass * RP / 32;                          // MFMA row block of this pass
-                if constexpr (EPI == 2) {
-                    if (pass + 1 < NPASS) load_res(pass + 1, hres[(pass + 1) & 1]);
-                }
-                // fp32: the pass covers rows 16 (pass % 2) .. + 15 of the block, held by the lanes with that fr / 16
-                if (kOut16 || (fr >> 4) == (pass & 1)) {
-#pragma unroll
-                    for (int tn = 0; tn < 4; ++tn)
-#pragma unroll
-                        for (int g = 0; g < 4; ++g) {
-                            float v[4];
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                v[e] = acc[tn][tm][4 * g + e];
-                                if constexpr (kOut16) v[e] += bvals[tn][g][e];
-                                if constexpr (EPI == 1) v[e] = v[e] > 0.0f ? v[e] : 0.0f;
-                            }
-                            const int run = tn * 8 + 2 * g + fh;         // which run of 4 columns (0..31) of the row
-                            if constexpr (kOut16) {
-                                // two outputs per conversion instruction (round to nearest even, as the single one does)
-                                auto pack2 = [](float lo, float hi) {
-                                    const f32x2 pr = {lo, hi};
-                                    if constexpr (DT == kBF16) return __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, bf16x2));
-                                    else return __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, f16x2));
-                                };
-                                uint2 o;
-                                o.x = pack2(v[0], v[1]);
-                                o.y = pack2(v[2], v[3]);
-                                *(uint2 *)(stage + fr * 256 + ((run ^ fr) << 3)) = o;      // 8-byte slots, XOR by the row
-                            } else {
-                                *(float4 *)(stage + (fr & 15) * 512 + ((run ^ (fr & 15)) << 4)) = float4{v[0], v[1], v[2], v[3]};
-                            }
-                        }
-                }
-                const int mbase = m0 + wm * 128 + pass * RP;
-                asm volatile("" ::: "memory");      // the wave's LDS operations execute in order; keep the compiler to it too
-                if constexpr (kOut16) {
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        const int r = 4 * i + (lane >> 4), c16 = lane & 15;           // 16 lanes x 16 bytes = one 256-byte row
-                        uint4 q = *(const uint4 *)(stage + r * 256 + ((c16 ^ (r >> 1)) << 4));
-                        if (r & 1) q = uint4{q.z, q.w, q.x, q.y};                    // odd rows hold the two runs swapped
-                        const int mr = mbase + r, nc = ncol0 + c16 * 8;
-                        if (mr < m_half && nc < n) __builtin_nontemporal_store(__builtin_bit_cast(u32x4, q), (u32x4 *)((uint16_t *)y + ((size_t)sign * m_half + mr) * n + nc));
-                    }
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        const int r = 2 * i + (lane >> 5), c = lane & 31;             // 32 lanes x 16 bytes = one 512-byte row
-                        const float4 q = *(const float4 *)(stage + r * 512 + ((c ^ r) << 4));
-                        const int mr = mbase + r, nc = ncol0 + c * 4;
-                        if (mr < m_half && nc < n) {
-                            float4 *p = (float4 *)((float *)y + ((size_t)sign * m_half + mr) * n + nc);
-                            if constexpr (EPI == 2) {
-                                float4 h = hres[pass & 1][i];
-                                h.x += q.x + bias4[0]; h.y += q.y + bias4[1]; h.z += q.z + bias4[2]; h.w += q.w + bias4[3];
-                                __builtin_nontemporal_store(f32x4{h.x, h.y, h.z, h.w}, (f32x4 *)p);
-                            } else {
-                                *p = q;
-                            }
-                        }
-                    }
-                }
-                asm volatile("" ::: "memory");
-            }
+            // staged in the wave's own slice of the activation stage that the tile's last slab has just left (every wave
+            // finished reading that stage before the slab's barrier, and the next loads into the slice are this wave's
+            // own, issued after the epilogue), or in an area of its own
+            char *stage = SH::kOwnArea ? (char *)(smem + kWEnd) + wave * kTileStageBytes<TN> : (char *)(smem + xfree) + wave * (1024 * LX);
+            store_tile<DT, EPI, TM, TN>(acc, stage, bias, y, sign, m_half, n, m0, n0, wm, wn, lane);
         }
         if (!has_next) break;
         cur = nxt;
@@ -624,82 +557,258 @@ __global__ __launch_bounds__(256) void linear_mfma256_kernel(const uint16_t *__r
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                 // the tail loads land before LDS is released
 }
 
-}  // namespace big
 
-template <int DT>
-void launch_t(const void *x, const void *wt_p, const void *wt_m, const void *b_p, const void *b_m, void *y, int n_sign,
-              int m_half, int n, int k, int epi, hipStream_t s)
+// ------------------------------------------------------------------ small tiles
+// One output tile of 64 x (64 TN) per workgroup of 2 x 2 waves, each with 1 x TN matrix tiles; slabs of 64 k through a ring
+// of ST LDS stages, one barrier per slab, and a second workgroup on the CU to work while this one waits.  For shapes
+// with few tiles: a slab of a larger tile is loaded at about 58 bytes a nanosecond and CU whatever the shape (what the
+// in-order return of loads that partly miss the L2 allows), so the more CUs take part, the sooner the operands are in.
+// m_half 160, n 2560, k 10240: 155 us on 128 x 128 register-staged tiles, 95 on pipelined 128 x 128, 50 here (240 CUs).
+constexpr int kSmallStages = 4;
+template <int TN> constexpr int kSmallLdsBytes = kSmallStages * (64 + 64 * TN) * BK * 2;
+template <int DT, int EPI, int TN>
+__global__ __launch_bounds__(256, 2) void linear_mfma_small_kernel(
+    const uint16_t *__restrict__ x, const uint16_t *__restrict__ wt_p, const uint16_t *__restrict__ wt_m, const uint16_t *__restrict__ b_p,
+    const uint16_t *__restrict__ b_m, void *__restrict__ y, int m_half, int n, int k, int tiles_m, int tiles_n, int total)
 {
-    const dim3 grid((n + BN - 1) / BN, (m_half + BM - 1) / BM, n_sign), block(256);
-#define ZO_L(E)                                                                                                   \
-    linear_mfma_kernel<DT, E><<<grid, block, 0, s>>>((const uint16_t *)x, (const uint16_t *)wt_p, (const uint16_t *)wt_m, \
-                                                     (const uint16_t *)b_p, (const uint16_t *)b_m, y, m_half, n, k)
-    switch (epi) {
-    case 0: ZO_L(0); break;
-    case 1: ZO_L(1); break;
-    case 2: ZO_L(2); break;
-    case 4: ZO_L(4); break;
-    default: ZO_L(3); break;
+    constexpr int ST = kSmallStages, BM = 64, BN = 64 * TN, LX = 2, LW = 2 * TN, L = LX + LW, CPR = BK / 8;
+    constexpr uint32_t kStageBytes = (uint32_t)(BM + BN) * BK * 2;
+    extern __shared__ __attribute__((aligned(16))) uint4 smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    const int fr = lane & 31, fh = lane >> 5;
+
+    // consecutive workgroup ids go round-robin to the 8 XCDs; each takes a contiguous share of the tile list
+    const int per_xcd = (total + 7) / 8;
+    const int lin = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
+    if (((int)blockIdx.x >> 3) >= per_xcd || lin >= total) return;
+    int sign, trow, tcol;
+    tile_at(lin, tiles_m, tiles_n, sign, trow, tcol);
+    const int m0 = trow * BM, n0 = tcol * BN;
+    const uint64_t xbase = uniform64((uint64_t)(uintptr_t)(x + ((size_t)sign * m_half + m0) * k));
+    const uint64_t wbase = uniform64((uint64_t)(uintptr_t)((sign ? wt_m : wt_p) + (size_t)n0 * k));
+
+    // one wave instruction loads 8 tile rows of 128 bytes; chunk c of row r sits at slot c ^ (r / 2 mod 8)
+    auto swz = [](int r) { return (r >> 1) & 7; };
+    uint32_t off[L];                            // LX loads of x, LW of w
+#pragma unroll
+    for (int i = 0; i < L; ++i) {
+        const int row = (i < LX ? wave * LX + i : wave * LW + i - LX) * 8 + (lane >> 3);
+        const int first = i < LX ? m0 : n0, end = i < LX ? m_half : n;
+        int r = first + row; r = r < end ? r : end - 1;                      // clamped: never stored
+        off[i] = ((uint32_t)(r - first) * (uint32_t)k + ((lane & 7) ^ swz(row)) * 8) * 2u;
     }
-#undef ZO_L
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint4 *)smem;
+    auto load_slab = [&](int slab, uint32_t stage) {
+        const uint32_t st = lds_base + stage * kStageBytes, adv = (uint32_t)slab * (BK * 2);
+#pragma unroll
+        for (int i = 0; i < L; ++i)
+            gload_lds16((i < LX ? xbase : wbase) + adv, off[i], st + (i < LX ? (uint32_t)(wave * LX + i) : (uint32_t)(BM / 8 + wave * LW + i - LX)) * 1024u);
+    };
+
+    f32x16 acc[TN][1] = {};
+    const int xrow = (wm * 32 + fr) * CPR, wrow = (BM + wn * 32 * TN + fr) * CPR;
+    auto mult_slab = [&](uint32_t stage) {
+        const uint4 *st = smem + stage * (kStageBytes / 16);
+#pragma unroll
+        for (int ks = 0; ks < BK / 16; ++ks) {
+            const int slot = (2 * ks + fh) ^ swz(fr);
+            uint4 wf[TN];
+            const uint4 xf = st[xrow + slot];
+#pragma unroll
+            for (int t = 0; t < TN; ++t) wf[t] = st[wrow + t * 32 * CPR + slot];
+#pragma unroll
+            for (int t = 0; t < TN; ++t) acc[t][0] = mfma32<DT>(wf[t], xf, acc[t][0]);
+        }
+    };
+    const int nk = k / BK;
+#pragma unroll
+    for (int s = 0; s < ST - 1; ++s)
+        if (s < nk) load_slab(s, s);
+    uint32_t rd = 0, wr = ST - 1;
+    int kt = 0;
+    for (; kt < nk - (ST - 2); ++kt) {
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((ST - 2) * L) : "memory");   // slab kt landed (this wave's part)
+        __builtin_amdgcn_s_barrier();
+        if (kt + ST - 1 < nk) load_slab(kt + ST - 1, wr);
+        mult_slab(rd);
+        rd = rd + 1 == ST ? 0 : rd + 1;
+        wr = wr + 1 == ST ? 0 : wr + 1;
+    }
+    for (; kt < nk; ++kt) {
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        mult_slab(rd);
+        rd = rd + 1 == ST ? 0 : rd + 1;
+    }
+
+    // ---- epilogue
+    if constexpr (EPI == 4) {
+        const int n_partial = 2 * tiles_n, mr = m0 + wm * 32 + fr;
+        const size_t row = (size_t)sign * m_half + (mr < m_half ? mr : m_half - 1);
+        f32x16 a[TN];
+#pragma unroll
+        for (int t = 0; t < TN; ++t) a[t] = acc[t][0];
+        ce_partial_row<TN>(a, n0 + wn * 32 * TN, fh, n, mr < m_half, ((const int32_t *)b_p)[row], (float *)b_m + row,
+                           (float2 *)y + row * n_partial + (tcol * 2 + wn));
+    } else {
+        static_assert(4 * kTileStageBytes<TN> <= ST * (int)kStageBytes, "the staging areas fit the ring");
+        __syncthreads();                                          // every wave is done with the ring
+        store_tile<DT, EPI, 1, TN>(acc, (char *)smem + wave * kTileStageBytes<TN>, sign ? b_m : b_p, y, sign, m_half, n, m0, n0, wm, wn, lane);
+    }
 }
 
-template <int DT>
-hipError_t launch_big_t(const void *x, const void *wt_p, const void *wt_m, const void *b_p, const void *b_m, void *y, int n_sign,
-                        int m_half, int n, int k, int epi, hipStream_t s)
+// ------------------------------------------------------------------ launchers
+// CUs of the current device, rounded down to whole XCDs' worth; 0 when the runtime does not say
+int cu_count()
 {
-    const int tiles_m = (m_half + big::BM - 1) / big::BM, tiles_n = (n + big::BN - 1) / big::BN;
-    const int total = n_sign * tiles_m * tiles_n;
-    // persistent workgroups: one per CU (the 160 KiB of LDS allow no second one), a multiple of the 8 XCDs
     static int n_cu = 0;
     if (n_cu == 0) {
         int dev = 0, v = 0;
-        hipError_t e = hipGetDevice(&dev);
-        if (e == hipSuccess) e = hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e != hipSuccess) return e;
+        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
         n_cu = v >= 8 ? v / 8 * 8 : 8;
     }
+    return n_cu;
+}
+
+struct Args {
+    const void *x, *wt_p, *wt_m, *b_p, *b_m;
+    void *y;
+    int n_sign, m_half, n, k;
+    hipStream_t s;
+};
+
+template <int DT, int EPI, class SH> hipError_t launch_pipe(const Args &a)
+{
+    const int tiles_m = (a.m_half + SH::BM - 1) / SH::BM, tiles_n = (a.n + SH::BN - 1) / SH::BN;
+    const int total = a.n_sign * tiles_m * tiles_n, n_cu = cu_count();
+    if (n_cu == 0 || a.k / BK <= SH::A) return hipErrorInvalidValue;
+    // persistent workgroups: one per CU (their LDS allows no second one), a multiple of the 8 XCDs
     const int want = (total + 7) / 8 * 8;
     const dim3 grid(want < n_cu ? want : n_cu), block(256);
-#define ZO_B(E)                                                                                                                  \
-    {                                                                                                                            \
-        auto kern = big::linear_mfma256_kernel<DT, E>;                                                                           \
-        static bool attr_set = false;                                                                                            \
-        if (!attr_set) {                                                                                                         \
-            hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, big::kLdsBytes);  \
-            if (e != hipSuccess) return e;                                                                                       \
-            attr_set = true;                                                                                                     \
-        }                                                                                                                        \
-        kern<<<grid, block, big::kLdsBytes, s>>>((const uint16_t *)x, (const uint16_t *)wt_p, (const uint16_t *)wt_m,            \
-                                                 (const uint16_t *)b_p, (const uint16_t *)b_m, y, m_half, n, k, n_sign, tiles_m,  \
-                                                 tiles_n, total);                                                                         \
+    auto kern = linear_mfma_pipe_kernel<DT, EPI, SH>;
+    static bool attr_set = false;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, SH::lds_bytes(EPI));
+        if (e != hipSuccess) return e;
+        attr_set = true;
     }
-    switch (epi) {
-    case 0: ZO_B(0) break;
-    case 1: ZO_B(1) break;
-    case 2: ZO_B(2) break;
-    case 4: ZO_B(4) break;
-    default: ZO_B(3) break;
-    }
-#undef ZO_B
+    kern<<<grid, block, SH::lds_bytes(EPI), a.s>>>((const uint16_t *)a.x, (const uint16_t *)a.wt_p, (const uint16_t *)a.wt_m, (const uint16_t *)a.b_p,
+                                                   (const uint16_t *)a.b_m, a.y, a.m_half, a.n, a.k, tiles_m, tiles_n, total);
     return hipGetLastError();
 }
 
-// The big tiling pays once its tiles occupy about half of the 256 CUs: measured at 192 tiles it is 1.5 times as
-// fast as the small tiling although a quarter of the CUs idle.
-bool use_big(int n_sign, int m_half, int n, int k)
+template <int DT, int EPI, int TN> hipError_t launch_small(const Args &a)
 {
-    if (k % big::BK || k < 3 * big::BK) return false;      // the pipeline runs two slabs ahead, and the first slab of a tile is special
-    const long tiles = (long)n_sign * ((m_half + big::BM - 1) / big::BM) * ((n + big::BN - 1) / big::BN);
+    const int tiles_m = (a.m_half + 63) / 64, tiles_n = (a.n + 64 * TN - 1) / (64 * TN), total = a.n_sign * tiles_m * tiles_n;
+    auto kern = linear_mfma_small_kernel<DT, EPI, TN>;
+    static bool attr_set = false;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kSmallLdsBytes<TN>);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    kern<<<dim3((total + 7) / 8 * 8), dim3(256), kSmallLdsBytes<TN>, a.s>>>((const uint16_t *)a.x, (const uint16_t *)a.wt_p, (const uint16_t *)a.wt_m,
+                                                                            (const uint16_t *)a.b_p, (const uint16_t *)a.b_m, a.y, a.m_half, a.n, a.k,
+                                                                            tiles_m, tiles_n, total);
+    return hipGetLastError();
+}
+
+enum Tile { T256x256, T256x192, T256x128, T192x128, T128x128, T64x64, kTiles };
+template <int DT, int EPI> hipError_t launch_tile(Tile t, const Args &a)
+{
+    switch (t) {
+    case T256x256: return launch_pipe<DT, EPI, Shape<4, 4, 2>>(a);
+    case T256x192: return launch_pipe<DT, EPI, Shape<4, 3, 2>>(a);
+    case T256x128: return launch_pipe<DT, EPI, Shape<4, 2, 2>>(a);
+    case T192x128: return launch_pipe<DT, EPI, Shape<3, 2, 3>>(a);
+    case T128x128: return launch_pipe<DT, EPI, Shape<2, 2, 4>>(a);
+    default: return launch_small<DT, EPI, 1>(a);
+    }
+}
+
+// The tile shape with the least estimated time in us: start + rounds (slabs slab + epilogue), where a round of tiles that
+// fills more than half of the CUs also pays slabs busy b, b = 0 .. 1 from half full to full (a full chip clocks lower and
+// shares the fabric), and fp32 outputs are paid for by how full the round is (their bursts share the memory).
+// Constants: least squares over 90 shapes (m_half 96 .. 8192, n and k 512 .. 19200) timed with every tile shape; the
+// estimates are within 5 - 8 % (rms), and the shape they pick is on average 0.25 % slower than the best one of each.
+// The 256 x 256 tile gets 3 % credit: near a tie it is the one that long contractions lose least with.  In us, picked
+// here / the former choice between 256 x 256 and a register-staged 128 x 128 kernel, m_half x n x k: 536 x 2304 x 768
+// 9.5 / 17.1, 692 x 5120 x 5120 80 / 114, 1028 x 1024 x 4096 30 / 53, 391 x 704 x 2816 13 / 39, 8192 x 2304 x 768 61 / 70;
+// 1.52 times as fast in the geometric mean of the 90, 0.99 in the worst case.
+Tile pick_tile(int n_sign, int m_half, int n, int k, int epi)
+{
+    static const struct { int bm, bn, min_slabs; float start, slab, busy, out16, out32; } kCost[kTiles] = {
+        {256, 256, 3, 4.9f, 1.00f, 0.52f, 3.5f, 31.2f}, {256, 192, 3, 3.6f, 0.79f, 0.38f, 3.1f, 25.6f},
+        {256, 128, 3, 3.6f, 0.59f, 0.28f, 1.6f, 16.4f}, {192, 128, 4, 4.1f, 0.49f, 0.21f, 0.9f, 10.0f},
+        {128, 128, 5, 4.1f, 0.38f, 0.16f, 0.3f, 5.3f},  {64, 64, 1, 2.6f, 0.21f, 0.41f, 0.4f, 1.7f}};
+    const float n_cu = cu_count() ? (float)cu_count() : 256.0f, slabs = (float)(k / BK);
+    Tile best = kTiles;
+    float best_us = 0.0f;
+    for (int t = 0; t < kTiles; ++t) {
+        const auto &c = kCost[t];
+        if (k / BK < c.min_slabs) continue;
+        const float tiles = (float)n_sign * (float)((m_half + c.bm - 1) / c.bm) * (float)((n + c.bn - 1) / c.bn);
+        float us;
+        if (t == T64x64) {
+            // two workgroups per CU: `slab` for one alone, `busy` for the two together
+            const float full = __builtin_floorf(tiles / (2 * n_cu)), rest = tiles - 2 * n_cu * full;
+            const float pairs = full + (rest > n_cu ? 1.0f : 0.0f), lone = rest > 0 && rest <= n_cu ? 1.0f : 0.0f;
+            us = c.start + slabs * (pairs * c.busy + lone * c.slab) + (pairs + lone) * (epi >= 2 ? c.out32 : c.out16);
+        } else {
+            const float full = __builtin_floorf(tiles / n_cu), part = tiles / n_cu - full, rounds = full + (part > 0 ? 1.0f : 0.0f);
+            const float b = full + (part > 0.5f ? 2 * part - 1 : 0.0f);
+            const float out = epi >= 2 ? c.out32 * (full + (part > 0 ? (part > 0.3f ? part : 0.3f) : 0.0f)) : c.out16 * rounds;
+            us = c.start + slabs * (rounds * c.slab + b * c.busy) + out;
+        }
+        if (t == T256x256) us *= 0.97f;
+        if (best == kTiles || us < best_us) { best = (Tile)t; best_us = us; }
+    }
+    return best;
+}
+
+// LM head (epilogue 4): strips of 128 columns per (max, sum-exp) pair when tiles 256 columns wide fill half the CUs, else
+// strips of 64.  The callers' scratch is sized for either.
+bool wide_strips(int n_sign, int m_half, int n, int k)
+{
+    if (k < 3 * BK) return false;
+    const long tiles = (long)n_sign * ((m_half + 255) / 256) * ((n + 255) / 256);
     return tiles >= 128;
+}
+
+// Rows of the 256-column tile: 256, or 192 / 128 where few rows would leave a taller tile mostly empty.  A row costs 6 - 8 %
+// more in tiles of 192 (15 % up to 512 rows, where their rounds come out badly) and 9 - 13 % more in tiles of 128 (whose
+// LDS takes a third slab ahead).  In us, tiles of 256 / 192 / 128, vocabulary 50272: 1048 rows a sign, d 2048, 419 / 399 /
+// 428; 700 rows, d 1024, 148 / 159 / 161; 536 rows, d 768, 118 / 98 / 109; 300 rows 92 / 83 / 76; 100 rows 54 / 51 / 46.
+template <int DT> hipError_t launch_ce(const Args &a)
+{
+    if (wide_strips(a.n_sign, a.m_half, a.n, a.k)) {
+        auto padded = [&](int bm) { return (float)((a.m_half + bm - 1) / bm * bm); };
+        const float c256 = padded(256), c192 = (a.m_half > 512 ? 1.08f : 1.15f) * padded(192), c128 = 1.12f * padded(128);
+        if (c128 < c192 && c128 < c256 && a.k / BK > 3) return launch_pipe<DT, 4, Shape<2, 4, 3>>(a);
+        if (c192 < c256) return launch_pipe<DT, 4, Shape<3, 4, 2>>(a);
+        return launch_pipe<DT, 4, Shape<4, 4, 2>>(a);
+    }
+    if (a.k / BK > 4) return launch_pipe<DT, 4, Shape<2, 2, 4>>(a);
+    return launch_small<DT, 4, 2>(a);
+}
+
+template <int DT> hipError_t launch_t(const Args &a, int epi)
+{
+    const Tile t = epi == 4 ? kTiles : pick_tile(a.n_sign, a.m_half, a.n, a.k, epi);
+    switch (epi) {
+    case 0: return launch_tile<DT, 0>(t, a);
+    case 1: return launch_tile<DT, 1>(t, a);
+    case 2: return launch_tile<DT, 2>(t, a);
+    case 3: return launch_tile<DT, 3>(t, a);
+    default: return launch_ce<DT>(a);
+    }
 }
 
 }  // namespace
 
-int mfma_ce_partials(int n_sign, int m_half, int n, int k)
-{
-    return use_big(n_sign, m_half, n, k) ? 2 * ((n + big::BN - 1) / big::BN) : 2 * ((n + BN - 1) / BN);
-}
+int mfma_ce_partials(int n_sign, int m_half, int n, int k) { return wide_strips(n_sign, m_half, n, k) ? 2 * ((n + 255) / 256) : 2 * ((n + 127) / 128); }
 
 bool mfma_linear_supported(int m_half, int n, int k) { return m_half >= 1 && n >= 8 && n % 8 == 0 && k >= BK && k % BK == 0; }
 
@@ -710,13 +819,8 @@ hipError_t launch_linear_mfma(const void *x, const void *wt_p, const void *wt_m,
     // 16-byte pieces everywhere (operand loads, row-wise stores, bias through the scalar cache)
     if ((uintptr_t)x % 16 || (uintptr_t)wt_p % 16 || (uintptr_t)wt_m % 16 || (uintptr_t)y % 16) return hipErrorInvalidValue;
     if (epilogue != 3 && epilogue != 4 && ((uintptr_t)b_p % 16 || (uintptr_t)b_m % 16)) return hipErrorInvalidValue;
-    if (use_big(n_sign, m_half, n, k)) {
-        return dtype == kBF16 ? launch_big_t<kBF16>(x, wt_p, wt_m, b_p, b_m, y, n_sign, m_half, n, k, epilogue, s)
-                              : launch_big_t<kFP16>(x, wt_p, wt_m, b_p, b_m, y, n_sign, m_half, n, k, epilogue, s);
-    }
-    if (dtype == kBF16) launch_t<kBF16>(x, wt_p, wt_m, b_p, b_m, y, n_sign, m_half, n, k, epilogue, s);
-    else launch_t<kFP16>(x, wt_p, wt_m, b_p, b_m, y, n_sign, m_half, n, k, epilogue, s);
-    return hipGetLastError();
+    const Args a{x, wt_p, wt_m, b_p, b_m, y, n_sign, m_half, n, k, s};
+    return dtype == kBF16 ? launch_t<kBF16>(a, epilogue) : launch_t<kFP16>(a, epilogue);
 }
 
 }  // namespace zo

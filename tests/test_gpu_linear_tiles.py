@@ -1,0 +1,84 @@
+"""The sign-batched linear layer over every tile shape its size rule picks (256 x 256, 256 x 192, 256 x 128, 192 x 128,
+128 x 128, 64 x 64): one row past a tile, ragged columns, contractions of one slab and up, each epilogue, both 16-bit types;
+and the LM head over each of its tile heights and strip widths.  Every output element is compared."""
+import pytest
+import torch
+
+import paper_2507_03211_amd as zo_amd
+import zo_inputs as zi
+from gpu_util import DEV
+
+pytestmark = pytest.mark.gpu
+
+TDT = {zi.BF16: torch.bfloat16, zi.FP16: torch.float16}
+ULP = {zi.BF16: 2.0**-8, zi.FP16: 2.0**-11}
+
+# m_half, n, k; the tile that the rule takes on 256 CUs is named for the reader, nothing depends on it
+SHAPES16 = [(3073, 4104, 192), (1537, 4104, 448),       # 256 x 256
+            (769, 5128, 192), (1281, 3080, 192),        # 256 x 192
+            (641, 4104, 192), (1281, 2056, 192),        # 256 x 128
+            (385, 5128, 256), (641, 3080, 256),         # 192 x 128
+            (257, 5128, 320), (641, 1544, 320),         # 128 x 128
+            (1, 8, 64), (65, 72, 128), (257, 520, 192), (100, 1000, 1024)]   # 64 x 64
+SHAPES32 = [(2561, 8200, 1024), (1025, 6152, 1024),     # 256 x 256, 256 x 192
+            (1281, 4104, 1024), (641, 5128, 2048),      # 256 x 128
+            (641, 3080, 768), (1281, 1544, 576),        # 192 x 128
+            (385, 2568, 576), (641, 1544, 448),         # 128 x 128
+            (3, 16, 64), (64, 64, 64), (130, 520, 320)] # 64 x 64
+
+
+def _inputs(m_half, n, k, dtype, seed):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    x = torch.randn(2 * m_half, k, device=DEV, generator=g).to(TDT[dtype])
+    w = [(0.05 * torch.randn(n, k, device=DEV, generator=g)).to(TDT[dtype]) for _ in range(2)]
+    b = [torch.randn(n, device=DEV, generator=g).to(TDT[dtype]) for _ in range(2)]
+    return g, x, w, b
+
+
+@pytest.mark.parametrize("dtype", [zi.BF16, zi.FP16])
+@pytest.mark.parametrize("m_half,n,k,epi", [s + (e,) for i, s in enumerate(SHAPES16) for e in ((0, 1) if i % 2 else (0,))] +
+                         [s + (e,) for i, s in enumerate(SHAPES32) for e in ((2, 3) if i % 2 else (2,))])
+def test_linear_tiles(m_half, n, k, epi, dtype):
+    g, x, w, b = _inputs(m_half, n, k, dtype, m_half + n + k + epi)
+    guard = 64                                  # values behind the result that must not change
+    flat = torch.full((2 * m_half * n + guard,), 3.0, device=DEV, dtype=TDT[dtype] if epi < 2 else torch.float32)
+    y = flat[:2 * m_half * n].view(2 * m_half, n)
+    if epi == 2:
+        y.normal_(generator=g)
+    y0 = y.double()
+    zo_amd.zo_kernel_linear_pm(x, w[0], w[1], b[0], b[1], y, dtype, m_half, n, k, epi)
+    for s in range(2):
+        rows = slice(s * m_half, (s + 1) * m_half)
+        want = x[rows].double() @ w[s].double().t()
+        size = x[rows].double().abs() @ w[s].double().abs().t() + 8.0
+        if epi != 3:
+            want = want + b[s].double()
+        if epi == 1:
+            want = want.clamp(min=0)
+        if epi == 2:
+            want = want + y0[rows]
+        # fp32 sums of k terms (each partial sum rounded by half of 2^-23 of at most `size`, in pieces of 16 or more, so far
+        # below this bound), then one rounding into the 16-bit type
+        bound = size * (k + 4) * 2.0**-24 + (ULP[dtype] * want.abs() if epi < 2 else 0.0)
+        assert bool(((y[rows].double() - want).abs() <= bound).all())
+    assert bool((flat[2 * m_half * n:] == 3.0).all())
+
+
+@pytest.mark.parametrize("dtype", [zi.BF16, zi.FP16])
+@pytest.mark.parametrize("m_half,d,vocab", [(257, 192, 17000), (520, 256, 8456), (100, 192, 17000), (193, 320, 20008),   # strips of 128
+                                            (65, 512, 1000), (3, 64, 520), (130, 128, 2056)])                          # strips of 64
+def test_lmhead_tiles(m_half, d, vocab, dtype):
+    g, x, e, _ = _inputs(m_half, vocab, d, dtype, m_half + d)
+    target = torch.randint(0, vocab, (2 * m_half,), device=DEV, dtype=torch.int32, generator=g)
+    target[::7] = -1
+    target[1] = vocab - 1
+    loss = torch.empty(2 * m_half, device=DEV, dtype=torch.float64)
+    scratch = torch.empty(zo_amd.zo_kernel_lmhead_scratch_bytes(dtype, m_half, vocab), device=DEV, dtype=torch.uint8)
+    zo_amd.zo_kernel_lmhead_ce(x, e[0], e[1], target, loss, scratch, dtype, m_half, d, vocab)
+    for s in range(2):
+        rows = slice(s * m_half, (s + 1) * m_half)
+        logits, tg = x[rows].double() @ e[s].double().t(), target[rows].long()
+        want = torch.logsumexp(logits, 1) - logits.gather(1, tg.clamp(min=0)[:, None])[:, 0]
+        want = torch.where(tg >= 0, want, torch.zeros_like(want))
+        assert float((loss[rows] - want).abs().max()) < 2e-4          # fp32 logits: accumulation order only
