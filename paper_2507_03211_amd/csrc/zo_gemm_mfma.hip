@@ -98,16 +98,18 @@ __device__ __forceinline__ void ce_partial_row(const f32x16 (&a)[TN], int col0, 
     const int rel = tg - col0;
     const bool mine = rel >= 0 && rel < 32 * TN && ((rel >> 2) & 1) == fh;
     const int which = (rel >> 5) * 16 + ((rel >> 3) & 3) * 4 + (rel & 3);
-    float t[NE];
+    if (__builtin_amdgcn_ballot_w64(mine) != 0) {        // of 50272 columns a wave holds 128: one wave in twelve
+        float t[NE];
 #pragma unroll
-    for (int k = 0; k < NE; ++k) t[k] = v[k];
+        for (int k = 0; k < NE; ++k) t[k] = v[k];
 #pragma unroll
-    for (int bit = 0, cnt = NE; cnt > 1; ++bit, cnt >>= 1) {
-        const bool odd = (which >> bit) & 1;
+        for (int bit = 0, cnt = NE; cnt > 1; ++bit, cnt >>= 1) {
+            const bool odd = (which >> bit) & 1;
 #pragma unroll
-        for (int k = 0; k < cnt / 2; ++k) t[k] = odd ? t[2 * k + 1] : t[2 * k];
+            for (int k = 0; k < cnt / 2; ++k) t[k] = odd ? t[2 * k + 1] : t[2 * k];
+        }
+        if (live && mine) *tgt_logit_row = t[0];
     }
-    if (live && mine) *tgt_logit_row = t[0];
     const float mo = __shfl_xor(mx, 32, 64), so = __shfl_xor(sum, 32, 64);
     const float m2 = mx > mo ? mx : mo;
     const float s2 = (mx > -INFINITY ? sum * __expf(mx - m2) : 0.0f) + (mo > -INFINITY ? so * __expf(mo - m2) : 0.0f);
@@ -191,28 +193,42 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[TN][TM], char *st
                 bvals[tn][g][3] = Prec<DT>::w2f((uint16_t)(hi >> 16));
             }
     }
-    // Residual epilogue: the 8 reads of the running sum that a pass needs are all issued one pass ahead
+    // Addresses: a wave-uniform base for the pass (scalar registers) plus a per-lane offset that is worked out once, and a
+    // row mask of one compare with a constant.  With a 64-bit address and both bounds worked out per row the epilogue
+    // was 1650 (16-bit outputs) / 2980 (residual) instructions per wave and 256 x 256 tile instead of 1390 / 2150.
+    constexpr int ES = kOut16 ? 2 : 4;
+    constexpr int NBV = 64 % LPR == 0 ? 1 : 3;                   // a lane's column and row step repeat after this many pieces
+    constexpr int RSTEP = 64 * NBV / LPR;                        // rows between those
+    static_assert(64 * NBV % LPR == 0 && NIO % NBV == 0, "pieces repeat");
+    const int row0 = m0 + wm * 32 * TM;
+    const uint64_t ybase = uniform64((uint64_t)(uintptr_t)y + (((uint64_t)sign * m_half + row0) * n + ncol0) * ES);
+    uint32_t voff[NBV];
+#pragma unroll
+    for (int v = 0; v < NBV; ++v) voff[v] = (uint32_t)((64 * v + lane) / LPR) * (uint32_t)n * ES + (uint32_t)((64 * v + lane) % LPR) * 16u;
+    typedef __attribute__((address_space(1))) f32x4 *out4;
+    const uint64_t step = (uint64_t)RSTEP * (uint32_t)n * ES;
+    // piece i of the pass that starts at the wave-uniform address `at`, which moves on with every NBV pieces
+    auto piece = [&](uint64_t at, int i) { return (out4)((__attribute__((address_space(1))) char *)(uintptr_t)at + voff[i % NBV]); };
+    uint64_t at_load = ybase, at_store = ybase;
+    int rows_left[NBV];          // rows from the lane's first one to the end of the output; none where its columns lie past the end
+#pragma unroll
+    for (int v = 0; v < NBV; ++v) rows_left[v] = ncol0 + (64 * v + lane) % LPR * (16 / ES) < n ? m_half - row0 - (64 * v + lane) / LPR : 0;
+    auto valid = [&](int pass, int i) { return pass * RP + i / NBV * RSTEP < rows_left[i % NBV]; };
+    // Residual epilogue: the reads of the running sum that a pass needs are all issued one pass ahead
     // (a load may not overtake an earlier store that the compiler cannot tell apart from it).  Reading
     // further ahead (two passes, which is what the registers allow) changes nothing: what the tile waits
     // for is the bandwidth of all workgroups' read-modify-write bursts arriving together, not one latency.
-    float4 hres[2][EPI == 2 ? NIO : 1];
-    auto load_res = [&](int pass, float4 (&h)[EPI == 2 ? NIO : 1]) {
+    f32x4 hres[2][EPI == 2 ? NIO : 1];
+    auto load_res = [&](int pass, f32x4 (&h)[EPI == 2 ? NIO : 1]) {
 #pragma unroll
         for (int i = 0; i < NIO; ++i) {
-            const int r = (64 * i + lane) / LPR, c = (64 * i + lane) % LPR;
-            const int mr = m0 + wm * 32 * TM + pass * 16 + r, nc = ncol0 + c * 4;
-            h[i] = float4{0.f, 0.f, 0.f, 0.f};
-            if (mr < m_half && nc < n) {
-                // read once, written once: neither the running sum nor any output is worth an L2 line that
-                // an operand slab could keep (non-temporal loads and stores)
-                const f32x4 t = __builtin_nontemporal_load((const f32x4 *)((const float *)y + ((size_t)sign * m_half + mr) * n + nc));
-                h[i] = float4{t.x, t.y, t.z, t.w};
-            }
+            // read once, written once: neither the running sum nor any output is worth an L2 line that
+            // an operand slab could keep (non-temporal loads and stores)
+            h[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (valid(pass, i)) h[i] = __builtin_nontemporal_load(piece(at_load, i));
+            if (i % NBV == NBV - 1) at_load = uniform64(at_load + step);
         }
     };
-    // a lane's columns are the same in every piece when a row's pieces divide the wave, else they repeat after 3
-    constexpr int NBV = 64 % LPR == 0 ? 1 : 3;
-    static_assert(NBV == 1 || (192 % LPR == 0), "a lane's columns repeat after three pieces");
     float bias4[EPI == 2 ? NBV : 1][4] = {};
     if constexpr (EPI == 2) {
         load_res(0, hres[0]);
@@ -228,6 +244,9 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[TN][TM], char *st
             }
         }
     }
+    // 16-bit rows that are a power of two long: chunk (two runs) and half within it, both XORed by row bits that spread
+    // a write of 32 rows over all banks; the half flips for rows 16 .. 31, whole pieces of the way out
+    auto chunk16 = [](int r) { return TN == 4 ? (r & 15) : TN == 2 ? ((r >> 1) & 7) : ((r >> 2) & 3); };
 #pragma unroll
     for (int pass = 0; pass < NPASS; ++pass) {
         const int tm = pass * RP / 32;                          // MFMA row block of this pass
@@ -255,40 +274,37 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[TN][TM], char *st
                             if constexpr (DT == kBF16) return __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, bf16x2));
                             else return __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, f16x2));
                         };
-                        uint2 o;
-                        o.x = pack2(v[0], v[1]);
-                        o.y = pack2(v[2], v[3]);
-                        *(uint2 *)(stage + fr * PITCH + ((kXor ? run ^ (fr & (NRUN - 1)) : run) << 3)) = o;      // 8-byte slots
+                        const uint2 o = {pack2(v[0], v[1]), pack2(v[2], v[3])};
+                        const int slot = kXor ? (((tn * 4 + g) ^ chunk16(fr)) << 1) + (fh ^ (fr >> 4)) : run;
+                        *(uint2 *)(stage + fr * PITCH + (slot << 3)) = o;
                     } else {
                         *(float4 *)(stage + (fr & 15) * PITCH + ((kXor ? run ^ (fr & 15 & (NRUN - 1)) : run) << 4)) = float4{v[0], v[1], v[2], v[3]};
                     }
                 }
         }
-        const int mbase = m0 + wm * 32 * TM + pass * RP;
         asm volatile("" ::: "memory");      // the wave's LDS operations execute in order; keep the compiler to it too
 #pragma unroll
         for (int i = 0; i < NIO; ++i) {
-            const int r = (64 * i + lane) / LPR, c = (64 * i + lane) % LPR, mr = mbase + r;
+            const int r = (64 * i + lane) / LPR, c = (64 * i + lane) % LPR;
             if constexpr (kOut16) {
-                uint4 q = *(const uint4 *)(stage + r * PITCH + ((kXor ? c ^ ((r & (NRUN - 1)) >> 1) : c) << 4));
-                if (kXor && (r & 1)) q = uint4{q.z, q.w, q.x, q.y};          // odd rows hold the two runs swapped
-                const int nc = ncol0 + c * 8;
-                if (mr < m_half && nc < n) __builtin_nontemporal_store(__builtin_bit_cast(u32x4, q), (u32x4 *)((uint16_t *)y + ((size_t)sign * m_half + mr) * n + nc));
+                u32x4 q = *(const u32x4 *)(stage + r * PITCH + ((kXor ? c ^ chunk16(r) : c) << 4));
+                if (kXor && i * 64 / LPR >= 16) q = u32x4{q.z, q.w, q.x, q.y};
+                if (valid(pass, i)) __builtin_nontemporal_store(__builtin_bit_cast(f32x4, q), piece(at_store, i));
             } else {
-                const float4 q = *(const float4 *)(stage + r * PITCH + ((kXor ? c ^ (r & (NRUN - 1)) : c) << 4));
-                const int nc = ncol0 + c * 4;
-                if (mr < m_half && nc < n) {
-                    float4 *p = (float4 *)((float *)y + ((size_t)sign * m_half + mr) * n + nc);
+                const f32x4 q = *(const f32x4 *)(stage + r * PITCH + ((kXor ? c ^ (r & (NRUN - 1)) : c) << 4));
+                if (valid(pass, i)) {
+                    const out4 p = piece(at_store, i);
                     if constexpr (EPI == 2) {
-                        float4 h = hres[pass & 1][i];
+                        f32x4 h = hres[pass & 1][i];
                         const float *b4 = bias4[i % NBV];
                         h.x += q.x + b4[0]; h.y += q.y + b4[1]; h.z += q.z + b4[2]; h.w += q.w + b4[3];
-                        __builtin_nontemporal_store(f32x4{h.x, h.y, h.z, h.w}, (f32x4 *)p);
+                        __builtin_nontemporal_store(h, p);
                     } else {
                         *p = q;
                     }
                 }
             }
+            if (i % NBV == NBV - 1) at_store = uniform64(at_store + step);
         }
         asm volatile("" ::: "memory");
     }
