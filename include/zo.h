@@ -22,7 +22,7 @@
  *     stream before writing through it.
  *   - Ownership: the caller owns all parameter, token and workspace memory and
  *     must keep it alive until zo_free.  The library owns only the opaque
- *     handle and a few HIP events.
+ *     handle, a few HIP events and 24 bytes of pinned host memory per handle.
  *
  * Parameter tensors, canonical order (tensor id = position in this list):
  *     0  embed_tokens [vocab, d_model]     (also the LM head: tied)

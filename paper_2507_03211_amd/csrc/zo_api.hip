@@ -162,6 +162,10 @@ struct zo_model {
     bool use_mfma;
     // device scalars
     double *loss_pm, *g;
+    // l+, l-, g of the latest step that was asked for them: pinned host memory that the loss kernel writes itself, so that
+    // a caller who wants them waits for the stream and nothing else (a copy of 24 bytes into pageable memory is a launch
+    // and a second wait: 137 -> 118 us for the tiny step).  host_res_dev is the same memory as the device addresses it.
+    double *host_res, *host_res_dev;
     float *s_cur, *s_pend;             // update scalars on the device: this step's (resident model), the pending steps' (streamed)
     uint32_t *flags;
     // streamed state
@@ -491,14 +495,16 @@ int forward_single(zo_model *m, const int32_t *tokens, int batch, int seq, int s
                          m->loss_pm + slot);
 }
 
+// Where the step's loss kernel also leaves l+, l- and g for read_back: nowhere when the caller did not ask.
+double *result_slot(zo_model *m, const double *host_g, const double *host_loss_pm) { return host_g || host_loss_pm ? m->host_res_dev : nullptr; }
+
 int read_back(zo_model *m, double *host_g, double *host_loss_pm)
 {
     if (!host_g && !host_loss_pm) return ZO_OK;
-    double tmp[3];
-    ZO_HIP(hipMemcpyAsync(tmp, m->loss_pm, 3 * sizeof(double), hipMemcpyDeviceToHost, m->compute));   // loss_pm[2], g adjacent
     ZO_HIP(hipStreamSynchronize(m->compute));
-    if (host_loss_pm) { host_loss_pm[0] = tmp[0]; host_loss_pm[1] = tmp[1]; }
-    if (host_g) *host_g = tmp[2];
+    const volatile double *r = m->host_res;
+    if (host_loss_pm) { host_loss_pm[0] = r[0]; host_loss_pm[1] = r[1]; }
+    if (host_g) *host_g = r[2];
     return ZO_OK;
 }
 
@@ -629,12 +635,12 @@ int stream_begin(zo_model *m, const int32_t *tokens, int batch, int seq, uint64_
     return ZO_OK;
 }
 
-int stream_end(zo_model *m, float lr)
+int stream_end(zo_model *m, float lr, double *result)
 {
     if (!m->step_open) return fail(ZO_ESTATE, "no streamed step is open");
     if (m->next_block != m->cfg.n_layers) return fail(ZO_ESTATE, "only %d of %d blocks were computed", m->next_block, m->cfg.n_layers);
     const int pend = m->pend_n >= m->wb_interval ? 0 : m->pend_n;      // 0: this step's uploads took them all and were written back
-    const GScalar gs{m->step_eps, lr, m->g, m->s_pend + pend, m->flags};
+    const GScalar gs{m->step_eps, lr, m->g, m->s_pend + pend, m->flags, result};
     ZO_TRY(head_and_loss(m, 2, m->step_batch, m->step_seq, m->ws + m->wsp.e_pm[0], m->ws + m->wsp.e_pm[1], m->ws + m->wsp.lnf_pm[0],
                          m->ws + m->wsp.lnf_pm[1], m->loss_pm, &gs));
     m->pend_n = pend;
@@ -737,6 +743,10 @@ extern "C" int zo_init_model(const zo_config *cfg, void *const *tensor_ptrs, int
         m->ev_step[s] = nullptr;
     }
     m->n_steps = 0; m->lookahead = 0;
+    m->host_res = m->host_res_dev = nullptr;
+    err = hipHostMalloc((void **)&m->host_res, 3 * sizeof(double), hipHostMallocDefault);
+    if (err == hipSuccess) err = hipHostGetDevicePointer((void **)&m->host_res_dev, m->host_res, 0);
+    if (err != hipSuccess) { zo_free(m); return fail(ZO_EHIP, "allocating pinned host memory failed: %s", hipGetErrorString(err)); }
     if (cfg->residency == ZO_STREAMED) {
         err = hipStreamCreateWithFlags(&m->download, hipStreamNonBlocking);
         m->own_download = err == hipSuccess;
@@ -767,6 +777,7 @@ extern "C" int zo_free(zo_model *m)
         if (m->ev_step[s]) (void)hipEventDestroy(m->ev_step[s]);
     }
     if (m->own_download) (void)hipStreamDestroy(m->download);
+    if (m->host_res) (void)hipHostFree(m->host_res);
     for (hipEvent_t ev : m->prof_ev) (void)hipEventDestroy(ev);
     for (auto &sp : m->spans) { (void)hipEventDestroy(sp.t0); (void)hipEventDestroy(sp.t1); }
     delete m;
@@ -790,18 +801,20 @@ int apply_pending_resident(zo_model *m)
 
 namespace {
 // Alg. 3: U(W_{i+1}) is in flight while C(W_i) runs; O(W_i) follows as soon as W_i is staged.
-int streamed_step(zo_model *m, const int32_t *tokens, int batch, int seq, uint64_t seed, float eps, float lr)
+int streamed_step(zo_model *m, const int32_t *tokens, int batch, int seq, uint64_t seed, float eps, float lr, double *result)
 {
-    ZO_TRY(stream_begin(m, tokens, batch, seq, seed, eps));
+    if (m->step_open) return fail(ZO_ESTATE, "a streamed step is already open");
+    // the first uploads go out before the embedding's launches: every block waits for them
     m->up_next = 0;
     ZO_TRY(stream_fill(m));
+    ZO_TRY(stream_begin(m, tokens, batch, seq, seed, eps));
     for (int l = 0; l < m->cfg.n_layers; ++l) {
         ZO_TRY(stream_compute(m, l, true));
         m->next_block = l + 1;
         ZO_TRY(stream_writeback(m, l));
         ZO_TRY(stream_fill(m));
     }
-    return stream_end(m, lr);
+    return stream_end(m, lr, result);
 }
 
 // A streamed step that failed half way (a HIP call returned an error): let what was enqueued finish, close the step and
@@ -876,7 +889,7 @@ extern "C" int zo_step(zo_model *m, const int32_t *tokens, int batch, int seq, u
     if (!(eps > 0.0f)) return fail(ZO_EINVAL, "eps must be positive");
     if (m->cfg.residency == ZO_RESIDENT) {
         const bool defer = m->deferred && mode == ZO_MODE_FUSED;       // Alg. 2: the update waits for the next pass over theta
-        const GScalar gs{eps, lr, m->g, defer ? m->s_pend : m->s_cur, m->flags};
+        const GScalar gs{eps, lr, m->g, defer ? m->s_pend : m->s_cur, m->flags, result_slot(m, host_g, host_loss_pm)};
         ZO_TRY(dual_forward(m, tokens, batch, seq, seed, eps, mode, nullptr, nullptr, &gs));
         if (defer) {
             m->pend_seed[0] = seed;
@@ -893,14 +906,14 @@ extern "C" int zo_step(zo_model *m, const int32_t *tokens, int batch, int seq, u
     // the order Alg. 3 gives them; bounded to one step, the next step's uploads and launches are queued while this
     // step still runs and nothing idles between steps.
     if (m->lookahead >= 1 && m->n_steps >= 2) ZO_HIP(hipEventSynchronize(m->ev_step[m->n_steps & 1]));
-    const int rc = streamed_step(m, tokens, batch, seq, seed, eps, lr);
+    const int rc = streamed_step(m, tokens, batch, seq, seed, eps, lr, result_slot(m, host_g, host_loss_pm));
     if (rc != ZO_OK) {
         stream_abort(m);
         return rc;
     }
     ZO_HIP(hipEventRecord(m->ev_step[m->n_steps & 1], m->compute));
     ++m->n_steps;
-    if (m->lookahead < 1) ZO_HIP(hipStreamSynchronize(m->compute));
+    if (m->lookahead < 1 && !host_g && !host_loss_pm) ZO_HIP(hipStreamSynchronize(m->compute));
     return read_back(m, host_g, host_loss_pm);
 }
 
@@ -934,7 +947,7 @@ extern "C" int zo_stream_end(zo_model *m, float lr, double *host_g, double *host
 {
     if (!m) return fail(ZO_EINVAL, "model is NULL");
     if (m->cfg.residency != ZO_STREAMED) return fail(ZO_ESTATE, "not a streamed model");
-    ZO_TRY(stream_end(m, lr));
+    ZO_TRY(stream_end(m, lr, result_slot(m, host_g, host_loss_pm)));
     return read_back(m, host_g, host_loss_pm);
 }
 

@@ -417,6 +417,7 @@ __device__ __forceinline__ void g_and_scalar(double lp, double lm, const GScalar
     if (!(g == g) || g - g != 0.0) { s = 0.0f; atomicOr(gs.flags, 1u); }
     *gs.g = g;
     *gs.s = s;
+    if (gs.result) { gs.result[0] = lp; gs.result[1] = lm; gs.result[2] = g; }
 }
 
 // L+- = sum of the sign's row losses / count, in a fixed order (deterministic); 512 threads per sign.  One workgroup for

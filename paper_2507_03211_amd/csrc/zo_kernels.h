@@ -71,7 +71,8 @@ hipError_t launch_attention(const void *qkv, void *out, int dtype, int n_seq, in
 hipError_t launch_ce_rows(const void *logits, const int32_t *target, double *row_loss, int dtype, int rows,
                           int vocab, hipStream_t s);
 // Eq. 1's g and Eq. 2's scalar: *g = (l+ - l-) / (2 eps), *s = -(lr g) rounded once, 0 (and flag bit 0) when g is not finite
-struct GScalar { float eps, lr; double *g; float *s; uint32_t *flags; };
+// (`result`, if not null: device address of pinned host memory that receives l+, l-, g)
+struct GScalar { float eps, lr; double *g; float *s; uint32_t *flags; double *result; };
 // L+- (n_sign of them) into loss_pm; with `gs` (n_sign == 2) g and the scalar too, in the same launch
 hipError_t launch_loss_reduce(const double *row_loss, int n_sign, int m_half, int count_per_sign, double *loss_pm,
                               const GScalar *gs, hipStream_t s);
