@@ -516,11 +516,15 @@ void stage_flat_kernel(StageBatch batch, uint64_t seed, float eps, uint64_t upd_
     if constexpr (!SINGLE) load_rayleigh_cells(ln_tab);
     float us = 0.0f;
     if constexpr (UPD != 0) us = *dev_scale;
+    typedef uint32_t Raw __attribute__((ext_vector_type(4)));      // native vector: arrays of it stay in registers
     struct Piece {
         W *theta, *dp, *dm;      // theta is written only when UPD != 0
         uint64_t numel, base;    // base: first element of the chunk in its tensor
-        uint32_t tid;
-        bool whole;              // the chunk lies wholly inside the tensor
+        uint32_t tid, whole;     // whole: the chunk lies wholly inside the tensor.  (A word and not a bool: the three bytes
+                                 // of padding behind a bool kept the compiler from splitting the struct into registers;
+                                 // it went to memory, and a launch took up to 15 us more than its work: 2.4 M bf16
+                                 // elements 19.4 -> 6.3 us, 7.1 M 24.2 -> 10.4 and with the update 31.3 -> 15.2, 105 M
+                                 // with the update 179.5 -> 172.5.)
     };
     int di = 0;
     auto piece_of = [&](uint32_t tile) {
@@ -534,14 +538,14 @@ void stage_flat_kernel(StageBatch batch, uint64_t seed, float eps, uint64_t upd_
         p.whole = p.base + kStageFlatTile <= p.numel;
         return p;
     };
-    auto load_chunk = [&](const Piece &p, uint4 (&v)[kIter]) {
+    auto load_chunk = [&](const Piece &p, Raw (&v)[kIter]) {
 #pragma unroll
-        for (int it = 0; it < kIter; ++it) v[it] = *(const uint4 *)(p.theta + p.base + (size_t)(it * kStreamThreads + threadIdx.x) * VN);
+        for (int it = 0; it < kIter; ++it) v[it] = *(const Raw *)(p.theta + p.base + (size_t)(it * kStreamThreads + threadIdx.x) * VN);
     };
     // 16 bytes of theta at element i0 (`raw` when `full`, else the tensor's ragged tail, read element-wise)
-    auto piece16 = [&](const Piece &p, uint64_t i0, const uint4 &raw, bool full) {
+    auto piece16 = [&](const Piece &p, uint64_t i0, const Raw &raw, bool full) {
         if constexpr (SINGLE) {
-            if (full) *(uint4 *)(p.dp + i0) = raw;
+            if (full) *(Raw *)(p.dp + i0) = raw;
             else for (int e = 0; e < VN && i0 + e < p.numel; ++e) p.dp[i0 + e] = p.theta[i0 + e];
         } else {
             float z[VN];
@@ -549,7 +553,7 @@ void stage_flat_kernel(StageBatch batch, uint64_t seed, float eps, uint64_t upd_
             for (int b = 0; b < VN / 4; ++b) normal4(philox_block(seed, p.tid, i0 / 4 + b), z + 4 * b, ln_tab);
             float th[VN], a[VN], b[VN];
             if (full) {
-                unpack16<DT>(raw, th);
+                unpack16<DT>(__builtin_bit_cast(uint4, raw), th);
             } else {
                 for (int e = 0; e < VN; ++e) th[e] = i0 + e < p.numel ? Prec<DT>::w2f(p.theta[i0 + e]) : 0.0f;
             }
@@ -594,7 +598,7 @@ void stage_flat_kernel(StageBatch batch, uint64_t seed, float eps, uint64_t upd_
     uint32_t c = blockIdx.x;
     if (c >= batch.total_tiles) return;
     Piece p = piece_of(c);
-    uint4 cur[kIter], nxt[kIter];
+    Raw cur[kIter], nxt[kIter];
     if (p.whole) load_chunk(p, cur);
     for (;;) {
         const uint32_t cn = c + gridDim.x;
@@ -613,8 +617,8 @@ void stage_flat_kernel(StageBatch batch, uint64_t seed, float eps, uint64_t upd_
                 const uint64_t i0 = p.base + (uint64_t)(it * kStreamThreads + threadIdx.x) * VN;
                 if (i0 >= p.numel) break;
                 const bool full = i0 + VN <= p.numel;
-                uint4 raw = uint4{0u, 0u, 0u, 0u};
-                if (full) raw = *(const uint4 *)(p.theta + i0);
+                Raw raw = {0u, 0u, 0u, 0u};
+                if (full) raw = *(const Raw *)(p.theta + i0);
                 piece16(p, i0, raw, full);
             }
         }
