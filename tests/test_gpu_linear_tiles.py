@@ -82,3 +82,21 @@ def test_lmhead_tiles(m_half, d, vocab, dtype):
         want = torch.logsumexp(logits, 1) - logits.gather(1, tg.clamp(min=0)[:, None])[:, 0]
         want = torch.where(tg >= 0, want, torch.zeros_like(want))
         assert float((loss[rows] - want).abs().max()) < 2e-4          # fp32 logits: accumulation order only
+
+
+@pytest.mark.parametrize("m_half,d,vocab", [(257, 192, 17000), (3, 64, 520)])     # a pipelined tile, the small one
+def test_lmhead_of_logits_near_the_fp32_range(m_half, d, vocab):
+    # one product per logit: the row's power of two times +- 1 (a target among equal largest ones, or as far below as it gets)
+    x = torch.zeros(2 * m_half, d, device=DEV)
+    x[:, 0] = torch.tensor([2.0**63, 2.0**61, -2.0**63, 1.0], device=DEV)[torch.arange(2 * m_half, device=DEV) % 4]
+    e = torch.zeros(vocab, d, device=DEV)
+    e[:, 0] = 2.0**63 * (1.0 - 2.0 * (torch.arange(vocab, device=DEV) % 2))
+    target = torch.arange(2 * m_half, device=DEV, dtype=torch.int32) % vocab
+    loss = torch.empty(2 * m_half, device=DEV, dtype=torch.float64)
+    scratch = torch.empty(zo_amd.zo_kernel_lmhead_scratch_bytes(zi.BF16, m_half, vocab), device=DEV, dtype=torch.uint8)
+    xb, eb = x.bfloat16(), e.bfloat16()
+    zo_amd.zo_kernel_lmhead_ce(xb, eb, eb, target, loss, scratch, zi.BF16, m_half, d, vocab)
+    logits = xb.double() @ eb.double().t()
+    want = torch.logsumexp(logits, 1) - logits.gather(1, target.long()[:, None])[:, 0]
+    # the products are exact; sums of equal terms in fp32 and one rounding of the pair's correction: a few 2^-24
+    assert bool(((loss - want).abs() <= 1e-6 + 1e-6 * want.abs()).all())
