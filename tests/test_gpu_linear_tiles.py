@@ -100,3 +100,25 @@ def test_lmhead_of_logits_near_the_fp32_range(m_half, d, vocab):
     want = torch.logsumexp(logits, 1) - logits.gather(1, target.long()[:, None])[:, 0]
     # the products are exact; sums of equal terms in fp32 and one rounding of the pair's correction: a few 2^-24
     assert bool(((loss - want).abs() <= 1e-6 + 1e-6 * want.abs()).all())
+
+
+@pytest.mark.parametrize("m_half,d,vocab", [(257, 192, 17000), (3, 64, 520)])
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_lmhead_of_large_logits_with_full_mantissas(m_half, d, vocab, sign):
+    # one product per logit, +-(1 + i / 128) 2^e times (1 + j / 128): 16 bits of mantissa, e from 20 up to the end of the fp32
+    # range.  Every fourth column is of the row's own sign; with sign = -1 the last strips hold large negative logits only.
+    rows, col = torch.arange(2 * m_half, device=DEV), torch.arange(vocab, device=DEV)
+    x = torch.zeros(2 * m_half, d, device=DEV)
+    x[:, 0] = (1.0 + (37 * rows % 128) / 128.0) * torch.exp2((rows * 107 // (2 * m_half) - 20).float())      # 2^-20 .. 2^86
+    e = torch.zeros(vocab, d, device=DEV)
+    e[:, 0] = (1.0 + (11 * col % 127) / 128.0) * 2.0**40 * torch.where((col % 4 == 0) & (col < vocab // 2), sign, -1.0)
+    target = (rows * 61 % vocab).to(torch.int32)
+    loss = torch.empty(2 * m_half, device=DEV, dtype=torch.float64)
+    scratch = torch.empty(zo_amd.zo_kernel_lmhead_scratch_bytes(zi.BF16, m_half, vocab), device=DEV, dtype=torch.uint8)
+    xb, eb = x.bfloat16(), e.bfloat16()
+    zo_amd.zo_kernel_lmhead_ce(xb, eb, eb, target, loss, scratch, zi.BF16, m_half, d, vocab)
+    logits = xb.double() @ eb.double().t()
+    assert bool((logits == logits.float().double()).all())                  # so that what follows is the exact answer
+    want = torch.logsumexp(logits, 1) - logits.gather(1, target.long()[:, None])[:, 0]
+    # the products are exact; a sum of equal terms in fp32 and one rounding of the pair's correction, as above
+    assert bool(((loss - want).abs() <= 1e-6 + 1e-6 * want.abs()).all())
