@@ -58,36 +58,70 @@ __device__ __forceinline__ void swap_halves(float x, float &a, float &b)
     b = __uint_as_float(r[1]);
 }
 
-// One query row the plain way, by a whole wavefront: scores of keys 0 .. t only, one key per lane, in fp32.  The matrix
-// path multiplies the zero probability of a future key with that key's value, which is not a number when the value is
-// infinite or not a number; rows that come out as such are worked again here, from the keys they may see.
-template <int DT>
-__device__ __attribute__((noinline)) void attention_row(const uint16_t *base, uint16_t *out, int ld, int d, int d_head, int t, float scale)
+// The query rows q0 .. q0 + 31 that `rows` marks, the plain way, by a whole wavefront: scores of keys 0 .. t only, in fp32.
+// The matrix path multiplies the zero probability of a future key with that key's value, which is not a number when the
+// value is infinite or not a number; rows that come out as such are worked again here, from the keys they may see.
+// A row belongs to the two lanes fr, fr + 32, each with half of its channels (those of the matrix path's fragments), so
+// that a key or value row is read once for all 32 query rows, 16 bytes at a time and from one address per half wave.
+// A diverged model has all its rows here.  32 heads of 80, not a number throughout, plain kernel / a wavefront per row /
+// here: 2 sequences of 2048 keys 6.4 / 77 / 2.5 ms, 8 of 64 keys 53 / 694 / 58 us.
+template <int DT, int DH>
+__device__ __forceinline__ void attention_rows(const uint16_t *base, uint16_t *out, int ld, int d, int q0, uint32_t rows)
 {
-    const int lane = threadIdx.x & 63;
-    auto score = [&](int j) {
-        const uint16_t *q = base + (size_t)t * ld, *k = base + (size_t)j * ld + d;
-        float s = 0.0f;
-        for (int c = 0; c < d_head; ++c) s += Prec<DT>::a2acc(q[c]) * Prec<DT>::a2acc(k[c]);
-        return s * scale;
+    constexpr int KS = DH / 16;
+    const int lane = threadIdx.x & 63, fr = lane & 31, fh = lane >> 5, t = q0 + fr;
+    const bool mine = (rows >> fr) & 1u;
+    const int last = q0 + 31 - __builtin_clz(rows);                // of the marked rows
+    const float scale = 1.0f / __builtin_sqrtf((float)DH);
+    auto piece = [&](int row, int what, int s) { return *(const uint4 *)(base + (size_t)row * ld + what * d + 16 * s + 8 * fh); };
+    auto elem = [](const uint4 &v, int e) {
+        const uint32_t w = e < 2 ? v.x : e < 4 ? v.y : e < 6 ? v.z : v.w;
+        return Prec<DT>::a2acc((uint16_t)(e & 1 ? w >> 16 : w & 0xffffu));
     };
-    float mx = -INFINITY;
-    for (int j = lane; j <= t; j += 64) mx = __builtin_fmaxf(mx, score(j));
-    for (int o = 32; o > 0; o >>= 1) mx = __builtin_fmaxf(mx, __shfl_xor(mx, o, 64));
-    float sum = 0.0f, a0 = 0.0f, a1 = 0.0f;                        // channels lane, lane + 64
-    for (int j0 = 0; j0 <= t; j0 += 64) {
-        const float p = j0 + lane <= t ? __expf(score(j0 + lane) - mx) : 0.0f;
-        sum += p;
-        for (int i = 0; i < 64 && j0 + i <= t; ++i) {
-            const float pi = __shfl(p, i, 64);
-            const uint16_t *v = base + (size_t)(j0 + i) * ld + 2 * d;
-            if (lane < d_head) a0 += pi * Prec<DT>::a2acc(v[lane]);
-            if (lane + 64 < d_head) a1 += pi * Prec<DT>::a2acc(v[lane + 64]);
+    uint4 q[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) q[s] = mine ? piece(t, 0, s) : uint4{0u, 0u, 0u, 0u};
+    // f(j, score) for the keys j = 0 .. last; a key is on its way while the one before it is worked
+    auto keys = [&](auto &&f) {
+        uint4 k[KS], next[KS];
+#pragma unroll
+        for (int s = 0; s < KS; ++s) k[s] = piece(0, 1, s);
+        for (int j = 0; j <= last; ++j) {
+            const int jn = j < last ? j + 1 : last;
+#pragma unroll
+            for (int s = 0; s < KS; ++s) next[s] = piece(jn, 1, s);
+            float part[2] = {0.0f, 0.0f}, a, b;
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) part[e & 1] = __builtin_fmaf(elem(q[s], e), elem(k[s], e), part[e & 1]);
+            swap_halves(part[0] + part[1], a, b);
+            f(j, (a + b) * scale);
+#pragma unroll
+            for (int s = 0; s < KS; ++s) k[s] = next[s];
         }
+    };
+    float mx = -INFINITY, sum = 0.0f, acc[8 * KS] = {};
+    keys([&](int j, float s) { if (j <= t) mx = __builtin_fmaxf(mx, s); });
+    keys([&](int j, float s) {
+        if (j > t) return;
+        const float p = __expf(s - mx);
+        sum += p;
+#pragma unroll
+        for (int i = 0; i < KS; ++i) {
+            const uint4 v = piece(j, 2, i);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[8 * i + e] = __builtin_fmaf(p, elem(v, e), acc[8 * i + e]);
+        }
+    });
+    if (!mine) return;
+    const float inv = 1.0f / sum;
+    uint16_t *o = out + (size_t)t * d + 8 * fh;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+        auto two = [&](int e) { return pack2<DT>(acc[8 * s + e] * inv, acc[8 * s + e + 1] * inv); };
+        *(uint4 *)(o + 16 * s) = uint4{two(0), two(2), two(4), two(6)};
     }
-    sum = wave_sum(sum);
-    if (lane < d_head) out[lane] = Prec<DT>::acc2a(a0 / sum);
-    if (lane + 64 < d_head) out[lane + 64] = Prec<DT>::acc2a(a1 / sum);
 }
 
 typedef short v4i16 __attribute__((ext_vector_type(4)));
@@ -108,6 +142,7 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
     // P V product as the sum of two 16-bit numbers (p rounded, and what the rounding left), two multiplies instead of
     // one.  Without the second the error against 64 bits was 2.1e-3 instead of 1.6e-3 (bf16, 2048 keys).
     constexpr bool SPLIT = DH != 64 && DH != 128;
+    constexpr bool kRedo = SPLIT;         // rows that are not finite are worked again (see the end)
     constexpr int KR = KS % 4 == 0 ? 4 : KS;   // depth of the K fragment ring (it divides KS: a fragment's slot is the same in every unit)
     // K and V tiles, both [key][channel] as they sit in memory, 16-byte chunks XOR-swizzled per key so that
     // the MFMA fragment reads of K (32 keys, one chunk) and the transposing reads of V (4 keys x 32 bytes
@@ -366,15 +401,22 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
     const int n_pairs = n_heads * n_seq, pairs_xcd = (n_pairs + 7) / 8;
     const int group_pairs = slots / n_qt > 1 ? slots / n_qt : 1, group_items = group_pairs * n_qt;
     const int n_lin = (pairs_xcd + group_pairs - 1) / group_pairs * group_items;
-    for (int round = 0; round * slots < n_lin; ++round) {
-        const int lin = round * slots + ((round & 1) ? slots - 1 - slot : slot);
-        if (lin >= n_lin) continue;
+    // the slot's entry of a round: its (head, sequence) pair, -1 if there is none, and its query tile
+    auto pair_at = [&](int lin, int &qt) {
+        if (lin >= n_lin) return -1;
         const int grp = lin / group_items, r = lin % group_items;
         const int gp = pairs_xcd - grp * group_pairs < group_pairs ? pairs_xcd - grp * group_pairs : group_pairs;
-        if (r >= gp * n_qt) continue;
+        if (r >= gp * n_qt) return -1;
+        qt = n_qt - 1 - r / gp;
         const int pair = (grp * group_pairs + r % gp) * 8 + xcd;
-        if (pair >= n_pairs) continue;
-        const int qt = n_qt - 1 - r / gp;
+        return pair < n_pairs ? pair : -1;
+    };
+    auto lin_of = [&](int round) { return round * slots + ((round & 1) ? slots - 1 - slot : slot); };
+    uint64_t again = 0;                              // rounds (mod 64) in which a row of this wave came out not finite
+    for (int round = 0; round * slots < n_lin; ++round) {
+        int qt;
+        const int pair = pair_at(lin_of(round), qt);
+        if (pair < 0) continue;
         const int head = pair % n_heads, sq = pair / n_heads;
         base = qkv + (size_t)sq * seq * ld + head * DH;
         // (the halves go through unsigned 32-bit variables: readfirstlane returns a signed int, which would
@@ -453,28 +495,46 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
 
         // Head sizes that ran on the plain kernel before this one took them keep its answer where a later token's value
         // is not finite (64 and 128 have always multiplied it with zero here): 20 instructions per work item.
-        if constexpr (DH != 64 && DH != 128) {
+        if constexpr (kRedo) {
             float probe = 0.0f;                                  // x times 0 is 0 for every finite x
 #pragma unroll
             for (int c = 0; c < CT; ++c)
 #pragma unroll
                 for (int i = 0; i < 16; ++i)
                     if (c * 32 + 8 * (i >> 2) < DH) probe = __builtin_fmaf(oacc[c][i], 0.0f, probe);
-            uint64_t bad = __builtin_amdgcn_ballot_w64(qrow < seq && !(probe == 0.0f));
-            if (bad != 0) {
-                // the rows' other results go out first: a lane that stored garbage over a recomputed row would race with it
-                uint32_t rows = (uint32_t)bad | (uint32_t)(bad >> 32);
-                const bool mine = (rows >> fr) & 1u;
-                if (qrow < seq && !mine) store_row(1.0f / l_run);
-                while (rows) {
-                    const int r = __builtin_ctz(rows);
-                    rows &= rows - 1;
-                    attention_row<DT>(base, out + ((size_t)sq * seq + q0 + r) * d + head * DH, ld, d, DH, q0 + r, 1.0f / __builtin_sqrtf((float)DH));
-                }
-                continue;
-            }
+            if (__builtin_amdgcn_ballot_w64(qrow < seq && !(probe == 0.0f)) != 0) again |= 1ull << (round & 63);
         }
         if (qrow < seq) store_row(1.0f / l_run);
+    }
+    // The rows that came out not finite, once more the plain way, after all items: nothing of the loop above is live any
+    // more, and a register that this needs is not missing there.  A lane finds its row's state in what it has stored itself.
+    if constexpr (kRedo) {
+        if (again == 0) return;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this wave's own stores lie behind the ones that follow
+        for (int round = 0; round * slots < n_lin; ++round) {
+            int qt;
+            const int pair = (again >> (round & 63)) & 1 ? pair_at(lin_of(round), qt) : -1;
+            if (pair < 0) continue;
+            const int head = pair % n_heads, sq = pair / n_heads;
+            q0 = qt * BQ + wave * 32;
+            qrow = q0 + fr;
+            uint16_t *rows0 = out + (size_t)sq * seq * d + head * DH;
+            bool bad = false;
+            if (qrow < seq) {
+#pragma unroll
+                for (int c = 0; c < DH / 8; ++c) {
+                    const uint2 v = *(const uint2 *)(rows0 + (size_t)qrow * d + 8 * c + 4 * fh);
+                    auto not_finite = [](uint32_t w) {           // either half's exponent is all ones
+                        const uint32_t e = DT == kBF16 ? 0x7f80u : 0x7c00u;
+                        return (w & e) == e || ((w >> 16) & e) == e;
+                    };
+                    bad = bad || not_finite(v.x) || not_finite(v.y);
+                }
+            }
+            const uint64_t lanes = __builtin_amdgcn_ballot_w64(bad);
+            if (lanes != 0)
+                attention_rows<DT, DH>(qkv + (size_t)sq * seq * ld + head * DH, rows0, ld, d, q0, (uint32_t)lanes | (uint32_t)(lanes >> 32));
+        }
     }
 }
 }  // namespace

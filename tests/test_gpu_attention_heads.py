@@ -77,3 +77,49 @@ def test_unaligned_buffers_still_run():
     want = _oracle(qkv, n_seq, seq, heads, dh)
     got = _run(qkv, n_seq, seq, heads, dh, zi.BF16)
     assert np.max(np.abs(got - want)) < 3 * ULP[zi.BF16] * (1 + np.abs(want).max())
+
+
+@pytest.mark.parametrize("dtype", [zi.BF16, zi.FP16])
+@pytest.mark.parametrize("n_seq,seq,heads,dh", [(40, 140, 9, 96), (1, 700, 3, 112), (2, 33, 2, 80)])     # 720 items on 512 workgroups
+def test_values_that_are_not_finite_reach_the_rows_that_see_them_and_no_other(dtype, n_seq, seq, heads, dh):
+    qkv = _qkv(n_seq, seq, heads, dh, dtype, 21).reshape(n_seq, seq, 3, heads, dh)
+    want = _oracle(qkv, n_seq, seq, heads, dh)
+    rng = np.random.Generator(np.random.PCG64(seq))
+    bad = np.zeros((n_seq, seq, heads, dh))
+    for _ in range(max(3, n_seq * heads // 3)):
+        at = (rng.integers(n_seq), rng.integers(seq), rng.integers(heads), rng.integers(dh))
+        value = [np.inf, -np.inf, np.nan][rng.integers(3)]
+        bad[at] = value
+        qkv[at[0], at[1], 2, at[2], at[3]] = float(value)
+    with np.errstate(invalid="ignore"):
+        want = want + np.cumsum(bad, axis=1)          # a row's probabilities are positive: infinities stay, opposite ones meet as NaN
+    got = _run(qkv.reshape(n_seq * seq, -1), n_seq, seq, heads, dh, dtype)
+    fin = np.isfinite(want)
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
+    assert np.max(np.abs(got[fin] - want[fin])) < 3 * ULP[dtype] * (1 + np.abs(want[fin]).max())
+
+
+@pytest.mark.parametrize("dh", [80, 112])
+@pytest.mark.parametrize("n_seq,seq", [(8, 64), (2, 1024)])
+def test_rows_that_are_not_finite_cost_no_more_than_on_the_plain_kernel(n_seq, seq, dh):
+    # buffers that are not 16-byte aligned take the plain kernel
+    heads = 32
+    n = n_seq * seq * 3 * heads * dh
+    flat = torch.full((n + 8,), float("nan"), device=DEV, dtype=torch.bfloat16)
+    out = torch.empty(n_seq * seq * heads * dh, device=DEV, dtype=torch.bfloat16)
+
+    def us(qkv):
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        best = 1e30
+        for _ in range(5):
+            ev[0].record()
+            for _ in range(3):
+                zo_amd.zo_kernel_attention(qkv, out, zi.BF16, n_seq, seq, heads, dh, torch.cuda.current_stream())
+            ev[1].record()
+            ev[1].synchronize()
+            best = min(best, ev[0].elapsed_time(ev[1]) / 3 * 1000)
+        return best
+
+    plain, here = us(flat[1:1 + n]), us(flat[:n])
+    assert bool(torch.isnan(out).all())
+    assert here < 1.5 * plain, (here, plain)          # 16 times with a wavefront per row
