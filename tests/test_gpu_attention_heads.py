@@ -123,3 +123,19 @@ def test_rows_that_are_not_finite_cost_no_more_than_on_the_plain_kernel(n_seq, s
     plain, here = us(flat[1:1 + n]), us(flat[:n])
     assert bool(torch.isnan(out).all())
     assert here < 1.5 * plain, (here, plain)          # 16 times with a wavefront per row
+
+
+@pytest.mark.parametrize("gap", [8.0, 17.0, 18.5, 20.0])
+@pytest.mark.parametrize("dh", [80, 112])
+def test_small_probabilities_count_in_fp16(dh, gap):
+    # key 0 outweighs each of the others by e^gap, and its value is zero: a row is what the many small probabilities add up to
+    n_seq, seq, heads = 1, 2000, 1
+    qkv = torch.zeros(n_seq, seq, 3, heads, dh, device=DEV)
+    qkv[:, :, 0, :, 0] = 16.0
+    qkv[:, 0, 1, :, 0] = gap * dh**0.5 / 16.0
+    qkv[:, 1:, 2] = 1000.0 * (1.0 + torch.arange(dh, device=DEV) / 128.0)
+    qkv = qkv.half().reshape(n_seq * seq, -1)
+    got, want = _run(qkv, n_seq, seq, heads, dh, zi.FP16), _oracle(qkv, n_seq, seq, heads, dh)
+    # a small probability, 2^11 e^-gap, within half a unit of 2^-24; the output within half a unit of its own or of 2^-24
+    bound = want * (2.0**-36 * np.exp(gap + 0.02) + 2.0**-10) + 2.0**-25
+    assert np.all(np.abs(got - want) <= bound), np.max(np.abs(got - want) / np.maximum(want, 1e-9))
