@@ -202,18 +202,19 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
     // this wave's pieces of K (which = 0) or V (which = 1) rows k0 .. k0 + 63, into buffer `buf` of that operand
     auto issue = [&](int which, int k0, int buf) {
         const uint32_t dst = (which ? vs_lds : ks_lds) + (uint32_t)buf * (TILE * 16) + (uint32_t)(NLD * wave) * 1024u;
+        const uint64_t gb = gbase0 + (uint64_t)k0 * (uint64_t)ld * 2u;
         if (k0 + BKV <= seq) {
-            const uint64_t gb = gbase0 + (uint64_t)k0 * (uint64_t)ld * 2u;
 #pragma unroll
             for (int i = 0; i < NLD; ++i) dma16(gb, which ? vgo[i] : kgo[i], dst + i * 1024u);
         } else {
-            // last, ragged tile of the sequence: key rows past its end re-read the last row (masked as future keys)
+            // last, ragged tile of the sequence: key rows past its end re-read the last row (masked as future keys).  Offsets
+            // are from the tile's first row here too: from the sequence's they would not fit 32 bits for long sequences.
+            int l = lane;
+            asm volatile("" : "+v"(l));                      // worked out here, once an item, and not kept in registers
 #pragma unroll
             for (int i = 0; i < NLD; ++i) {
-                const int pidx = 64 * (NLD * wave + i) + lane, r = pidx / CH, slot = pidx % CH;
-                const int kr = k0 + r < seq ? k0 + r : seq - 1;
-                const int chunk = in_row(which ? (slot ^ vswz(r)) : (slot ^ kswz(r)));
-                dma16(gbase0, (uint32_t)(kr * ld + (which ? 2 * d : d) + chunk * 8) * 2u, dst + i * 1024u);
+                const int past = k0 + (64 * (NLD * wave + i) + l) / CH - (seq - 1);
+                dma16(gb, (which ? vgo[i] : kgo[i]) - (uint32_t)(past > 0 ? past : 0) * (uint32_t)ld * 2u, dst + i * 1024u);
             }
         }
     };
@@ -550,9 +551,10 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
 // odd multiples of 8 and buffers that are not 16-byte aligned take the plain kernel.  Measured at 4 x 2048 tokens, 32
 // heads of 80, bf16: 12.7 ms on the plain kernel (a workgroup per query row, K and V re-read per row), 0.165 ms here
 // (0.130 with probabilities rounded to 16 bits).
+// Any length; the offsets inside a tile of 64 keys are 32-bit.
 bool mfma_attention_supported(int seq, int n_heads, int d_head)
 {
-    return seq >= 1 && d_head >= 64 && d_head <= 128 && d_head % 16 == 0 && 3LL * seq * n_heads * d_head < 0x7fffffffLL;
+    return seq >= 1 && d_head >= 64 && d_head <= 128 && d_head % 16 == 0 && 3LL * BKV * n_heads * d_head < 0x7fffffffLL;
 }
 
 hipError_t launch_attention_mfma(const void *qkv, void *out, int dtype, int n_seq, int seq, int n_heads, int d_head,

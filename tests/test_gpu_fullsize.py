@@ -91,6 +91,26 @@ def test_attention_long_context_sampled_heads(seq):
         assert np.max(np.abs(got - want)) < 3 * 2.0**-8 * (1 + np.abs(want).max())
 
 
+@pytest.mark.parametrize("seq", [58304, 58270])
+def test_attention_beyond_32_bit_offsets(seq):
+    """One sequence whose q, k, v pass 2^32 bytes (the 175B width): whole key tiles and a ragged last one.  Rows around the
+    first and last tiles, first and last head, against 64 bits."""
+    heads, dh = 96, 128
+    d = heads * dh
+    assert 2 * 3 * seq * d > 2**32
+    qkv = torch.empty(seq, 3 * d, device=DEV, dtype=torch.bfloat16).normal_(generator=_gen(seq))
+    out = torch.full((seq, d), float("nan"), device=DEV, dtype=torch.bfloat16)
+    zo_amd.zo_kernel_attention(qkv, out, BF, 1, seq, heads, dh)
+    for head in (0, heads - 1):
+        q, k, v = (qkv[:, o * d + head * dh:o * d + (head + 1) * dh].double() for o in range(3))
+        for t in (0, 63, 64, seq // 2, seq - 65, seq - 64, seq - 2, seq - 1):
+            p = torch.softmax((k[:t + 1] @ q[t]) / dh**0.5, 0)
+            want = (p[:, None] * v[:t + 1]).sum(0)
+            got = out[t, head * dh:(head + 1) * dh].double()
+            assert float((got - want).abs().max()) < 3 * 2.0**-8 * float(want.abs().max()) + 2.0**-12, (head, t)
+    assert not bool(torch.isnan(out).any())
+
+
 @pytest.mark.parametrize("n_seq,seq,heads,dh", [(2, 1024, 40, 128), (2, 1100, 48, 64), (3, 300, 5, 128)])
 def test_attention_work_list_covers_every_item(n_seq, seq, heads, dh):
     """More (query tile, head, sequence) items than resident workgroups: several rounds over the per-XCD item list,
