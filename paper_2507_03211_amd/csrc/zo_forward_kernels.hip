@@ -548,8 +548,8 @@ hipError_t launch_linear(const void *x, const void *wt_p, const void *wt_m, cons
 hipError_t launch_attention(const void *qkv, void *out, int dtype, int n_seq, int seq, int n_heads, int d_head,
                             bool allow_mfma, hipStream_t s)
 {
-    // the matrix path reads and writes in pieces of 16 and 8 bytes; 64 and 128 have always gone there unasked
-    const bool aligned = d_head == 64 || d_head == 128 || ((uintptr_t)qkv % 16 == 0 && (uintptr_t)out % 16 == 0);
+    // the matrix path reads and writes in pieces of 16 and 8 bytes
+    const bool aligned = (uintptr_t)qkv % 16 == 0 && (uintptr_t)out % 16 == 0;
     if (allow_mfma && dtype != kFP32 && aligned && mfma_attention_supported(seq, n_heads, d_head))
         return launch_attention_mfma(qkv, out, dtype, n_seq, seq, n_heads, d_head, s);
     const dim3 grid(seq, n_heads, n_seq), block(128);

@@ -79,6 +79,26 @@ def test_unaligned_buffers_still_run():
     assert np.max(np.abs(got - want)) < 3 * ULP[zi.BF16] * (1 + np.abs(want).max())
 
 
+@pytest.mark.parametrize("dh", [64, 80, 128])
+@pytest.mark.parametrize("off_in,off_out", [(1, 0), (0, 1), (4, 4)])
+def test_unaligned_buffers_of_any_head_size(dh, off_in, off_out):
+    # off a 16-byte boundary by 2 and by 8 bytes: all head sizes leave the matrix path, bit for bit the same whichever buffer it is
+    n_seq, seq, heads = 1, 40, 2
+    flat = _qkv(n_seq, seq + 1, heads, dh, zi.BF16, 5).reshape(-1)
+    n = n_seq * seq * 3 * heads * dh
+    qkv = flat[1:1 + n].reshape(n_seq * seq, 3 * heads * dh)
+    want = _oracle(qkv, n_seq, seq, heads, dh)
+    src = torch.empty(n + 8, device=DEV, dtype=torch.bfloat16)[off_in:off_in + n].copy_(qkv.reshape(-1))
+    out = torch.full((n // 3 + 8,), 7.0, device=DEV, dtype=torch.bfloat16)
+    zo_amd.zo_kernel_attention(src, out[off_out:], zi.BF16, n_seq, seq, heads, dh)
+    got = out[off_out:off_out + n // 3].double().cpu().numpy().reshape(want.shape)
+    assert np.max(np.abs(got - want)) < 3 * ULP[zi.BF16] * (1 + np.abs(want).max())
+    assert bool((out[:off_out] == 7.0).all()) and bool((out[off_out + n // 3:] == 7.0).all())
+    other = torch.empty_like(out)
+    zo_amd.zo_kernel_attention(qkv, other, zi.BF16, n_seq, seq, heads, dh)          # 2 bytes off, on the plain kernel
+    assert torch.equal(other[:n // 3], out[off_out:off_out + n // 3])
+
+
 @pytest.mark.parametrize("dtype", [zi.BF16, zi.FP16])
 @pytest.mark.parametrize("n_seq,seq,heads,dh", [(40, 140, 9, 96), (1, 700, 3, 112), (2, 33, 2, 80)])     # 720 items on 512 workgroups
 def test_values_that_are_not_finite_reach_the_rows_that_see_them_and_no_other(dtype, n_seq, seq, heads, dh):
