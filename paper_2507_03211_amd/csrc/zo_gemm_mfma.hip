@@ -21,6 +21,7 @@
 //  * linear_mfma_small_kernel, 64 x 64 tiles, one workgroup per tile and two of them per CU: any K, and shapes so small
 //    that what counts is how many CUs take part.
 // pick_tile() at the end chooses between the tile shapes.
+#include "zo_device_once.h"
 #include "zo_kernels.h"
 #include "zo_types.hip.h"
 
@@ -713,12 +714,11 @@ template <int DT, int EPI, class SH> hipError_t launch_pipe(const Args &a)
     const int want = (total + 7) / 8 * 8;
     const dim3 grid(want < n_cu ? want : n_cu), block(256);
     auto kern = linear_mfma_pipe_kernel<DT, EPI, SH>;
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, SH::lds_bytes(EPI));
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
+    static std::atomic<uint64_t> lds_allowed{0};
+    const hipError_t e = once_per_device(lds_allowed, [&] {
+        return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, SH::lds_bytes(EPI));
+    });
+    if (e != hipSuccess) return e;
     kern<<<grid, block, SH::lds_bytes(EPI), a.s>>>((const uint16_t *)a.x, (const uint16_t *)a.wt_p, (const uint16_t *)a.wt_m, (const uint16_t *)a.b_p,
                                                    (const uint16_t *)a.b_m, a.y, a.m_half, a.n, a.k, tiles_m, tiles_n, total);
     return hipGetLastError();
@@ -728,12 +728,11 @@ template <int DT, int EPI, int TN> hipError_t launch_small(const Args &a)
 {
     const int tiles_m = (a.m_half + 63) / 64, tiles_n = (a.n + 64 * TN - 1) / (64 * TN), total = a.n_sign * tiles_m * tiles_n;
     auto kern = linear_mfma_small_kernel<DT, EPI, TN>;
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kSmallLdsBytes<TN>);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
+    static std::atomic<uint64_t> lds_allowed{0};
+    const hipError_t e = once_per_device(lds_allowed, [&] {
+        return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kSmallLdsBytes<TN>);
+    });
+    if (e != hipSuccess) return e;
     kern<<<dim3((total + 7) / 8 * 8), dim3(256), kSmallLdsBytes<TN>, a.s>>>((const uint16_t *)a.x, (const uint16_t *)a.wt_p, (const uint16_t *)a.wt_m,
                                                                             (const uint16_t *)a.b_p, (const uint16_t *)a.b_m, a.y, a.m_half, a.n, a.k,
                                                                             tiles_m, tiles_n, total);
