@@ -39,6 +39,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 namespace {
 
 constexpr int BK = 64;                      // contraction slab; k is a multiple of it
+constexpr int kMaxColumns = 1 << 24;        // 16 fp32 rows within 2^30 bytes: what an epilogue pass addresses with 32 bits
 
 template <int DT> __device__ __forceinline__ f32x16 mfma32(const uint4 &a, const uint4 &b, const f32x16 &c)
 {
@@ -203,41 +204,57 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[TN][TM], char *st
                 bvals[tn][g][3] = Prec<DT>::w2f((uint16_t)(hi >> 16));
             }
     }
-    // Addresses: a wave-uniform base for the pass (scalar registers) plus a per-lane offset that is worked out once, and a
-    // row mask of one compare with a constant.  With a 64-bit address and both bounds worked out per row the epilogue
-    // was 1650 (16-bit outputs) / 2980 (residual) instructions per wave and 256 x 256 tile instead of 1390 / 2150.
+    // Addresses: a wave-uniform base for the pass (scalar registers) plus a per-lane offset that is worked out once.  With a
+    // 64-bit address and both bounds worked out per row the epilogue was 1650 (16-bit outputs) / 2980 (residual)
+    // instructions per wave and 256 x 256 tile instead of 1390 / 2150.
+    // 16-bit outputs: a row mask of one compare with a constant.  fp32: buffer accesses, which drop (or read as zero) what
+    // lies past the pass's last row, and lanes whose columns lie past the end point behind any buffer.  With a branch
+    // around each piece the compiler cannot count what is under way and lets every piece of the residual epilogue wait for
+    // all memory operations before it, the stores of the piece before included: us, m_half x n x k, code with both bounds
+    // per row / branches / here, residual: 8192 x 4096 x 1024 184 / 188 / 175, 2794 x 16304 x 512 193 / 205 / 185, 8192 x
+    // 5120 x 5120 670 / 680 / 656.  (16-bit outputs wait for nothing here; as buffer stores they were up to 6 % slower.)
     constexpr int ES = kOut16 ? 2 : 4;
     constexpr int NBV = 64 % LPR == 0 ? 1 : 3;                   // a lane's column and row step repeat after this many pieces
     constexpr int RSTEP = 64 * NBV / LPR;                        // rows between those
     static_assert(64 * NBV % LPR == 0 && NIO % NBV == 0, "pieces repeat");
     const int row0 = m0 + wm * 32 * TM;
     const uint64_t ybase = uniform64((uint64_t)(uintptr_t)y + (((uint64_t)sign * m_half + row0) * n + ncol0) * ES);
+    constexpr uint32_t kOutside = 0xc0000000u;                   // with a pass's offsets on top still below 2^32 (kMaxColumns)
     uint32_t voff[NBV];
-#pragma unroll
-    for (int v = 0; v < NBV; ++v) voff[v] = (uint32_t)((64 * v + lane) / LPR) * (uint32_t)n * ES + (uint32_t)((64 * v + lane) % LPR) * 16u;
-    typedef __attribute__((address_space(1))) f32x4 *out4;
-    const uint64_t step = (uint64_t)RSTEP * (uint32_t)n * ES;
-    // piece i of the pass that starts at the wave-uniform address `at`, which moves on with every NBV pieces
-    auto piece = [&](uint64_t at, int i) { return (out4)((__attribute__((address_space(1))) char *)(uintptr_t)at + voff[i % NBV]); };
-    uint64_t at_load = ybase, at_store = ybase;
     int rows_left[NBV];          // rows from the lane's first one to the end of the output; none where its columns lie past the end
 #pragma unroll
-    for (int v = 0; v < NBV; ++v) rows_left[v] = ncol0 + (64 * v + lane) % LPR * (16 / ES) < n ? m_half - row0 - (64 * v + lane) / LPR : 0;
+    for (int v = 0; v < NBV; ++v) {
+        const int r = (64 * v + lane) / LPR, c = (64 * v + lane) % LPR;
+        const bool in = ncol0 + c * (16 / ES) < n;
+        rows_left[v] = in ? m_half - row0 - r : 0;
+        voff[v] = kOut16 || in ? (uint32_t)r * (uint32_t)n * ES + (uint32_t)c * 16u : kOutside;
+    }
+    const uint32_t step = (uint32_t)RSTEP * (uint32_t)n * ES;
+    // 16-bit: piece i of the pass that starts at the wave-uniform address `at`, which moves on with every NBV pieces
+    typedef __attribute__((address_space(1))) f32x4 *out4;
+    auto piece = [&](uint64_t at, int i) { return (out4)((__attribute__((address_space(1))) char *)(uintptr_t)at + voff[i % NBV]); };
     auto valid = [&](int pass, int i) { return pass * RP + i / NBV * RSTEP < rows_left[i % NBV]; };
+    uint64_t at_store = ybase;
+    // fp32: the rows of a pass that exist, up to the last one's last column, and piece i's offset in them
+    auto pass_rows = [&](int pass) {
+        const int left = m_half - row0 - pass * RP, rows = left < RP ? left : RP;
+        const uint32_t bytes = left > 0 && ncol0 < n ? ((uint32_t)(rows - 1) * (uint32_t)n + (uint32_t)(n - ncol0)) * ES : 0u;
+        const uint64_t first = ybase + (uint64_t)pass * RP * (uint32_t)n * ES;
+        return __builtin_amdgcn_make_buffer_rsrc((void *)(uintptr_t)first, 0, __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
+    };
+    auto offset = [&](int i) { return voff[i % NBV] + (uint32_t)(i / NBV) * step; };
+    constexpr int kNonTemporal = 2;                              // of a buffer access' cache policy
     // Residual epilogue: the reads of the running sum that a pass needs are all issued one pass ahead
     // (a load may not overtake an earlier store that the compiler cannot tell apart from it).  Reading
     // further ahead (two passes, which is what the registers allow) changes nothing: what the tile waits
     // for is the bandwidth of all workgroups' read-modify-write bursts arriving together, not one latency.
     f32x4 hres[2][EPI == 2 ? NIO : 1];
     auto load_res = [&](int pass, f32x4 (&h)[EPI == 2 ? NIO : 1]) {
+        // read once, written once: neither the running sum nor any output is worth an L2 line that
+        // an operand slab could keep (non-temporal loads and stores)
+        const auto rows = pass_rows(pass);
 #pragma unroll
-        for (int i = 0; i < NIO; ++i) {
-            // read once, written once: neither the running sum nor any output is worth an L2 line that
-            // an operand slab could keep (non-temporal loads and stores)
-            h[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (valid(pass, i)) h[i] = __builtin_nontemporal_load(piece(at_load, i));
-            if (i % NBV == NBV - 1) at_load = uniform64(at_load + step);
-        }
+        for (int i = 0; i < NIO; ++i) h[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rows, offset(i), 0, kNonTemporal));
     };
     float bias4[EPI == 2 ? NBV : 1][4] = {};
     if constexpr (EPI == 2) {
@@ -293,28 +310,28 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[TN][TM], char *st
                 }
         }
         asm volatile("" ::: "memory");      // the wave's LDS operations execute in order; keep the compiler to it too
+        if constexpr (kOut16) {
 #pragma unroll
-        for (int i = 0; i < NIO; ++i) {
-            const int r = (64 * i + lane) / LPR, c = (64 * i + lane) % LPR;
-            if constexpr (kOut16) {
+            for (int i = 0; i < NIO; ++i) {
+                const int r = (64 * i + lane) / LPR, c = (64 * i + lane) % LPR;
                 u32x4 q = *(const u32x4 *)(stage + r * PITCH + ((kXor ? c ^ chunk16(r) : c) << 4));
                 if (kXor && i * 64 / LPR >= 16) q = u32x4{q.z, q.w, q.x, q.y};
                 if (valid(pass, i)) __builtin_nontemporal_store(__builtin_bit_cast(f32x4, q), piece(at_store, i));
-            } else {
-                const f32x4 q = *(const f32x4 *)(stage + r * PITCH + ((kXor ? c ^ (r & (NRUN - 1)) : c) << 4));
-                if (valid(pass, i)) {
-                    const out4 p = piece(at_store, i);
-                    if constexpr (EPI == 2) {
-                        f32x4 h = hres[pass & 1][i];
-                        const float *b4 = bias4[i % NBV];
-                        h.x += q.x + b4[0]; h.y += q.y + b4[1]; h.z += q.z + b4[2]; h.w += q.w + b4[3];
-                        __builtin_nontemporal_store(h, p);
-                    } else {
-                        *p = q;
-                    }
-                }
+                if (i % NBV == NBV - 1) at_store = uniform64(at_store + step);
             }
-            if (i % NBV == NBV - 1) at_store = uniform64(at_store + step);
+        } else {
+            const auto rows = pass_rows(pass);
+#pragma unroll
+            for (int i = 0; i < NIO; ++i) {
+                const int r = (64 * i + lane) / LPR, c = (64 * i + lane) % LPR;
+                f32x4 q = *(const f32x4 *)(stage + r * PITCH + ((kXor ? c ^ (r & (NRUN - 1)) : c) << 4));
+                if constexpr (EPI == 2) {
+                    const f32x4 h = hres[pass & 1][i];
+                    const float *b4 = bias4[i % NBV];
+                    q = f32x4{h.x + (q.x + b4[0]), h.y + (q.y + b4[1]), h.z + (q.z + b4[2]), h.w + (q.w + b4[3])};
+                }
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, q), rows, offset(i), 0, EPI == 2 ? kNonTemporal : 0);
+            }
         }
         asm volatile("" ::: "memory");
     }
@@ -835,7 +852,7 @@ template <int DT> hipError_t launch_t(const Args &a, int epi)
 
 int mfma_ce_partials(int n_sign, int m_half, int n, int k) { return wide_strips(n_sign, m_half, n, k) ? 2 * ((n + 255) / 256) : 2 * ((n + 127) / 128); }
 
-bool mfma_linear_supported(int m_half, int n, int k) { return m_half >= 1 && n >= 8 && n % 8 == 0 && k >= BK && k % BK == 0; }
+bool mfma_linear_supported(int m_half, int n, int k) { return m_half >= 1 && n >= 8 && n < kMaxColumns && n % 8 == 0 && k >= BK && k % BK == 0; }
 
 hipError_t launch_linear_mfma(const void *x, const void *wt_p, const void *wt_m, const void *b_p, const void *b_m, void *y,
                               int dtype, int n_sign, int m_half, int n, int k, int epilogue, hipStream_t s)
