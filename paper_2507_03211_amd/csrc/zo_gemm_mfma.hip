@@ -158,9 +158,9 @@ __device__ __forceinline__ void tile_at(int lin, int tiles_m, int tiles_n, int &
 }
 
 // Epilogues 0 - 3 of a wave's 32 TM x 32 TN outputs (rows m0 + wm 32 TM .., columns n0 + wn 32 TN .. of sign `sign`).
-// `stage`: kTileStageBytes<TN> bytes of LDS that are this wave's alone.
+// `stage`: kTileStageBytes<TN> bytes of LDS that are this wave's alone.  NT: non-temporal accesses (see launch_small).
 template <int TN> constexpr int kTileStageBytes = (TN & (TN - 1)) ? 2048 * TN + 512 : 2048 * TN;
-template <int DT, int EPI, int TM, int TN>
+template <int DT, int EPI, int TM, int TN, bool NT>
 __device__ __forceinline__ void store_tile(const f32x16 (&acc)[TN][TM], char *stage, const uint16_t *__restrict__ bias, void *__restrict__ y,
                                            int sign, int m_half, int n, int m0, int n0, int wm, int wn, int lane)
 {
@@ -243,7 +243,7 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[TN][TM], char *st
         return __builtin_amdgcn_make_buffer_rsrc((void *)(uintptr_t)first, 0, __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
     };
     auto offset = [&](int i) { return voff[i % NBV] + (uint32_t)(i / NBV) * step; };
-    constexpr int kNonTemporal = 2;                              // of a buffer access' cache policy
+    constexpr int kPolicy = NT && EPI == 2 ? 2 : 0;              // of a buffer access: non-temporal or not
     // Residual epilogue: the reads of the running sum that a pass needs are all issued one pass ahead
     // (a load may not overtake an earlier store that the compiler cannot tell apart from it).  Reading
     // further ahead (two passes, which is what the registers allow) changes nothing: what the tile waits
@@ -254,7 +254,7 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[TN][TM], char *st
         // an operand slab could keep (non-temporal loads and stores)
         const auto rows = pass_rows(pass);
 #pragma unroll
-        for (int i = 0; i < NIO; ++i) h[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rows, offset(i), 0, kNonTemporal));
+        for (int i = 0; i < NIO; ++i) h[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rows, offset(i), 0, kPolicy));
     };
     float bias4[EPI == 2 ? NBV : 1][4] = {};
     if constexpr (EPI == 2) {
@@ -316,7 +316,10 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[TN][TM], char *st
                 const int r = (64 * i + lane) / LPR, c = (64 * i + lane) % LPR;
                 u32x4 q = *(const u32x4 *)(stage + r * PITCH + ((kXor ? c ^ chunk16(r) : c) << 4));
                 if (kXor && i * 64 / LPR >= 16) q = u32x4{q.z, q.w, q.x, q.y};
-                if (valid(pass, i)) __builtin_nontemporal_store(__builtin_bit_cast(f32x4, q), piece(at_store, i));
+                if (valid(pass, i)) {
+                    if constexpr (NT) __builtin_nontemporal_store(__builtin_bit_cast(f32x4, q), piece(at_store, i));
+                    else *piece(at_store, i) = __builtin_bit_cast(f32x4, q);
+                }
                 if (i % NBV == NBV - 1) at_store = uniform64(at_store + step);
             }
         } else {
@@ -330,7 +333,7 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[TN][TM], char *st
                     const float *b4 = bias4[i % NBV];
                     q = f32x4{h.x + (q.x + b4[0]), h.y + (q.y + b4[1]), h.z + (q.z + b4[2]), h.w + (q.w + b4[3])};
                 }
-                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, q), rows, offset(i), 0, EPI == 2 ? kNonTemporal : 0);
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, q), rows, offset(i), 0, kPolicy);
             }
         }
         asm volatile("" ::: "memory");
@@ -591,7 +594,7 @@ __global__ __launch_bounds__(256) void linear_mfma_pipe_kernel(const uint16_t *_
             // finished reading that stage before the slab's barrier, and the next loads into the slice are this wave's
             // own, issued after the epilogue), or in an area of its own
             char *stage = SH::kOwnArea ? (char *)(smem + kWEnd) + wave * kTileStageBytes<TN> : (char *)(smem + xfree) + wave * (1024 * LX);
-            store_tile<DT, EPI, TM, TN>(acc, stage, bias, y, sign, m_half, n, m0, n0, wm, wn, lane);
+            store_tile<DT, EPI, TM, TN, true>(acc, stage, bias, y, sign, m_half, n, m0, n0, wm, wn, lane);
         }
         if (!has_next) break;
         cur = nxt;
@@ -603,19 +606,19 @@ __global__ __launch_bounds__(256) void linear_mfma_pipe_kernel(const uint16_t *_
 
 // ------------------------------------------------------------------ small tiles
 // One output tile of 64 x (64 TN) per workgroup of 2 x 2 waves, each with 1 x TN matrix tiles; slabs of 64 k through a ring
-// of ST LDS stages, one barrier per slab, and a second workgroup on the CU to work while this one waits.  For shapes
+// of up to ST LDS stages, one barrier per slab, and a second workgroup on the CU to work while this one waits.  For shapes
 // with few tiles: a slab of a larger tile is loaded at about 58 bytes a nanosecond and CU whatever the shape (what the
 // in-order return of loads that partly miss the L2 allows), so the more CUs take part, the sooner the operands are in.
 // m_half 160, n 2560, k 10240: 155 us on 128 x 128 register-staged tiles, 95 on pipelined 128 x 128, 50 here (240 CUs).
 constexpr int kSmallStages = 4;
-template <int TN> constexpr int kSmallLdsBytes = kSmallStages * (64 + 64 * TN) * BK * 2;
-template <int DT, int EPI, int TN>
+template <int TN> constexpr int kSmallStageBytes = (64 + 64 * TN) * BK * 2;
+template <int DT, int EPI, int TN, bool NT>
 __global__ __launch_bounds__(256, 2) void linear_mfma_small_kernel(
     const uint16_t *__restrict__ x, const uint16_t *__restrict__ wt_p, const uint16_t *__restrict__ wt_m, const uint16_t *__restrict__ b_p,
     const uint16_t *__restrict__ b_m, void *__restrict__ y, int m_half, int n, int k, int tiles_m, int tiles_n, int total)
 {
     constexpr int ST = kSmallStages, BM = 64, BN = 64 * TN, LX = 2, LW = 2 * TN, L = LX + LW, CPR = BK / 8;
-    constexpr uint32_t kStageBytes = (uint32_t)(BM + BN) * BK * 2;
+    constexpr uint32_t kStageBytes = kSmallStageBytes<TN>;
     extern __shared__ __attribute__((aligned(16))) uint4 smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -696,9 +699,9 @@ __global__ __launch_bounds__(256, 2) void linear_mfma_small_kernel(
         ce_partial_row<TN>(a, n0 + wn * 32 * TN, fh, n, mr < m_half, ((const int32_t *)b_p)[row], (float *)b_m + row,
                            (float2 *)y + row * n_partial + (tcol * 2 + wn));
     } else {
-        static_assert(4 * kTileStageBytes<TN> <= ST * (int)kStageBytes, "the staging areas fit the ring");
+        static_assert(4 * kTileStageBytes<TN> <= (int)kStageBytes, "the staging areas fit the ring, of one stage at least");
         __syncthreads();                                          // every wave is done with the ring
-        store_tile<DT, EPI, 1, TN>(acc, (char *)smem + wave * kTileStageBytes<TN>, sign ? b_m : b_p, y, sign, m_half, n, m0, n0, wm, wn, lane);
+        store_tile<DT, EPI, 1, TN, NT>(acc, (char *)smem + wave * kTileStageBytes<TN>, sign ? b_m : b_p, y, sign, m_half, n, m0, n0, wm, wn, lane);
     }
 }
 
@@ -741,19 +744,37 @@ template <int DT, int EPI, class SH> hipError_t launch_pipe(const Args &a)
     return hipGetLastError();
 }
 
-template <int DT, int EPI, int TN> hipError_t launch_small(const Args &a)
+template <int DT, int EPI, int TN, bool NT> hipError_t launch_small_t(const Args &a)
 {
     const int tiles_m = (a.m_half + 63) / 64, tiles_n = (a.n + 64 * TN - 1) / (64 * TN), total = a.n_sign * tiles_m * tiles_n;
-    auto kern = linear_mfma_small_kernel<DT, EPI, TN>;
+    auto kern = linear_mfma_small_kernel<DT, EPI, TN, NT>;
     static std::atomic<uint64_t> lds_allowed{0};
     const hipError_t e = once_per_device(lds_allowed, [&] {
-        return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kSmallLdsBytes<TN>);
+        return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kSmallStages * kSmallStageBytes<TN>);
     });
     if (e != hipSuccess) return e;
-    kern<<<dim3((total + 7) / 8 * 8), dim3(256), kSmallLdsBytes<TN>, a.s>>>((const uint16_t *)a.x, (const uint16_t *)a.wt_p, (const uint16_t *)a.wt_m,
-                                                                            (const uint16_t *)a.b_p, (const uint16_t *)a.b_m, a.y, a.m_half, a.n, a.k,
-                                                                            tiles_m, tiles_n, total);
+    // no more stages than there are slabs: with one or two, 8 or 5 workgroups fit a CU instead of 2, and what such a shape
+    // takes is the workgroups' latency (both signs 6217 x 6320 x 64, 16-bit outputs: 70 -> 41 us)
+    const int stages = a.k / BK < kSmallStages ? a.k / BK : kSmallStages;
+    kern<<<dim3((total + 7) / 8 * 8), dim3(256), stages * kSmallStageBytes<TN>, a.s>>>((const uint16_t *)a.x, (const uint16_t *)a.wt_p,
+                                                                                       (const uint16_t *)a.wt_m, (const uint16_t *)a.b_p,
+                                                                                       (const uint16_t *)a.b_m, a.y, a.m_half, a.n, a.k,
+                                                                                       tiles_m, tiles_n, total);
     return hipGetLastError();
+}
+
+// A wave's rows of a 64 x 64 tile are 64 (16-bit) or 128 bytes long: parts of cache lines, all of them when n is not a
+// multiple of 64.  Written past the L2 each part is a memory transaction of its own, left there it meets the rest of its
+// line.  fp32 read-modify-write: always left in the L2 (median 1.02 - 1.2 times as fast, 0.87 - 1.6, the more the shorter the
+// contraction).  16-bit: left there where one or two slabs make the outputs most of the traffic and rows share lines (5740 x
+// 4592 x 64 57 -> 26 us, 6217 x 6320 x 128 76 -> 57); past it otherwise, where operands want the room (2 % from 512 on; whole
+// lines 4096 x 16384 x 64 70 -> 58).
+template <int DT, int EPI, int TN> hipError_t launch_small(const Args &a)
+{
+    if constexpr (EPI < 2) {
+        if (a.k >= 3 * BK || a.n % 64 == 0) return launch_small_t<DT, EPI, TN, true>(a);
+    }
+    return launch_small_t<DT, EPI, TN, false>(a);
 }
 
 enum Tile { T256x256, T256x192, T256x128, T192x128, T128x128, T64x64, kTiles };

@@ -122,3 +122,13 @@ def test_lmhead_of_large_logits_with_full_mantissas(m_half, d, vocab, sign):
     want = torch.logsumexp(logits, 1) - logits.gather(1, target.long()[:, None])[:, 0]
     # the products are exact; a sum of equal terms in fp32 and one rounding of the pair's correction, as above
     assert bool(((loss - want).abs() <= 1e-6 + 1e-6 * want.abs()).all())
+
+
+@pytest.mark.parametrize("dtype", [zi.BF16, zi.FP16])
+@pytest.mark.parametrize("epi", [0, 1, 2, 3])
+@pytest.mark.parametrize("m_half,n", [(65, 128), (70, 136)])
+@pytest.mark.parametrize("slabs", [1, 2, 3, 4, 5])
+def test_small_tile_of_few_slabs(m_half, n, slabs, epi, dtype):
+    # 64 x 64 tiles: a ring of as many stages as there are slabs, up to four; rows of whole cache lines and others, whose
+    # 16-bit outputs of one or two slabs are stored another way
+    test_linear_tiles(m_half, n, 64 * slabs, epi, dtype)
