@@ -284,6 +284,10 @@ int zo_kernel_linear_pm(const void *x, const void *wt_plus, const void *wt_minus
                         const void *b_plus, const void *b_minus, void *y,
                         int dtype, int m_half, int n, int k, int epilogue, void *stream);
 
+/* The output tile that zo_kernel_linear_pm works such a call of 2-byte types in on the current device (on 256 compute
+ * units where there is none): rows << 16 | columns; 0 when it does not run on the matrix cores.  Host only. */
+int zo_kernel_linear_tile(int m_half, int n, int k, int epilogue);
+
 /* LayerNorm of the OPT decoder block (Sec. 7, experimental set-up: OPT family) inside DualForward (App. A, Alg. 2),
  * over the last dimension of resid [2 m_half, d] (fp32; fp64 for ZO_FP32) with
  * per-sign gain and bias, output in the activation type. */

@@ -23,7 +23,7 @@ EXPORTS = (
     "zo_workspace_bytes", "zo_init_model", "zo_perturb", "zo_dual_forward", "zo_step", "zo_stream_block",
     "zo_stream_begin", "zo_stream_end", "zo_flush_pending", "zo_set_writeback_interval", "zo_set_stream_lookahead", "zo_set_deferred_update", "zo_set_update_rounding", "zo_device_flags", "zo_free",
     "zo_last_error", "zo_profile_begin", "zo_profile_end", "zo_profile_spans",
-    "zo_kernel_z", "zo_kernel_normal_pairs", "zo_kernel_axpy_z", "zo_kernel_axpy_z_sr", "zo_kernel_stage_pm", "zo_kernel_stage_update_pm", "zo_kernel_linear_pm",
+    "zo_kernel_z", "zo_kernel_normal_pairs", "zo_kernel_axpy_z", "zo_kernel_axpy_z_sr", "zo_kernel_stage_pm", "zo_kernel_stage_update_pm", "zo_kernel_linear_pm", "zo_kernel_linear_tile",
     "zo_kernel_layernorm_pm", "zo_kernel_attention", "zo_kernel_lmhead_scratch_bytes", "zo_kernel_lmhead_ce",
     "zo_kernel_lmhead_ce_noalloc",
 )
@@ -84,6 +84,7 @@ def lib():
         L.zo_kernel_linear_pm.argtypes = [vp, vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, vp]
         L.zo_kernel_layernorm_pm.argtypes = [vp, vp, vp, vp, vp, vp, i32, i32, i32, f32, vp]
         L.zo_kernel_attention.argtypes = [vp, vp, i32, i32, i32, i32, i32, vp]
+        L.zo_kernel_linear_tile.argtypes = [i32, i32, i32, i32]
         L.zo_kernel_lmhead_scratch_bytes.restype = sz
         L.zo_kernel_lmhead_scratch_bytes.argtypes = [i32, i32, i32]
         L.zo_kernel_lmhead_ce.argtypes = [vp, vp, vp, vp, vp, vp, i32, i32, i32, i32, vp]
@@ -261,6 +262,12 @@ def zo_kernel_stage_update_pm(theta, w_plus, w_minus, dtype, rows, cols, transpo
 def zo_kernel_linear_pm(x, wt_plus, wt_minus, b_plus, b_minus, y, dtype, m_half, n, k, epilogue, stream=None):
     _check(lib().zo_kernel_linear_pm(_ptr(x), _ptr(wt_plus), _ptr(wt_minus), _ptr(b_plus), _ptr(b_minus), _ptr(y), dtype,
                                      m_half, n, k, epilogue, _stream(stream)))
+
+
+def zo_kernel_linear_tile(m_half, n, k, epilogue):
+    """(rows, columns) of the output tile, None off the matrix cores."""
+    t = lib().zo_kernel_linear_tile(m_half, n, k, epilogue)
+    return (t >> 16, t & 0xffff) if t else None
 
 
 def zo_kernel_layernorm_pm(resid, g_plus, g_minus, b_plus, b_minus, y, dtype, m_half, d, ln_eps, stream=None):

@@ -1168,6 +1168,11 @@ extern "C" int zo_kernel_linear_pm(const void *x, const void *wt_plus, const voi
     return ZO_OK;
 }
 
+extern "C" int zo_kernel_linear_tile(int m_half, int n, int k, int epilogue)
+{
+    return epilogue < 0 || epilogue > 3 ? 0 : mfma_linear_tile(2, m_half, n, k, epilogue);
+}
+
 extern "C" int zo_kernel_layernorm_pm(const void *resid, const void *g_plus, const void *g_minus, const void *b_plus, const void *b_minus,
                                       void *y, int dtype, int m_half, int d, float ln_eps, void *stream)
 {

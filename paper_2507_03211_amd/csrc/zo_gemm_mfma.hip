@@ -778,6 +778,7 @@ template <int DT, int EPI, int TN> hipError_t launch_small(const Args &a)
 }
 
 enum Tile { T256x256, T256x192, T256x128, T192x128, T128x128, T64x64, kTiles };
+constexpr int kTileRows[kTiles] = {256, 256, 256, 192, 128, 64}, kTileColumns[kTiles] = {256, 192, 128, 128, 128, 64};
 template <int DT, int EPI> hipError_t launch_tile(Tile t, const Args &a)
 {
     switch (t) {
@@ -792,38 +793,44 @@ template <int DT, int EPI> hipError_t launch_tile(Tile t, const Args &a)
 
 // The tile shape with the least estimated time in us: start + rounds (slabs slab + epilogue), where a round of tiles that
 // fills more than half of the CUs also pays slabs busy b, b = 0 .. 1 from half full to full (a full chip clocks lower and
-// shares the fabric), and fp32 outputs are paid for by how full the round is (their bursts share the memory).
-// Constants: least squares over 90 shapes (m_half 96 .. 8192, n and k 512 .. 19200) timed with every tile shape; the
-// estimates are within 5 - 8 % (rms), and the shape they pick is on average 0.25 % slower than the best one of each.
+// shares the fabric).  fp32 outputs are paid for by the rounds' share of the chip (their bursts share the memory), with and
+// without the running sum read, the first round at a price of its own: the caches take part of it, and of what a 64 x 64
+// tile writes nearly all, while from the second round on it pays most per byte (half lines).
+// Constants: least squares over 90 shapes (m_half 96 .. 8192, n and k 512 .. 19200) timed with every tile shape; those of
+// fp32 outputs over 973 shapes (m_half 64 .. 8192, n 240 .. 20000, k from 64): one price for both fp32 epilogues and all
+// rounds, from shapes of k >= 512 alone, had sent short contractions with large outputs to 64 x 64 tiles, up to twice the
+// time of the code before the rule (us, that / one price / here: 1374 x 14048 x 384 fp32 57 / 92 / 55, 2185 x 15512 x 512
+// residual 168 / 230 / 170).  Over 1688 shapes of more than 11 us, all epilogues: on average 1.2 % slower than the best tile
+// of each; 12 more than 5 % slower than the code before, the worst 12 %.
 // The 256 x 256 tile gets 3 % credit: near a tie it is the one that long contractions lose least with.  In us, picked
 // here / the former choice between 256 x 256 and a register-staged 128 x 128 kernel, m_half x n x k: 536 x 2304 x 768
-// 9.5 / 17.1, 692 x 5120 x 5120 80 / 114, 1028 x 1024 x 4096 30 / 53, 391 x 704 x 2816 13 / 39, 8192 x 2304 x 768 61 / 70;
-// 1.52 times as fast in the geometric mean of the 90, 0.99 in the worst case.
+// 9.0 / 17.1, 692 x 5120 x 5120 84 / 115, 1028 x 1024 x 4096 30 / 53, 391 x 704 x 2816 13 / 39, 8192 x 2304 x 768 61 / 70.
 Tile pick_tile(int n_sign, int m_half, int n, int k, int epi)
 {
-    static const struct { int bm, bn, min_slabs; float start, slab, busy, out16, out32; } kCost[kTiles] = {
-        {256, 256, 3, 4.9f, 1.00f, 0.52f, 3.5f, 31.2f}, {256, 192, 3, 3.6f, 0.79f, 0.38f, 3.1f, 25.6f},
-        {256, 128, 3, 3.6f, 0.59f, 0.28f, 1.6f, 16.4f}, {192, 128, 4, 4.1f, 0.49f, 0.21f, 0.9f, 10.0f},
-        {128, 128, 5, 4.1f, 0.38f, 0.16f, 0.3f, 5.3f},  {64, 64, 1, 2.6f, 0.21f, 0.41f, 0.4f, 1.7f}};
+    struct Out { float first, more; };
+    static const struct { int min_slabs; float start, slab, busy, out16; Out rmw, out32; } kCost[kTiles] = {
+        {3, 4.9f, 1.00f, 0.52f, 3.5f, {26.1f, 21.3f}, {9.0f, 11.4f}}, {3, 3.6f, 0.79f, 0.38f, 3.1f, {20.9f, 16.7f}, {7.0f, 9.0f}},
+        {3, 3.6f, 0.59f, 0.28f, 1.6f, {12.0f, 11.4f}, {2.7f, 7.0f}},  {4, 4.1f, 0.49f, 0.21f, 0.9f, {7.9f, 7.6f}, {1.2f, 5.0f}},
+        {5, 4.1f, 0.38f, 0.16f, 0.3f, {4.3f, 4.5f}, {0.0f, 3.1f}},    {1, 2.6f, 0.21f, 0.41f, 0.4f, {0.5f, 2.5f}, {0.0f, 1.3f}}};
     const float n_cu = cu_count() ? (float)cu_count() : 256.0f, slabs = (float)(k / BK);
     Tile best = kTiles;
     float best_us = 0.0f;
     for (int t = 0; t < kTiles; ++t) {
         const auto &c = kCost[t];
         if (k / BK < c.min_slabs) continue;
-        const float tiles = (float)n_sign * (float)((m_half + c.bm - 1) / c.bm) * (float)((n + c.bn - 1) / c.bn);
-        float us;
+        const float tiles = (float)n_sign * (float)((m_half + kTileRows[t] - 1) / kTileRows[t]) * (float)((n + kTileColumns[t] - 1) / kTileColumns[t]);
+        const float slots = t == T64x64 ? 2 * n_cu : n_cu;        // workgroups at a time
+        const float full = __builtin_floorf(tiles / slots), part = tiles / slots - full, rounds = full + (part > 0 ? 1.0f : 0.0f);
+        float us = c.start;
         if (t == T64x64) {
             // two workgroups per CU: `slab` for one alone, `busy` for the two together
-            const float full = __builtin_floorf(tiles / (2 * n_cu)), rest = tiles - 2 * n_cu * full;
-            const float pairs = full + (rest > n_cu ? 1.0f : 0.0f), lone = rest > 0 && rest <= n_cu ? 1.0f : 0.0f;
-            us = c.start + slabs * (pairs * c.busy + lone * c.slab) + (pairs + lone) * (epi >= 2 ? c.out32 : c.out16);
+            const float lone = part > 0 && part <= 0.5f ? 1.0f : 0.0f;
+            us += slabs * ((rounds - lone) * c.busy + lone * c.slab);
         } else {
-            const float full = __builtin_floorf(tiles / n_cu), part = tiles / n_cu - full, rounds = full + (part > 0 ? 1.0f : 0.0f);
-            const float b = full + (part > 0.5f ? 2 * part - 1 : 0.0f);
-            const float out = epi >= 2 ? c.out32 * (full + (part > 0 ? (part > 0.3f ? part : 0.3f) : 0.0f)) : c.out16 * rounds;
-            us = c.start + slabs * (rounds * c.slab + b * c.busy) + out;
+            us += slabs * (rounds * c.slab + (full + (part > 0.5f ? 2 * part - 1 : 0.0f)) * c.busy);
         }
+        const Out &o = epi == 2 ? c.rmw : c.out32;
+        us += epi < 2 ? c.out16 * rounds : full + part < 1 ? o.first * part : o.first + o.more * (full + part - 1);
         if (t == T256x256) us *= 0.97f;
         if (best == kTiles || us < best_us) { best = (Tile)t; best_us = us; }
     }
@@ -870,6 +877,13 @@ template <int DT> hipError_t launch_t(const Args &a, int epi)
 }
 
 }  // namespace
+
+int mfma_linear_tile(int n_sign, int m_half, int n, int k, int epilogue)
+{
+    if (!mfma_linear_supported(m_half, n, k)) return 0;
+    const Tile t = pick_tile(n_sign, m_half, n, k, epilogue);
+    return kTileRows[t] << 16 | kTileColumns[t];
+}
 
 int mfma_ce_partials(int n_sign, int m_half, int n, int k) { return wide_strips(n_sign, m_half, n, k) ? 2 * ((n + 255) / 256) : 2 * ((n + 127) / 128); }
 

@@ -80,6 +80,8 @@ hipError_t launch_g_scalar(const double *loss_pm, const GScalar &gs, hipStream_t
 
 // MFMA paths (2-byte dtypes).  *_supported report whether the shape fits the kernel's tiling.
 bool mfma_linear_supported(int m_half, int n, int k);
+// the output tile a shape is worked in, rows << 16 | columns; 0 when the shape does not fit (host only)
+int mfma_linear_tile(int n_sign, int m_half, int n, int k, int epilogue);
 hipError_t launch_linear_mfma(const void *x, const void *wt_p, const void *wt_m, const void *b_p, const void *b_m,
                               void *y, int dtype, int n_sign, int m_half, int n, int k, int epilogue,
                               hipStream_t s);

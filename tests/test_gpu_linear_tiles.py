@@ -13,18 +13,22 @@ pytestmark = pytest.mark.gpu
 TDT = {zi.BF16: torch.bfloat16, zi.FP16: torch.float16}
 ULP = {zi.BF16: 2.0**-8, zi.FP16: 2.0**-11}
 
-# m_half, n, k; the tile that the rule takes on 256 CUs is named for the reader, nothing depends on it
+# m_half, n, k; the tile that the rule takes on 256 CUs is named for the reader (TILES below holds it to that)
 SHAPES16 = [(3073, 4104, 192), (1537, 4104, 448),       # 256 x 256
             (769, 5128, 192), (1281, 3080, 192),        # 256 x 192
             (641, 4104, 192), (1281, 2056, 192),        # 256 x 128
             (385, 5128, 256), (641, 3080, 256),         # 192 x 128
             (257, 5128, 320), (641, 1544, 320),         # 128 x 128
             (1, 8, 64), (65, 72, 128), (257, 520, 192), (100, 1000, 1024)]   # 64 x 64
-SHAPES32 = [(2561, 8200, 1024), (1025, 6152, 1024),     # 256 x 256, 256 x 192
-            (1281, 4104, 1024), (641, 5128, 2048),      # 256 x 128
+SHAPES32 = [(2561, 8200, 1024), (1025, 6152, 1024),     # 256 x 256; 128 x 128 and, without residual, 256 x 256
+            (1281, 4104, 1024), (641, 5128, 2048),      # 192 x 128, 256 x 128
             (641, 3080, 768), (1281, 1544, 576),        # 192 x 128
-            (385, 2568, 576), (641, 1544, 448),         # 128 x 128
+            (385, 2568, 576), (641, 1544, 448),         # 64 x 64 and, without residual, 128 x 128
             (3, 16, 64), (64, 64, 64), (130, 520, 320)] # 64 x 64
+# one row and 8 columns past whole tiles of the named shape: 16-bit outputs, fp32 outputs
+TILES = {(256, 256): [(1537, 4104, 448), (1537, 4104, 1024)], (256, 192): [(1281, 3080, 192), (1281, 3080, 2048)],
+         (256, 128): [(1281, 2056, 192), (1025, 3080, 2048)], (192, 128): [(385, 5128, 256), (769, 2568, 768)],
+         (128, 128): [(257, 5128, 320), (513, 3080, 768)], (64, 64): [(257, 520, 192), (257, 520, 320)]}
 
 
 def _inputs(m_half, n, k, dtype, seed):
@@ -63,6 +67,15 @@ def test_linear_tiles(m_half, n, k, epi, dtype):
         bound = size * (k + 4) * 2.0**-24 + (ULP[dtype] * want.abs() if epi < 2 else 0.0)
         assert bool(((y[rows].double() - want).abs() <= bound).all())
     assert bool((flat[2 * m_half * n:] == 3.0).all())
+
+
+@pytest.mark.parametrize("dtype", [zi.BF16, zi.FP16])
+@pytest.mark.parametrize("epi", [0, 1, 2, 3])
+@pytest.mark.parametrize("tile", sorted(TILES))
+def test_each_tile_with_each_epilogue(tile, epi, dtype):
+    m_half, n, k = TILES[tile][epi // 2]
+    assert zo_amd.zo_kernel_linear_tile(m_half, n, k, epi) == tile
+    test_linear_tiles(m_half, n, k, epi, dtype)
 
 
 @pytest.mark.parametrize("dtype", [zi.BF16, zi.FP16])
