@@ -285,7 +285,8 @@ int zo_kernel_linear_pm(const void *x, const void *wt_plus, const void *wt_minus
                         int dtype, int m_half, int n, int k, int epilogue, void *stream);
 
 /* The output tile that zo_kernel_linear_pm works such a call of 2-byte types in on the current device (on 256 compute
- * units where there is none): rows << 16 | columns; 0 when it does not run on the matrix cores.  Host only. */
+ * units where there is none): rows << 16 | columns; 0 when it does not run on the matrix cores.  epilogue 4: the LM head's
+ * (zo_kernel_lmhead_ce, n = vocab, k = d).  Host only. */
 int zo_kernel_linear_tile(int m_half, int n, int k, int epilogue);
 
 /* LayerNorm of the OPT decoder block (Sec. 7, experimental set-up: OPT family) inside DualForward (App. A, Alg. 2),

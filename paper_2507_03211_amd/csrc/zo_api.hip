@@ -1170,7 +1170,7 @@ extern "C" int zo_kernel_linear_pm(const void *x, const void *wt_plus, const voi
 
 extern "C" int zo_kernel_linear_tile(int m_half, int n, int k, int epilogue)
 {
-    return epilogue < 0 || epilogue > 3 ? 0 : mfma_linear_tile(2, m_half, n, k, epilogue);
+    return epilogue < 0 || epilogue > 4 ? 0 : mfma_linear_tile(2, m_half, n, k, epilogue);
 }
 
 extern "C" int zo_kernel_layernorm_pm(const void *resid, const void *g_plus, const void *g_minus, const void *b_plus, const void *b_minus,

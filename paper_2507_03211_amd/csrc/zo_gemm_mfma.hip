@@ -846,22 +846,41 @@ bool wide_strips(int n_sign, int m_half, int n, int k)
     return tiles >= 128;
 }
 
-// Rows of the 256-column tile: 256, or 192 / 128 where few rows would leave a taller tile mostly empty.  A row costs 6 - 8 %
-// more in tiles of 192 (15 % up to 512 rows, where their rounds come out badly) and 9 - 13 % more in tiles of 128 (whose
-// LDS takes a third slab ahead).  In us, tiles of 256 / 192 / 128, vocabulary 50272: 1048 rows a sign, d 2048, 419 / 399 /
-// 428; 700 rows, d 1024, 148 / 159 / 161; 536 rows, d 768, 118 / 98 / 109; 300 rows 92 / 83 / 76; 100 rows 54 / 51 / 46.
-// (Taken while the epilogue spent one instruction more per logit, which was 1 - 2 % of each.)
+// Its tile.  256 columns wide: the height of least estimated time in us, start + slabs (rounds slab + r share) + rounds out +
+// r out_share, with r the rounds and the last one's fraction.  Constants: least squares over 1100 shapes (40 - 4500 rows a
+// sign, vocabularies 2 k - 64 k and OPT's 50272, d 192 - 2700) timed with each height; the picked one is on average 0.15 %
+// slower than the best.  (By padded rows alone, from one vocabulary, shorter tiles were taken where they need a round more:
+// 616 rows, d 1280, 6824 columns 31.8 us at 256, 37.4 at 128.)  In us, heights 256 / 192 / 128, vocabulary 50272: 1048
+// rows, d 2048, 419 / 399 / 428; 700 rows, d 1024, 148 / 159 / 161; 536 rows, d 768, 118 / 98 / 109; 300 rows 92 / 83 /
+// 76; 100 rows 54 / 51 / 46.  (These last while the epilogue spent one instruction more per logit, 1 - 2 % of each.)
+enum HeadTile { H256x256, H192x256, H128x256, H128x128, H64x128 };
+HeadTile pick_head(int n_sign, int m_half, int n, int k)
+{
+    if (!wide_strips(n_sign, m_half, n, k)) return k / BK > 4 ? H128x128 : H64x128;
+    static const struct { int rows, min_slabs; float start, slab, share, out, out_share; } kCost[3] = {
+        {256, 3, 9.2f, 0.99f, 0.44f, 3.6f, 0.0f}, {192, 3, 9.0f, 1.13f, 0.0f, 2.4f, 0.4f}, {128, 4, 9.2f, 0.86f, 0.0f, 1.3f, 0.3f}};
+    const float n_cu = cu_count() ? (float)cu_count() : 256.0f, slabs = (float)(k / BK);
+    HeadTile best = H256x256;
+    float best_us = 0.0f;
+    for (int t = 0; t < 3; ++t) {
+        const auto &c = kCost[t];
+        if (k / BK < c.min_slabs) continue;
+        const float r = (float)n_sign * (float)((m_half + c.rows - 1) / c.rows) * (float)((n + 255) / 256) / n_cu;
+        const float us = c.start + slabs * (__builtin_ceilf(r) * c.slab + r * c.share) + __builtin_ceilf(r) * c.out + r * c.out_share;
+        if (t == 0 || us < best_us) { best = (HeadTile)t; best_us = us; }
+    }
+    return best;
+}
+
 template <int DT> hipError_t launch_ce(const Args &a)
 {
-    if (wide_strips(a.n_sign, a.m_half, a.n, a.k)) {
-        auto padded = [&](int bm) { return (float)((a.m_half + bm - 1) / bm * bm); };
-        const float c256 = padded(256), c192 = (a.m_half > 512 ? 1.08f : 1.15f) * padded(192), c128 = 1.12f * padded(128);
-        if (c128 < c192 && c128 < c256 && a.k / BK > 3) return launch_pipe<DT, 4, Shape<2, 4, 3>>(a);
-        if (c192 < c256) return launch_pipe<DT, 4, Shape<3, 4, 2>>(a);
-        return launch_pipe<DT, 4, Shape<4, 4, 2>>(a);
+    switch (pick_head(a.n_sign, a.m_half, a.n, a.k)) {
+    case H256x256: return launch_pipe<DT, 4, Shape<4, 4, 2>>(a);
+    case H192x256: return launch_pipe<DT, 4, Shape<3, 4, 2>>(a);
+    case H128x256: return launch_pipe<DT, 4, Shape<2, 4, 3>>(a);
+    case H128x128: return launch_pipe<DT, 4, Shape<2, 2, 4>>(a);
+    default: return launch_small<DT, 4, 2>(a);
     }
-    if (a.k / BK > 4) return launch_pipe<DT, 4, Shape<2, 2, 4>>(a);
-    return launch_small<DT, 4, 2>(a);
 }
 
 template <int DT> hipError_t launch_t(const Args &a, int epi)
@@ -881,6 +900,10 @@ template <int DT> hipError_t launch_t(const Args &a, int epi)
 int mfma_linear_tile(int n_sign, int m_half, int n, int k, int epilogue)
 {
     if (!mfma_linear_supported(m_half, n, k)) return 0;
+    if (epilogue == 4) {
+        static const int kHead[] = {256 << 16 | 256, 192 << 16 | 256, 128 << 16 | 256, 128 << 16 | 128, 64 << 16 | 128};
+        return kHead[pick_head(n_sign, m_half, n, k)];
+    }
     const Tile t = pick_tile(n_sign, m_half, n, k, epilogue);
     return kTileRows[t] << 16 | kTileColumns[t];
 }

@@ -25,6 +25,10 @@ SHAPES32 = [(2561, 8200, 1024), (1025, 6152, 1024),     # 256 x 256; 128 x 128 a
             (641, 3080, 768), (1281, 1544, 576),        # 192 x 128
             (385, 2568, 576), (641, 1544, 448),         # 64 x 64 and, without residual, 128 x 128
             (3, 16, 64), (64, 64, 64), (130, 520, 320)] # 64 x 64
+# LM head: rows a sign, d, vocabulary of each tile; its edges one row or 8 columns past where the rule allows it
+HEADS = [((256, 256), 193, 320, 20008), ((256, 256), 769, 192, 20232), ((192, 256), 257, 192, 17000), ((192, 256), 385, 256, 8200),
+         ((128, 256), 100, 320, 17000), ((128, 256), 300, 256, 17000), ((128, 256), 1, 256, 20232), ((128, 128), 65, 512, 1000),
+         ((128, 128), 1, 320, 264), ((64, 128), 65, 256, 1032), ((64, 128), 3, 64, 520)]
 # one row and 8 columns past whole tiles of the named shape: 16-bit outputs, fp32 outputs
 TILES = {(256, 256): [(1537, 4104, 448), (1537, 4104, 1024)], (256, 192): [(1281, 3080, 192), (1281, 3080, 2048)],
          (256, 128): [(1281, 2056, 192), (1025, 3080, 2048)], (192, 128): [(385, 5128, 256), (769, 2568, 768)],
@@ -95,6 +99,13 @@ def test_lmhead_tiles(m_half, d, vocab, dtype):
         want = torch.logsumexp(logits, 1) - logits.gather(1, tg.clamp(min=0)[:, None])[:, 0]
         want = torch.where(tg >= 0, want, torch.zeros_like(want))
         assert float((loss[rows] - want).abs().max()) < 2e-4          # fp32 logits: accumulation order only
+
+
+@pytest.mark.parametrize("dtype", [zi.BF16, zi.FP16])
+@pytest.mark.parametrize("tile,m_half,d,vocab", HEADS)
+def test_each_lmhead_tile(tile, m_half, d, vocab, dtype):
+    assert zo_amd.zo_kernel_linear_tile(m_half, vocab, d, 4) == tile
+    test_lmhead_tiles(m_half, d, vocab, dtype)
 
 
 @pytest.mark.parametrize("m_half,d,vocab", [(257, 192, 17000), (3, 64, 520)])     # a pipelined tile, the small one

@@ -43,7 +43,24 @@ def test_picked_tile_is_no_slower_than_before_the_rule(m_half, n, k, epi, before
     assert us[TILES.index(tile)] <= 1.06 * before, tile
 
 
+# LM head of few rounds: rows a sign, d, vocabulary, us with heights of 256, 192, 128 (256 columns)
+HEADS = [
+    (616, 1280, 6824, (31.6, 28.7, 37.4)),
+    (595, 2624, 8296, (57.7, 85.3, 63.4)),
+    (363, 832, 12392, (26.0, 21.6, 28.2)),
+    (334, 1088, 12984, (32.0, 27.0, 34.3)),
+    (828, 1280, 32000, (132.6, 136.9, 145.3)),
+    (1048, 2048, 50272, (419.0, 399.0, 428.0)),
+]
+
+
+@pytest.mark.parametrize("rows,d,vocab,us", HEADS)
+def test_picked_height_of_the_lm_head_is_near_the_best(rows, d, vocab, us):
+    height, columns = zo_amd.zo_kernel_linear_tile(rows, vocab, d, 4)
+    assert columns == 256 and us[(256, 192, 128).index(height)] <= 1.04 * min(us)
+
+
 def test_shapes_off_the_matrix_cores_have_no_tile():
     assert zo_amd.zo_kernel_linear_tile(64, 64, 64, 0) == (64, 64)
-    for m_half, n, k, epi in ((64, 64, 96, 0), (64, 60, 64, 0), (0, 64, 64, 0), (64, 64, 64, 4), (64, 64, 64, -1), (1, 1 << 24, 64, 2)):
+    for m_half, n, k, epi in ((64, 64, 96, 0), (64, 60, 64, 0), (0, 64, 64, 0), (64, 64, 64, 5), (64, 64, 64, -1), (1, 1 << 24, 64, 2)):
         assert zo_amd.zo_kernel_linear_tile(m_half, n, k, epi) is None
