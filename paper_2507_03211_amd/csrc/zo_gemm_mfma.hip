@@ -347,10 +347,7 @@ template <int TM_, int TN_, int A_> struct Shape {
     static constexpr int BM = 64 * TM, BN = 64 * TN;
     static constexpr int STX = A + 1, STW = A;                   // LDS stages of the activation tile / of the weight tile
     static constexpr int XU4 = BM * (BK / 8), WU4 = BN * (BK / 8);   // uint4 per stage
-    // the epilogue passes a wave's rows through its own slice of an activation stage where that is large enough, else
-    // through an area of its own
-    static constexpr bool kOwnArea = kTileStageBytes<TN> > 2048 * TM;
-    static constexpr int lds_bytes(int epi) { return (STX * XU4 + STW * WU4) * 16 + (kOwnArea && epi != 4 ? 4 * kTileStageBytes<TN> : 0); }
+    static constexpr int kLdsBytes = (STX * XU4 + STW * WU4) * 16;
     static constexpr int LX = 2 * TM, LW = 2 * TN, NM = TM * TN, R = TM + TN;   // loads per wave and slab; multiplies and fragments per quarter
     static_assert(NM % 2 == 0 && R <= NM, "the schedules below");
     // Fragment reads that have gone out before multiply j of quarter q, for the quarter after it.
@@ -592,8 +589,9 @@ __global__ __launch_bounds__(256) void linear_mfma_pipe_kernel(const uint16_t *_
         } else {
             // staged in the wave's own slice of the activation stage that the tile's last slab has just left (every wave
             // finished reading that stage before the slab's barrier, and the next loads into the slice are this wave's
-            // own, issued after the epilogue), or in an area of its own
-            char *stage = SH::kOwnArea ? (char *)(smem + kWEnd) + wave * kTileStageBytes<TN> : (char *)(smem + xfree) + wave * (1024 * LX);
+            // own, issued after the epilogue)
+            static_assert(kTileStageBytes<TN> <= 1024 * LX, "a pass fits the slice");
+            char *stage = (char *)(smem + xfree) + wave * (1024 * LX);
             store_tile<DT, EPI, TM, TN, true>(acc, stage, bias, y, sign, m_half, n, m0, n0, wm, wn, lane);
         }
         if (!has_next) break;
@@ -736,10 +734,10 @@ template <int DT, int EPI, class SH> hipError_t launch_pipe(const Args &a)
     auto kern = linear_mfma_pipe_kernel<DT, EPI, SH>;
     static std::atomic<uint64_t> lds_allowed{0};
     const hipError_t e = once_per_device(lds_allowed, [&] {
-        return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, SH::lds_bytes(EPI));
+        return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, SH::kLdsBytes);
     });
     if (e != hipSuccess) return e;
-    kern<<<grid, block, SH::lds_bytes(EPI), a.s>>>((const uint16_t *)a.x, (const uint16_t *)a.wt_p, (const uint16_t *)a.wt_m, (const uint16_t *)a.b_p,
+    kern<<<grid, block, SH::kLdsBytes, a.s>>>((const uint16_t *)a.x, (const uint16_t *)a.wt_p, (const uint16_t *)a.wt_m, (const uint16_t *)a.b_p,
                                                    (const uint16_t *)a.b_m, a.y, a.m_half, a.n, a.k, tiles_m, tiles_n, total);
     return hipGetLastError();
 }
