@@ -11,15 +11,15 @@
 // activation tile the B operand, so a lane's 16 accumulators are 4 runs of 4 consecutive n of
 // one output row, which makes the epilogue 8/16-byte stores.
 //
-// Two kernels:
+// Two kernels (K a multiple of 64; others take the plain kernel):
 //  * linear_mfma_pipe_kernel, for K of some slabs and more: one persistent workgroup of 2 x 2 waves per CU that walks its
 //    XCD's share of the tile list, tiles of 256 x 256 down to 128 x 128 with slabs of 64 k.  Operand tiles go from global
 //    memory straight into LDS (global_load_lds_dwordx4, no register staging), whole 128-byte lines per tile row, several
 //    slabs ahead, and the pipeline runs on from one tile into the next.  16-byte chunks are XOR-swizzled on the global
 //    side so that fragment reads are free of bank conflicts.  Tiles are numbered so that each XCD (its own L2) owns a
 //    contiguous band of 8 tile-rows and walks it column by column.  Outputs leave through LDS as whole rows.
-//  * linear_mfma_small_kernel, 64 x 64 tiles, one workgroup per tile and two of them per CU: any K, and shapes so small
-//    that what counts is how many CUs take part.
+//  * linear_mfma_small_kernel, 64 x 64 tiles, one workgroup per tile and two or more of them per CU: any number of slabs,
+//    and shapes so small that what counts is how many CUs take part.
 // pick_tile() at the end chooses between the tile shapes.
 #include "zo_device_once.h"
 #include "zo_kernels.h"

@@ -537,7 +537,7 @@ void stage_flat_kernel(StageBatch batch, uint64_t seed, float eps, uint64_t upd_
                                  // of padding behind a bool kept the compiler from splitting the struct into registers;
                                  // it went to memory, and a launch took up to 15 us more than its work: 2.4 M bf16
                                  // elements 19.4 -> 6.3 us, 7.1 M 24.2 -> 10.4 and with the update 31.3 -> 15.2, 105 M
-                                 // with the update 179.5 -> 172.5.)
+                                 // with the update 180 -> 172.)
     };
     int di = 0;
     auto piece_of = [&](uint32_t tile) {
