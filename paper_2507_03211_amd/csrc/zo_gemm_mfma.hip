@@ -167,9 +167,10 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[TN][TM], char *st
     const int fr = lane & 31, fh = lane >> 5;
     // Output through LDS so that global stores are whole rows: in the MFMA layout a lane holds runs of 4
     // consecutive columns of ONE row and a wave instruction would touch 32 rows with 16 or 32 bytes each.
-    // A wave stages 2 KiB x TN at a time (32 rows of two-byte columns, or 16 rows of fp32).  No workgroup barrier.  The
-    // run-wise writes and the row-wise 16-byte reads are free of bank conflicts: rows whose length is a power of two
-    // are XOR-swizzled by the row, others have 16 bytes of padding.
+    // A wave stages 2 KiB x TN at a time (32 rows of two-byte columns, or 16 rows of fp32).  No workgroup barrier.  Rows whose
+    // length is a power of two are XOR-swizzled by the row: the run-wise writes and the row-wise 16-byte reads are free of
+    // bank conflicts (16-bit rows of one tile apart, see chunk16 below).  Others have 16 bytes of padding, which leaves two
+    // lanes per bank in the writes (15 % of the LDS cycles of a 12-slab launch of 256 x 192 tiles).
     constexpr bool kOut16 = (EPI == 0 || EPI == 1);              // 2-byte outputs; else fp32
     constexpr int RP = kOut16 ? 32 : 16;                         // rows per pass
     constexpr int NPASS = 32 * TM / RP;
@@ -271,9 +272,14 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[TN][TM], char *st
             }
         }
     }
-    // 16-bit rows that are a power of two long: chunk (two runs) and half within it, both XORed by row bits that spread
-    // a write of 32 rows over all banks; the half flips for rows 16 .. 31, whole pieces of the way out
-    auto chunk16 = [](int r) { return TN == 4 ? (r & 15) : TN == 2 ? ((r >> 1) & 7) : ((r >> 2) & 3); };
+    // 16-bit rows that are a power of two long: the chunk (two runs) is XORed by row bits, and the half within it flips with
+    // row bit kFlip, a whole piece's rows at a time on the way out.  Written runs are 8 bytes of 32 rows (lanes): they spread
+    // over all 64 banks, and those of 16 rows over the 32 that an access of 8 bytes a lane reaches in one go.  (TN == 1 has
+    // no row bit to flip by that is one value per piece and within 16 rows: two lanes per bank there.)
+    constexpr int kFlip = TN == 1 ? 4 : 3;
+    auto chunk16 = [](int r) {
+        return TN == 4 ? (r & 7) | ((r >> 4) & 1) << 3 : TN == 2 ? ((r >> 1) & 3) | ((r ^ (r >> 4)) & 1) << 2 : ((r >> 2) & 3);
+    };
 #pragma unroll
     for (int pass = 0; pass < NPASS; ++pass) {
         const int tm = pass * RP / 32;                          // MFMA row block of this pass
@@ -302,7 +308,7 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[TN][TM], char *st
                             else return __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, f16x2));
                         };
                         const uint2 o = {pack2(v[0], v[1]), pack2(v[2], v[3])};
-                        const int slot = kXor ? (((tn * 4 + g) ^ chunk16(fr)) << 1) + (fh ^ (fr >> 4)) : run;
+                        const int slot = kXor ? (((tn * 4 + g) ^ chunk16(fr)) << 1) + (fh ^ ((fr >> kFlip) & 1)) : run;
                         *(uint2 *)(stage + fr * PITCH + (slot << 3)) = o;
                     } else {
                         *(float4 *)(stage + (fr & 15) * PITCH + ((kXor ? run ^ (fr & 15 & (NRUN - 1)) : run) << 4)) = float4{v[0], v[1], v[2], v[3]};
@@ -315,7 +321,7 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[TN][TM], char *st
             for (int i = 0; i < NIO; ++i) {
                 const int r = (64 * i + lane) / LPR, c = (64 * i + lane) % LPR;
                 u32x4 q = *(const u32x4 *)(stage + r * PITCH + ((kXor ? c ^ chunk16(r) : c) << 4));
-                if (kXor && i * 64 / LPR >= 16) q = u32x4{q.z, q.w, q.x, q.y};
+                if (kXor && ((i * 64 / LPR) >> kFlip & 1)) q = u32x4{q.z, q.w, q.x, q.y};
                 if (valid(pass, i)) {
                     if constexpr (NT) __builtin_nontemporal_store(__builtin_bit_cast(f32x4, q), piece(at_store, i));
                     else *piece(at_store, i) = __builtin_bit_cast(f32x4, q);
