@@ -208,14 +208,19 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
 #pragma unroll
             for (int i = 0; i < NLD; ++i) dma16(gb, which ? vgo[i] : kgo[i], dst + i * 1024u);
         } else {
-            // last, ragged tile of the sequence: key rows past its end re-read the last row (masked as future keys).  Offsets
-            // are from the tile's first row here too: from the sequence's they would not fit 32 bits for long sequences.
-            int l = lane;
-            asm volatile("" : "+v"(l));                      // worked out here, once an item, and not kept in registers
+            // last, ragged tile of the sequence: what lies past its end is read from the values of its last row instead,
+            // the lane's channels where no row is worked again (masked as future keys; no value that is not finite comes in
+            // but that row's own).  Offsets are from the tile's first row here too: from the sequence's they would not
+            // fit 32 bits for long sequences.  (The empty asm keeps the comparisons here, once an item: ahead of the item
+            // loop they take registers.)
+            int left = seq - k0;
+            asm volatile("" : "+s"(left));
+            const uint32_t end = (uint32_t)left * (uint32_t)ld * 2u;
+            const uint32_t last = end - (uint32_t)d * 2u + (kRedo ? 0u : (uint32_t)((lane % CH) ^ vswz(lane / CH)) * 16u);
 #pragma unroll
             for (int i = 0; i < NLD; ++i) {
-                const int past = k0 + (64 * (NLD * wave + i) + l) / CH - (seq - 1);
-                dma16(gb, (which ? vgo[i] : kgo[i]) - (uint32_t)(past > 0 ? past : 0) * (uint32_t)ld * 2u, dst + i * 1024u);
+                const uint32_t off = which ? vgo[i] : kgo[i];
+                dma16(gb, off < end ? off : last, dst + i * 1024u);
             }
         }
     };
