@@ -550,7 +550,14 @@ hipError_t launch_attention(const void *qkv, void *out, int dtype, int n_seq, in
 {
     // the matrix path reads and writes in pieces of 16 and 8 bytes
     const bool aligned = (uintptr_t)qkv % 16 == 0 && (uintptr_t)out % 16 == 0;
-    if (allow_mfma && dtype != kFP32 && aligned && mfma_attention_supported(seq, n_heads, d_head))
+    // Sequences of one to four tokens with heads of 80 to 112 channels: an item of the matrix path is 128 query rows whatever the
+    // length, and 512 are in flight; once they take a second round the plain kernel, one block a token, is done first, up to
+    // 3 tokens or 2048 items.  bf16, heads of 80 channels, us plain / matrix: 1024 items of 1 token 5.8 / 8.4, 2 tokens 6.1 / 8.3,
+    // 3 tokens 7.2 / 8.6, 4 tokens 8.0 / 8.5; 8192 items 14 / 51, 24 / 51, 42 / 52, 57 / 53; 512 items 5.2 / 5.5, 5.9 / 5.6,
+    // 6.2 / 5.7, 6.3 / 5.7.  112 channels, 1024 items: 6.5 / 9.2, 6.7 / 9.2, 7.7 / 9.2, 8.6 / 9.7.
+    const long items = (long)n_seq * n_heads;
+    const bool tiny = d_head != 64 && d_head != 128 && items >= (seq == 1 ? 512 : 513) && (seq <= 3 || (seq == 4 && items <= 2048));
+    if (allow_mfma && dtype != kFP32 && aligned && !tiny && mfma_attention_supported(seq, n_heads, d_head))
         return launch_attention_mfma(qkv, out, dtype, n_seq, seq, n_heads, d_head, s);
     const dim3 grid(seq, n_heads, n_seq), block(128);
     const size_t smem = (size_t)(seq + d_head + 16) * acc_bytes(dtype);

@@ -1,6 +1,7 @@
 """Causal attention on the matrix path for the head sizes between 64 and 128 whose last channel tile is padded or whose
 number of contraction steps is odd (80, 96, 112), against the oracle: edges of the 32-key units, the 64-key tiles and the
-128-row work items; every key weighed exactly once; values that are not finite behind a row's last visible key."""
+128-row work items; every key weighed exactly once; values that are not finite behind a row's last visible key; where many
+sequences of a few tokens leave the matrix path."""
 import numpy as np
 import pytest
 import torch
@@ -159,3 +160,20 @@ def test_small_probabilities_count_in_fp16(dh, gap):
     # a small probability, 2^11 e^-gap, within half a unit of 2^-24; the output within half a unit of its own or of 2^-24
     bound = want * (2.0**-36 * np.exp(gap + 0.02) + 2.0**-10) + 2.0**-25
     assert np.all(np.abs(got - want) <= bound), np.max(np.abs(got - want) / np.maximum(want, 1e-9))
+
+
+@pytest.mark.parametrize("dtype", [zi.BF16, zi.FP16])
+@pytest.mark.parametrize("dh", [80, 96, 112])
+@pytest.mark.parametrize("n_seq,seq,heads,plain", [(512, 1, 1, True), (511, 1, 1, False), (27, 2, 19, True), (256, 2, 2, False),
+                                                   (171, 3, 3, True), (128, 3, 4, False), (129, 4, 4, True), (512, 4, 4, True), (2049, 4, 1, False),
+                                                   (129, 5, 4, False)])
+def test_many_sequences_of_a_few_tokens(dtype, dh, n_seq, seq, heads, plain):
+    # both sides of the line: right on each, and beyond it bit for bit what a buffer off a 16-byte boundary gives (the plain kernel)
+    qkv = _qkv(n_seq, seq, heads, dh, dtype, 6)
+    want = _oracle(qkv, n_seq, seq, heads, dh)
+    got = _run(qkv, n_seq, seq, heads, dh, dtype)
+    assert np.max(np.abs(got - want)) < 3 * ULP[dtype] * (1 + np.abs(want).max())
+    if plain:
+        flat = torch.empty(qkv.numel() + 1, device=DEV, dtype=qkv.dtype)
+        off = flat[1:].view_as(qkv).copy_(qkv)
+        assert np.array_equal(got, _run(off, n_seq, seq, heads, dh, dtype))
