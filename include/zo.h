@@ -298,7 +298,9 @@ int zo_kernel_layernorm_pm(const void *resid, const void *g_plus, const void *g_
 
 /* Causal multi-head attention of the decoder block inside DualForward (App. A, Alg. 2; both signs are
  * simply more sequences): qkv [n_seq * seq, 3 d] (q | k | v, heads contiguous inside each)
- * -> out [n_seq * seq, d], softmax(q k^T / sqrt(d_head)) v per (sequence, head). */
+ * -> out [n_seq * seq, d], softmax(q k^T / sqrt(d_head)) v per (sequence, head).
+ * The matrix path (16-bit types, d_head 64, 80, 96, 112, 128) wants qkv and out on 16-byte boundaries; anything else runs
+ * on a slower kernel that keeps a row's scores in LDS, and a sequence too long for that is refused. */
 int zo_kernel_attention(const void *qkv, void *out, int dtype, int n_seq, int seq, int n_heads,
                         int d_head, void *stream);
 
