@@ -2,8 +2,8 @@
 // part of the paired forward passes of Eq. 1 (DistZO2, Preliminaries).  Both signs are just
 // more sequences: the kernel sees n_seq = 2 * batch independent sequences.
 //
-// One work item = (128 query rows, one head, one sequence); 4 waves x 32 query rows.  Persistent workgroups, as
-// many as the chip holds at once, walk a per-XCD item list.  Key / value tiles of 64 keys stream through LDS.
+// One work item = (128 query rows, one head, one sequence); 4 waves x 32 query rows.  Workgroups walk a per-XCD item list,
+// as many as the chip holds at once or one per item (see the launcher).  Key / value tiles of 64 keys stream through LDS.
 // Everything is computed transposed so that a lane owns one query row:
 //     S^T[key, q] = K Q^T        (MFMA A = K rows, B = Q rows; lane: column q, 16 keys)
 //     O^T[c, q]  += V^T P^T      (MFMA A = V^T rows, B = P^T; lane: column q, 16 channels)
@@ -124,12 +124,20 @@ __device__ __forceinline__ void attention_rows(const uint16_t *base, uint16_t *o
     }
 }
 
+template <int LO, int HI, class F> __device__ __forceinline__ void static_for(F &&f)
+{
+    if constexpr (LO < HI) {
+        f(std::integral_constant<int, LO>{});
+        static_for<LO + 1, HI>(f);
+    }
+}
+
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // native vector: stays in registers across the loop
 
 template <int DT, int DH>
 __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(const uint16_t *__restrict__ qkv, uint16_t *__restrict__ out, int seq,
-                                                        int n_heads, int n_seq)
+                                                        int n_heads, int n_seq, int fill)
 {
     constexpr int KS = DH / 16, CT = (DH + 31) / 32;   // contraction steps of K Q^T, channel tiles of O^T
     constexpr int CHD = DH / 8;           // 16-byte chunks per K / V row in memory
@@ -197,32 +205,20 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
     }
     const uint32_t ks_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)&ks3[0][0];
     const uint32_t vs_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)&vs2[0][0];
-    auto dma16 = [](uint64_t gbase, uint32_t lane_off, uint32_t lds_off) {
-        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane_off), "s"(gbase), "s"(lds_off) : "memory", "m0");
+    // Buffer accesses, the buffer as long as what exists of the tile: rows past the end of the sequence come as zeros (masked
+    // as future keys) without a branch or a comparison.  Offsets are from the tile's first row: from the sequence's they would
+    // not fit 32 bits for long sequences.
+    auto dma16 = [](u32x4 rows, uint32_t lane_off, uint32_t lds_off) {
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(lane_off), "s"(rows), "s"(lds_off) : "memory", "m0");
     };
     // this wave's pieces of K (which = 0) or V (which = 1) rows k0 .. k0 + 63, into buffer `buf` of that operand
     auto issue = [&](int which, int k0, int buf) {
         const uint32_t dst = (which ? vs_lds : ks_lds) + (uint32_t)buf * (TILE * 16) + (uint32_t)(NLD * wave) * 1024u;
         const uint64_t gb = gbase0 + (uint64_t)k0 * (uint64_t)ld * 2u;
-        if (k0 + BKV <= seq) {
+        const int left = seq - k0 < BKV ? seq - k0 : BKV;
+        const u32x4 rows = {(uint32_t)gb, (uint32_t)(gb >> 32), (uint32_t)left * (uint32_t)ld * 2u, 0x00020000u};
 #pragma unroll
-            for (int i = 0; i < NLD; ++i) dma16(gb, which ? vgo[i] : kgo[i], dst + i * 1024u);
-        } else {
-            // last, ragged tile of the sequence: what lies past its end is read from the values of its last row instead,
-            // the lane's channels where no row is worked again (masked as future keys; no value that is not finite comes in
-            // but that row's own).  Offsets are from the tile's first row here too: from the sequence's they would not
-            // fit 32 bits for long sequences.  (The empty asm keeps the comparisons here, once an item: ahead of the item
-            // loop they take registers.)
-            int left = seq - k0;
-            asm volatile("" : "+s"(left));
-            const uint32_t end = (uint32_t)left * (uint32_t)ld * 2u;
-            const uint32_t last = end - (uint32_t)d * 2u + (kRedo ? 0u : (uint32_t)((lane % CH) ^ vswz(lane / CH)) * 16u);
-#pragma unroll
-            for (int i = 0; i < NLD; ++i) {
-                const uint32_t off = which ? vgo[i] : kgo[i];
-                dma16(gb, off < end ? off : last, dst + i * 1024u);
-            }
-        }
+        for (int i = 0; i < NLD; ++i) dma16(rows, which ? vgo[i] : kgo[i], dst + i * 1024u);
     };
     // Transposing LDS read (ds_read_b64_tr_b16): in every group of 16 lanes, lane j hands in the address of
     // four consecutive 16-bit elements ("row j") and lane i gets back element i%4 of rows i/4, i/4+4, i/4+8,
@@ -287,12 +283,18 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
         for (int i = 3; i < 15; i += 2) t = __builtin_fmaxf(__builtin_fmaxf(x[i], x[i + 1]), t);
         return __builtin_fmaxf(t, x[15]);
     };
-    auto causal_mask = [&](f32x16 &x, int key0) {    // key > query: a future key
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int key = key0 + 8 * (i >> 2) + 4 * fh + (i & 3);
-            if (key > qrow) x[i] = -INFINITY;
-        }
+    // Future keys (key > query) of the unit on a wave's diagonal: its first key is the wave's first row, so which lanes a
+    // register loses is the same for every wave and item, a constant: one select per register and scalar moves beside it,
+    // where comparing keys and rows takes a vector comparison each that the select has to wait for.  (In a step a score's last
+    // product lies a channel tile's multiplies and half the softmax, 26 instructions and more, ahead of this.)
+    auto causal_mask = [&](f32x16 &x) {
+        const float none = -INFINITY;
+        static_for<0, 16>([&](auto ic) {
+            constexpr int key = 8 * (decltype(ic)::value >> 2) + (decltype(ic)::value & 3);      // + 4 fh
+            float v = x[decltype(ic)::value];
+            asm("s_mov_b32 vcc_lo, %2\n\ts_mov_b32 vcc_hi, %3\n\tv_cndmask_b32 %0, %0, %1, vcc" : "+v"(v) : "v"(none), "i"((1u << key) - 1), "i"((1u << (key + 4)) - 1) : "vcc");
+            x[decltype(ic)::value] = v;
+        });
     };
     // scores of unit u from K buffer `buf`, half `half`, into dst; the ring then holds the first fragments of the
     // unit after it (buffer nbuf, half nhalf).  `between(i)`: what to issue after the i-th multiply.
@@ -395,7 +397,7 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
                     if (e & 1) cvt(e);
                 }
             } else if (c == 0) {
-                if (s + 1 == u_last) causal_mask(Sn, 32 * (s + 1));
+                if (s + 1 == u_last) causal_mask(Sn);
             } else if (c == 1) {
                 tmax = unit_max(Sn);
             }
@@ -403,17 +405,17 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
         }
     };
 
-    // Work items: (query tile, head, sequence).  Persistent workgroups, as many as the chip holds at once: the
-    // hardware deals consecutive workgroup ids round-robin to the 8 XCDs, so workgroup b sits on XCD b % 8 and is
-    // that XCD's slot b / 8.  Every (head, sequence) pair goes to one XCD with all its query tiles, so the XCDs hold
-    // equal shares of the causal triangle and the K and V of a pair are fetched into one L2 instead of eight.  The
-    // XCD's items are listed in groups of as many pairs as fill its slots once, long rows first within a group, and
-    // slot j takes entry j of the even rounds and entry slots - 1 - j of the odd ones: a long tile is followed by
-    // a short one and every slot ends up with the same number of key tiles.
+    // Work items: (query tile, head, sequence).  The hardware deals consecutive workgroup ids round-robin to the 8 XCDs, so
+    // workgroup b sits on XCD b % 8 and is that XCD's slot b / 8.  Every (head, sequence) pair goes to one XCD with all its
+    // query tiles, so the XCDs hold equal shares of the causal triangle and the K and V of a pair are fetched into one L2
+    // instead of eight.  The XCD's items are listed in groups of as many pairs as fill the workgroups it holds at once
+    // (`fill`), long rows first within a group.  Persistent workgroups: slot j takes entry j of the even rounds and entry
+    // slots - 1 - j of the odd ones, so that a long tile is followed by a short one.  One workgroup per item: the list is
+    // one round, and a workgroup that ends makes room for the next entry.
     const int n_qt = (seq + BQ - 1) / BQ;
     const int slots = (int)gridDim.x >> 3, slot = (int)blockIdx.x >> 3, xcd = (int)blockIdx.x & 7;
     const int n_pairs = n_heads * n_seq, pairs_xcd = (n_pairs + 7) / 8;
-    const int group_pairs = slots / n_qt > 1 ? slots / n_qt : 1, group_items = group_pairs * n_qt;
+    const int group_pairs = fill / n_qt > 1 ? fill / n_qt : 1, group_items = group_pairs * n_qt;
     const int n_lin = (pairs_xcd + group_pairs - 1) / group_pairs * group_items;
     // the slot's entry of a round: its (head, sequence) pair, -1 if there is none, and its query tile
     auto pair_at = [&](int lin, int &qt) {
@@ -443,9 +445,9 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
         const int qload = qrow < seq ? qrow : seq - 1;
         const int q_hi = qt * BQ + BQ - 1 < seq - 1 ? qt * BQ + BQ - 1 : seq - 1;   // last query row of the workgroup
         n_tiles = q_hi / BKV + 1;
-        // last unit this wave needs (the one on its diagonal); a wave whose rows all lie past a ragged end stops with
-        // the last unit loaded, its results are not stored
-        u_last = q0 / 32 < 2 * n_tiles - 1 ? q0 / 32 : 2 * n_tiles - 1;
+        // last unit this wave needs (the one on its diagonal); none where its rows all lie past a ragged end: it takes its
+        // share of the loads and leaves the CU's issue slots to the others
+        u_last = q0 < seq ? q0 / 32 : -1;
         kb0 = 0, kb1 = 1, kb2 = 2;
         m_run = -INFINITY, l_lane = 0.0f, moff = 0.0f, thr = -INFINITY;
         // everybody is done with the LDS tiles of the previous item: the first tiles of this one go out, then Q is
@@ -472,7 +474,11 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
     #pragma unroll
         for (int r = 0; r < KR; ++r) kf[r] = k_frag(0, 0, r);
         qk_unit(S[0], 0, 0, 0, 1, [](int) { __builtin_amdgcn_sched_barrier(0); });
-        if (u_last == 0) causal_mask(S[0], 0);
+        if (u_last == 0) {
+            // (the select is written out, so the distance that a product needs before its first use is ours to keep)
+            asm volatile("s_nop 15\n\ts_nop 3" : "+v"(S[0]));
+            causal_mask(S[0]);
+        }
         tmax = unit_max(S[0]);
 
 
@@ -488,16 +494,18 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
             }
         }
         auto store_row = [&](float inv) {
-            uint16_t *o = out + ((size_t)sq * seq + qrow) * d + head * DH;
+            uint16_t *o = out + ((size_t)sq * seq + qrow) * d + head * DH;   // (rows past the end store nothing)
+            // A lane holds four channels of each run of eight, its partner half a wave away the other four: of two runs the
+            // lower lane takes the first whole and the upper one the second, 16 bytes a store instead of 8.
 #pragma unroll
             for (int c = 0; c < CT; ++c)
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
+                for (int g = 0; g < 4; g += 2) {
                     if (c * 32 + 8 * g >= DH) continue;          // the padding of the last channel tile
-                    uint2 v;
-                    v.x = pack2<DT>(oacc[c][4 * g] * inv, oacc[c][4 * g + 1] * inv);
-                    v.y = pack2<DT>(oacc[c][4 * g + 2] * inv, oacc[c][4 * g + 3] * inv);
-                    *(uint2 *)(o + c * 32 + 8 * g + 4 * fh) = v;
+                    auto two = [&](int e) { return pack2<DT>(oacc[c][e] * inv, oacc[c][e + 1] * inv); };
+                    const auto lo = __builtin_amdgcn_permlane32_swap(two(4 * g), two(4 * g + 4), false, false);
+                    const auto hi = __builtin_amdgcn_permlane32_swap(two(4 * g + 2), two(4 * g + 6), false, false);
+                    if (qrow < seq) *(uint4 *)(o + c * 32 + 8 * g + 8 * fh) = uint4{lo[0], hi[0], lo[1], hi[1]};
                 }
         };
         float l_run;
@@ -518,7 +526,7 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
                     if (c * 32 + 8 * (i >> 2) < DH) probe = __builtin_fmaf(oacc[c][i], 0.0f, probe);
             if (__builtin_amdgcn_ballot_w64(qrow < seq && !(probe == 0.0f)) != 0) again |= 1ull << (round & 63);
         }
-        if (qrow < seq) store_row(1.0f / l_run);
+        store_row(1.0f / l_run);
     }
     // The rows that came out not finite, once more the plain way, after all items: nothing of the loop above is live any
     // more, and a register that this needs is not missing there.  A lane finds its row's state in what it has stored itself.
@@ -568,8 +576,6 @@ hipError_t launch_attention_mfma(const void *qkv, void *out, int dtype, int n_se
 {
     if (!mfma_attention_supported(seq, n_heads, d_head) || (dtype != kBF16 && dtype != kFP16)) return hipErrorInvalidValue;
     if (n_heads < 1 || n_seq < 1) return hipErrorInvalidValue;
-    // persistent workgroups: as many as are resident at once (2 per CU, 3 at d_head 64; the CU count is
-    // rounded down to whole XCDs' worth), fewer when there are fewer work items
     static int n_cu = 0;
     if (n_cu == 0) {
         int dev = 0, v = 0;
@@ -580,15 +586,26 @@ hipError_t launch_attention_mfma(const void *qkv, void *out, int dtype, int n_se
     }
     const long long pairs_xcd = ((long long)n_heads * n_seq + 7) / 8;
     const long long items_xcd = pairs_xcd * ((seq + BQ - 1) / BQ);
+    // Workgroups resident at once: 2 per CU, 3 at d_head 64 (the CU count is rounded down to whole XCDs' worth).  When the
+    // query tiles of a sequence divide that number, rounds of the list are whole groups, the zigzag gives every slot the same
+    // number of key tiles, and persistent workgroups save an item's start.  When they don't, a group's long tiles come to lie
+    // at both ends of a round and some slots get two of them: then a workgroup per item, for which the hardware finds the free
+    // place.  us, persistent / per item, heads of 128 unless said: 1500 tokens (12 tiles, 64 slots) x 64 (sequence, head) pairs
+    // 67 / 50, x 320 259 / 236; 1100 x 320 172 / 137; 600 x 160 35 / 28; heads of 64, 850 x 640 130 / 104; but 1024 x 160
+    // 63 / 72, 400 x 320 32 / 38.  Over many rounds, or some with a ragged last tile, which is shorter than the zigzag takes it
+    // for, the dynamic order wins by a little as well: 2048 x 320 402 / 397, heads of 64, 331 x 1024 50.6 / 48.3.
     const long long slots_max = (long long)(n_cu / 8) * (d_head == 64 ? 3 : 2);
     if (items_xcd > 0x7fffffffLL / 64) return hipErrorInvalidValue;      // the kernel's item indices are ints
-    const dim3 grid((unsigned)(8 * (items_xcd < slots_max ? items_xcd : slots_max))), block(256);
+    const int n_qt = (seq + BQ - 1) / BQ, fill = (int)(items_xcd < slots_max ? items_xcd : slots_max);
+    const long long rounds = items_xcd / slots_max, group = fill / n_qt > 1 ? fill / n_qt : 1;
+    const bool per_item = items_xcd > slots_max && (slots_max % n_qt != 0 || (n_qt >= 3 && (rounds >= 8 || (rounds >= 4 && seq % BQ != 0))));
+    const dim3 grid((unsigned)(8 * (per_item ? (pairs_xcd + group - 1) / group * group * n_qt : fill))), block(256);
     const uint16_t *q = (const uint16_t *)qkv;
     uint16_t *o = (uint16_t *)out;
 #define ZO_ATTN(DH)                                                                                       \
     case DH:                                                                                              \
-        if (dtype == kBF16) attn_mfma_kernel<kBF16, DH><<<grid, block, 0, s>>>(q, o, seq, n_heads, n_seq); \
-        else attn_mfma_kernel<kFP16, DH><<<grid, block, 0, s>>>(q, o, seq, n_heads, n_seq);                \
+        if (dtype == kBF16) attn_mfma_kernel<kBF16, DH><<<grid, block, 0, s>>>(q, o, seq, n_heads, n_seq, fill); \
+        else attn_mfma_kernel<kFP16, DH><<<grid, block, 0, s>>>(q, o, seq, n_heads, n_seq, fill);                \
         break;
     switch (d_head) {
     ZO_ATTN(64) ZO_ATTN(80) ZO_ATTN(96) ZO_ATTN(112) ZO_ATTN(128)
