@@ -399,12 +399,26 @@ __global__ __launch_bounds__(256) void ce_finish_kernel(const float2 *__restrict
     const int tg = target[r];
     if (tg == -1) { if (lane == 0) row_loss[r] = 0.0; return; }
     const float2 *p = partials + (size_t)r * n_partial;
+    // A lane keeps its first pairs (512 a row: 65536 columns in strips of 128) in registers, so that they are read once and
+    // all loads are under way together; what lies beyond is read again for the sum.  us, read twice /
+    // here: 2096 rows of 394 pairs 9.3 / 8.2, 16352 rows 26.8 / 23.2 (the exponentials in 64 bits are most of it).
+    constexpr int KEEP = 8;
+    float2 v[KEEP];
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i) v[i] = lane + 64 * i < n_partial ? p[lane + 64 * i] : float2{-INFINITY, 0.0f};
     float mx = -INFINITY;
-    for (int i = lane; i < n_partial; i += 64) mx = p[i].x > mx ? p[i].x : mx;
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i) mx = v[i].x > mx ? v[i].x : mx;
+    for (int i = lane + 64 * KEEP; i < n_partial; i += 64) mx = p[i].x > mx ? p[i].x : mx;
     mx = wave_max(mx);
     double s = 0.0;
-    for (int i = lane; i < n_partial; i += 64)
-        if (p[i].x > -INFINITY) s += (double)p[i].y * exp((double)p[i].x - (double)mx);
+    auto add = [&](float2 q) {
+        if (q.x > -INFINITY) s += (double)q.y * exp((double)q.x - (double)mx);
+    };
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i)
+        if (64 * i < n_partial) add(v[i]);
+    for (int i = lane + 64 * KEEP; i < n_partial; i += 64) add(p[i]);
     s = wave_sum(s);
     if (lane == 0) row_loss[r] = tg >= 0 ? (log(s) + (double)mx - (double)target_logit[r]) : (double)__builtin_nan("");
 }
