@@ -539,7 +539,13 @@ void stage_flat_kernel(StageBatch batch, uint64_t seed, float eps, uint64_t upd_
                                  // elements 19.4 -> 6.3 us, 7.1 M 24.2 -> 10.4 and with the update 31.3 -> 15.2, 105 M
                                  // with the update 180 -> 172.)
     };
+    // the first tile's tensor from all the table's entries at once: one by one, each is a scalar load that the next one waits
+    // for (staging a block of 16 tensors, 50 k parameters: 7.2 us / 5.0 here)
     int di = 0;
+    if (batch.n > 1) {
+#pragma unroll
+        for (int i = 1; i < kStageMaxDesc; ++i) di += (int)(i < batch.n) & (int)(batch.d[i].first_tile <= blockIdx.x);
+    }
     auto piece_of = [&](uint32_t tile) {
         while (di + 1 < batch.n && batch.d[di + 1].first_tile <= tile) ++di;
         const StageDesc &d = batch.d[di];
