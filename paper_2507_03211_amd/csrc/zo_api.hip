@@ -372,26 +372,47 @@ int block_forward(zo_model *m, int n_sign, int batch, int seq)
     const double rows = (double)n_sign * m_half;
     const double ln_bytes = rows * d * (resid_bytes(dt) + act_bytes(dt));
     const double attn_flops = 2.0 * (double)n_sign * batch * c.n_heads * ((double)seq * (seq + 1)) * (d / c.n_heads);
-    ZO_PROF(m, K_NORM, ln_bytes, launch_layernorm(resid, at(P, L.st_ln1g), at(M, L.st_ln1g), at(P, L.st_ln1b), at(M, L.st_ln1b), x, dt,
-                                                  n_sign, m_half, d, c.ln_eps, s));
-    ZO_PROF(m, K_LINEAR, 2.0 * rows * 3 * d * d, launch_linear(x, at(P, L.st_wqkv), at(M, L.st_wqkv), at(P, L.st_bqkv), at(M, L.st_bqkv),
-                                                               qkv, dt, n_sign, m_half, 3 * d, d, 0, m->use_mfma, s));
+    // LayerNorm and the layer behind it: one launch where the layer can take it on the way
+    auto norm_linear = [&](size_t g, size_t b, size_t wt, size_t bias, void *out, int n, int epilogue) {
+        const double flops = 2.0 * rows * (double)n * d;
+        if (norm_linear_fused(resid, at(P, g), at(M, g), at(P, b), at(M, b), at(P, wt), at(M, wt), dt, n_sign, m_half, n, d)) {
+            ZO_PROF(m, K_LINEAR, flops, launch_norm_linear(resid, at(P, g), at(M, g), at(P, b), at(M, b), c.ln_eps, at(P, wt), at(M, wt),
+                                                           at(P, bias), at(M, bias), out, n_sign, m_half, n, d, epilogue, s));
+            return (int)ZO_OK;
+        }
+        ZO_PROF(m, K_NORM, ln_bytes, launch_layernorm(resid, at(P, g), at(M, g), at(P, b), at(M, b), x, dt, n_sign, m_half, d, c.ln_eps, s));
+        ZO_PROF(m, K_LINEAR, flops, launch_linear(x, at(P, wt), at(M, wt), at(P, bias), at(M, bias), out, dt, n_sign, m_half, n, d, epilogue,
+                                                  m->use_mfma, s));
+        return (int)ZO_OK;
+    };
+    ZO_TRY(norm_linear(L.st_ln1g, L.st_ln1b, L.st_wqkv, L.st_bqkv, qkv, 3 * d, 0));
     ZO_PROF(m, K_ATTN, attn_flops, launch_attention(qkv, att, dt, n_sign * batch, seq, c.n_heads, d / c.n_heads, m->use_mfma, s));
     ZO_PROF(m, K_LINEAR, 2.0 * rows * d * d, launch_linear(att, at(P, L.st_wo), at(M, L.st_wo), at(P, L.st_bo), at(M, L.st_bo), resid, dt,
                                                            n_sign, m_half, d, d, 2, m->use_mfma, s));
-    ZO_PROF(m, K_NORM, ln_bytes, launch_layernorm(resid, at(P, L.st_ln2g), at(M, L.st_ln2g), at(P, L.st_ln2b), at(M, L.st_ln2b), x, dt,
-                                                  n_sign, m_half, d, c.ln_eps, s));
-    ZO_PROF(m, K_LINEAR, 2.0 * rows * d * f, launch_linear(x, at(P, L.st_w1), at(M, L.st_w1), at(P, L.st_b1), at(M, L.st_b1), mid, dt,
-                                                           n_sign, m_half, f, d, 1, m->use_mfma, s));
+    ZO_TRY(norm_linear(L.st_ln2g, L.st_ln2b, L.st_w1, L.st_b1, mid, f, 1));
     ZO_PROF(m, K_LINEAR, 2.0 * rows * d * f, launch_linear(mid, at(P, L.st_w2), at(M, L.st_w2), at(P, L.st_b2), at(M, L.st_b2), resid, dt,
                                                            n_sign, m_half, d, f, 2, m->use_mfma, s));
     return ZO_OK;
 }
 
 // LM head (tied) + cross entropy over row chunks.  x: final-LayerNormed activations [n_sign*m_half, d].
-int lmhead_ce(zo_model *prof, hipStream_t s, const void *x, const void *e_p, const void *e_m, const int32_t *target, double *row_loss,
-              void *logits, int logits_rows, int dtype, int n_sign, int m_half, int d, int vocab, bool use_mfma)
+// `norm`, if not null: x is the residual stream, to be normalised on the way (see head_norm_fused)
+struct HeadNorm { const void *g_p, *g_m, *b_p, *b_m; float eps; };
+bool head_norm_fused(const void *resid, const HeadNorm &v, const void *e_p, const void *e_m, int logits_rows, int dtype, int n_sign, int m_half,
+                     int d, int vocab)
 {
+    return n_sign == 2 && 2 * (long)m_half <= logits_rows && norm_linear_fused(resid, v.g_p, v.g_m, v.b_p, v.b_m, e_p, e_m, dtype, 2, m_half, vocab, d);
+}
+
+int lmhead_ce(zo_model *prof, hipStream_t s, const void *x, const void *e_p, const void *e_m, const int32_t *target, double *row_loss,
+              void *logits, int logits_rows, int dtype, int n_sign, int m_half, int d, int vocab, bool use_mfma, const HeadNorm *norm = nullptr)
+{
+    if (norm) {
+        ZO_PROF(prof, K_LINEAR, 4.0 * m_half * (double)vocab * d,
+                launch_norm_linear(x, norm->g_p, norm->g_m, norm->b_p, norm->b_m, norm->eps, e_p, e_m, nullptr, nullptr, logits, 2, m_half, vocab, d, 3, s));
+        ZO_PROF(prof, K_CE, 2.0 * m_half * vocab * acc_bytes(dtype), launch_ce_rows(logits, target, row_loss, dtype, 2 * m_half, vocab, s));
+        return ZO_OK;
+    }
     const size_t ab = act_bytes(dtype);
     if (use_mfma && dtype != kFP32 && mfma_linear_supported(m_half, vocab, d)) {
         // fused: one sign-batched launch over all rows, no logits in memory
@@ -440,11 +461,13 @@ int head_and_loss(zo_model *m, int n_sign, int batch, int seq, const void *e_p, 
     void *resid = m->ws + m->wsp.resid, *x = m->ws + m->wsp.xbuf;
     int32_t *target = wsp_ptr<int32_t>(m, m->wsp.target);
     double *row_loss = wsp_ptr<double>(m, m->wsp.row_loss);
-    ZO_PROF(m, K_NORM, (double)n_sign * m_half * d * (resid_bytes(c.dtype) + act_bytes(c.dtype)),
-            launch_layernorm(resid, lnf_p, lnf_m, (const char *)lnf_p + d * e, (const char *)lnf_m + d * e, x, c.dtype, n_sign, m_half, d,
-                             c.ln_eps, m->compute));
-    ZO_TRY(lmhead_ce(m, m->compute, x, e_p, e_m, target, row_loss, m->ws + m->wsp.logits, m->wsp.logits_rows, c.dtype, n_sign, m_half, d,
-                     c.vocab, m->use_mfma));
+    const HeadNorm norm{lnf_p, lnf_m, (const char *)lnf_p + d * e, (const char *)lnf_m + d * e, c.ln_eps};
+    const bool fused = head_norm_fused(resid, norm, e_p, e_m, m->wsp.logits_rows, c.dtype, n_sign, m_half, d, c.vocab);
+    if (!fused)
+        ZO_PROF(m, K_NORM, (double)n_sign * m_half * d * (resid_bytes(c.dtype) + act_bytes(c.dtype)),
+                launch_layernorm(resid, norm.g_p, norm.g_m, norm.b_p, norm.b_m, x, c.dtype, n_sign, m_half, d, c.ln_eps, m->compute));
+    ZO_TRY(lmhead_ce(m, m->compute, fused ? resid : x, e_p, e_m, target, row_loss, m->ws + m->wsp.logits, m->wsp.logits_rows, c.dtype, n_sign,
+                     m_half, d, c.vocab, m->use_mfma, fused ? &norm : nullptr));
     ZO_PROF(m, K_OTHER, 8.0 * n_sign * m_half, launch_loss_reduce(row_loss, n_sign, m_half, batch * (seq - 1), loss_out, gs, m->compute));
     return ZO_OK;
 }

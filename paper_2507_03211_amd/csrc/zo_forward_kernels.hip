@@ -256,12 +256,18 @@ __global__ __launch_bounds__(256) void linear_plain_kernel(const void *x, const 
 // plain kernel.  Both signs of m_half x n x k, plain kernel / here: 64 x 64 x 256 52 / 5.1 us, 64 x 192 x 64 16.6 / 5.0,
 // 256 x 128 x 512 100 / 5.3, 512 x 768 x 768 202 / 33, 8192 x 768 x 768 985 / 430 (45 TFLOP/s; what bounds it there is
 // L2 traffic, 5.3 flop a byte).
+// NORM: x is the residual stream and the layer's input its LayerNorm, taken on the way: 16 lanes a row find mean and variance,
+// the operands are normalised as they are loaded.  Every column tile does that over again, for rows that it reads anyway; a
+// LayerNorm launch ahead of the layer takes 4 us and more for any size.  Taken while the layer itself is a chain of latencies
+// (16 x 16 tiles) and its rows are short (k <= 512).  64 rows a sign, us, two launches / one: 64 x 192 4.0 + 3.2 / 4.9; a step of
+// 2 layers of 64 channels 105 / 94, of 3 layers of 128 at 256 rows a sign 207 / 184.
+struct NormArgs { const float *g_p, *g_m, *b_p, *b_m; float eps; };
 typedef double f64x4 __attribute__((ext_vector_type(4)));
-template <int EPI, int TB>
+template <int EPI, int TB, bool NORM>
 __global__ __launch_bounds__(256) void linear_f64_mfma_kernel(const double *__restrict__ x, const float *__restrict__ wt_p,
                                                               const float *__restrict__ wt_m, const float *__restrict__ b_p,
                                                               const float *__restrict__ b_m, double *__restrict__ y, int m_half, int n,
-                                                              int k)
+                                                              int k, NormArgs norm)
 {
     constexpr int BT = 16 * TB;
     __shared__ double part[4][BT][BT + 1];
@@ -279,17 +285,53 @@ __global__ __launch_bounds__(256) void linear_f64_mfma_kernel(const double *__re
         xr[t] = xa + (size_t)(xi < m_half ? xi : m_half - 1) * k + 4 * g;
         wr[t] = wt + (size_t)(wi < n ? wi : n - 1) * k + 4 * g;
     }
+    double mean[TB], rstd[TB];
+    const float *gr = sign ? norm.g_m : norm.g_p, *br = sign ? norm.b_m : norm.b_p;
+    if constexpr (NORM) {
+        __shared__ double stats[BT][2];
+        const int lane16 = threadIdx.x & 15;
+        auto sum16 = [](double v) {
+#pragma unroll
+            for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+            return v;
+        };
+#pragma unroll
+        for (int t = 0; t < TB; ++t) {
+            const int r = 16 * t + (int)(threadIdx.x >> 4), xi = m0 + r;
+            const double *h = xa + (size_t)(xi < m_half ? xi : m_half - 1) * k;
+            double s = 0.0, v = 0.0;
+            for (int c = 4 * lane16; c < k; c += 64) s += (h[c] + h[c + 1]) + (h[c + 2] + h[c + 3]);
+            const double mu = sum16(s) / (double)k;
+            for (int c = 4 * lane16; c < k; c += 64)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { const double q = h[c + e] - mu; v += q * q; }
+            const double var = sum16(v) / (double)k;
+            if (lane16 == 0) { stats[r][0] = mu; stats[r][1] = 1.0 / __builtin_sqrt(var + (double)norm.eps); }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < TB; ++t) { mean[t] = stats[16 * t + r16][0]; rstd[t] = stats[16 * t + r16][1]; }
+    }
     f64x4 acc[TB][TB] = {};
 #pragma unroll 4
     for (int k0 = 16 * wave; k0 < k; k0 += 64) {
         f64x4 xv[TB], wv[TB];
         const bool in = k0 + 4 * g < k;                                    // k % 4 == 0: a lane's four are all in or all out
+        float4 gv = {}, bv = {};
+        if constexpr (NORM) {
+            if (in) { gv = *(const float4 *)(gr + k0 + 4 * g); bv = *(const float4 *)(br + k0 + 4 * g); }
+        }
 #pragma unroll
         for (int t = 0; t < TB; ++t) {
             const double2 a = in ? *(const double2 *)(xr[t] + k0) : double2{0.0, 0.0};
             const double2 b = in ? *(const double2 *)(xr[t] + k0 + 2) : double2{0.0, 0.0};
             const float4 w = in ? *(const float4 *)(wr[t] + k0) : float4{0.0f, 0.0f, 0.0f, 0.0f};
             xv[t] = f64x4{a.x, a.y, b.x, b.y};
+            if constexpr (NORM) {
+                xv[t] = f64x4{(a.x - mean[t]) * rstd[t] * (double)gv.x + (double)bv.x, (a.y - mean[t]) * rstd[t] * (double)gv.y + (double)bv.y,
+                              (b.x - mean[t]) * rstd[t] * (double)gv.z + (double)bv.z, (b.y - mean[t]) * rstd[t] * (double)gv.w + (double)bv.w};
+                if (!in) xv[t] = f64x4{0.0, 0.0, 0.0, 0.0};                // (weights are zero there: a row that is not finite stays out of it)
+            }
             wv[t] = f64x4{(double)w.x, (double)w.y, (double)w.z, (double)w.w};
         }
 #pragma unroll
@@ -361,11 +403,28 @@ __global__ __launch_bounds__(128) void attention_plain_kernel(const void *qkv_, 
     sum = block_sum(sum, red);
     __syncthreads();
     typename P::A *o = (typename P::A *)out_ + ((size_t)sq * seq + t) * d + head * d_head;
-    for (int c = threadIdx.x; c < d_head; c += blockDim.x) {
-        Acc a = 0;
-        for (int j = 0; j <= t; ++j) a += sc[j] * P::a2acc(qkv[(size_t)j * 3 * d + 2 * d + head * d_head + c]);
-        o[c] = P::acc2a(a / sum);
+    const typename P::A *vr = qkv + 2 * d + head * d_head;
+    // heads of up to half a block: the keys are dealt to as many groups of d_head threads as there are (4 sequences of 32
+    // tokens, 4 heads of 16, fp64: 7.7 us with one group / 6.1)
+    const int groups = d_head <= 64 ? (int)blockDim.x / d_head : 1;
+    if (groups == 1) {
+        for (int c = threadIdx.x; c < d_head; c += blockDim.x) {
+            Acc a = 0;
+            for (int j = 0; j <= t; ++j) a += sc[j] * P::a2acc(vr[(size_t)j * 3 * d + c]);
+            o[c] = P::acc2a(a / sum);
+        }
+        return;
     }
+    __shared__ Acc part[128];
+    const int c = (int)threadIdx.x % d_head, grp = (int)threadIdx.x / d_head;
+    Acc a = 0;
+    if (grp < groups)
+        for (int j = grp; j <= t; j += groups) a += sc[j] * P::a2acc(vr[(size_t)j * 3 * d + c]);
+    part[threadIdx.x] = a;
+    __syncthreads();
+    if (grp != 0) return;
+    for (int i = 1; i < groups; ++i) a += part[i * d_head + c];
+    o[c] = P::acc2a(a / sum);
 }
 
 // ------------------------------------------------------------------ cross entropy over stored logits
@@ -525,21 +584,43 @@ static void linear_plain_launch(const void *x, const void *wt_p, const void *wt_
     }
 }
 
-template <int TB>
+template <int TB, bool NORM>
 static void linear_f64_launch(const void *x, const void *wt_p, const void *wt_m, const void *b_p, const void *b_m, void *y, int n_sign,
-                              int m_half, int n, int k, int epi, hipStream_t s)
+                              int m_half, int n, int k, int epi, const NormArgs &norm, hipStream_t s)
 {
     const dim3 grid((n + 16 * TB - 1) / (16 * TB), (m_half + 16 * TB - 1) / (16 * TB), n_sign), block(256);
 #define ZO_F64(E)                                                                                                       \
-    linear_f64_mfma_kernel<E, TB><<<grid, block, 0, s>>>((const double *)x, (const float *)wt_p, (const float *)wt_m,   \
-                                                         (const float *)b_p, (const float *)b_m, (double *)y, m_half, n, k)
+    linear_f64_mfma_kernel<E, TB, NORM><<<grid, block, 0, s>>>((const double *)x, (const float *)wt_p, (const float *)wt_m,   \
+                                                               (const float *)b_p, (const float *)b_m, (double *)y, m_half, n, k, norm)
     switch (epi) {
     case 0: ZO_F64(0); break;
     case 1: ZO_F64(1); break;
-    case 2: ZO_F64(2); break;
+    case 2: if constexpr (!NORM) ZO_F64(2); break;
     default: ZO_F64(3); break;
     }
 #undef ZO_F64
+}
+
+// 32 x 32 tiles once they give every CU two workgroups, else 16 x 16 (times in us, both tilings): 256 x 384 x 128
+// (192 tiles) 5.0 / 5.3, 256 x 128 x 512 (64) 5.3 / 11.8, 512 x 768 x 768 (768) 50 / 33, 2048 x 768 x 3072 753 / 417
+static bool f64_tiles32(int n_sign, int m_half, int n) { return (long)n_sign * ((m_half + 31) / 32) * ((n + 31) / 32) >= 512; }
+
+bool norm_linear_fused(const void *resid, const void *g_p, const void *g_m, const void *lb_p, const void *lb_m, const void *wt_p,
+                       const void *wt_m, int dtype, int n_sign, int m_half, int n, int k)
+{
+    auto off = [](const void *p) { return (uintptr_t)p % 16 != 0; };
+    return dtype == kFP32 && k % 4 == 0 && k <= 512 && !f64_tiles32(n_sign, m_half, n) && !off(resid) && !off(g_p) && !off(g_m) && !off(lb_p) &&
+           !off(lb_m) && !off(wt_p) && !off(wt_m);
+}
+
+hipError_t launch_norm_linear(const void *resid, const void *g_p, const void *g_m, const void *lb_p, const void *lb_m, float eps,
+                              const void *wt_p, const void *wt_m, const void *b_p, const void *b_m, void *y, int n_sign,
+                              int m_half, int n, int k, int epilogue, hipStream_t s)
+{
+    if (epilogue != 0 && epilogue != 1 && epilogue != 3) return hipErrorInvalidValue;
+    const NormArgs norm{(const float *)g_p, (const float *)g_m, (const float *)lb_p, (const float *)lb_m, eps};
+    linear_f64_launch<1, true>(resid, wt_p, wt_m, b_p, b_m, y, n_sign, m_half, n, k, epilogue, norm, s);
+    return hipGetLastError();
 }
 
 hipError_t launch_linear(const void *x, const void *wt_p, const void *wt_m, const void *b_p, const void *b_m, void *y,
@@ -548,11 +629,8 @@ hipError_t launch_linear(const void *x, const void *wt_p, const void *wt_m, cons
     if (allow_mfma && dtype != kFP32 && mfma_linear_supported(m_half, n, k))
         return launch_linear_mfma(x, wt_p, wt_m, b_p, b_m, y, dtype, n_sign, m_half, n, k, epilogue, s);
     if (dtype == kFP32 && k % 4 == 0 && (uintptr_t)x % 16 == 0 && (uintptr_t)wt_p % 16 == 0 && (uintptr_t)wt_m % 16 == 0) {
-        // 32 x 32 tiles once they give every CU two workgroups, else 16 x 16 (times in us, both tilings): 256 x 384 x 128
-        // (192 tiles) 5.0 / 5.3, 256 x 128 x 512 (64) 5.3 / 11.8, 512 x 768 x 768 (768) 50 / 33, 2048 x 768 x 3072 753 / 417
-        const long tiles32 = (long)n_sign * ((m_half + 31) / 32) * ((n + 31) / 32);
-        if (tiles32 >= 512) linear_f64_launch<2>(x, wt_p, wt_m, b_p, b_m, y, n_sign, m_half, n, k, epilogue, s);
-        else linear_f64_launch<1>(x, wt_p, wt_m, b_p, b_m, y, n_sign, m_half, n, k, epilogue, s);
+        if (f64_tiles32(n_sign, m_half, n)) linear_f64_launch<2, false>(x, wt_p, wt_m, b_p, b_m, y, n_sign, m_half, n, k, epilogue, NormArgs{}, s);
+        else linear_f64_launch<1, false>(x, wt_p, wt_m, b_p, b_m, y, n_sign, m_half, n, k, epilogue, NormArgs{}, s);
         return hipGetLastError();
     }
     ZO_DISPATCH_DT(dtype, (linear_plain_launch<DT>(x, wt_p, wt_m, b_p, b_m, y, n_sign, m_half, n, k, epilogue, s)));

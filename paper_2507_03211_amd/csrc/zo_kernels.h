@@ -66,6 +66,13 @@ hipError_t launch_layernorm(const void *resid, const void *g_p, const void *g_m,
 hipError_t launch_linear(const void *x, const void *wt_p, const void *wt_m, const void *b_p, const void *b_m,
                          void *y, int dtype, int n_sign, int m_half, int n, int k, int epilogue,
                          bool allow_mfma, hipStream_t s);
+// LayerNorm of the residual stream and the linear layer behind it in one launch (small fp32 models); norm_linear_fused says
+// whether a shape takes it
+bool norm_linear_fused(const void *resid, const void *g_p, const void *g_m, const void *lb_p, const void *lb_m, const void *wt_p,
+                       const void *wt_m, int dtype, int n_sign, int m_half, int n, int k);
+hipError_t launch_norm_linear(const void *resid, const void *g_p, const void *g_m, const void *lb_p, const void *lb_m, float eps,
+                              const void *wt_p, const void *wt_m, const void *b_p, const void *b_m, void *y, int n_sign,
+                              int m_half, int n, int k, int epilogue, hipStream_t s);
 hipError_t launch_attention(const void *qkv, void *out, int dtype, int n_seq, int seq, int n_heads, int d_head,
                             bool allow_mfma, hipStream_t s);
 hipError_t launch_ce_rows(const void *logits, const int32_t *target, double *row_loss, int dtype, int rows,
