@@ -377,7 +377,7 @@ __global__ __launch_bounds__(256) void linear_f64_mfma_kernel(const double *__re
 // One workgroup per (query row, head, sequence): scores into LDS, softmax, then P V.
 template <int DT>
 __global__ __launch_bounds__(128) void attention_plain_kernel(const void *qkv_, void *out_, int seq, int n_heads,
-                                                              int d_head)
+                                                              int d_head, int groups)
 {
     using P = Prec<DT>;
     using Acc = typename P::Acc;
@@ -417,7 +417,6 @@ __global__ __launch_bounds__(128) void attention_plain_kernel(const void *qkv_, 
     const typename P::A *vr = qkv + 2 * d + head * d_head;
     // heads of up to half a block: the keys are dealt to as many groups of d_head threads as there are (4 sequences of 32
     // tokens, 4 heads of 16, fp64: 7.7 us with one group / 6.1)
-    const int groups = d_head <= 64 ? (int)blockDim.x / d_head : 1;
     if (groups == 1) {
         for (int c = threadIdx.x; c < d_head; c += blockDim.x) {
             Acc a = 0;
@@ -426,7 +425,7 @@ __global__ __launch_bounds__(128) void attention_plain_kernel(const void *qkv_, 
         }
         return;
     }
-    __shared__ Acc part[128];
+    Acc *part = red + 16;               // [blockDim.x]
     const int c = (int)threadIdx.x % d_head, grp = (int)threadIdx.x / d_head;
     Acc a = 0;
     if (grp < groups)
@@ -664,8 +663,11 @@ hipError_t launch_attention(const void *qkv, void *out, int dtype, int n_seq, in
     if (allow_mfma && dtype != kFP32 && aligned && !tiny && mfma_attention_supported(seq, n_heads, d_head))
         return launch_attention_mfma(qkv, out, dtype, n_seq, seq, n_heads, d_head, s);
     const dim3 grid(seq, n_heads, n_seq), block(128);
-    const size_t smem = (size_t)(seq + d_head + 16) * acc_bytes(dtype);
-    ZO_DISPATCH_DT(dtype, (attention_plain_kernel<DT><<<grid, block, smem, s>>>(qkv, out, seq, n_heads, d_head)));
+    size_t smem = (size_t)(seq + d_head + 16) * acc_bytes(dtype);
+    // groups of threads over a row's keys, where their partial sums have room (lengths near the LDS limit stay with one group)
+    const int groups = d_head <= 64 && smem + block.x * acc_bytes(dtype) <= 32768 ? (int)block.x / d_head : 1;
+    if (groups > 1) smem += block.x * acc_bytes(dtype);
+    ZO_DISPATCH_DT(dtype, (attention_plain_kernel<DT><<<grid, block, smem, s>>>(qkv, out, seq, n_heads, d_head, groups)));
     return hipGetLastError();
 }
 

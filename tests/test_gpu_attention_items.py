@@ -55,3 +55,16 @@ def test_a_workgroup_per_item_gives_the_bits_of_persistent_ones(dtype, n_seq, se
 def test_ragged_ends(dh, seq):
     qkv = _qkv(2, seq, 3, dh, zi.BF16, seq + dh)
     _check(_run(qkv, 2, seq, 3, dh, zi.BF16), qkv, 2, seq, 3, dh, zi.BF16)
+
+
+@pytest.mark.parametrize("seq", [40, 75, 140])
+@pytest.mark.parametrize("n_seq,heads,dh", [(24, 40, 64), (24, 40, 128), (24, 30, 80)])
+def test_sequences_of_nan_leave_their_neighbours_alone(seq, n_seq, heads, dh):
+    # what a ragged tile holds past its sequence's end must not be what the workgroup's item before it left there
+    qkv = _qkv(n_seq, seq, heads, dh, zi.BF16, seq)
+    clean = _run(qkv, n_seq, seq, heads, dh, zi.BF16).reshape(n_seq, seq, heads * dh)
+    bad = qkv.clone().reshape(n_seq, seq, 3 * heads * dh)
+    bad[1::2] = float("nan")
+    got = _run(bad.reshape(qkv.shape).contiguous(), n_seq, seq, heads, dh, zi.BF16).reshape(n_seq, seq, heads * dh)
+    assert torch.equal(got[0::2], clean[0::2])
+    assert bool(torch.isnan(got[1::2]).all())
