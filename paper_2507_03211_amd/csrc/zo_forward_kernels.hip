@@ -5,6 +5,7 @@
 //
 // Row layout everywhere: row = sign * m_half + b * seq + t, sign 0 = theta + eps z,
 // sign 1 = theta - eps z; each sign reads its own copy of every parameter.
+#include "zo_choices.h"
 #include "zo_kernels.h"
 #include "zo_types.hip.h"
 
@@ -267,20 +268,21 @@ __global__ __launch_bounds__(256) void linear_plain_kernel(const void *x, const 
 // plain kernel.  Both signs of m_half x n x k, plain kernel / here: 64 x 64 x 256 52 / 5.1 us, 64 x 192 x 64 16.6 / 5.0,
 // 256 x 128 x 512 100 / 5.3, 512 x 768 x 768 202 / 33, 8192 x 768 x 768 985 / 430 (45 TFLOP/s; what bounds it there is
 // L2 traffic, 5.3 flop a byte).
-// NORM: x is the residual stream and the layer's input its LayerNorm, taken on the way: 16 lanes a row find mean and variance,
-// the operands are normalised as they are loaded.  Every column tile does that over again, for rows that it reads anyway; a
-// LayerNorm launch ahead of the layer takes 4 us and more for any size.  Taken while the layer itself is a chain of latencies
-// (16 x 16 tiles) and its rows are short (k <= 512).  64 rows a sign, us, two launches / one: 64 x 192 4.0 + 3.2 / 4.9; a step of
-// 2 layers of 64 channels 105 / 94, of 3 layers of 128 at 256 rows a sign 207 / 184.
+// NP > 0: x is the residual stream and the layer's input its LayerNorm, taken on the way: 16 lanes a row find mean and variance,
+// the operands are normalised as they are loaded.  A lane holds its share of the row, NP pieces of 64 elements among the 16, in
+// registers, loaded in one burst: read piece by piece, and again for the variance, a row of 512 waits for memory 16 times (9 rows
+// a sign, 512 columns, 10.7 us / 9.6 in one burst; two launches take 10.4).  Two pieces where they do: eight leave room
+// for five waves per SIMD, two for six.  Where this is taken: norm_on_the_way.
 struct NormArgs { const float *g_p, *g_m, *b_p, *b_m; float eps; };
 typedef double f64x4 __attribute__((ext_vector_type(4)));
-template <int EPI, int TB, bool NORM>
+template <int EPI, int TB, int NP>
 __global__ __launch_bounds__(256) void linear_f64_mfma_kernel(const double *__restrict__ x, const float *__restrict__ wt_p,
                                                               const float *__restrict__ wt_m, const float *__restrict__ b_p,
                                                               const float *__restrict__ b_m, double *__restrict__ y, int m_half, int n,
                                                               int k, NormArgs norm)
 {
     constexpr int BT = 16 * TB;
+    constexpr bool NORM = NP > 0;
     __shared__ double part[4][BT][BT + 1];
     const int sign = blockIdx.z;
     const double *xa = x + (size_t)sign * m_half * k;
@@ -310,12 +312,28 @@ __global__ __launch_bounds__(256) void linear_f64_mfma_kernel(const double *__re
         for (int t = 0; t < TB; ++t) {
             const int r = 16 * t + (int)(threadIdx.x >> 4), xi = m0 + r;
             const double *h = xa + (size_t)(xi < m_half ? xi : m_half - 1) * k;
-            double s = 0.0, v = 0.0;
-            for (int c = 4 * lane16; c < k; c += 64) s += (h[c] + h[c + 1]) + (h[c + 2] + h[c + 3]);
-            const double mu = sum16(s) / (double)k;
-            for (int c = 4 * lane16; c < k; c += 64)
+            double2 p[NP][2];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) { const double q = h[c + e] - mu; v += q * q; }
+            for (int i = 0; i < NP; ++i) {
+                if (64 * i >= k) break;
+                const int c = 4 * lane16 + 64 * i < k ? 4 * lane16 + 64 * i : k - 4;                     // past the row: not counted
+                p[i][0] = *(const double2 *)(h + c);
+                p[i][1] = *(const double2 *)(h + c + 2);
+            }
+            double s = 0.0, v = 0.0;
+#pragma unroll
+            for (int i = 0; i < NP; ++i)
+                if (4 * lane16 + 64 * i < k) s += (p[i][0].x + p[i][0].y) + (p[i][1].x + p[i][1].y);
+            const double mu = sum16(s) / (double)k;
+            auto square = [&](double q) { v += (q - mu) * (q - mu); };
+#pragma unroll
+            for (int i = 0; i < NP; ++i)
+                if (4 * lane16 + 64 * i < k) {
+                    square(p[i][0].x);
+                    square(p[i][0].y);
+                    square(p[i][1].x);
+                    square(p[i][1].y);
+                }
             const double var = sum16(v) / (double)k;
             if (lane16 == 0) { stats[r][0] = mu; stats[r][1] = 1.0 / __builtin_sqrt(var + (double)norm.eps); }
         }
@@ -595,32 +613,28 @@ static void linear_plain_launch(const void *x, const void *wt_p, const void *wt_
     }
 }
 
-template <int TB, bool NORM>
+template <int TB, int NP>
 static void linear_f64_launch(const void *x, const void *wt_p, const void *wt_m, const void *b_p, const void *b_m, void *y, int n_sign,
                               int m_half, int n, int k, int epi, const NormArgs &norm, hipStream_t s)
 {
     const dim3 grid((n + 16 * TB - 1) / (16 * TB), (m_half + 16 * TB - 1) / (16 * TB), n_sign), block(256);
 #define ZO_F64(E)                                                                                                       \
-    linear_f64_mfma_kernel<E, TB, NORM><<<grid, block, 0, s>>>((const double *)x, (const float *)wt_p, (const float *)wt_m,   \
-                                                               (const float *)b_p, (const float *)b_m, (double *)y, m_half, n, k, norm)
+    linear_f64_mfma_kernel<E, TB, NP><<<grid, block, 0, s>>>((const double *)x, (const float *)wt_p, (const float *)wt_m,   \
+                                                             (const float *)b_p, (const float *)b_m, (double *)y, m_half, n, k, norm)
     switch (epi) {
     case 0: ZO_F64(0); break;
     case 1: ZO_F64(1); break;
-    case 2: if constexpr (!NORM) ZO_F64(2); break;
+    case 2: if constexpr (NP == 0) ZO_F64(2); break;
     default: ZO_F64(3); break;
     }
 #undef ZO_F64
 }
 
-// 32 x 32 tiles once they give every CU two workgroups, else 16 x 16 (times in us, both tilings): 256 x 384 x 128
-// (192 tiles) 5.0 / 5.3, 256 x 128 x 512 (64) 5.3 / 11.8, 512 x 768 x 768 (768) 50 / 33, 2048 x 768 x 3072 753 / 417
-static bool f64_tiles32(int n_sign, int m_half, int n) { return (long)n_sign * ((m_half + 31) / 32) * ((n + 31) / 32) >= 512; }
-
 bool norm_linear_fused(const void *resid, const void *g_p, const void *g_m, const void *lb_p, const void *lb_m, const void *wt_p,
                        const void *wt_m, int dtype, int n_sign, int m_half, int n, int k)
 {
     auto off = [](const void *p) { return (uintptr_t)p % 16 != 0; };
-    return dtype == kFP32 && k % 4 == 0 && k <= 512 && !f64_tiles32(n_sign, m_half, n) && !off(resid) && !off(g_p) && !off(g_m) && !off(lb_p) &&
+    return dtype == kFP32 && k % 4 == 0 && norm_on_the_way(n_sign, m_half, n, k) && !off(resid) && !off(g_p) && !off(g_m) && !off(lb_p) &&
            !off(lb_m) && !off(wt_p) && !off(wt_m);
 }
 
@@ -628,9 +642,10 @@ hipError_t launch_norm_linear(const void *resid, const void *g_p, const void *g_
                               const void *wt_p, const void *wt_m, const void *b_p, const void *b_m, void *y, int n_sign,
                               int m_half, int n, int k, int epilogue, hipStream_t s)
 {
-    if (epilogue != 0 && epilogue != 1 && epilogue != 3) return hipErrorInvalidValue;
+    if ((epilogue != 0 && epilogue != 1 && epilogue != 3) || k > kNormRowMax || k % 4 != 0) return hipErrorInvalidValue;
     const NormArgs norm{(const float *)g_p, (const float *)g_m, (const float *)lb_p, (const float *)lb_m, eps};
-    linear_f64_launch<1, true>(resid, wt_p, wt_m, b_p, b_m, y, n_sign, m_half, n, k, epilogue, norm, s);
+    if (k <= kNormRowShort) linear_f64_launch<1, kNormRowShort / 64>(resid, wt_p, wt_m, b_p, b_m, y, n_sign, m_half, n, k, epilogue, norm, s);
+    else linear_f64_launch<1, kNormRowMax / 64>(resid, wt_p, wt_m, b_p, b_m, y, n_sign, m_half, n, k, epilogue, norm, s);
     return hipGetLastError();
 }
 
@@ -640,8 +655,8 @@ hipError_t launch_linear(const void *x, const void *wt_p, const void *wt_m, cons
     if (allow_mfma && dtype != kFP32 && mfma_linear_supported(m_half, n, k))
         return launch_linear_mfma(x, wt_p, wt_m, b_p, b_m, y, dtype, n_sign, m_half, n, k, epilogue, s);
     if (dtype == kFP32 && k % 4 == 0 && (uintptr_t)x % 16 == 0 && (uintptr_t)wt_p % 16 == 0 && (uintptr_t)wt_m % 16 == 0) {
-        if (f64_tiles32(n_sign, m_half, n)) linear_f64_launch<2, false>(x, wt_p, wt_m, b_p, b_m, y, n_sign, m_half, n, k, epilogue, NormArgs{}, s);
-        else linear_f64_launch<1, false>(x, wt_p, wt_m, b_p, b_m, y, n_sign, m_half, n, k, epilogue, NormArgs{}, s);
+        if (f64_tiles32(n_sign, m_half, n)) linear_f64_launch<2, 0>(x, wt_p, wt_m, b_p, b_m, y, n_sign, m_half, n, k, epilogue, NormArgs{}, s);
+        else linear_f64_launch<1, 0>(x, wt_p, wt_m, b_p, b_m, y, n_sign, m_half, n, k, epilogue, NormArgs{}, s);
         return hipGetLastError();
     }
     ZO_DISPATCH_DT(dtype, (linear_plain_launch<DT>(x, wt_p, wt_m, b_p, b_m, y, n_sign, m_half, n, k, epilogue, s)));
