@@ -29,4 +29,8 @@ inline bool norm_on_the_way(int n_sign, int m_half, int n, int k)
     return k <= kNormRowShort || (tiles <= 1152 && (double)tiles * k * __builtin_sqrt(k / 300.0) <= 140000.0 + 150.0 * (double)(rows < 256 ? rows : 256));
 }
 
+// Pieces of 256 elements that a wavefront holds of a LayerNorm row of 16-bit models (three at least); 0: longer than 2048, a
+// workgroup's.
+inline int layernorm_pieces(int d) { return d > 2048 ? 0 : d <= 768 ? 3 : (d + 255) / 256; }
+
 }  // namespace zo

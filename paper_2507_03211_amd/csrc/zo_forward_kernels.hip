@@ -77,10 +77,11 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const void *resid, const
 
 
 // Fast path for 2-byte activations and rows of up to 2048 elements: one wavefront per row, the row held in registers
-// (NV float4 per lane), so the residual stream is read once; statistics by wavefront shuffles only.  d % 4 == 0.
+// (NV float4 per lane), so the residual stream is read once; statistics without LDS.  d % 4 == 0.
 // What a wave waits for is latency: the row, twelve exchanges of the two sums, gain and bias.  Exchanges in the vector pipe and
 // gain and bias loaded with the row, 16384 rows, us before / here: d 768 14.0 / 13.3, 1024 17.9 / 15.9 (6.3 TB/s), 2048 37.0 /
-// 34.4.
+// 34.4.  As many pieces as the row has: with eight for all rows above 1024, 88 registers a lane (5 waves per SIMD) and loads of
+// pieces that are not there, 4096 rows of 1280 8.7 us / 7.5 with five, of 1536 9.8 / 8.3 with six, of 1792 10.4 / 9.5 with seven.
 template <int DT, int NV>
 __global__ __launch_bounds__(256) void layernorm_wave_kernel(const float *__restrict__ resid, const uint16_t *__restrict__ g_p,
                                                              const uint16_t *__restrict__ g_m, const uint16_t *__restrict__ b_p,
@@ -582,13 +583,19 @@ hipError_t launch_layernorm(const void *resid, const void *g_p, const void *g_m,
                                                                     (const uint16_t *)g_m, (const uint16_t *)b_p,             \
                                                                     (const uint16_t *)b_m, (uint16_t *)y, m_half, d, eps)
 #define ZO_LNW_D(DT)                          \
-    if (d <= 768) ZO_LNW(DT, 3);              \
-    else if (d <= 1024) ZO_LNW(DT, 4);        \
-    else if (d <= 2048) ZO_LNW(DT, 8);        \
-    else if (d <= 4096) ZO_LNB(DT, 4);        \
-    else if (d <= 5120) ZO_LNB(DT, 5);        \
-    else if (d <= 8192) ZO_LNB(DT, 8);        \
-    else ZO_LNB(DT, 12);
+    switch (layernorm_pieces(d)) {            \
+    case 3: ZO_LNW(DT, 3); break;             \
+    case 4: ZO_LNW(DT, 4); break;             \
+    case 5: ZO_LNW(DT, 5); break;             \
+    case 6: ZO_LNW(DT, 6); break;             \
+    case 7: ZO_LNW(DT, 7); break;             \
+    case 8: ZO_LNW(DT, 8); break;             \
+    default:                                  \
+        if (d <= 4096) ZO_LNB(DT, 4);         \
+        else if (d <= 5120) ZO_LNB(DT, 5);    \
+        else if (d <= 8192) ZO_LNB(DT, 8);    \
+        else ZO_LNB(DT, 12);                  \
+    }
         if (dtype == kBF16) { ZO_LNW_D(kBF16) } else { ZO_LNW_D(kFP16) }
 #undef ZO_LNB
 #undef ZO_LNW_D

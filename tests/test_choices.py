@@ -10,11 +10,14 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PROGRAM = r"""
 #include "zo_choices.h"
 #include <cstdio>
-#include <cstring>
-int main(int argc, char **argv)
+int main()
 {
+    char what;
     int a[4];
-    while (scanf("%d %d %d %d", a, a + 1, a + 2, a + 3) == 4) printf("%d\n", (int)zo::norm_on_the_way(a[0], a[1], a[2], a[3]));
+    while (scanf(" %c %d %d %d %d", &what, a, a + 1, a + 2, a + 3) == 5) {
+        if (what == 'n') printf("%d\n", (int)zo::norm_on_the_way(a[0], a[1], a[2], a[3]));
+        if (what == 'l') printf("%d\n", zo::layernorm_pieces(a[0]));
+    }
     return 0;
 }
 """
@@ -29,8 +32,8 @@ def choose(tmp_path_factory):
     src.write_text(PROGRAM)
     subprocess.run([cxx, "-std=c++17", "-I", os.path.join(ROOT, "paper_2507_03211_amd", "csrc"), str(src), "-o", str(exe)], check=True, timeout=120)
 
-    def ask(rows):
-        run = subprocess.run([str(exe)], input="\n".join(" ".join(map(str, r)) for r in rows), capture_output=True, text=True, timeout=60, check=True)
+    def ask(what, rows):
+        run = subprocess.run([str(exe)], input="\n".join(" ".join(map(str, (what,) + r)) for r in rows), capture_output=True, text=True, timeout=60, check=True)
         return [int(x) for x in run.stdout.split()]
 
     return ask
@@ -50,11 +53,16 @@ NORM = [
 
 
 def test_a_layer_takes_its_layernorm_on_the_way_where_that_is_faster(choose):
-    took = choose([(2, m, n, k) for m, n, k, _, _ in NORM])
+    took = choose("n", [(2, m, n, k) for m, n, k, _, _ in NORM])
     for (m, n, k, two, one), t in zip(NORM, took):
         # 2 % is what repeated measurements of one size differ by; what the rule leaves it may give away 10 % of
         assert one <= 1.02 * two if t else two <= 1.1 * one, (m, n, k)
 
 
 def test_rows_that_do_not_fit_the_registers_take_two_launches(choose):
-    assert choose([(2, 9, 64, 512), (2, 9, 64, 516), (2, 9, 64, 4096), (1, 9, 64, 512), (2, 1 << 20, 64, 64)]) == [1, 0, 0, 1, 0]
+    assert choose("n", [(2, 9, 64, 512), (2, 9, 64, 516), (2, 9, 64, 4096), (1, 9, 64, 512), (2, 1 << 20, 64, 64)]) == [1, 0, 0, 1, 0]
+
+
+def test_a_layernorm_row_has_as_many_pieces_as_it_needs(choose):
+    for d, n in zip(range(4, 2304, 4), choose("l", [(d, 0, 0, 0) for d in range(4, 2304, 4)])):
+        assert n == (0 if d > 2048 else max(3, -(-d // 256))), d
