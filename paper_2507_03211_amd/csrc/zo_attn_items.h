@@ -1,0 +1,80 @@
+// How the causal attention's work items are listed and dealt to workgroups: what the kernel and its launcher share.
+//
+// Work items: (128 query rows, head, sequence).  The hardware deals consecutive workgroup ids round-robin to the 8 XCDs, so
+// workgroup b sits on XCD b % 8 and is that XCD's slot b / 8.  Every (head, sequence) pair goes to one XCD with all its query
+// tiles, so the XCDs hold equal shares of the causal triangle and the K and V of a pair are fetched into one L2 instead of eight.
+// An XCD's items are listed in groups of pairs, long rows first within a group.  Persistent workgroups: slot j takes entry j of
+// the even rounds and entry slots - 1 - j of the odd ones, so that a long tile is followed by a short one.  One workgroup per
+// item: the list is one round, and a workgroup that ends makes room for the next entry.
+#pragma once
+#include <hip/hip_runtime_api.h>
+
+namespace zo {
+
+constexpr int kAttnRows = 128;
+
+struct AttnItems {
+    int n_qt, n_pairs, pairs_xcd, group_pairs, group_items, n_lin;      // n_lin: entries of an XCD's list, empty ones among them
+    // `fill`: as many of an XCD's items as a group is to have at least, if that is more than one pair
+    __host__ __device__ __forceinline__ AttnItems(int seq, int n_heads, int n_seq, int fill)
+    {
+        n_qt = (seq + kAttnRows - 1) / kAttnRows;
+        n_pairs = n_heads * n_seq, pairs_xcd = (n_pairs + 7) / 8;
+        group_pairs = fill / n_qt > 1 ? fill / n_qt : 1, group_items = group_pairs * n_qt;
+        n_lin = (pairs_xcd + group_pairs - 1) / group_pairs * group_items;
+    }
+    // the (head, sequence) pair of an entry, -1 if it is empty, and its query tile
+    __host__ __device__ __forceinline__ int pair_at(int lin, int xcd, int &qt) const
+    {
+        if (lin >= n_lin) return -1;
+        const int grp = lin / group_items, r = lin % group_items;
+        const int gp = pairs_xcd - grp * group_pairs < group_pairs ? pairs_xcd - grp * group_pairs : group_pairs;
+        if (r >= gp * n_qt) return -1;
+        qt = n_qt - 1 - r / gp;
+        const int pair = (grp * group_pairs + r % gp) * 8 + xcd;
+        return pair < n_pairs ? pair : -1;
+    }
+};
+
+// Slots an XCD's workgroups have (persistent: as many as are resident at once) and the list's `fill`.
+struct AttnPlan { int slots, fill; };
+
+// When the query tiles of a sequence divide the resident workgroups, rounds of the list are whole groups, the zigzag gives every
+// slot the same number of key tiles, and persistent workgroups save an item's start.  When they don't, a group's long tiles come
+// to lie at both ends of a round and some slots get two of them: then a workgroup per item, for which the hardware finds the free
+// place.  us, persistent / per item, heads of 128 unless said: 1500 tokens (12 tiles, 64 slots) x 64 (sequence, head) pairs
+// 67 / 50, x 320 259 / 236; 1100 x 320 172 / 137; 600 x 160 35 / 28; heads of 64, 850 x 640 130 / 104; but 1024 x 160 63 / 72.
+// From some round on the dynamic order wins there as well: with heads of 64 (three workgroups a CU) from the fifth, with up to 4
+// tiles a sequence from the fourth; with larger heads from the seventh and the fifth.  One and two tiles stay persistent: an
+// item's start is most of it.  Persistent time over per item's, whole tiles | a ragged last one:
+//   rounds             4           4.5         5           6           7           8           12.5
+//   heads of 64,  3 t  1.03 | 1.05 1.03 | 0.98 1.06 | 1.04 1.09 | 1.08 1.08 | 1.08 1.07 | 1.08 1.09 | 1.08
+//                 8 t  0.98 | 1.00 0.96 | 0.96 1.00 | 1.02 1.02 | 1.05 1.02 | 1.03 1.04 | 1.05 1.03 | 1.06
+//                32 t  1.00 | 1.00 0.95 | 0.95 1.00 | 1.02 1.01 | 1.02
+//   heads of 128, 4 t  1.00 | 1.02 0.94 | 0.95 1.01 | 1.06 1.02 | 1.05 1.02 | 1.07 1.01 | 1.08 1.02 | 1.06
+//                16 t  0.97 | 0.99 0.93 | 0.94 1.00 | 1.01 1.00 | 1.00 1.02 | 1.04 1.01 | 1.01
+//   heads of 80,  8 t  0.98 | 0.99 0.95 | 0.91 1.00 | 0.99 1.00 | 1.01 1.02 | 1.01 1.02 | 1.04 1.01 | 1.02
+//
+// The list of a workgroup per item: a group keeps few pairs' K and V in the L2, but the last one begins with its longest rows when
+// the others are nearly done.  Over few rounds that tail is the longer, and all pairs make one group: the longest rows of all
+// come first.  us, persistent / groups / one group: heads of 64, 4224 tokens x 40 pairs (1.7 rounds) 118 / 128 / 107, 6400 x 32
+// (2.1) 212 / 224 / 186; heads of 128, 3328 x 56 (2.8) 179 / 187 / 166, 3584 x 40 (2.2) 154 / 156 / 135.  Up to three rounds from 8
+// tiles on; shorter sequences leave groups sooner: groups / one group, heads of 64, 640 tokens x 384 (2.5) 1.02, heads of 128, 640 x 128
+// (1.2) 1.01, x 160 (1.6) 0.98, x 224 (2.2) 0.96.  Two whole groups that fill the slots have no such tail, and with large heads
+// two groups' K and V are twice the L2: heads of 128, 1792 x 64 62.7 / 66.8, 1408 x 80 52.9 / 54.8, of 112 68.1 / 69.9
+// (heads of 80: 63.1 / 61.9, 53.1 / 51.8).
+inline AttnPlan attention_plan(long long pairs, int n_qt, int slots_max, int d_head)
+{
+    const long long pairs_xcd = (pairs + 7) / 8, items = pairs_xcd * n_qt;
+    if (items <= slots_max) return {(int)items, (int)items};
+    const int rounds = d_head == 64 ? (n_qt <= 4 ? 4 : 5) : (n_qt <= 4 ? 5 : 7);
+    const bool per_item = slots_max % n_qt != 0 || (n_qt >= 3 && items / slots_max >= rounds);
+    if (!per_item) return {slots_max, slots_max};
+    const long long in_slots = slots_max / n_qt > 1 ? slots_max / n_qt : 1;          // pairs
+    const bool even = d_head > 80 && n_qt <= slots_max && pairs_xcd == 2 * in_slots && 7 * in_slots * n_qt >= 6 * slots_max;
+    const bool one_group = 2 * items <= (n_qt >= 8 ? 6 : d_head == 64 ? 5 : 3) * (long long)slots_max && !even;
+    const long long group = one_group ? pairs_xcd : in_slots;
+    return {(int)((pairs_xcd + group - 1) / group * group * n_qt), one_group ? (int)items : slots_max};
+}
+
+}  // namespace zo

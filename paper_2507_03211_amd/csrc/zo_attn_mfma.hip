@@ -3,7 +3,7 @@
 // more sequences: the kernel sees n_seq = 2 * batch independent sequences.
 //
 // One work item = (128 query rows, one head, one sequence); 4 waves x 32 query rows.  Workgroups walk a per-XCD item list,
-// as many as the chip holds at once or one per item (see the launcher).  Key / value tiles of 64 keys stream through LDS.
+// as many as the chip holds at once or one per item (zo_attn_items.h).  Key / value tiles of 64 keys stream through LDS.
 // Everything is computed transposed so that a lane owns one query row:
 //     S^T[key, q] = K Q^T        (MFMA A = K rows, B = Q rows; lane: column q, 16 keys)
 //     O^T[c, q]  += V^T P^T      (MFMA A = V^T rows, B = P^T; lane: column q, 16 channels)
@@ -13,6 +13,7 @@
 // transposed fragments come from the LDS transposing read of gfx950.  The key loop is software-pipelined in units of
 // 32 keys: the vector arithmetic of one unit's softmax is issued between the matrix instructions of the next
 // unit's scores and of its own P V product.
+#include "zo_attn_items.h"
 #include "zo_kernels.h"
 #include "zo_types.hip.h"
 #include <type_traits>
@@ -25,7 +26,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 namespace {
 
-constexpr int BQ = 128, BKV = 64;
+constexpr int BQ = kAttnRows, BKV = 64;
 
 template <int DT> __device__ __forceinline__ f32x16 mfma32(const uint4 &a, const uint4 &b, const f32x16 &c)
 {
@@ -405,33 +406,13 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
         }
     };
 
-    // Work items: (query tile, head, sequence).  The hardware deals consecutive workgroup ids round-robin to the 8 XCDs, so
-    // workgroup b sits on XCD b % 8 and is that XCD's slot b / 8.  Every (head, sequence) pair goes to one XCD with all its
-    // query tiles, so the XCDs hold equal shares of the causal triangle and the K and V of a pair are fetched into one L2
-    // instead of eight.  The XCD's items are listed in groups of as many pairs as fill the workgroups it holds at once
-    // (`fill`), long rows first within a group.  Persistent workgroups: slot j takes entry j of the even rounds and entry
-    // slots - 1 - j of the odd ones, so that a long tile is followed by a short one.  One workgroup per item: the list is
-    // one round, and a workgroup that ends makes room for the next entry.
-    const int n_qt = (seq + BQ - 1) / BQ;
     const int slots = (int)gridDim.x >> 3, slot = (int)blockIdx.x >> 3, xcd = (int)blockIdx.x & 7;
-    const int n_pairs = n_heads * n_seq, pairs_xcd = (n_pairs + 7) / 8;
-    const int group_pairs = fill / n_qt > 1 ? fill / n_qt : 1, group_items = group_pairs * n_qt;
-    const int n_lin = (pairs_xcd + group_pairs - 1) / group_pairs * group_items;
-    // the slot's entry of a round: its (head, sequence) pair, -1 if there is none, and its query tile
-    auto pair_at = [&](int lin, int &qt) {
-        if (lin >= n_lin) return -1;
-        const int grp = lin / group_items, r = lin % group_items;
-        const int gp = pairs_xcd - grp * group_pairs < group_pairs ? pairs_xcd - grp * group_pairs : group_pairs;
-        if (r >= gp * n_qt) return -1;
-        qt = n_qt - 1 - r / gp;
-        const int pair = (grp * group_pairs + r % gp) * 8 + xcd;
-        return pair < n_pairs ? pair : -1;
-    };
+    const AttnItems list(seq, n_heads, n_seq, fill);
     auto lin_of = [&](int round) { return round * slots + ((round & 1) ? slots - 1 - slot : slot); };
     uint64_t again = 0;                              // rounds (mod 64) in which a row of this wave came out not finite
-    for (int round = 0; round * slots < n_lin; ++round) {
+    for (int round = 0; round * slots < list.n_lin; ++round) {
         int qt;
-        const int pair = pair_at(lin_of(round), qt);
+        const int pair = list.pair_at(lin_of(round), xcd, qt);
         if (pair < 0) continue;
         const int head = pair % n_heads, sq = pair / n_heads;
         base = qkv + (size_t)sq * seq * ld + head * DH;
@@ -533,9 +514,9 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
     if constexpr (kRedo) {
         if (again == 0) return;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this wave's own stores lie behind the ones that follow
-        for (int round = 0; round * slots < n_lin; ++round) {
+        for (int round = 0; round * slots < list.n_lin; ++round) {
             int qt;
-            const int pair = (again >> (round & 63)) & 1 ? pair_at(lin_of(round), qt) : -1;
+            const int pair = (again >> (round & 63)) & 1 ? list.pair_at(lin_of(round), xcd, qt) : -1;
             if (pair < 0) continue;
             const int head = pair % n_heads, sq = pair / n_heads;
             q0 = qt * BQ + wave * 32;
@@ -584,22 +565,13 @@ hipError_t launch_attention_mfma(const void *qkv, void *out, int dtype, int n_se
         if (e != hipSuccess) return e;
         n_cu = v >= 8 ? v / 8 * 8 : 8;
     }
-    const long long pairs_xcd = ((long long)n_heads * n_seq + 7) / 8;
-    const long long items_xcd = pairs_xcd * ((seq + BQ - 1) / BQ);
-    // Workgroups resident at once: 2 per CU, 3 at d_head 64 (the CU count is rounded down to whole XCDs' worth).  When the
-    // query tiles of a sequence divide that number, rounds of the list are whole groups, the zigzag gives every slot the same
-    // number of key tiles, and persistent workgroups save an item's start.  When they don't, a group's long tiles come to lie
-    // at both ends of a round and some slots get two of them: then a workgroup per item, for which the hardware finds the free
-    // place.  us, persistent / per item, heads of 128 unless said: 1500 tokens (12 tiles, 64 slots) x 64 (sequence, head) pairs
-    // 67 / 50, x 320 259 / 236; 1100 x 320 172 / 137; 600 x 160 35 / 28; heads of 64, 850 x 640 130 / 104; but 1024 x 160
-    // 63 / 72, 400 x 320 32 / 38.  Over many rounds, or some with a ragged last tile, which is shorter than the zigzag takes it
-    // for, the dynamic order wins by a little as well: 2048 x 320 402 / 397, heads of 64, 331 x 1024 50.6 / 48.3.
-    const long long slots_max = (long long)(n_cu / 8) * (d_head == 64 ? 3 : 2);
-    if (items_xcd > 0x7fffffffLL / 64) return hipErrorInvalidValue;      // the kernel's item indices are ints
-    const int n_qt = (seq + BQ - 1) / BQ, fill = (int)(items_xcd < slots_max ? items_xcd : slots_max);
-    const long long rounds = items_xcd / slots_max, group = fill / n_qt > 1 ? fill / n_qt : 1;
-    const bool per_item = items_xcd > slots_max && (slots_max % n_qt != 0 || (n_qt >= 3 && (rounds >= 8 || (rounds >= 4 && seq % BQ != 0))));
-    const dim3 grid((unsigned)(8 * (per_item ? (pairs_xcd + group - 1) / group * group * n_qt : fill))), block(256);
+    // workgroups resident at once: 2 per CU, 3 at d_head 64 (the CU count is rounded down to whole XCDs' worth)
+    const int slots_max = n_cu / 8 * (d_head == 64 ? 3 : 2), n_qt = (seq + BQ - 1) / BQ;
+    const long long pairs = (long long)n_heads * n_seq;
+    if ((pairs + 7) / 8 * n_qt > 0x7fffffffLL / 64) return hipErrorInvalidValue;      // the kernel's item indices are ints
+    const AttnPlan plan = attention_plan(pairs, n_qt, slots_max, d_head);
+    const int fill = plan.fill;
+    const dim3 grid(8u * (unsigned)plan.slots), block(256);
     const uint16_t *q = (const uint16_t *)qkv;
     uint16_t *o = (uint16_t *)out;
 #define ZO_ATTN(DH)                                                                                       \

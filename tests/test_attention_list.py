@@ -1,0 +1,86 @@
+"""The causal attention's work items (csrc/zo_attn_items.h), compiled for the host: every query tile of every (sequence, head) pair is
+worked by one workgroup exactly once, whatever the plan, and the plan is about the fastest of the three that were measured."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+# for each line "seq heads sequences slots d_head": slots and fill of the plan, whether each item comes once
+PROGRAM = r"""
+#include "zo_attn_items.h"
+#include <cstdio>
+#include <vector>
+int main()
+{
+    int seq, heads, n_seq, slots_max, d_head;
+    while (scanf("%d %d %d %d %d", &seq, &heads, &n_seq, &slots_max, &d_head) == 5) {
+        const int n_qt = (seq + zo::kAttnRows - 1) / zo::kAttnRows;
+        const zo::AttnPlan plan = zo::attention_plan((long long)heads * n_seq, n_qt, slots_max, d_head);
+        const zo::AttnItems list(seq, heads, n_seq, plan.fill);
+        std::vector<int> seen((size_t)heads * n_seq * n_qt, 0);
+        bool good = true;
+        for (int xcd = 0; xcd < 8; ++xcd)
+            for (int slot = 0; slot < plan.slots; ++slot)
+                for (int round = 0; round * plan.slots < list.n_lin; ++round) {
+                    int qt = -1;
+                    const int pair = list.pair_at(round * plan.slots + (round & 1 ? plan.slots - 1 - slot : slot), xcd, qt);
+                    if (pair < 0) continue;
+                    good = good && pair < heads * n_seq && pair % 8 == xcd && qt >= 0 && qt < n_qt;
+                    if (good) ++seen[(size_t)pair * n_qt + qt];
+                }
+        for (int s : seen) good = good && s == 1;
+        printf("%d %d %d\n", plan.slots, plan.fill, (int)good);
+    }
+    return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plans(tmp_path_factory):
+    cxx = shutil.which("g++") or shutil.which("c++")
+    rocm = next((p for p in (os.environ.get("ROCM_PATH"), "/opt/rocm") if p and os.path.exists(os.path.join(p, "include", "hip"))), None)
+    if not cxx or not rocm:
+        pytest.skip("no host compiler or no HIP headers")
+    folder = tmp_path_factory.mktemp("items")
+    src, exe = folder / "items.cpp", folder / "items"
+    src.write_text(PROGRAM)
+    subprocess.run([cxx, "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROOT, "paper_2507_03211_amd", "csrc"),
+                    "-I", os.path.join(rocm, "include"), str(src), "-o", str(exe)], check=True, timeout=120)
+
+    def ask(rows):
+        run = subprocess.run([str(exe)], input="\n".join(" ".join(map(str, r)) for r in rows), capture_output=True, text=True, timeout=120, check=True)
+        return [tuple(map(int, line.split())) for line in run.stdout.splitlines()]
+
+    return ask
+
+
+def test_every_item_comes_once(plans):
+    rows = [(seq, heads, n_seq, slots, 64 if slots % 3 == 0 else dh) for slots, dh in ((2, 80), (3, 64), (64, 80), (64, 128), (96, 64)) for seq in (1, 128, 129, 300, 640, 1023, 1500, 2048, 4200, 8320)
+            for heads, n_seq in ((1, 1), (3, 3), (8, 1), (5, 8), (17, 2), (40, 8), (32, 32)) if heads * n_seq * seq <= 2000000]
+    for row, (slots, fill, good) in zip(rows, plans(rows)):
+        assert good and slots >= 1 and fill >= 1, row
+
+
+# d_head, tokens, pairs, us: persistent, a workgroup per item in groups, the same in one group (bf16, 256 CUs; None: not timed)
+MEASURED = [
+    (64, 4224, 40, 117.8, 127.9, 107.2), (64, 6400, 32, 212.1, 223.9, 186.3), (64, 4224, 56, 159.1, 168.2, 144.5), (64, 8320, 24, 243.1, 255.6, 229.3),
+    (64, 3328, 32, 73.8, 74.3, 58.9), (64, 640, 160, 28.0, 22.1, 18.5), (128, 3328, 56, 178.9, 187.2, 166.4), (128, 3584, 40, 153.6, 156.5, 134.7),
+    (128, 2176, 48, 83.6, 66.3, 67.5), (80, 4224, 32, 160.9, 167.0, 152.4), (80, 5120, 16, 140.4, 142.8, 121.0), (80, 8320, 16, 285.2, 301.4, 288.2), (128, 1792, 64, 82.3, 62.7, 66.8), (112, 1408, 80, 84.5, 68.1, 69.9),
+    (128, 640, 224, 44.3, 43.4, 45.4), (128, 384, 640, 69.3, 62.9, 72.2), (128, 768, 256, 70.5, 72.2, 73.6), (128, 768, 320, 97.6, 81.7, 95.0),
+    (128, 1152, 224, 127.3, 107.3, 114.5), (80, 896, 256, 99.4, 80.1, 82.2), (128, 1024, 128, 45.5, 48.3, None), (64, 512, 384, 27.9, 30.3, None),
+    (64, 512, 576, 39.2, 39.9, None), (64, 331, 1024, 49.9, 48.8, None), (64, 384, 1280, 70.2, 63.9, None), (64, 2048, 240, 175.0, 168.8, None),
+    (128, 459, 512, 65.0, 65.5, None), (80, 1024, 256, 94.7, 96.6, None), (80, 1995, 224, 286.4, 275.9, None),
+]
+
+
+def test_the_plan_is_about_the_fastest(plans):
+    got = plans([(seq, 1, pairs, 96 if dh == 64 else 64, dh) for dh, seq, pairs, *_ in MEASURED])
+    for (dh, seq, pairs, *us), (slots, fill, _) in zip(MEASURED, got):
+        items, resident = pairs // 8 * -(-seq // 128), 96 if dh == 64 else 64
+        t = us[0] if slots == resident else us[2] if fill == items else us[1]
+        # 2 % and more is what repeated measurements of one size differ by
+        assert t <= 1.025 * min(u for u in us if u is not None), (dh, seq, pairs)

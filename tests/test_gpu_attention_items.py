@@ -36,9 +36,11 @@ def _check(out, qkv, n_seq, seq, heads, dh, dtype):
     assert np.max(np.abs(out.double().cpu().numpy() - want)) < 3 * ULP[dtype] * (1 + np.abs(want).max())
 
 
-# 8 XCDs hold 96 workgroups each with heads of 64, 64 otherwise; items of 128 rows, (sequence, head) pairs dealt to the XCDs
+# 8 XCDs hold 96 workgroups each with heads of 64, 64 otherwise; items of 128 rows, (sequence, head) pairs dealt to the XCDs.  All pairs in
+# one group, but for the second (four rounds), the last two (1.6 rounds; two whole groups)
 @pytest.mark.parametrize("dtype", [zi.BF16, zi.FP16])
-@pytest.mark.parametrize("n_seq,seq,heads,dh", [(10, 600, 16, 64), (32, 331, 32, 64), (7, 300, 31, 128), (4, 257, 45, 80), (3, 1300, 16, 128)])
+@pytest.mark.parametrize("n_seq,seq,heads,dh", [(10, 600, 16, 64), (32, 331, 32, 64), (7, 300, 31, 128), (4, 257, 45, 80), (3, 1300, 16, 128), (10, 600, 16, 128),
+                                               (5, 1408, 16, 128)])
 def test_a_workgroup_per_item_gives_the_bits_of_persistent_ones(dtype, n_seq, seq, heads, dh):
     qkv = _qkv(n_seq, seq, heads, dh, dtype, seq)
     out = _run(qkv, n_seq, seq, heads, dh, dtype)
