@@ -510,7 +510,8 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
         store_row(1.0f / l_run);
     }
     // The rows that came out not finite, once more the plain way, after all items: nothing of the loop above is live any
-    // more, and a register that this needs is not missing there.  A lane finds its row's state in what it has stored itself.
+    // more, and a register that this needs is not missing there.  A lane finds its half of its row's state in what it has stored
+    // itself; the row is worked again if either half is not finite.
     if constexpr (kRedo) {
         if (again == 0) return;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this wave's own stores lie behind the ones that follow
@@ -525,13 +526,13 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
             bool bad = false;
             if (qrow < seq) {
 #pragma unroll
-                for (int c = 0; c < DH / 8; ++c) {
-                    const uint2 v = *(const uint2 *)(rows0 + (size_t)qrow * d + 8 * c + 4 * fh);
+                for (int s = 0; s < KS; ++s) {                   // the pieces that store_row wrote from this lane
+                    const uint4 v = *(const uint4 *)(rows0 + (size_t)qrow * d + 16 * s + 8 * fh);
                     auto not_finite = [](uint32_t w) {           // either half's exponent is all ones
                         const uint32_t e = DT == kBF16 ? 0x7f80u : 0x7c00u;
                         return (w & e) == e || ((w >> 16) & e) == e;
                     };
-                    bad = bad || not_finite(v.x) || not_finite(v.y);
+                    bad = bad || not_finite(v.x) || not_finite(v.y) || not_finite(v.z) || not_finite(v.w);
                 }
             }
             const uint64_t lanes = __builtin_amdgcn_ballot_w64(bad);

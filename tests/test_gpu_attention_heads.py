@@ -101,7 +101,8 @@ def test_unaligned_buffers_of_any_head_size(dh, off_in, off_out):
 
 
 @pytest.mark.parametrize("dtype", [zi.BF16, zi.FP16])
-@pytest.mark.parametrize("n_seq,seq,heads,dh", [(40, 140, 9, 96), (1, 700, 3, 112), (2, 33, 2, 80)])     # 720 items on 512 workgroups
+@pytest.mark.parametrize("n_seq,seq,heads,dh", [(40, 140, 9, 96), (1, 700, 3, 112), (2, 33, 2, 80),      # 720 items on 512 workgroups
+                                               (4, 257, 45, 80), (10, 600, 17, 112)])                   # a workgroup per item: one group, groups of 12 pairs
 def test_values_that_are_not_finite_reach_the_rows_that_see_them_and_no_other(dtype, n_seq, seq, heads, dh):
     qkv = _qkv(n_seq, seq, heads, dh, dtype, 21).reshape(n_seq, seq, 3, heads, dh)
     want = _oracle(qkv, n_seq, seq, heads, dh)
