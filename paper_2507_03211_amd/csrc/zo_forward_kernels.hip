@@ -487,9 +487,9 @@ __global__ __launch_bounds__(256) void ce_finish_kernel(const float2 *__restrict
     const int tg = target[r];
     if (tg == -1) { if (lane == 0) row_loss[r] = 0.0; return; }
     const float2 *p = partials + (size_t)r * n_partial;
-    // A lane keeps its first pairs (512 a row: 65536 columns in strips of 128) in registers, so that they are read once and
-    // all loads are under way together; what lies beyond is read again for the sum.  us, read twice /
-    // here: 2096 rows of 394 pairs 9.3 / 8.2, 16352 rows 26.8 / 23.2 (the exponentials in 64 bits are most of it).
+    // A lane keeps its first pairs (512 a row: 65536 columns in strips of 128, 32768 in strips of 64) in registers, so that they
+    // are read once and all loads are under way together; what lies beyond is read again for the sum.  us, read twice / here:
+    // 2096 rows of 394 pairs 9.3 / 8.2, 16352 rows 26.8 / 23.2 (the exponentials in 64 bits are most of it).
     constexpr int KEEP = 8;
     float2 v[KEEP];
 #pragma unroll
@@ -673,7 +673,7 @@ hipError_t launch_linear(const void *x, const void *wt_p, const void *wt_m, cons
 hipError_t launch_attention(const void *qkv, void *out, int dtype, int n_seq, int seq, int n_heads, int d_head,
                             bool allow_mfma, hipStream_t s)
 {
-    // the matrix path reads and writes in pieces of 16 and 8 bytes
+    // the matrix path reads and writes in pieces of 16 bytes
     const bool aligned = (uintptr_t)qkv % 16 == 0 && (uintptr_t)out % 16 == 0;
     // Sequences of one to four tokens with heads of 80 to 112 channels: an item of the matrix path is 128 query rows whatever the
     // length, and 512 are in flight; once they take a second round the plain kernel, one block a token, is done first, up to

@@ -1,5 +1,5 @@
-"""Merging a row's (maximum, sum) pairs: rows with fewer pairs than a wavefront has lanes, with as many as a lane keeps in
-registers (512), one more, and more than that, against the cross entropy in fp64."""
+"""Merging a row's (maximum, sum) pairs: rows with fewer pairs than a wavefront has lanes, with as many as its lanes keep
+in registers (512), the next count (514), and more than that, against the cross entropy in fp64."""
 import numpy as np
 import pytest
 import torch
@@ -11,7 +11,9 @@ from gpu_util import DEV
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("vocab", [40, 4096, 16000, 65536, 65544, 70400])      # 2 .. 552 pairs a row
+# strips of 64 columns with d 64: 2, 64, 250, 512, 514, 1024, 1026, 1100 pairs a row; of 128 with d 192 from 32768 columns on: 256, 258,
+# 512, 514, 550
+@pytest.mark.parametrize("vocab", [40, 4096, 16000, 32768, 32776, 65536, 65544, 70400])
 @pytest.mark.parametrize("d", [64, 192])
 def test_pairs_of_a_row(vocab, d):
     m_half = 5
