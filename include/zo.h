@@ -210,7 +210,8 @@ int zo_device_flags(zo_model *m, uint32_t *host_flags);
  * max_launches launches; later ones are not recorded).  zo_profile_end synchronises the compute
  * stream and fills three host arrays of ZO_K_CLASSES entries: summed kernel milliseconds, number
  * of launches, and summed algorithmic work (FLOP for LINEAR and ATTENTION -- 2 m n k, causal half
- * for attention -- bytes that must cross HBM for the others). */
+ * for attention -- bytes that must cross HBM for the others).  A layer of a ZO_FP32 model that takes its LayerNorm on the
+ * way (short rows, few tiles) is one LINEAR launch; there is no NORM record for it. */
 enum { ZO_K_LINEAR = 0, ZO_K_ATTENTION = 1, ZO_K_STAGE = 2, ZO_K_UPDATE = 3, ZO_K_NORM = 4, ZO_K_CE = 5, ZO_K_OTHER = 6,
        ZO_K_CLASSES = 7 };
 int zo_profile_begin(zo_model *m, int max_launches);
@@ -232,7 +233,9 @@ const char *zo_last_error(void);
 /* ------------------------------------------------------------------------
  * Kernel-level entry points.  They run exactly the kernels the calls above
  * use, on caller-provided buffers, so that each can be checked against the
- * oracle and timed against its roofline at real shapes.  All pointers are
+ * oracle and timed against its roofline at real shapes.  (Small ZO_FP32
+ * models merge LayerNorm and the layer behind it in one launch; here they are
+ * two calls, equal but for the rounding of fp64 sums.)  All pointers are
  * device pointers; `stream` is a hipStream_t (NULL = null stream); dtype is
  * ZO_FP32 / ZO_BF16 / ZO_FP16.
  * ---------------------------------------------------------------------- */
