@@ -90,7 +90,7 @@ __device__ __forceinline__ void ce_partial_row(const f32x16 (&a)[TN], int col0, 
     }
     // (two maxima and four sums side by side: with one wave per SIMD an instruction that waits for the one before it issues
     // after 8 cycles instead of 5, and 64 additions in a row are half of such waits.  With the row targets loaded together, see
-    // the caller: LM head of 50272 columns, us before / here: 8176 rows a sign, d 768, 1046 / 1004; 1048 rows, d 2048, 387 / 378)
+    // the caller: LM head of 50272 columns, us before / here: 8176 rows a sign, d 768, 1048 / 1022; 1048 rows, d 2048, 389 / 384)
     float mx2[2] = {v[0], v[1]};
 #pragma unroll
     for (int k = 2; k < NE; k += 4) {
