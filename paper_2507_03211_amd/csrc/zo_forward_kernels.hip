@@ -477,6 +477,7 @@ __global__ __launch_bounds__(256) void ce_rows_kernel(const Acc *__restrict__ lo
 }
 
 // Merge the (max, sum-exp) pairs the fused LM-head epilogue left for a row: one wavefront per row.
+template <int KEEP>
 __global__ __launch_bounds__(256) void ce_finish_kernel(const float2 *__restrict__ partials, int n_partial,
                                                         const float *__restrict__ target_logit,
                                                         const int32_t *__restrict__ target, double *__restrict__ row_loss,
@@ -487,10 +488,11 @@ __global__ __launch_bounds__(256) void ce_finish_kernel(const float2 *__restrict
     const int tg = target[r];
     if (tg == -1) { if (lane == 0) row_loss[r] = 0.0; return; }
     const float2 *p = partials + (size_t)r * n_partial;
-    // A lane keeps its first pairs (512 a row: 65536 columns in strips of 128, 32768 in strips of 64) in registers, so that they
-    // are read once and all loads are under way together; what lies beyond is read again for the sum.  us, read twice / here:
-    // 2096 rows of 394 pairs 9.3 / 8.2, 16352 rows 26.8 / 23.2 (the exponentials in 64 bits are most of it).
-    constexpr int KEEP = 8;
+    // A lane keeps its first KEEP pairs (8: 512 a row, 65536 columns in strips of 128, 32768 in strips of 64) in registers, so that
+    // they are read once and all loads are under way together; what lies beyond is read again for the sum.  us, read twice / here:
+    // 4192 rows of 394 pairs 7.8 / 7.1, 16352 rows 22.8 / 19.2 (the exponentials in 64 bits are most of it).  Each kept pair has an
+    // exponential's code of its own, which short rows pay for without use (128 rows of 64 pairs, read twice / 2 / 4 / 8 kept: 3.24 /
+    // 3.12 / 3.27 / 3.55; of 250 4.18 / 4.09 / 3.93 / 4.18): 2 up to 128 pairs, 4 up to 256.
     float2 v[KEEP];
 #pragma unroll
     for (int i = 0; i < KEEP; ++i) v[i] = lane + 64 * i < n_partial ? p[lane + 64 * i] : float2{-INFINITY, 0.0f};
@@ -706,8 +708,12 @@ hipError_t launch_ce_finish(const void *partials, int n_partial, const float *ta
                             double *row_loss, int rows, hipStream_t s)
 {
     if (rows == 0) return hipSuccess;
-    ce_finish_kernel<<<dim3((rows + 3) / 4), dim3(256), 0, s>>>((const float2 *)partials, n_partial, target_logit, target, row_loss,
-                                                                rows);
+#define ZO_CE(KEEP) \
+    ce_finish_kernel<KEEP><<<dim3((rows + 3) / 4), dim3(256), 0, s>>>((const float2 *)partials, n_partial, target_logit, target, row_loss, rows)
+    if (n_partial <= 128) ZO_CE(2);
+    else if (n_partial <= 256) ZO_CE(4);
+    else ZO_CE(8);
+#undef ZO_CE
     return hipGetLastError();
 }
 

@@ -11,9 +11,9 @@ from gpu_util import DEV
 pytestmark = pytest.mark.gpu
 
 
-# strips of 64 columns with d 64: 2, 64, 250, 512, 514, 1024, 1026, 1100 pairs a row; of 128 with d 192 from 32768 columns on: 256, 258,
-# 512, 514, 550
-@pytest.mark.parametrize("vocab", [40, 4096, 16000, 32768, 32776, 65536, 65544, 70400])
+# strips of 64 columns with d 64: 2, 64, 128, 130, 250, 256, 258, 512, 514, 1024, 1026, 1100 pairs a row (2, 4 and 8 of a lane are kept);
+# of 128 with d 192 from 32768 columns on: 256, 258, 512, 514, 550
+@pytest.mark.parametrize("vocab", [40, 4096, 8192, 8200, 16000, 16384, 16392, 32768, 32776, 65536, 65544, 70400])
 @pytest.mark.parametrize("d", [64, 192])
 def test_pairs_of_a_row(vocab, d):
     m_half = 5
