@@ -10,18 +10,18 @@ inline long f64_tiles(int n_sign, int m_half, int n, int edge) { return (long)n_
 // 2048 x 768 x 3072 753 / 417
 inline bool f64_tiles32(int n_sign, int m_half, int n) { return f64_tiles(n_sign, m_half, n, 32) >= 512; }
 
-// The longest row a lane group of the fp64 layer holds in registers for its LayerNorm, and the longest one of the two
-// instances that holds fewer pieces.
-constexpr int kNormRowMax = 512, kNormRowShort = 128;
+// The longest row that an fp64 layer takes its LayerNorm of, and the longest one of the two instances that holds fewer pieces.
+constexpr int kNormRowMax = 320, kNormRowShort = 128;
 
 // Does an fp64 layer take its LayerNorm on the way (one launch) or behind one (two)?  The launch costs 2 to 5 us, the more the
 // more rows it has.  On the way every column tile normalises its rows over again: that costs with the tiles and, each tile's
-// chain being longer and the rows leaving the L1, with more than the first power of the row's length.  So while the tiles
-// are 16 x 16 and either the rows are short or tiles x length^1.5 stays below a bound.  m_half x n x k, both signs, us, two launches / one:
-// 512 x 480 x 128 13.2 / 11.9, 250 x 976 x 104 10.1 / 10.1 (the last short rows before 32 x 32 tiles); 128 x 1024 x 192 10.2 / 9.4,
-// 1280 columns of 200 10.1 / 10.8; 128 x 512 x 320 10.1 / 9.2, 512 x 128 x 352 12.5 / 13.2; 64 x 512 x 512 11.1 / 10.3, 640
-// columns 12.0 / 12.3, 559 x 184 x 496 17.5 / 21.9.  Over 492 sizes of 136 to 512 none that is taken is more than 2 % slower than
-// two launches; of the 193 left, 9 are 10 to 19 % faster on the way, 46 as much and more slower.
+// chain being longer and the rows leaving the L1, with more than the first power of the row's length.  In a step, where rows and
+// weights are fresh from other kernels, one launch instead of two gains per layer (16 to 128 rows a sign) 3.2 us at 64, 2.6 at
+// 128, 1.5 at 192, 0.8 at 256, 0.4 at 320 and loses 0.4 at 384, 1.5 at 448 and 1 - 2 at 512.  Below that limit: 16 x 16 tiles, and
+// short rows or tiles x length^1.5 below a bound.  m_half x n x k, both signs, us, two launches / one, operands in the L2: 512 x 480 x
+// 128 13.2 / 11.9, 250 x 976 x 104 10.1 / 10.1 (the last short rows before 32 x 32 tiles); 128 x 1024 x 192 10.2 / 9.4, 1280
+// columns of 200 10.1 / 10.8; 128 x 512 x 320 10.1 / 9.2, 256 x 960 x 320 21.6 / 23.4.  A step of 4 layers, 256 rows a sign, d 192
+// 304 / 294 (all layers on the way: 303).
 inline bool norm_on_the_way(int n_sign, int m_half, int n, int k)
 {
     if (k > kNormRowMax || f64_tiles32(n_sign, m_half, n)) return false;

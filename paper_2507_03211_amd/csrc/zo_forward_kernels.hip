@@ -271,9 +271,9 @@ __global__ __launch_bounds__(256) void linear_plain_kernel(const void *x, const 
 // L2 traffic, 5.3 flop a byte).
 // NP > 0: x is the residual stream and the layer's input its LayerNorm, taken on the way: 16 lanes a row find mean and variance,
 // the operands are normalised as they are loaded.  A lane holds its share of the row, NP pieces of 64 elements among the 16, in
-// registers, loaded in one burst: read piece by piece, and again for the variance, a row of 512 waits for memory 16 times (9 rows
-// a sign, 512 columns, 10.7 us / 9.6 in one burst; two launches take 10.4).  Two pieces where they do: eight leave room
-// for five waves per SIMD, two for six.  Where this is taken: norm_on_the_way.
+// registers, loaded in one burst: read piece by piece, and again for the variance, a row of 320 waits for memory 10 times (9 rows
+// a sign, 960 columns, 7.6 us / 7.2 in one burst; two launches take 8.8).  Two pieces where they do, with fewer registers.  Where
+// this is taken: norm_on_the_way.
 struct NormArgs { const float *g_p, *g_m, *b_p, *b_m; float eps; };
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 template <int EPI, int TB, int NP>

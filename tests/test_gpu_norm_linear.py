@@ -11,10 +11,10 @@ from gpu_util import Model
 pytestmark = pytest.mark.gpu
 
 
-# rows of 8, 40 (no multiple of the 16-deep pieces), 512 (the longest taken) and 520; 1440 rows a sign (32 x 32 tiles: two launches
-# for QKV, one for a narrow layer); heads of 8, 16, 24, 64 and 68 channels (16, 8, 5, 2 and 1 groups of keys), and of 104 and 128
+# rows of 8, 40 (no multiple of the 16-deep pieces), 320 (the longest taken), 328, 512 and 520; 1440 rows a sign (32 x 32 tiles: two launches
+# for QKV, one for a narrow layer); heads of 8, 16, 24, 64 and 68 channels (8, 8, 5, 1 and 1 groups of keys; one with 3 tokens), and of 104 and 128
 @pytest.mark.parametrize("d,heads,ffn,vocab,batch,seq", [(8, 1, 8, 16, 1, 3), (40, 5, 40, 56, 3, 17), (72, 3, 40, 56, 2, 21), (64, 4, 64, 40, 16, 90),
-                                                        (128, 2, 64, 64, 2, 33), (136, 2, 40, 24, 1, 20), (256, 4, 64, 72, 2, 19), (512, 4, 64, 72, 1, 19), (520, 5, 64, 24, 1, 9)])
+                                                        (128, 2, 64, 64, 2, 33), (136, 2, 40, 24, 1, 20), (256, 4, 64, 72, 2, 19), (320, 4, 64, 72, 1, 19), (328, 4, 64, 72, 1, 9), (512, 4, 64, 72, 1, 19), (520, 5, 64, 24, 1, 9)])
 def test_losses_of_fp32_models(d, heads, ffn, vocab, batch, seq):
     mdl = Model(2, d, heads, ffn, vocab, seq, zi.FP32, batch, seq, seed=d, plain_small=False, std=0.05)
     tok, tok_dev = mdl.tokens()
@@ -36,8 +36,8 @@ def _losses_and_layernorms(mdl, tok_dev, batch, seq):
 
 
 # LayerNorms of one block and the head that are launches of their own, for one sequence and for eight of them
-@pytest.mark.parametrize("d,heads,ffn,vocab,seq,few,many", [(64, 4, 256, 512, 24, 0, 0), (256, 4, 1024, 1536, 24, 0, 3), (448, 7, 896, 1344, 16, 0, 3), (512, 8, 128, 128, 8, 0, 1),
-                                                           (512, 8, 512, 512, 30, 1, 3)])
+@pytest.mark.parametrize("d,heads,ffn,vocab,seq,few,many", [(64, 4, 256, 512, 24, 0, 0), (256, 4, 1024, 1536, 24, 0, 3), (320, 5, 960, 640, 16, 0, 3), (320, 5, 128, 128, 24, 0, 1),
+                                                           (512, 8, 128, 128, 8, 3, 3)])
 def test_both_routes_give_the_same_losses(d, heads, ffn, vocab, seq, few, many):
     # eight copies of a sequence have the mean loss of one of them: other tile counts, so other routes, of the same layers
     mdl = Model(1, d, heads, ffn, vocab, seq, zi.FP32, 8, seq, seed=d, plain_small=False, std=0.05)
