@@ -33,4 +33,16 @@ inline bool norm_on_the_way(int n_sign, int m_half, int n, int k)
 // workgroup's.
 inline int layernorm_pieces(int d) { return d > 2048 ? 0 : d <= 768 ? 3 : (d + 255) / 256; }
 
+// Groups of d_head threads of the plain attention's 128 that a row's keys are dealt to; `room`: of the LDS for their partial sums.
+// us, one group / as many as there are: fp64, 8 x 128 tokens, 8 heads of 8 channels (16 groups) 29.1 / 14.4, of 16 33.0 / 20.6, of
+// 32 44.8 / 38.6, of 40 (3 groups) 50.4 / 48.7; two lose, their sums' loop waits for each product where that of one group is
+// unrolled: of 48 55.4 / 63.3, of 64 66.4 / 69.3; bf16, 4 x 700 tokens, 2 heads of 48 74 / 86.  A group has two keys at least: 2
+// sequences of 1 token 3.73 / 4.06 with 16 groups, of 6 3.91 / 4.06 (3: 3.87), of 9 4.08 / 4.09 (4: 4.04).
+inline int plain_attention_groups(int seq, int d_head, bool room)
+{
+    const int groups = 128 / d_head;
+    if (groups < 3 || !room) return 1;
+    return seq >= 2 * groups ? groups : seq >= 4 ? seq / 2 : 1;
+}
+
 }  // namespace zo

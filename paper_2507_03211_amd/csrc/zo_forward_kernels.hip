@@ -434,8 +434,7 @@ __global__ __launch_bounds__(128) void attention_plain_kernel(const void *qkv_, 
     __syncthreads();
     typename P::A *o = (typename P::A *)out_ + ((size_t)sq * seq + t) * d + head * d_head;
     const typename P::A *vr = qkv + 2 * d + head * d_head;
-    // heads of up to half a block: the keys are dealt to as many groups of d_head threads as there are (4 sequences of 32
-    // tokens, 4 heads of 16, fp64: 7.7 us with one group / 6.1)
+    // small heads: the keys are dealt to groups of d_head threads (plain_attention_groups)
     if (groups == 1) {
         for (int c = threadIdx.x; c < d_head; c += blockDim.x) {
             Acc a = 0;
@@ -688,8 +687,8 @@ hipError_t launch_attention(const void *qkv, void *out, int dtype, int n_seq, in
         return launch_attention_mfma(qkv, out, dtype, n_seq, seq, n_heads, d_head, s);
     const dim3 grid(seq, n_heads, n_seq), block(128);
     size_t smem = (size_t)(seq + d_head + 16) * acc_bytes(dtype);
-    // groups of threads over a row's keys, where their partial sums have room (lengths near the LDS limit stay with one group)
-    const int groups = d_head <= 64 && smem + block.x * acc_bytes(dtype) <= 32768 ? (int)block.x / d_head : 1;
+    // (lengths near the LDS limit stay with one group)
+    const int groups = plain_attention_groups(seq, d_head, smem + block.x * acc_bytes(dtype) <= 32768);
     if (groups > 1) smem += block.x * acc_bytes(dtype);
     ZO_DISPATCH_DT(dtype, (attention_plain_kernel<DT><<<grid, block, smem, s>>>(qkv, out, seq, n_heads, d_head, groups)));
     return hipGetLastError();

@@ -16,6 +16,7 @@ int main()
     int a[4];
     while (scanf(" %c %d %d %d %d", &what, a, a + 1, a + 2, a + 3) == 5) {
         if (what == 'n') printf("%d\n", (int)zo::norm_on_the_way(a[0], a[1], a[2], a[3]));
+        if (what == 'g') printf("%d\n", zo::plain_attention_groups(a[0], a[1], a[2] != 0));
         if (what == 'l') printf("%d\n", zo::layernorm_pieces(a[0]));
     }
     return 0;
@@ -64,3 +65,24 @@ def test_rows_that_do_not_fit_the_registers_take_two_launches(choose):
 def test_a_layernorm_row_has_as_many_pieces_as_it_needs(choose):
     for d, n in zip(range(4, 2304, 4), choose("l", [(d, 0, 0, 0) for d in range(4, 2304, 4)])):
         assert n == (0 if d > 2048 else max(3, -(-d // 256))), d
+
+
+# plain attention: tokens, d_head, us with 1, 2, 3, 4, 8 groups and with as many as the block has (fp64)
+GROUPS = [
+    (1, 8, (3.73, 3.75, 3.79, 3.81, 3.93, 4.06)), (6, 8, (3.88, 3.94, 3.87, 3.92, 3.91, 4.06)), (9, 8, (7.72, 7.78, 7.64, 7.62, 7.76, 8.02)),
+    (17, 8, (4.33, 4.61, 4.35, 4.24, 4.13, 4.17)), (33, 8, (5.52, 5.91, 5.35, 5.15, 4.81, 4.76)), (128, 8, (29.06, 24.72, 20.65, 18.50, 15.48, 14.41)), (2, 16, (3.86, 3.84, 3.88, 3.93, 4.03, 4.03)),
+    (128, 16, (33.05, 29.37, 24.91, 22.74, 20.54, 20.59)), (700, 24, (111.9, 101.5, 96.3, 84.9, None, 78.8)), (33, 32, (6.13, 6.73, 6.12, 5.94, None, 5.94)),
+    (700, 40, (146.6, 159.8, 130.8, None, None, 130.0)), (128, 48, (55.3, 63.2, None, None, None, 63.3)), (700, 64, (195.6, 207.0, None, None, None, 206.8)),
+]
+
+
+def test_groups_of_the_plain_attention_are_about_the_fastest(choose):
+    for (seq, dh, us), n in zip(GROUPS, choose("g", [(seq, dh, 1, 0) for seq, dh, _ in GROUPS])):
+        t = us[5] if n == 128 // dh else us[{1: 0, 2: 1, 3: 2, 4: 3, 8: 4}[n]]
+        assert t <= 1.02 * min(u for u in us if u is not None), (seq, dh, n)
+
+
+def test_groups_of_the_plain_attention_fit_the_block(choose):
+    rows = [(seq, dh, room, 0) for seq in (1, 2, 3, 4, 5, 31, 4000) for dh in range(1, 129) for room in (0, 1)]
+    for (seq, dh, room, _), n in zip(rows, choose("g", rows)):
+        assert 1 <= n and n * dh <= 128 and n <= max(1, seq // 2) and (room or n == 1)

@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 
 # (seq + d_head + 16) scores of 8 bytes (4 for 16-bit types), and 128 partial sums with groups, of 32 KiB: 3936 and 3937, 8032 and
 # 8033 lie on either side; 64 KiB without: 8160 (16-bit types: not reached here)
-@pytest.mark.parametrize("dtype,seq,dh", [(zi.FP32, 1, 16), (zi.FP32, 130, 1), (zi.FP32, 130, 48), (zi.FP32, 3936, 16), (zi.FP32, 3937, 16), (zi.FP32, 8160, 16),
+@pytest.mark.parametrize("dtype,seq,dh", [(zi.FP32, 1, 16), (zi.FP32, 130, 1), (zi.FP32, 130, 48), (zi.FP32, 5, 16), (zi.FP32, 9, 8),
+                                          (zi.FP32, 130, 40), (zi.FP32, 3936, 16), (zi.FP32, 3937, 16), (zi.FP32, 8160, 16),
                                           (zi.BF16, 300, 8), (zi.BF16, 8032, 16), (zi.BF16, 8033, 16)])
 def test_groups_of_keys_up_to_the_longest_sequence(dtype, seq, dh):
     heads = 2 if seq < 1000 else 1
