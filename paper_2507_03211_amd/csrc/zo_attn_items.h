@@ -36,8 +36,8 @@ struct AttnItems {
     }
 };
 
-// Slots an XCD's workgroups have (persistent: as many as are resident at once) and the list's `fill`.
-struct AttnPlan { int slots, fill; };
+// Slots an XCD's workgroups have (persistent: as many as are resident at once), the list's `fill` and workgroups a CU.
+struct AttnPlan { int slots, fill, per_cu = 0; };
 
 // When the query tiles of a sequence divide the resident workgroups, rounds of the list are whole groups, the zigzag gives every
 // slot the same number of key tiles, and persistent workgroups save an item's start.  When they don't, a group's long tiles come
@@ -75,6 +75,42 @@ inline AttnPlan attention_plan(long long pairs, int n_qt, int slots_max, int d_h
     const bool one_group = 2 * items <= (n_qt >= 8 ? 6 : d_head == 64 ? 5 : 3) * (long long)slots_max && !even;
     const long long group = one_group ? pairs_xcd : in_slots;
     return {(int)((pairs_xcd + group - 1) / group * group * n_qt), one_group ? (int)items : slots_max};
+}
+
+// How many workgroups share a CU, and the plan.  Heads of 64 channels leave room for four, of 80 for three, larger ones for two.  One
+// less is better where the rounds of persistent workgroups come out so, and with heads of 64 for short sequences: those take the
+// time that their operands need, and more pairs at a time leave the L2 (3 tiles x 1024 pairs, us, three / four 50.1 / 51.1, 4 x 976
+// 77.5 / 80.9, 3 x 2432 105 / 110), unless all items fit at once (2 tiles x 444 18.2 / 15.6, 6 x 144 29.9 / 23.3).
+// Heads of 80: a round of three a CU takes about 1.3 times as long as one of two.  Time with two over time with three, persistent:
+// 16 tiles x 128 pairs (4 rounds or 3) 1.05, x 96 (3 or 2) 1.10, 4 x 448 1.07, 3 x 512 1.06, but 6 x 400 (5 or 4) 0.96, 1 x 832 0.96, 4
+// x 248 0.95; all items at once, 7 tiles and less 1.02 - 1.20, 10 x 64 0.96 (the longest item's chain is all there is).
+// The larger number's plan: a workgroup per item from the fourth round on (persistent over per item's time, 64: 8 tiles, 4 rounds 1.05, 16
+// tiles 1.02; 80: 4 tiles 1.05, 6 tiles, 4 rounds 1.04, 6 1.05; 8 and more only from the sixth: 16 tiles, 4 rounds 0.98, 6 1.03),
+// and all pairs in one group, over few rounds, also where the tiles divide the slots (over persistent's, 64: 16 tiles, 1.5 rounds 1.07, 2.6
+// 1.05, 3 1.04, 8 tiles, 2.75 0.91; 80: 16 tiles, 1.3 1.06, 2 1.02, 2.7 1.03, 6 tiles, 1.1 1.16, 1.6 0.99, 3.1 0.98).
+inline AttnPlan attention_plan_on(long long pairs, int n_qt, int cus_xcd, int d_head)
+{
+    const int full = d_head == 64 ? 4 : d_head == 80 ? 3 : 2, slots = full * cus_xcd, fewer = slots - cus_xcd;
+    const long long pairs_xcd = (pairs + 7) / 8, items = pairs_xcd * n_qt;
+    bool more = full > 2;
+    if (d_head == 64) more = n_qt >= 6 || items <= slots;
+    if (d_head == 80 && items <= slots) more = n_qt < 8;
+    else if (d_head == 80 && slots % n_qt == 0 && (n_qt < 6 || items >= 2 * slots))
+        more = 13 * ((items + slots - 1) / slots) <= 10 * ((items + fewer - 1) / fewer);
+    if (!more) {
+        AttnPlan plan = attention_plan(pairs, n_qt, full > 2 ? fewer : slots, d_head);
+        plan.per_cu = full > 2 ? full - 1 : full;
+        return plan;
+    }
+    if (items <= slots) return {(int)items, (int)items, full};
+    const int rounds = d_head == 64 || n_qt <= 6 ? 4 : 6;
+    const bool few = (n_qt >= 16 && items <= 3 * slots) || (n_qt >= 6 && items < (d_head == 80 ? 2 : 1) * slots);
+    const bool per_item = slots % n_qt != 0 || few || (n_qt >= 3 && items >= rounds * slots);
+    if (!per_item) return {slots, slots, full};
+    const long long in_slots = slots / n_qt > 1 ? slots / n_qt : 1;
+    const bool one_group = few || 2 * items <= (n_qt >= 8 ? 6 : d_head == 64 ? 5 : 3) * (long long)slots;
+    const long long group = one_group ? pairs_xcd : in_slots;
+    return {(int)((pairs_xcd + group - 1) / group * group * n_qt), one_group ? (int)items : slots, full};
 }
 
 }  // namespace zo

@@ -136,16 +136,25 @@ template <int LO, int HI, class F> __device__ __forceinline__ void static_for(F 
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // native vector: stays in registers across the loop
 
+// Workgroups a CU: four with 64 channels and three with 80, two with more.  A wave waits (for its item's first tiles, for LDS, for
+// its workgroup at a tile's barrier) more than it works, so a further workgroup is worth two K fragments less in flight (a ring of
+// two, 128 registers at 64 channels) and LDS rows without padding (80 channels: 50 KiB a workgroup, 162 registers).  us, a
+// workgroup less / so, all of it: 64 channels, 2048 tokens x 256 (head, sequence) pairs 189 / 174, 277 x 288 17.9 / 14.8; 80, 2048 x
+// 128 166 / 146, 847 x 124 41.7 / 35.4.  Bit for bit the same.  Registers spilled to memory cost more than the workgroup gains (138
+// registers held to 128: 277 x 288 16.5, 512 x 384 32 -> 37).
+template <int DH> constexpr int kAttnPerCu = DH == 64 ? 4 : DH == 80 ? 3 : 2;
 template <int DT, int DH>
-__global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(const uint16_t *__restrict__ qkv, uint16_t *__restrict__ out, int seq,
+__global__ __launch_bounds__(256, kAttnPerCu<DH>) void attn_mfma_kernel(const uint16_t *__restrict__ qkv, uint16_t *__restrict__ out, int seq,
                                                         int n_heads, int n_seq, int fill)
 {
     constexpr int KS = DH / 16, CT = (DH + 31) / 32;   // contraction steps of K Q^T, channel tiles of O^T
     constexpr int CHD = DH / 8;           // 16-byte chunks per K / V row in memory
     // 16-byte chunks per K / V row in LDS: whole channel tiles, so that the row pitch is 128, 192 or 256 bytes.  The
-    // chunks past a row's end hold its chunk two (of four) places before over again: the last channel tile of O^T then
-    // multiplies finite data, and what comes out in the channels past DH is not stored.
-    constexpr int CH = 4 * CT;
+    // chunks past a row's end hold its chunk two (of four) places before over again; what the last channel tile of O^T makes of
+    // them lies in the channels past DH and is not stored.  Without padding (TIGHT) it reads the first chunks of the next row
+    // there, two chunks behind the tile for the last one: whatever they hold stays in those channels too.
+    constexpr bool TIGHT = DH == 80;
+    constexpr int CH = TIGHT ? CHD : 4 * CT;
     constexpr int TILE = BKV * CH;        // 16-byte chunks per K / V tile
     // Head sizes that the plain kernel served before this one: there a probability is an fp32 number.  Here it enters the
     // P V product as the sum of two 16-bit numbers (p rounded, and what the rounding left), two multiplies instead of one:
@@ -153,17 +162,18 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
     // (bf16) and 2.01e-4 (fp16) at 2048 keys; with one number it was 2.1e-3 (bf16).
     constexpr bool SPLIT = DH != 64 && DH != 128;
     constexpr bool kRedo = SPLIT;         // rows that are not finite are worked again (see the end)
-    constexpr int KR = KS % 4 == 0 ? 4 : KS;   // depth of the K fragment ring (it divides KS: a fragment's slot is the same in every unit)
+    constexpr int KR = DH <= 80 ? 2 : KS % 4 == 0 ? 4 : KS;   // depth of the K fragment ring (it divides 2 KS: a fragment's slot is the same in every other unit)
     // K and V tiles, both [key][channel] as they sit in memory, 16-byte chunks XOR-swizzled per key so that
     // the MFMA fragment reads of K (32 keys, one chunk) and the transposing reads of V (4 keys x 32 bytes
     // per 16 lanes) are free of conflicts on the 64-bank LDS.
     // Three K and two V buffers: tiles arrive (global memory straight into LDS) while earlier ones are multiplied.
     __shared__ u32x4 ks3[3][TILE];
-    __shared__ u32x4 vs2[2][TILE];
+    __shared__ u32x4 vs2[2 * TILE + 4 * CT - CH];
     // (pitch 192 bytes: 4 consecutive rows start on 4 different quarters of the 64 banks, which is all the reads of V
-    // need; K's 16 rows per read are told apart by the row bits above)
-    auto kswz = [](int r) { return CH == 16 ? (r & 15) : CH == 12 ? ((r >> 2) & 3) : ((r >> 1) & 7); };
-    auto vswz = [](int r) { return CH == 16 ? ((r & 3) << 2) : CH == 12 ? 0 : (((r >> 1) & 1) << 2); };
+    // need; K's 16 rows per read are told apart by the row bits above.  Pitch 160: 8 consecutive rows start on the 8 multiples of
+    // 8 banks, and K's other 8 rows have their chunks swapped in pairs)
+    auto kswz = [](int r) { return TIGHT ? ((r >> 3) & 1) : CH == 16 ? (r & 15) : CH == 12 ? ((r >> 2) & 3) : ((r >> 1) & 7); };
+    auto vswz = [](int r) { return CH == 16 ? ((r & 3) << 2) : CH == 12 || TIGHT ? 0 : (((r >> 1) & 1) << 2); };
     auto in_row = [](int chunk) { return chunk < CHD ? chunk : chunk - 2; };
 
     const int d = n_heads * DH, ld = 3 * d;
@@ -192,20 +202,24 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
     float m_run = -INFINITY, l_lane = 0.0f, moff = 0.0f, thr = -INFINITY;   // (set per work item)
 
     // global -> LDS for a K/V tile, without passing through registers: one wave instruction moves 64 x 16
-    // bytes and lane L's piece lands at the instruction's LDS base + 16 L.  Piece p = 64 (NLD wave + i) + L of
-    // a tile is slot p % CH of key row p / CH; the slot holds logical chunk slot ^ swizzle(row), so the
+    // bytes and lane L's piece lands at the instruction's LDS base + 16 L.  Piece p = 64 load_no + L of a tile
+    // is slot p % CH of key row p / CH; the slot holds logical chunk slot ^ swizzle(row), so the
     // swizzle is applied on the global side (still whole 16-byte pieces of one row per lane).  The lane part
     // of the address does not change from tile to tile: the key advance goes into a scalar base.
-    constexpr int NLD = TILE / 256;       // instructions per wave and operand
+    constexpr int NLD = (TILE + 255) / 256;       // instructions per wave and operand, at most
+    // a wave's i-th instruction of K (which = 0) or V (1): where they are no multiple of four, two waves load three of K's and two of
+    // V's, the others the other way round
+    auto load_no = [&](int which, int i) { return TIGHT ? ((wave + 2 * which) & 3) + 4 * i : NLD * wave + i; };
+    auto load_is = [&](int which, int i) { return 256 * (i + 1) <= TILE || load_no(which, i) < TILE / 64; };
     uint32_t kgo[NLD], vgo[NLD];          // byte offsets from the tile's first key row
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
-        const int pidx = 64 * (NLD * wave + i) + lane, r = pidx / CH, slot = pidx % CH;
-        kgo[i] = (uint32_t)(r * ld + d + in_row(slot ^ kswz(r)) * 8) * 2u;
-        vgo[i] = (uint32_t)(r * ld + 2 * d + in_row(slot ^ vswz(r)) * 8) * 2u;
+        const int pk = 64 * load_no(0, i) + lane, rk = pk / CH, sk = pk % CH, pv = 64 * load_no(1, i) + lane, rv = pv / CH, sv = pv % CH;
+        kgo[i] = (uint32_t)(rk * ld + d + in_row(sk ^ kswz(rk)) * 8) * 2u;
+        vgo[i] = (uint32_t)(rv * ld + 2 * d + in_row(sv ^ vswz(rv)) * 8) * 2u;
     }
     const uint32_t ks_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)&ks3[0][0];
-    const uint32_t vs_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)&vs2[0][0];
+    const uint32_t vs_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)&vs2[0];
     // Buffer accesses, the buffer as long as what exists of the tile: rows past the end of the sequence come as zeros (masked
     // as future keys) without a branch or a comparison.  Offsets are from the tile's first row: from the sequence's they would
     // not fit 32 bits for long sequences.
@@ -214,12 +228,13 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
     };
     // this wave's pieces of K (which = 0) or V (which = 1) rows k0 .. k0 + 63, into buffer `buf` of that operand
     auto issue = [&](int which, int k0, int buf) {
-        const uint32_t dst = (which ? vs_lds : ks_lds) + (uint32_t)buf * (TILE * 16) + (uint32_t)(NLD * wave) * 1024u;
+        const uint32_t dst = (which ? vs_lds : ks_lds) + (uint32_t)buf * (TILE * 16);
         const uint64_t gb = gbase0 + (uint64_t)k0 * (uint64_t)ld * 2u;
         const int left = seq - k0 < BKV ? seq - k0 : BKV;
         const u32x4 rows = {(uint32_t)gb, (uint32_t)(gb >> 32), (uint32_t)left * (uint32_t)ld * 2u, 0x00020000u};
 #pragma unroll
-        for (int i = 0; i < NLD; ++i) dma16(rows, which ? vgo[i] : kgo[i], dst + i * 1024u);
+        for (int i = 0; i < NLD; ++i)
+            if (load_is(which, i)) dma16(rows, which ? vgo[i] : kgo[i], dst + (uint32_t)load_no(which, i) * 1024u);
     };
     // Transposing LDS read (ds_read_b64_tr_b16): in every group of 16 lanes, lane j hands in the address of
     // four consecutive 16-bit elements ("row j") and lane i gets back element i%4 of rows i/4, i/4+4, i/4+8,
@@ -238,7 +253,7 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
         voff[c] = (key * CH + ((chan >> 3) ^ vswz(key))) * 8 + (chan & 7);
     }
     auto vt_frag = [&](const u32x4 *vs, int kb16, int ctile) {   // keys kb16 + 4 fh + tr_key, kb16 a multiple of 8
-        const uint16_t *p = (const uint16_t *)vs + voff[ctile] + kb16 * CH * 8;
+        const uint16_t *p = (const uint16_t *)vs + (TIGHT ? voff[0] + 32 * ctile : voff[ctile]) + kb16 * CH * 8;
         return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4i16 *)p);
     };
     int koff[KS];                                                // u32x4 index of (key fr, k-step s)
@@ -277,7 +292,7 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
     uint4 pf[2];                                     // probabilities of the unit's two 16-key steps, packed
     uint4 pl[SPLIT ? 2 : 1];                         // what rounding left of them
     float tmax;                                      // this lane's maximum over S of the unit about to be exponentiated
-    auto k_frag = [&](int buf, int half, int f) { return ks3[buf][half * 32 * CH + koff[f]]; };
+    auto k_frag = [&](int buf, int half, int f) { return ks3[buf][half * 32 * CH + (TIGHT ? koff[0] + 2 * f : koff[f])]; };
     auto unit_max = [&](const f32x16 &x) {
         float t = __builtin_fmaxf(__builtin_fmaxf(x[0], x[1]), x[2]);
 #pragma unroll
@@ -298,18 +313,19 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
         });
     };
     // scores of unit u from K buffer `buf`, half `half`, into dst; the ring then holds the first fragments of the
-    // unit after it (buffer nbuf, half nhalf).  `between(i)`: what to issue after the i-th multiply.
-    auto qk_unit = [&](f32x16 &dst, int buf, int half, int nbuf, int nhalf, auto &&between) {
+    // unit after it (buffer nbuf, half nhalf).  `odd`: u's lowest bit, a constant.  `between(i)`: what to issue after the i-th multiply.
+    auto qk_unit = [&](auto odd, f32x16 &dst, int buf, int half, int nbuf, int nhalf, auto &&between) {
+        constexpr int R0 = decltype(odd)::value * KS;
 #pragma unroll
         for (int i = 0; i < KS; ++i) {
             if (i == 0) {
                 const f32x16 zero = {};
-                dst = mfma32<DT>(__builtin_bit_cast(uint4, kf[0]), qf[0], zero);
+                dst = mfma32<DT>(__builtin_bit_cast(uint4, kf[R0 % KR]), qf[0], zero);
             } else {
-                dst = mfma32<DT>(__builtin_bit_cast(uint4, kf[i % KR]), qf[i], dst);
+                dst = mfma32<DT>(__builtin_bit_cast(uint4, kf[(R0 + i) % KR]), qf[i], dst);
             }
             __builtin_amdgcn_sched_barrier(0);       // the refill goes out after the multiply that frees its slot
-            kf[i % KR] = i + KR < KS ? k_frag(buf, half, i + KR) : k_frag(nbuf, nhalf, i + KR - KS);
+            kf[(R0 + i) % KR] = i + KR < KS ? k_frag(buf, half, i + KR) : k_frag(nbuf, nhalf, i + KR - KS);
             between(i);
         }
     };
@@ -362,10 +378,10 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
         __builtin_amdgcn_sched_barrier(0);
         // phase A.  K of unit s + 1: H = 0: tile T, second half; H = 1: tile T + 1, first half.  Unit s + 2 is
         // tile T + 1 either way.
-        qk_unit(Sn, H == 0 ? kb0 : kb1, H == 0 ? 1 : 0, kb1, H == 0 ? 0 : 1, [&](int i) {
+        qk_unit(std::integral_constant<int, H ^ 1>{}, Sn, H == 0 ? kb0 : kb1, H == 0 ? 1 : 0, kb1, H == 0 ? 0 : 1, [&](int i) {
             if (i < CT) {                            // V^T fragments of this unit's first 16 keys
-                vf[i][0] = vt_frag(vs2[(s >> 1) & 1], 32 * H, i);
-                vf[i][1] = vt_frag(vs2[(s >> 1) & 1], 32 * H + 8, i);
+                vf[i][0] = vt_frag(vs2 + ((s >> 1) & 1) * TILE, 32 * H, i);
+                vf[i][1] = vt_frag(vs2 + ((s >> 1) & 1) * TILE, 32 * H + 8, i);
             }
             __builtin_amdgcn_sched_barrier(0);
             // a KS-th of the elements of each 16-key step per slot
@@ -387,8 +403,8 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
             oacc[c] = mfma32<DT>(uint4{lo2.x, lo2.y, hi2.x, hi2.y}, pf[kstep], oacc[c]);
             if constexpr (SPLIT) oacc[c] = mfma32<DT>(uint4{lo2.x, lo2.y, hi2.x, hi2.y}, pl[kstep], oacc[c]);
             if (kstep == 0) {                        // the slot's fragments are in the matrix pipe: read the next step's
-                vf[c][0] = vt_frag(vs2[(s >> 1) & 1], 32 * H + 16, c);
-                vf[c][1] = vt_frag(vs2[(s >> 1) & 1], 32 * H + 24, c);
+                vf[c][0] = vt_frag(vs2 + ((s >> 1) & 1) * TILE, 32 * H + 16, c);
+                vf[c][1] = vt_frag(vs2 + ((s >> 1) & 1) * TILE, 32 * H + 24, c);
             }
             __builtin_amdgcn_sched_barrier(0);
             if (kstep == 0) {
@@ -454,7 +470,7 @@ __global__ __launch_bounds__(256, (DH == 64 ? 3 : 2)) void attn_mfma_kernel(cons
         // prologue: scores of unit 0, nothing to overlap them with
     #pragma unroll
         for (int r = 0; r < KR; ++r) kf[r] = k_frag(0, 0, r);
-        qk_unit(S[0], 0, 0, 0, 1, [](int) { __builtin_amdgcn_sched_barrier(0); });
+        qk_unit(std::integral_constant<int, 0>{}, S[0], 0, 0, 0, 1, [](int) { __builtin_amdgcn_sched_barrier(0); });
         if (u_last == 0) {
             // (the select is written out, so the distance that a product needs before its first use is ours to keep)
             asm volatile("s_nop 15\n\ts_nop 3" : "+v"(S[0]));
@@ -566,19 +582,20 @@ hipError_t launch_attention_mfma(const void *qkv, void *out, int dtype, int n_se
         if (e != hipSuccess) return e;
         n_cu = v >= 8 ? v / 8 * 8 : 8;
     }
-    // workgroups resident at once: 2 per CU, 3 at d_head 64 (the CU count is rounded down to whole XCDs' worth)
-    const int slots_max = n_cu / 8 * (d_head == 64 ? 3 : 2), n_qt = (seq + BQ - 1) / BQ;
+    const int n_qt = (seq + BQ - 1) / BQ;
     const long long pairs = (long long)n_heads * n_seq;
     if ((pairs + 7) / 8 * n_qt > 0x7fffffffLL / 64) return hipErrorInvalidValue;      // the kernel's item indices are ints
-    const AttnPlan plan = attention_plan(pairs, n_qt, slots_max, d_head);
+    const AttnPlan plan = attention_plan_on(pairs, n_qt, n_cu / 8, d_head);
     const int fill = plan.fill;
+    // a workgroup less a CU: by LDS that nobody uses
+    const size_t spare = (d_head == 64 && plan.per_cu == 3) || (d_head == 80 && plan.per_cu == 2) ? 12 * 1024 : 0;
     const dim3 grid(8u * (unsigned)plan.slots), block(256);
     const uint16_t *q = (const uint16_t *)qkv;
     uint16_t *o = (uint16_t *)out;
 #define ZO_ATTN(DH)                                                                                       \
     case DH:                                                                                              \
-        if (dtype == kBF16) attn_mfma_kernel<kBF16, DH><<<grid, block, 0, s>>>(q, o, seq, n_heads, n_seq, fill); \
-        else attn_mfma_kernel<kFP16, DH><<<grid, block, 0, s>>>(q, o, seq, n_heads, n_seq, fill);                \
+        if (dtype == kBF16) attn_mfma_kernel<kBF16, DH><<<grid, block, spare, s>>>(q, o, seq, n_heads, n_seq, fill); \
+        else attn_mfma_kernel<kFP16, DH><<<grid, block, spare, s>>>(q, o, seq, n_heads, n_seq, fill);                \
         break;
     switch (d_head) {
     ZO_ATTN(64) ZO_ATTN(80) ZO_ATTN(96) ZO_ATTN(112) ZO_ATTN(128)
