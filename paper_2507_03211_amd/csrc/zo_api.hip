@@ -301,46 +301,14 @@ struct BlockPtrs {   // staged parameter pointers of one block, per sign
     const char *base[2];
 };
 
-// Stage the embeddings and the final LayerNorm: W+- copies (fused) or nothing (literal reads theta itself).
-// upd_mode != 0: a pending update (seed m->pend_seed[0], scalar m->s_pend[0]) is applied to these tensors on the way.
-// Only the first `seq` position rows are staged, so the position table takes its update in a pass of its own.
-int stage_globals(zo_model *m, int seq, uint64_t seed, float eps, int upd_mode)
+// A block's tensors in a staging batch.  `slot_base` == nullptr: they are read where the caller keeps them (resident model,
+// separately allocated); otherwise from a device copy of the block laid out contiguously in canonical order (streamed model).
+void add_block(zo_model *m, StageBatch &b, int layer, const char *slot_base)
 {
-    const zo_config &c = m->cfg;
-    StageBatch b{}, bpos{};
-    const int lnf = 2 + kPerBlock * c.n_layers;
-    const size_t e = elem_bytes(c.dtype);
-    stage_batch_add(b, m->tptr[0], m->ws + m->wsp.e_pm[0], m->ws + m->wsp.e_pm[1], c.vocab, c.d_model, 0, false);
-    stage_batch_add(upd_mode ? bpos : b, m->tptr[1], m->ws + m->wsp.pos_pm[0], m->ws + m->wsp.pos_pm[1], seq, c.d_model, 1, false);
-    stage_batch_add(b, m->tptr[lnf], m->ws + m->wsp.lnf_pm[0], m->ws + m->wsp.lnf_pm[1], 1, c.d_model, lnf, false);
-    stage_batch_add(b, m->tptr[lnf + 1], m->ws + m->wsp.lnf_pm[0] + c.d_model * e, m->ws + m->wsp.lnf_pm[1] + c.d_model * e, 1,
-                    c.d_model, lnf + 1, false);
-    const double n_rest = (double)c.vocab * c.d_model + 2.0 * c.d_model, n_pos = (double)seq * c.d_model;
-    if (upd_mode) {
-        const int keep = m->update_rounding;           // the rounding the pending step asked for
-        m->update_rounding = m->pend_round;
-        const int rc = axpy_range(m, 1, 1, m->pend_seed[0], 0.0f, m->s_pend, true);
-        m->update_rounding = keep;
-        ZO_TRY(rc);
-        ZO_PROF(m, K_STAGE, 4.0 * e * n_rest, launch_stage(b, c.dtype, seed, eps, false, m->compute, upd_mode, m->pend_seed[0], m->s_pend));
-        ZO_PROF(m, K_STAGE, 3.0 * e * n_pos, launch_stage(bpos, c.dtype, seed, eps, false, m->compute));
-    } else {
-        ZO_PROF(m, K_STAGE, 3.0 * e * (n_rest + n_pos), launch_stage(b, c.dtype, seed, eps, false, m->compute));
-    }
-    return ZO_OK;
-}
-
-// Stage one block into the per-sign scratch.  `slot_base` == nullptr: the block's 16 tensors are read
-// where the caller keeps them (resident model, separately allocated); otherwise from a device copy of
-// the block laid out contiguously in canonical order (streamed model).
-int stage_block(zo_model *m, int layer, const char *slot_base, uint64_t seed, float eps, bool single, int upd_mode = 0, int pend = 0)
-{
-    const zo_config &c = m->cfg;
     const BlockLayout &L = m->lay;
-    const size_t e = elem_bytes(c.dtype), D = c.d_model;
+    const size_t e = elem_bytes(m->cfg.dtype), D = m->cfg.d_model;
     char *sp = m->ws + m->wsp.stage[0], *sm = m->ws + m->wsp.stage[1];
     const int t0 = 2 + kPerBlock * layer;
-    StageBatch b{};
     auto add = [&](int k, size_t dst_off) {
         const void *src = slot_base ? (const void *)(slot_base + L.src_off[k] * e) : (const void *)m->tptr[t0 + k];
         stage_batch_add(b, src, sp + dst_off * e, sm + dst_off * e, L.rows[k], L.cols[k], t0 + k, false);
@@ -352,7 +320,48 @@ int stage_block(zo_model *m, int layer, const char *slot_base, uint64_t seed, fl
     add(T_LN2G, L.st_ln2g); add(T_LN2B, L.st_ln2b);
     add(T_W1, L.st_w1); add(T_B1, L.st_b1);
     add(T_W2, L.st_w2); add(T_B2, L.st_b2);
-    ZO_PROF(m, K_STAGE, (single ? 2.0 : upd_mode ? 4.0 : 3.0) * e * (double)L.total,
+}
+
+// Stage the embeddings and the final LayerNorm: W+- copies (fused) or nothing (literal reads theta itself).
+// upd_mode != 0: a pending update (seed m->pend_seed[0], scalar m->s_pend[0]) is applied to these tensors on the way.
+// Only the first `seq` position rows are staged: where that is not the whole table, it takes its update in a pass of its own.
+// `with_block`: block 0 of a resident model in the same launch.  A launch is 3.7 us at least, host and device together: steps of two
+// layers of a tiny fp32 model 101.6 -> 95.9 us, with the update pending 107 -> 92 (there the position table rode along too); of three
+// layers of 384 with 136 rows 211 -> 206.
+int stage_globals(zo_model *m, int seq, uint64_t seed, float eps, int upd_mode, bool with_block = false)
+{
+    const zo_config &c = m->cfg;
+    StageBatch b{}, bpos{};
+    const int lnf = 2 + kPerBlock * c.n_layers;
+    const size_t e = elem_bytes(c.dtype);
+    const bool pos_apart = upd_mode && seq < c.max_pos;
+    stage_batch_add(b, m->tptr[0], m->ws + m->wsp.e_pm[0], m->ws + m->wsp.e_pm[1], c.vocab, c.d_model, 0, false);
+    stage_batch_add(pos_apart ? bpos : b, m->tptr[1], m->ws + m->wsp.pos_pm[0], m->ws + m->wsp.pos_pm[1], seq, c.d_model, 1, false);
+    stage_batch_add(b, m->tptr[lnf], m->ws + m->wsp.lnf_pm[0], m->ws + m->wsp.lnf_pm[1], 1, c.d_model, lnf, false);
+    stage_batch_add(b, m->tptr[lnf + 1], m->ws + m->wsp.lnf_pm[0] + c.d_model * e, m->ws + m->wsp.lnf_pm[1] + c.d_model * e, 1,
+                    c.d_model, lnf + 1, false);
+    if (with_block) add_block(m, b, 0, nullptr);
+    const double n_pos = (double)seq * c.d_model;
+    const double n_rest = (double)c.vocab * c.d_model + 2.0 * c.d_model + (pos_apart ? 0.0 : n_pos) + (with_block ? (double)m->lay.total : 0.0);
+    if (pos_apart) {
+        const int keep = m->update_rounding;           // the rounding the pending step asked for
+        m->update_rounding = m->pend_round;
+        const int rc = axpy_range(m, 1, 1, m->pend_seed[0], 0.0f, m->s_pend, true);
+        m->update_rounding = keep;
+        ZO_TRY(rc);
+        ZO_PROF(m, K_STAGE, 3.0 * e * n_pos, launch_stage(bpos, c.dtype, seed, eps, false, m->compute));
+    }
+    ZO_PROF(m, K_STAGE, (upd_mode ? 4.0 : 3.0) * e * n_rest, launch_stage(b, c.dtype, seed, eps, false, m->compute, upd_mode, m->pend_seed[0], m->s_pend));
+    return ZO_OK;
+}
+
+// Stage one block into the per-sign scratch.
+int stage_block(zo_model *m, int layer, const char *slot_base, uint64_t seed, float eps, bool single, int upd_mode = 0, int pend = 0)
+{
+    const zo_config &c = m->cfg;
+    StageBatch b{};
+    add_block(m, b, layer, slot_base);
+    ZO_PROF(m, K_STAGE, (single ? 2.0 : upd_mode ? 4.0 : 3.0) * elem_bytes(c.dtype) * (double)m->lay.total,
             launch_stage(b, c.dtype, seed, eps, single, m->compute, upd_mode, m->pend_seed[pend], m->s_pend + pend));
     return ZO_OK;
 }
@@ -487,11 +496,11 @@ int forward_fused_resident(zo_model *m, const int32_t *tokens, int batch, int se
     const zo_config &c = m->cfg;
     // a pending update (deferred mode) rides on this step's staging passes: every parameter is read here anyway
     const int upd_mode = m->pend_n > 0 ? (m->pend_round == ZO_ROUND_STOCHASTIC ? 2 : 1) : 0;
-    ZO_TRY(stage_globals(m, seq, seed, eps, upd_mode));
+    ZO_TRY(stage_globals(m, seq, seed, eps, upd_mode, true));
     const char *ep = m->ws + m->wsp.e_pm[0], *em = m->ws + m->wsp.e_pm[1];
     ZO_TRY(embed(m, tokens, 2, batch, seq, ep, em, m->ws + m->wsp.pos_pm[0], m->ws + m->wsp.pos_pm[1]));
     for (int l = 0; l < c.n_layers; ++l) {
-        ZO_TRY(stage_block(m, l, nullptr, seed, eps, false, upd_mode));
+        if (l > 0) ZO_TRY(stage_block(m, l, nullptr, seed, eps, false, upd_mode));
         ZO_TRY(block_forward(m, 2, batch, seq));
     }
     m->pend_n = 0;

@@ -30,7 +30,7 @@ struct StageDesc {           // one tensor of an out-of-place W+- staging pass
     uint32_t first_tile;
     uint32_t tiles_c;        // tiles along cols (transpose) ; unused otherwise
 };
-constexpr int kStageMaxDesc = 16;
+constexpr int kStageMaxDesc = 20;          // a block's tensors, the embeddings and the final LayerNorm's two
 struct StageBatch { StageDesc d[kStageMaxDesc]; int n; uint32_t total_tiles; };
 constexpr uint32_t kStageTile = 64;          // transposing tile edge
 constexpr uint32_t kStageFlatTile = 8192;    // consecutive elements per tile when not transposing
