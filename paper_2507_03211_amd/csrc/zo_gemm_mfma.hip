@@ -11,7 +11,7 @@
 // activation tile the B operand, so a lane's 16 accumulators are 4 runs of 4 consecutive n of
 // one output row, which makes the epilogue 8/16-byte stores.
 //
-// Two kernels (K a multiple of 64; others take the plain kernel):
+// Three kernels (K a multiple of 64; others take the plain kernel):
 //  * linear_mfma_pipe_kernel, for K of some slabs and more: one persistent workgroup of 2 x 2 waves per CU that walks its
 //    XCD's share of the tile list, tiles of 256 x 256 down to 128 x 128 with slabs of 64 k.  Operand tiles go from global
 //    memory straight into LDS (global_load_lds_dwordx4, no register staging), whole 128-byte lines per tile row, several
@@ -20,6 +20,7 @@
 //    contiguous band of 8 tile-rows and walks it column by column.  Outputs leave through LDS as whole rows.
 //  * linear_mfma_small_kernel, 64 x 64 tiles, one workgroup per tile and two or more of them per CU: any number of slabs,
 //    and shapes so small that what counts is how many CUs take part.
+//  * linear_mfma_split_kernel, 32 x 32 tiles whose waves share the contraction: shapes so small that each tile has a CU of its own.
 // pick_tile() at the end chooses between the tile shapes.
 #include "zo_device_once.h"
 #include "zo_kernels.h"
@@ -725,6 +726,113 @@ __global__ __launch_bounds__(256, 2) void linear_mfma_small_kernel(
     }
 }
 
+// ------------------------------------------------------------------ few tiles, deep contractions
+// One output tile of 32 x 32 per workgroup; its four waves take every fourth slab of the contraction each, through rings of
+// their own (kSplitStages slabs of 32 rows of x and of the weights), so that nothing waits for another wave until the four
+// partial sums meet in LDS, in a fixed order.  For shapes whose tiles leave most CUs idle at 64 x 64: four times as many take part, a
+// CU loads half as much a slab, and the chain of slabs is a fourth as long.  What bounds it is a CU's loads: 32 KB of lines under way at
+// most, 55 B/ns from far memory and 110 from the L2.  Two stages are as fast as three (a second workgroup fits besides).
+// Both signs of m_half x n x k, us, operands far / near, 64 x 64 tiles -> here: 96 x 1024 x 4096 20.7 / 15.5 -> 12.2 / 7.1, 213 x 576 x
+// 2304 11.3 / 10.0 -> 7.0 / 5.4, 68 x 384 x 1536 8.6 / 7.6 -> 5.4 / 4.5, 213 x 576 x 576 5.6 / 4.9 -> 4.3 / 3.7.
+constexpr int kSplitStages = 2, kSplitBytes = 4 * kSplitStages * 64 * BK * 2;
+template <int DT, int EPI>
+__global__ __launch_bounds__(256, 2) void linear_mfma_split_kernel(
+    const uint16_t *__restrict__ x, const uint16_t *__restrict__ wt_p, const uint16_t *__restrict__ wt_m, const uint16_t *__restrict__ b_p,
+    const uint16_t *__restrict__ b_m, void *__restrict__ y, int m_half, int n, int k, int tiles_m, int tiles_n, int total)
+{
+    constexpr int ST = kSplitStages, BM = 32, BN = 32, L = 8, CPR = BK / 8;      // L: loads of a slab, four of x and four of w
+    extern __shared__ __attribute__((aligned(16))) uint4 smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int fr = lane & 31, fh = lane >> 5;
+    const int per_xcd = (total + 7) / 8;
+    const int lin = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
+    if (((int)blockIdx.x >> 3) >= per_xcd || lin >= total) return;
+    int sign, trow, tcol;
+    tile_at(lin, tiles_m, tiles_n, sign, trow, tcol);
+    const int m0 = trow * BM, n0 = tcol * BN;
+    const uint64_t xbase = uniform64((uint64_t)(uintptr_t)(x + ((size_t)sign * m_half + m0) * k));
+    const uint64_t wbase = uniform64((uint64_t)(uintptr_t)((sign ? wt_m : wt_p) + (size_t)n0 * k));
+    auto swz = [](int r) { return (r >> 1) & 7; };              // chunk c of row r sits at slot c ^ swz(r)
+    uint32_t off[L];
+#pragma unroll
+    for (int i = 0; i < L; ++i) {
+        const int row = (i & 3) * 8 + (lane >> 3), first = i < 4 ? m0 : n0, end = i < 4 ? m_half : n;
+        int r = first + row; r = r < end ? r : end - 1;                      // clamped: never stored
+        off[i] = ((uint32_t)(r - first) * (uint32_t)k + ((lane & 7) ^ swz(row)) * 8) * 2u;
+    }
+    // the epilogue's operands of this thread: row tid / 8, columns 4 (tid % 8) ..
+    const int er = m0 + (tid >> 3), ec = n0 + 4 * (tid & 7);
+    const bool live = er < m_half && ec < n;
+    const size_t eo = ((size_t)sign * m_half + (er < m_half ? er : m_half - 1)) * n + (ec < n ? ec : n - 4);
+    const uint32_t ring = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint4 *)smem + (uint32_t)wave * (ST * 8192u);
+    auto load_slab = [&](int slab, uint32_t stage) {
+        const uint32_t adv = (uint32_t)slab * (BK * 2);
+#pragma unroll
+        for (int i = 0; i < L; ++i) gload_lds16((i < 4 ? xbase : wbase) + adv, off[i], ring + stage * 8192u + (uint32_t)i * 1024u);
+    };
+    f32x16 acc = {};
+    const int nk = k / BK, mine = (nk - wave + 3) / 4;                        // slabs wave, wave + 4, ..
+#pragma unroll
+    for (int s = 0; s < ST; ++s)
+        if (s < mine) load_slab(wave + 4 * s, s);
+    uint32_t rd = 0;
+    for (int i = 0; i < mine; ++i) {
+        if (i + ST - 1 < mine) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((ST - 1) * L) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        const uint4 *st = smem + (wave * ST + rd) * 512;
+        uint4 xf[4], wf[4];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            const int slot = (2 * ks + fh) ^ swz(fr);
+            xf[ks] = st[fr * CPR + slot];
+            wf[ks] = st[256 + fr * CPR + slot];
+        }
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) acc = mfma32<DT>(wf[ks], xf[ks], acc);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                       // the stage's reads are in registers
+        if (i + ST < mine) load_slab(wave + 4 * (i + ST), rd);
+        rd = rd + 1 == ST ? 0 : rd + 1;
+    }
+    // the four partial sums meet in LDS: row fr, runs of four columns 8 g + 4 fh
+    __syncthreads();
+    float *part = (float *)smem;
+    constexpr int PITCH = 36;
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+        *(float4 *)(part + (wave * 32 + fr) * PITCH + 8 * g + 4 * fh) = float4{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
+    __syncthreads();
+    float v[4];
+    {
+        const float *q = part + (tid >> 3) * PITCH + 4 * (tid & 7);
+        const f32x4 a = *(const f32x4 *)q, b = *(const f32x4 *)(q + 32 * PITCH), c = *(const f32x4 *)(q + 64 * PITCH), d = *(const f32x4 *)(q + 96 * PITCH);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = (a[e] + b[e]) + (c[e] + d[e]);
+    }
+    if (!live) return;
+    if constexpr (EPI != 3) {
+        const uint2 raw = *(const uint2 *)((sign ? b_m : b_p) + ec);
+        const float bias[4] = {Prec<DT>::w2f((uint16_t)(raw.x & 0xffff)), Prec<DT>::w2f((uint16_t)(raw.x >> 16)), Prec<DT>::w2f((uint16_t)(raw.y & 0xffff)), Prec<DT>::w2f((uint16_t)(raw.y >> 16))};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] += bias[e];
+    }
+    if constexpr (EPI < 2) {
+        if constexpr (EPI == 1) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.0f ? v[e] : 0.0f;
+        }
+        uint2 o;
+        o.x = (uint32_t)Prec<DT>::acc2a(v[0]) | ((uint32_t)Prec<DT>::acc2a(v[1]) << 16);
+        o.y = (uint32_t)Prec<DT>::acc2a(v[2]) | ((uint32_t)Prec<DT>::acc2a(v[3]) << 16);
+        *(uint2 *)((uint16_t *)y + eo) = o;
+    } else {
+        f32x4 *p = (f32x4 *)((float *)y + eo);
+        f32x4 o = {v[0], v[1], v[2], v[3]};
+        if constexpr (EPI == 2) { const f32x4 h = *p; o = f32x4{h.x + o.x, h.y + o.y, h.z + o.z, h.w + o.w}; }
+        *p = o;
+    }
+}
+
 // ------------------------------------------------------------------ launchers
 // CUs of the current device, rounded down to whole XCDs' worth; 0 when the runtime does not say
 int cu_count()
@@ -797,8 +905,23 @@ template <int DT, int EPI, int TN> hipError_t launch_small(const Args &a)
     return launch_small_t<DT, EPI, TN, false>(a);
 }
 
-enum Tile { T256x256, T256x192, T256x128, T192x128, T128x128, T64x64, kTiles };
-constexpr int kTileRows[kTiles] = {256, 256, 256, 192, 128, 64}, kTileColumns[kTiles] = {256, 192, 128, 128, 128, 64};
+template <int DT, int EPI> hipError_t launch_split(const Args &a)
+{
+    const int tiles_m = (a.m_half + 31) / 32, tiles_n = (a.n + 31) / 32, total = a.n_sign * tiles_m * tiles_n;
+    auto kern = linear_mfma_split_kernel<DT, EPI>;
+    static std::atomic<uint64_t> lds_allowed{0};
+    const hipError_t e = once_per_device(lds_allowed, [&] {
+        return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kSplitBytes);
+    });
+    if (e != hipSuccess) return e;
+    kern<<<dim3((total + 7) / 8 * 8), dim3(256), kSplitBytes, a.s>>>((const uint16_t *)a.x, (const uint16_t *)a.wt_p, (const uint16_t *)a.wt_m,
+                                                                         (const uint16_t *)a.b_p, (const uint16_t *)a.b_m, a.y, a.m_half, a.n, a.k,
+                                                                         tiles_m, tiles_n, total);
+    return hipGetLastError();
+}
+
+enum Tile { T256x256, T256x192, T256x128, T192x128, T128x128, T64x64, T32x32, kTiles };
+constexpr int kTileRows[kTiles] = {256, 256, 256, 192, 128, 64, 32}, kTileColumns[kTiles] = {256, 192, 128, 128, 128, 64, 32};
 template <int DT, int EPI> hipError_t launch_tile(Tile t, const Args &a)
 {
     switch (t) {
@@ -807,8 +930,19 @@ template <int DT, int EPI> hipError_t launch_tile(Tile t, const Args &a)
     case T256x128: return launch_pipe<DT, EPI, Shape<4, 2, 2>>(a);
     case T192x128: return launch_pipe<DT, EPI, Shape<3, 2, 3>>(a);
     case T128x128: return launch_pipe<DT, EPI, Shape<2, 2, 4>>(a);
-    default: return launch_small<DT, EPI, 1>(a);
+    case T64x64: return launch_small<DT, EPI, 1>(a);
+    default: return launch_split<DT, EPI>(a);
     }
+}
+
+// Do the 32 x 32 tiles get a CU each?  From five slabs on, where each wave has one at least, they are then faster than any other
+// shape: 1.52 times in the geometric mean over 159 shapes (24 - 870 rows a sign, n 80 - 5120, k 320 - 14592, all epilogues), 1.19 at
+// least, 2.0 at most.  Two to four slabs would gain 0.3 - 0.6 us of a launch's 3.5; with 2.0 tiles a CU (250 x 1024 x 4096) the gain is
+// 1.14, with 3.2 (536 x 768 x 3072) 0.78.
+bool one_small_tile_a_cu(int n_sign, int m_half, int n, int k)
+{
+    const long tiles = (long)n_sign * ((m_half + 31) / 32) * ((n + 31) / 32);
+    return k >= 5 * BK && tiles <= (cu_count() ? cu_count() : 256);
 }
 
 // The tile shape with the least estimated time in us: start + rounds (slabs slab + epilogue), where a round of tiles that
@@ -828,14 +962,15 @@ template <int DT, int EPI> hipError_t launch_tile(Tile t, const Args &a)
 Tile pick_tile(int n_sign, int m_half, int n, int k, int epi)
 {
     struct Out { float first, more; };
-    static const struct { int min_slabs; float start, slab, busy, out16; Out rmw, out32; } kCost[kTiles] = {
+    static const struct { int min_slabs; float start, slab, busy, out16; Out rmw, out32; } kCost[T32x32] = {
         {3, 4.9f, 1.00f, 0.52f, 3.5f, {26.1f, 21.3f}, {9.0f, 11.4f}}, {3, 3.6f, 0.79f, 0.38f, 3.1f, {20.9f, 16.7f}, {7.0f, 9.0f}},
         {3, 3.6f, 0.59f, 0.28f, 1.6f, {12.0f, 11.4f}, {2.7f, 7.0f}},  {4, 4.1f, 0.49f, 0.21f, 0.9f, {7.9f, 7.6f}, {1.2f, 5.0f}},
         {5, 4.1f, 0.38f, 0.16f, 0.3f, {4.3f, 4.5f}, {0.0f, 3.1f}},    {1, 2.6f, 0.21f, 0.41f, 0.4f, {0.5f, 2.5f}, {0.0f, 1.3f}}};
+    if (one_small_tile_a_cu(n_sign, m_half, n, k)) return T32x32;
     const float n_cu = cu_count() ? (float)cu_count() : 256.0f, slabs = (float)(k / BK);
     Tile best = kTiles;
     float best_us = 0.0f;
-    for (int t = 0; t < kTiles; ++t) {
+    for (int t = 0; t < T32x32; ++t) {
         const auto &c = kCost[t];
         if (k / BK < c.min_slabs) continue;
         const float tiles = (float)n_sign * (float)((m_half + kTileRows[t] - 1) / kTileRows[t]) * (float)((n + kTileColumns[t] - 1) / kTileColumns[t]);
