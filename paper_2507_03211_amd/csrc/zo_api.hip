@@ -3,6 +3,7 @@
 // dual forward with the deferred update) and Alg. 3 (upload / compute / offload overlap).
 #include "../../include/zo.h"
 
+#include <algorithm>
 #include <hip/hip_runtime.h>
 
 #include <cstdarg>
@@ -297,21 +298,45 @@ int axpy_range(zo_model *m, int first, int n, uint64_t seed, float scale, const 
     return ZO_OK;
 }
 
-struct BlockPtrs {   // staged parameter pointers of one block, per sign
-    const char *base[2];
-};
+struct Staged { char *p, *m; };   // where a block's staged copies lie, per sign
+
+Staged first_staged(zo_model *m) { return {m->ws + m->wsp.stage[0], m->ws + m->wsp.stage[1]}; }
+
+// A resident model's blocks are staged in groups: a launch of one small block is mostly its start (7 M elements: 10 us of work in 19).
+// A group's first copies lie in the staging buffers, the others in the LM head's region, which holds nothing before the last block's
+// output is there; where that is small (few rows) or the model is large, groups are of one block.  Whole steps, one block a launch / here:
+// 3 layers of 384, 68 rows 196 -> 183 us, 12 of 768, 96 rows 827 -> 770, 16 x 512 rows 5154 -> 5124, 8 of 1024, 8 x 512 rows 3076 -> 3063.
+// The copies have to stay in the 256 MiB of the memory-side cache until the layers read them: two blocks of 1152 (122 MiB) 830 ->
+// 811 and 1437 -> 1427, but two of 1280 (150 MiB) 2497 -> 2535 and two of 1536 (216 MiB) 1434 -> 1551.
+constexpr int kStageGroup = 4;
+constexpr size_t kStageGroupBytes = 128u << 20;
+static_assert(4 + kStageGroup * kPerBlock <= kStageMaxDesc, "the embeddings, the final LayerNorm and a group in one launch");
+size_t block_copy_bytes(const zo_model *m) { return align_up(m->lay.total * elem_bytes(m->cfg.dtype)); }
+int stage_group(const zo_model *m)
+{
+    const size_t copies = 2 * block_copy_bytes(m);
+    const size_t room = lmhead_region_bytes(m->cfg.dtype, 2 * (size_t)m->max_batch * m->max_seq, m->cfg.vocab) / copies;
+    const size_t fit = kStageGroupBytes / copies;
+    const size_t g = std::min(room + 1, fit);
+    return (int)std::min<size_t>(std::max<size_t>(g, 1), kStageGroup);
+}
+Staged group_staged(zo_model *m, int i)
+{
+    if (i == 0) return first_staged(m);
+    char *at = m->ws + m->wsp.logits + (size_t)(i - 1) * 2 * block_copy_bytes(m);
+    return {at, at + block_copy_bytes(m)};
+}
 
 // A block's tensors in a staging batch.  `slot_base` == nullptr: they are read where the caller keeps them (resident model,
 // separately allocated); otherwise from a device copy of the block laid out contiguously in canonical order (streamed model).
-void add_block(zo_model *m, StageBatch &b, int layer, const char *slot_base)
+void add_block(zo_model *m, StageBatch &b, int layer, const char *slot_base, Staged to)
 {
     const BlockLayout &L = m->lay;
     const size_t e = elem_bytes(m->cfg.dtype), D = m->cfg.d_model;
-    char *sp = m->ws + m->wsp.stage[0], *sm = m->ws + m->wsp.stage[1];
     const int t0 = 2 + kPerBlock * layer;
     auto add = [&](int k, size_t dst_off) {
         const void *src = slot_base ? (const void *)(slot_base + L.src_off[k] * e) : (const void *)m->tptr[t0 + k];
-        stage_batch_add(b, src, sp + dst_off * e, sm + dst_off * e, L.rows[k], L.cols[k], t0 + k, false);
+        stage_batch_add(b, src, to.p + dst_off * e, to.m + dst_off * e, L.rows[k], L.cols[k], t0 + k, false);
     };
     add(T_LN1G, L.st_ln1g); add(T_LN1B, L.st_ln1b);
     add(T_WQ, L.st_wqkv); add(T_WK, L.st_wqkv + D * D); add(T_WV, L.st_wqkv + 2 * D * D);
@@ -325,10 +350,10 @@ void add_block(zo_model *m, StageBatch &b, int layer, const char *slot_base)
 // Stage the embeddings and the final LayerNorm: W+- copies (fused) or nothing (literal reads theta itself).
 // upd_mode != 0: a pending update (seed m->pend_seed[0], scalar m->s_pend[0]) is applied to these tensors on the way.
 // Only the first `seq` position rows are staged: where that is not the whole table, it takes its update in a pass of its own.
-// `with_block`: block 0 of a resident model in the same launch.  A launch is 3.7 us at least, host and device together: steps of two
+// `n_blocks`: the first blocks of a resident model in the same launch.  A launch is 3.7 us at least, host and device together: steps of two
 // layers of a tiny fp32 model 101.6 -> 95.9 us, with the update pending 107 -> 92 (there the position table rode along too); of three
 // layers of 384 with 136 rows 211 -> 206.
-int stage_globals(zo_model *m, int seq, uint64_t seed, float eps, int upd_mode, bool with_block = false)
+int stage_globals(zo_model *m, int seq, uint64_t seed, float eps, int upd_mode, int n_blocks = 0)
 {
     const zo_config &c = m->cfg;
     StageBatch b{}, bpos{};
@@ -340,9 +365,9 @@ int stage_globals(zo_model *m, int seq, uint64_t seed, float eps, int upd_mode, 
     stage_batch_add(b, m->tptr[lnf], m->ws + m->wsp.lnf_pm[0], m->ws + m->wsp.lnf_pm[1], 1, c.d_model, lnf, false);
     stage_batch_add(b, m->tptr[lnf + 1], m->ws + m->wsp.lnf_pm[0] + c.d_model * e, m->ws + m->wsp.lnf_pm[1] + c.d_model * e, 1,
                     c.d_model, lnf + 1, false);
-    if (with_block) add_block(m, b, 0, nullptr);
+    for (int i = 0; i < n_blocks; ++i) add_block(m, b, i, nullptr, group_staged(m, i));
     const double n_pos = (double)seq * c.d_model;
-    const double n_rest = (double)c.vocab * c.d_model + 2.0 * c.d_model + (pos_apart ? 0.0 : n_pos) + (with_block ? (double)m->lay.total : 0.0);
+    const double n_rest = (double)c.vocab * c.d_model + 2.0 * c.d_model + (pos_apart ? 0.0 : n_pos) + n_blocks * (double)m->lay.total;
     if (pos_apart) {
         const int keep = m->update_rounding;           // the rounding the pending step asked for
         m->update_rounding = m->pend_round;
@@ -355,25 +380,25 @@ int stage_globals(zo_model *m, int seq, uint64_t seed, float eps, int upd_mode, 
     return ZO_OK;
 }
 
-// Stage one block into the per-sign scratch.
-int stage_block(zo_model *m, int layer, const char *slot_base, uint64_t seed, float eps, bool single, int upd_mode = 0, int pend = 0)
+// Stage one block, or `n` of a resident model, into the per-sign scratch.
+int stage_block(zo_model *m, int layer, const char *slot_base, uint64_t seed, float eps, bool single, int upd_mode = 0, int pend = 0, int n = 1)
 {
     const zo_config &c = m->cfg;
     StageBatch b{};
-    add_block(m, b, layer, slot_base);
-    ZO_PROF(m, K_STAGE, (single ? 2.0 : upd_mode ? 4.0 : 3.0) * elem_bytes(c.dtype) * (double)m->lay.total,
+    for (int i = 0; i < n; ++i) add_block(m, b, layer + i, slot_base, group_staged(m, i));
+    ZO_PROF(m, K_STAGE, (single ? 2.0 : upd_mode ? 4.0 : 3.0) * elem_bytes(c.dtype) * n * (double)m->lay.total,
             launch_stage(b, c.dtype, seed, eps, single, m->compute, upd_mode, m->pend_seed[pend], m->s_pend + pend));
     return ZO_OK;
 }
 
 // One decoder block on the staged parameters; activations in the workspace.
-int block_forward(zo_model *m, int n_sign, int batch, int seq)
+int block_forward(zo_model *m, int n_sign, int batch, int seq, Staged w)
 {
     const zo_config &c = m->cfg;
     const BlockLayout &L = m->lay;
     const size_t e = elem_bytes(c.dtype);
     const int m_half = batch * seq, d = c.d_model, f = c.d_ffn, dt = c.dtype;
-    const char *P = m->ws + m->wsp.stage[0], *M = m->ws + m->wsp.stage[1];
+    const char *P = w.p, *M = w.m;
     void *resid = m->ws + m->wsp.resid, *x = m->ws + m->wsp.xbuf, *qkv = m->ws + m->wsp.qkv, *att = m->ws + m->wsp.att,
          *mid = m->ws + m->wsp.mid;
     hipStream_t s = m->compute;
@@ -496,12 +521,13 @@ int forward_fused_resident(zo_model *m, const int32_t *tokens, int batch, int se
     const zo_config &c = m->cfg;
     // a pending update (deferred mode) rides on this step's staging passes: every parameter is read here anyway
     const int upd_mode = m->pend_n > 0 ? (m->pend_round == ZO_ROUND_STOCHASTIC ? 2 : 1) : 0;
-    ZO_TRY(stage_globals(m, seq, seed, eps, upd_mode, true));
+    const int group = stage_group(m), first = std::min(group, c.n_layers);
+    ZO_TRY(stage_globals(m, seq, seed, eps, upd_mode, first));
     const char *ep = m->ws + m->wsp.e_pm[0], *em = m->ws + m->wsp.e_pm[1];
     ZO_TRY(embed(m, tokens, 2, batch, seq, ep, em, m->ws + m->wsp.pos_pm[0], m->ws + m->wsp.pos_pm[1]));
     for (int l = 0; l < c.n_layers; ++l) {
-        if (l > 0) ZO_TRY(stage_block(m, l, nullptr, seed, eps, false, upd_mode));
-        ZO_TRY(block_forward(m, 2, batch, seq));
+        if (l > 0 && l % group == 0) ZO_TRY(stage_block(m, l, nullptr, seed, eps, false, upd_mode, 0, std::min(group, c.n_layers - l)));
+        ZO_TRY(block_forward(m, 2, batch, seq, group_staged(m, l % group)));
     }
     m->pend_n = 0;
     return head_and_loss(m, 2, batch, seq, ep, em, m->ws + m->wsp.lnf_pm[0], m->ws + m->wsp.lnf_pm[1], m->loss_pm, gs);
@@ -521,7 +547,7 @@ int forward_single(zo_model *m, const int32_t *tokens, int batch, int seq, int s
     ZO_TRY(embed(m, tokens, 1, batch, seq, m->tptr[0], m->tptr[0], m->tptr[1], m->tptr[1]));
     for (int l = 0; l < c.n_layers; ++l) {
         ZO_TRY(stage_block(m, l, nullptr, 0, 0.0f, true));
-        ZO_TRY(block_forward(m, 1, batch, seq));
+        ZO_TRY(block_forward(m, 1, batch, seq, first_staged(m)));
     }
     return head_and_loss(m, 1, batch, seq, m->tptr[0], m->tptr[0], m->ws + m->wsp.lnf_pm[0], m->ws + m->wsp.lnf_pm[0],
                          m->loss_pm + slot);
@@ -577,7 +603,7 @@ int stream_compute(zo_model *m, int block, bool forward, bool force_writeback = 
         if (forward) {
             // the pending update rides on the staging pass, which reads theta anyway
             ZO_TRY(stage_block(m, block, nullptr, m->step_seed, m->step_eps, false, m->pend_n > 0 ? sr_mode : 0, m->pend_n > 0 ? m->pend_n - 1 : 0));
-            ZO_TRY(block_forward(m, 2, m->step_batch, m->step_seq));
+            ZO_TRY(block_forward(m, 2, m->step_batch, m->step_seq, first_staged(m)));
         }
         return ZO_OK;
     }
@@ -609,7 +635,7 @@ int stream_compute(zo_model *m, int block, bool forward, bool force_writeback = 
         ZO_TRY(stage_block(m, block, m->ws + m->wsp.slot[slot], m->step_seed, m->step_eps, false,
                            fold ? (m->update_rounding == ZO_ROUND_STOCHASTIC ? 2 : 1) : 0, 0));
     ZO_HIP(hipEventRecord(m->ev_staged[slot], m->compute));
-    if (forward) ZO_TRY(block_forward(m, 2, m->step_batch, m->step_seq));
+    if (forward) ZO_TRY(block_forward(m, 2, m->step_batch, m->step_seq, first_staged(m)));
     m->slot_state[slot] = SLOT_COMPUTED;
     return ZO_OK;
 }

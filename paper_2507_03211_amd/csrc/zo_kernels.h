@@ -27,11 +27,16 @@ struct StageDesc {           // one tensor of an out-of-place W+- staging pass
     uint32_t rows, cols;     // source is [rows, cols] row-major
     uint32_t tid;
     uint32_t transpose;      // write [cols, rows]
-    uint32_t first_tile;
     uint32_t tiles_c;        // tiles along cols (transpose) ; unused otherwise
 };
-constexpr int kStageMaxDesc = 20;          // a block's tensors, the embeddings and the final LayerNorm's two
-struct StageBatch { StageDesc d[kStageMaxDesc]; int n; uint32_t total_tiles; };
+constexpr int kStageMaxDesc = 68;          // the embeddings, the final LayerNorm's two and four blocks' tensors
+struct StageBatch {
+    uint32_t first[kStageMaxDesc];         // each tensor's first tile, side by side: the search for a tile's tensor reads nothing else
+    int n;
+    uint32_t total_tiles;
+    StageDesc d[kStageMaxDesc];
+};
+static_assert(sizeof(StageBatch) + 64 <= 4096, "passed by value: a kernel takes 4 KiB of arguments");
 constexpr uint32_t kStageTile = 64;          // transposing tile edge
 constexpr uint32_t kStageFlatTile = 8192;    // consecutive elements per tile when not transposing
 

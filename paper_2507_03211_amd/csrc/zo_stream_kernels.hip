@@ -372,9 +372,9 @@ __global__ __launch_bounds__(kStageThreads) __attribute__((amdgpu_waves_per_eu((
         const bool active = blk < batch.total_tiles;
         int di = 0;
         for (int i = 1; i < batch.n; ++i)
-            if (batch.d[i].first_tile <= blk) di = i;
+            if (batch.first[i] <= blk) di = i;
         const StageDesc &d = batch.d[di];
-        const uint32_t tile = blk - d.first_tile;
+        const uint32_t tile = blk - batch.first[di];
         W *const theta = (W *)const_cast<void *>(d.src);      // written only when UPD != 0
         const W *src = theta;
         W *__restrict__ dp = (W *)d.dst_plus;
@@ -539,20 +539,26 @@ void stage_flat_kernel(StageBatch batch, uint64_t seed, float eps, uint64_t upd_
                                  // elements 19.4 -> 6.3 us, 7.1 M 24.2 -> 10.4 and with the update 31.3 -> 15.2, 105 M
                                  // with the update 180 -> 172.)
     };
-    // the first tile's tensor from all the table's entries at once: one by one, each is a scalar load that the next one waits
-    // for (staging a block of 16 tensors, 50 k parameters: 7.2 us / 5.0 here)
+    // the first tile's tensor from all the table's entries at once, a lane each: one by one, each is a load that the next one waits for
+    // (staging a block of 16 tensors, 50 k parameters: 7.2 us / 5.0 so).  `touch` asks for the records in the same trip: without it
+    // the one that is found is a second trip to the argument buffer, which no cache holds when a launch begins, and the chunk's
+    // loads wait for both (3 - 5 us a launch, 2.4 M to 7 M bf16 elements)
+    static_assert(kStageMaxDesc <= 128, "two entries a lane");
     int di = 0;
+    uint32_t touch = 0;
     if (batch.n > 1) {
-#pragma unroll
-        for (int i = 1; i < kStageMaxDesc; ++i) di += (int)(i < batch.n) & (int)(batch.d[i].first_tile <= blockIdx.x);
+        const int l = threadIdx.x & 63, l2 = l + 64 < kStageMaxDesc ? l + 64 : kStageMaxDesc - 1;
+        const uint32_t f1 = batch.first[l], f2 = batch.first[l2];
+        if ((int)threadIdx.x < batch.n) touch = batch.d[threadIdx.x].tid;
+        di = __popcll(__ballot(l < batch.n && f1 <= blockIdx.x)) + __popcll(__ballot(l + 64 < batch.n && f2 <= blockIdx.x)) - 1;
     }
     auto piece_of = [&](uint32_t tile) {
-        while (di + 1 < batch.n && batch.d[di + 1].first_tile <= tile) ++di;
+        while (di + 1 < batch.n && batch.first[di + 1] <= tile) ++di;
         const StageDesc &d = batch.d[di];
         Piece p;
         p.theta = (W *)const_cast<void *>(d.src); p.dp = (W *)d.dst_plus; p.dm = (W *)d.dst_minus;
         p.numel = (uint64_t)d.rows * d.cols;
-        p.base = (uint64_t)(tile - d.first_tile) * kStageFlatTile;
+        p.base = (uint64_t)(tile - batch.first[di]) * kStageFlatTile;
         p.tid = d.tid;
         p.whole = p.base + kStageFlatTile <= p.numel;
         return p;
@@ -619,6 +625,7 @@ void stage_flat_kernel(StageBatch batch, uint64_t seed, float eps, uint64_t upd_
     Piece p = piece_of(c);
     Raw cur[kIter], nxt[kIter];
     if (p.whole) load_chunk(p, cur);
+    asm volatile("" ::"v"(touch));
     for (;;) {
         const uint32_t cn = c + gridDim.x;
         const bool has_next = cn < batch.total_tiles;
@@ -762,10 +769,10 @@ hipError_t launch_axpy_single(const TensorDesc &d, int dtype, uint64_t seed, flo
 void stage_batch_add(StageBatch &b, const void *src, void *dp, void *dm, uint32_t rows, uint32_t cols, uint32_t tid,
                      bool transpose)
 {
+    b.first[b.n] = b.total_tiles;
     StageDesc &d = b.d[b.n++];
     d.src = src; d.dst_plus = dp; d.dst_minus = dm; d.rows = rows; d.cols = cols; d.tid = tid;
     d.transpose = transpose ? 1u : 0u;
-    d.first_tile = b.total_tiles;
     if (transpose) {
         d.tiles_c = (cols + kStageTile - 1) / kStageTile;
         b.total_tiles += d.tiles_c * ((rows + kStageTile - 1) / kStageTile);
