@@ -349,25 +349,29 @@ void add_block(zo_model *m, StageBatch &b, int layer, const char *slot_base, Sta
 
 // Stage the embeddings and the final LayerNorm: W+- copies (fused) or nothing (literal reads theta itself).
 // upd_mode != 0: a pending update (seed m->pend_seed[0], scalar m->s_pend[0]) is applied to these tensors on the way.
-// Only the first `seq` position rows are staged: where that is not the whole table, it takes its update in a pass of its own.
+// Without an update only the first `seq` position rows are staged.  With one the whole table takes it, and staging the rows beyond `seq`
+// along with the others costs less than a pass of its own and a launch more while they are up to 16 MiB: tables of 2048 rows of 64 (fp32)
+// 84.8 -> 78.4 us a step, of 384 178 -> 171, 768 758 -> 746, 2048 643 -> 637, 8192 of 1024 305 -> 304; 12288 of 1024 308 -> 311.
 // `n_blocks`: the first blocks of a resident model in the same launch.  A launch is 3.7 us at least, host and device together: steps of two
 // layers of a tiny fp32 model 101.6 -> 95.9 us, with the update pending 107 -> 92 (there the position table rode along too); of three
 // layers of 384 with 136 rows 211 -> 206.
+constexpr size_t kPosAlongBytes = 16u << 20;
 int stage_globals(zo_model *m, int seq, uint64_t seed, float eps, int upd_mode, int n_blocks = 0)
 {
     const zo_config &c = m->cfg;
     StageBatch b{}, bpos{};
     const int lnf = 2 + kPerBlock * c.n_layers;
     const size_t e = elem_bytes(c.dtype);
-    const bool pos_apart = upd_mode && seq < c.max_pos;
+    const bool pos_apart = upd_mode && (size_t)(c.max_pos - seq) * c.d_model * e > kPosAlongBytes;
+    const int pos_rows = upd_mode && !pos_apart ? c.max_pos : seq;
     stage_batch_add(b, m->tptr[0], m->ws + m->wsp.e_pm[0], m->ws + m->wsp.e_pm[1], c.vocab, c.d_model, 0, false);
-    stage_batch_add(pos_apart ? bpos : b, m->tptr[1], m->ws + m->wsp.pos_pm[0], m->ws + m->wsp.pos_pm[1], seq, c.d_model, 1, false);
+    stage_batch_add(pos_apart ? bpos : b, m->tptr[1], m->ws + m->wsp.pos_pm[0], m->ws + m->wsp.pos_pm[1], pos_rows, c.d_model, 1, false);
     stage_batch_add(b, m->tptr[lnf], m->ws + m->wsp.lnf_pm[0], m->ws + m->wsp.lnf_pm[1], 1, c.d_model, lnf, false);
     stage_batch_add(b, m->tptr[lnf + 1], m->ws + m->wsp.lnf_pm[0] + c.d_model * e, m->ws + m->wsp.lnf_pm[1] + c.d_model * e, 1,
                     c.d_model, lnf + 1, false);
     for (int i = 0; i < n_blocks; ++i) add_block(m, b, i, nullptr, group_staged(m, i));
-    const double n_pos = (double)seq * c.d_model;
-    const double n_rest = (double)c.vocab * c.d_model + 2.0 * c.d_model + (pos_apart ? 0.0 : n_pos) + n_blocks * (double)m->lay.total;
+    const double n_pos = (double)pos_rows * c.d_model;
+    const double n_rest = (c.vocab + 2.0) * c.d_model + (pos_apart ? 0.0 : n_pos) + n_blocks * (double)m->lay.total;
     if (pos_apart) {
         const int keep = m->update_rounding;           // the rounding the pending step asked for
         m->update_rounding = m->pend_round;
