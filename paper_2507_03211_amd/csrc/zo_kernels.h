@@ -30,12 +30,14 @@ struct StageDesc {           // one tensor of an out-of-place W+- staging pass
     uint32_t tiles_c;        // tiles along cols (transpose) ; unused otherwise
 };
 constexpr int kStageMaxDesc = 68;          // the embeddings, the final LayerNorm's two and four blocks' tensors
-struct StageBatch {
-    uint32_t first[kStageMaxDesc];         // each tensor's first tile, side by side: the search for a tile's tensor reads nothing else
+template <int N> struct StageBatchOf {
+    static constexpr int kMax = N;
+    uint32_t first[N];                    // each tensor's first tile, side by side: the search for a tile's tensor reads nothing else
     int n;
     uint32_t total_tiles;
-    StageDesc d[kStageMaxDesc];
+    StageDesc d[N];
 };
+using StageBatch = StageBatchOf<kStageMaxDesc>;
 static_assert(sizeof(StageBatch) + 64 <= 4096, "passed by value: a kernel takes 4 KiB of arguments");
 constexpr uint32_t kStageTile = 64;          // transposing tile edge
 constexpr uint32_t kStageFlatTile = 8192;    // consecutive elements per tile when not transposing

@@ -515,9 +515,9 @@ __global__ __launch_bounds__(kStageThreads) __attribute__((amdgpu_waves_per_eu((
 // 512-thread workgroups per CU that fill the radius table once, chunks of kStageFlatTile consecutive elements of
 // one tensor, the next chunk's theta fetched into registers while this one is computed.  Chunk numbering and
 // arithmetic are those of stage_kernel's flat tiles.
-template <int DT, bool SINGLE, int UPD>
+template <int DT, bool SINGLE, int UPD, class Batch>
 __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu((DT != kFP32 && UPD == 0) ? 8 : 4)))
-void stage_flat_kernel(StageBatch batch, uint64_t seed, float eps, uint64_t upd_seed,
+void stage_flat_kernel(Batch batch, uint64_t seed, float eps, uint64_t upd_seed,
                                                                     const float *__restrict__ dev_scale)
 {
     using W = typename Prec<DT>::W;
@@ -543,17 +543,18 @@ void stage_flat_kernel(StageBatch batch, uint64_t seed, float eps, uint64_t upd_
     // (staging a block of 16 tensors, 50 k parameters: 7.2 us / 5.0 so).  `touch` asks for the records in the same trip: without it
     // the one that is found is a second trip to the argument buffer, which no cache holds when a launch begins, and the chunk's
     // loads wait for both (3 - 5 us a launch, 2.4 M to 7 M bf16 elements)
-    static_assert(kStageMaxDesc <= 128, "two entries a lane");
+    static_assert(Batch::kMax <= 128, "two entries a lane");
     int di = 0;
     uint32_t touch = 0;
-    if (batch.n > 1) {
-        const int l = threadIdx.x & 63, l2 = l + 64 < kStageMaxDesc ? l + 64 : kStageMaxDesc - 1;
-        const uint32_t f1 = batch.first[l], f2 = batch.first[l2];
+    if constexpr (Batch::kMax > 1) {
+        const int l = threadIdx.x & 63, l1 = l < Batch::kMax ? l : Batch::kMax - 1, l2 = l + 64 < Batch::kMax ? l + 64 : Batch::kMax - 1;
+        const uint32_t f1 = batch.first[l1], f2 = batch.first[l2];
         if ((int)threadIdx.x < batch.n) touch = batch.d[threadIdx.x].tid;
         di = __popcll(__ballot(l < batch.n && f1 <= blockIdx.x)) + __popcll(__ballot(l + 64 < batch.n && f2 <= blockIdx.x)) - 1;
     }
     auto piece_of = [&](uint32_t tile) {
-        while (di + 1 < batch.n && batch.first[di + 1] <= tile) ++di;
+        if constexpr (Batch::kMax > 1)
+            while (di + 1 < batch.n && batch.first[di + 1] <= tile) ++di;
         const StageDesc &d = batch.d[di];
         Piece p;
         p.theta = (W *)const_cast<void *>(d.src); p.dp = (W *)d.dst_plus; p.dm = (W *)d.dst_minus;
@@ -799,18 +800,24 @@ hipError_t launch_stage(const StageBatch &b, int dtype, uint64_t seed, float eps
         if (hipError_t e = persistent_grid(b.total_tiles, per_cu, &g); e != hipSuccess) return e;
         const dim3 grid(g), block(kStreamThreads);
 #define ZO_STAGE(DT)                                                                                                   \
-    if (single_copy) stage_flat_kernel<DT, true, 0><<<grid, block, 0, s>>>(b, seed, eps, 0, nullptr);                   \
-    else if (upd_mode == 0) stage_flat_kernel<DT, false, 0><<<grid, block, 0, s>>>(b, seed, eps, 0, nullptr);           \
-    else if (upd_mode == 1) stage_flat_kernel<DT, false, 1><<<grid, block, 0, s>>>(b, seed, eps, upd_seed, dev_scale);  \
-    else if constexpr (DT != kFP32) stage_flat_kernel<DT, false, 2><<<grid, block, 0, s>>>(b, seed, eps, upd_seed, dev_scale); \
+    if (single_copy) stage_flat_kernel<DT, true, 0><<<grid, block, 0, s>>>(v, seed, eps, 0, nullptr);                   \
+    else if (upd_mode == 0) stage_flat_kernel<DT, false, 0><<<grid, block, 0, s>>>(v, seed, eps, 0, nullptr);           \
+    else if (upd_mode == 1) stage_flat_kernel<DT, false, 1><<<grid, block, 0, s>>>(v, seed, eps, upd_seed, dev_scale);  \
+    else if constexpr (DT != kFP32) stage_flat_kernel<DT, false, 2><<<grid, block, 0, s>>>(v, seed, eps, upd_seed, dev_scale); \
     return hipGetLastError();
-        switch (dtype) {
-        case kFP32: ZO_STAGE(kFP32)
-        case kBF16: ZO_STAGE(kBF16)
-        case kFP16: ZO_STAGE(kFP16)
-        }
+        auto launch = [&](const auto &v) {
+            switch (dtype) {
+            case kFP32: ZO_STAGE(kFP32)
+            case kBF16: ZO_STAGE(kBF16)
+            case kFP16: ZO_STAGE(kFP16)
+            }
+            return hipErrorInvalidValue;
+        };
 #undef ZO_STAGE
-        return hipErrorInvalidValue;
+        // one tensor: no search, and the arguments are the one record (768 x 768 in bf16: 4.6 us with the table of a batch, 4.0 so, with the
+        // update 5.9 / 5.6; 2368 x 2368 9.2 / 8.5 and 12.8 / 12.4)
+        if (b.n > 1) return launch(b);
+        return launch(StageBatchOf<1>{{0}, 1, b.total_tiles, {b.d[0]}});
     }
     // LDS per workgroup of four groups: 58 KiB (16-bit types), 92 KiB (fp32), 34 / 68 KiB for the plain copy
     constexpr int G = kStageThreads / 256;
