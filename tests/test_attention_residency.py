@@ -82,3 +82,44 @@ def test_the_choice_is_about_the_faster_one(plans):
     for (dh, seq, pairs, fewer, full), (per_cu, *_) in zip(MEASURED, got):
         # 2 % and more is what repeated measurements of one size differ by
         assert (full if per_cu == (4 if dh == 64 else 3) else fewer) <= 1.025 * min(fewer, full), (dh, seq, pairs)
+
+
+# d_head, tokens, pairs, us with one workgroup a CU less than there is room for: persistent, a workgroup per item in groups of pairs, the same
+# in one group; the three with all of them (bf16, 256 CUs)
+PLANS = [
+    (64, 1024, 104, (31.6, 32.7, 24.6, 25.1, 25.1, 25.1)),
+    (64, 1024, 128, (32.8, 34.7, 30.1, 27.5, 27.6, 27.6)),
+    (64, 1024, 136, (34.2, 36.9, 31.7, 39.6, 39.6, 30.2)),
+    (64, 1024, 176, (39.9, 42.1, 37.5, 42.5, 44.4, 37.0)),
+    (64, 1024, 256, (51.7, 58.5, 55.1, 53.7, 56.8, 54.2)),
+    (64, 1024, 288, (59.8, 61.6, 62.1, 58.8, 63.3, 61.6)),
+    (64, 1024, 344, (73.5, 73.7, 74.9, 68.6, 73.5, 74.4)),
+    (64, 1024, 464, (94.2, 94.2, 105.2, 96.9, 92.5, 105.6)),
+    (64, 768, 192, (31.4, 32.3, 28.7, 41.3, 34.4, 30.1)),
+    (64, 768, 320, (43.3, 47.7, 45.2, 52.0, 47.5, 44.9)),
+    (64, 768, 464, (63.5, 62.9, 66.9, 64.6, 62.7, 67.0)),
+    (64, 896, 288, (53.2, 52.5, 50.8, 58.4, 53.7, 50.1)),
+    (64, 896, 392, (80.5, 66.2, 70.7, 69.7, 68.1, 70.0)),
+    (64, 1152, 88, (29.7, 29.7, 25.6, 26.0, 26.0, 25.9)),
+    (64, 1152, 320, (98.6, 79.8, 84.9, 86.0, 81.9, 84.3)),
+    (64, 1152, 368, (100.7, 93.5, 98.9, 114.5, 91.4, 98.5)),
+    (64, 1280, 128, (53.9, 45.0, 39.0, 53.4, 49.9, 38.8)),
+    (64, 1408, 264, (118.3, 99.3, 100.5, 100.0, 96.2, 97.5)),
+    (64, 1536, 160, (67.8, 75.3, 65.2, 81.9, 73.0, 63.1)),
+    (64, 1536, 256, (104.7, 103.4, 108.4, 112.6, 108.3, 108.4)),
+    (64, 2048, 200, (141.7, 144.4, 132.3, 147.0, 144.2, 129.0)),
+    (64, 2048, 240, (169.1, 167.0, 167.2, 166.4, 158.5, 167.4)),
+    (64, 2560, 176, (201.6, 183.3, 173.1, 210.6, 175.6, 168.6)),
+    (64, 4096, 112, (280.6, 291.7, 263.9, 280.2, 280.0, 257.8)),
+    (64, 8192, 120, (1173.7, 1145.2, 1143.0, 1140.0, 1119.5, 1105.4)),
+    (64, 8192, 152, (1486.1, 1439.2, 1488.2, 1450.7, 1405.5, 1449.2)),
+]
+
+
+def test_the_plan_over_few_rounds_is_about_the_fastest(plans):
+    got = plans([(seq, 1, pairs, 32, dh) for dh, seq, pairs, _ in PLANS])
+    for (dh, seq, pairs, us), (per_cu, slots, fill, _) in zip(PLANS, got):
+        items, full = pairs // 8 * -(-seq // 128), {64: 4, 80: 3}[dh]
+        shape = 2 if fill == items else 0 if slots == 32 * per_cu else 1
+        # repeated measurements differ by 2 %; lines that hold for every number of tiles cost up to 5 % at some
+        assert us[3 * (per_cu == full) + shape] <= 1.055 * min(us), (dh, seq, pairs)
