@@ -114,6 +114,7 @@ inline AttnPlan attention_plan_64(long long pairs, int n_qt, int cus_xcd)
 // Three a CU: a workgroup per item from the fourth round on (persistent over per item's time, 4 tiles 1.05, 6 tiles, 4 rounds 1.04, 6
 // 1.05; 8 and more only from the sixth: 16 tiles, 4 rounds 0.98, 6 1.03), and all pairs in one group, over few rounds, also where the
 // tiles divide the slots (over persistent's, 16 tiles, 1.3 rounds 1.06, 2 1.02, 2.7 1.03, 6 tiles, 1.1 1.16, 1.6 0.99, 3.1 0.98).
+// Five tiles, groups / one group, us: 29 pairs an XCD (1.5 rounds) 48.5 / 42.1, 36 (1.9) 51.1 / 49.5, 38 (2.0) 52.8 / 54.3.
 inline AttnPlan attention_plan_on(long long pairs, int n_qt, int cus_xcd, int d_head)
 {
     const int full = d_head == 64 ? 4 : d_head == 80 ? 3 : 2, slots = full * cus_xcd, fewer = slots - cus_xcd;
@@ -135,7 +136,7 @@ inline AttnPlan attention_plan_on(long long pairs, int n_qt, int cus_xcd, int d_
     const bool per_item = slots % n_qt != 0 || few || (n_qt >= 3 && items >= rounds * slots);
     if (!per_item) return {slots, slots, full};
     const long long in_slots = slots / n_qt > 1 ? slots / n_qt : 1;
-    const bool one_group = few || 2 * items <= (n_qt >= 8 ? 6 : 3) * (long long)slots;
+    const bool one_group = few || (n_qt >= 8 ? items <= 3 * slots : 8 * items <= 15 * slots);
     const long long group = one_group ? pairs_xcd : in_slots;
     return {(int)((pairs_xcd + group - 1) / group * group * n_qt), one_group ? (int)items : slots, full};
 }

@@ -113,6 +113,11 @@ PLANS = [
     (64, 4096, 112, (280.6, 291.7, 263.9, 280.2, 280.0, 257.8)),
     (64, 8192, 120, (1173.7, 1145.2, 1143.0, 1140.0, 1119.5, 1105.4)),
     (64, 8192, 152, (1486.1, 1439.2, 1488.2, 1450.7, 1405.5, 1449.2)),
+    (80, 640, 160, (39.3, 32.7, 31.1, 42.4, 32.4, 27.9)),
+    (80, 640, 232, (44.8, 44.0, 46.3, 47.2, 48.5, 42.1)),
+    (80, 640, 288, (51.8, 48.1, 55.0, 55.3, 51.1, 49.5)),
+    (80, 640, 304, (52.0, 54.5, 57.4, 56.0, 52.8, 54.3)),
+    (80, 640, 416, (75.2, 70.4, 77.3, 72.4, 68.2, 73.0)),
 ]
 
 
