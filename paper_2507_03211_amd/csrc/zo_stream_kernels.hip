@@ -344,9 +344,10 @@ constexpr int kStageThreads = ZO_STAGE_THREADS;       // groups of 256 threads, 
 // persistent loop each group takes one tile (group g of workgroup w: tiles (w + i gridDim.x) G + g).  A transposing
 // tile goes through the group's LDS buffer one sign at a time (W+ out, then W-), which halves the buffer and lets
 // two 1024-thread workgroups, all 32 wave slots, share a CU next to the 24 KiB table.  The barriers of a round are
-// the same for every group whether it has a tile or not.
+// the same for every group whether it has a tile or not.  One tensor a launch: its record alone is the argument (bf16, 768 x 768,
+// 7.08 us with the table of a batch, 6.93 so, with the update 10.42 / 9.80; 2368 x 2368 13.15 / 12.9 and 19.5 / 18.4).
 template <int DT, bool SINGLE, int UPD>
-__global__ __launch_bounds__(kStageThreads) __attribute__((amdgpu_waves_per_eu((DT != kFP32 && UPD != 2) ? 8 : 4))) void stage_kernel(StageBatch batch, uint64_t seed, float eps, uint64_t upd_seed,
+__global__ __launch_bounds__(kStageThreads) __attribute__((amdgpu_waves_per_eu((DT != kFP32 && UPD != 2) ? 8 : 4))) void stage_kernel(StageBatchOf<1> batch, uint64_t seed, float eps, uint64_t upd_seed,
                                                               const float *__restrict__ dev_scale)
 {
     using W = typename Prec<DT>::W;
@@ -370,11 +371,10 @@ __global__ __launch_bounds__(kStageThreads) __attribute__((amdgpu_waves_per_eu((
     for (uint32_t blk0 = blockIdx.x * G; blk0 < batch.total_tiles; blk0 += gridDim.x * G) {
         const uint32_t blk = blk0 + (uint32_t)grp;
         const bool active = blk < batch.total_tiles;
-        int di = 0;
-        for (int i = 1; i < batch.n; ++i)
-            if (batch.first[i] <= blk) di = i;
+        int di = 0;                               // read anew for each tile: held in registers over the loop, the record costs spills
+        asm("" : "+s"(di));
         const StageDesc &d = batch.d[di];
-        const uint32_t tile = blk - batch.first[di];
+        const uint32_t tile = blk;
         W *const theta = (W *)const_cast<void *>(d.src);      // written only when UPD != 0
         const W *src = theta;
         W *__restrict__ dp = (W *)d.dst_plus;
@@ -789,10 +789,11 @@ hipError_t launch_stage(const StageBatch &b, int dtype, uint64_t seed, float eps
     if (b.total_tiles == 0) return hipSuccess;
     if (upd_mode < 0 || upd_mode > 2 || (upd_mode != 0 && (single_copy || !dev_scale)) || (upd_mode == 2 && dtype == kFP32))
         return hipErrorInvalidValue;
-    // tensors that keep their layout and tensors to transpose take different kernels; no caller mixes them in a batch
+    // tensors that keep their layout and tensors to transpose take different kernels; these come one at a time
     int n_tr = 0;
     for (int i = 0; i < b.n; ++i) n_tr += b.d[i].transpose != 0;
-    if (n_tr != 0 && n_tr != b.n) return hipErrorInvalidValue;
+    if (n_tr != 0 && b.n != 1) return hipErrorInvalidValue;
+    const StageBatchOf<1> one{{0}, 1, b.total_tiles, {b.d[0]}};
     unsigned g = 0;
     if (n_tr == 0) {
         // registers allow four workgroups per CU for the plain 16-bit pass, three with the update folded in, two in fp32
@@ -817,17 +818,17 @@ hipError_t launch_stage(const StageBatch &b, int dtype, uint64_t seed, float eps
         // one tensor: no search, and the arguments are the one record (768 x 768 in bf16: 4.6 us with the table of a batch, 4.0 so, with the
         // update 5.9 / 5.6; 2368 x 2368 9.2 / 8.5 and 12.8 / 12.4)
         if (b.n > 1) return launch(b);
-        return launch(StageBatchOf<1>{{0}, 1, b.total_tiles, {b.d[0]}});
+        return launch(one);
     }
     // LDS per workgroup of four groups: 58 KiB (16-bit types), 92 KiB (fp32), 34 / 68 KiB for the plain copy
     constexpr int G = kStageThreads / 256;
     if (hipError_t e = persistent_grid((b.total_tiles + G - 1) / G, dtype == kFP32 ? 1 : ZO_STAGE_PER_CU, &g); e != hipSuccess) return e;
     const dim3 grid(g), block(kStageThreads);
 #define ZO_STAGE(DT)                                                                                              \
-    if (single_copy) stage_kernel<DT, true, 0><<<grid, block, 0, s>>>(b, seed, eps, 0, nullptr);                   \
-    else if (upd_mode == 0) stage_kernel<DT, false, 0><<<grid, block, 0, s>>>(b, seed, eps, 0, nullptr);           \
-    else if (upd_mode == 1) stage_kernel<DT, false, 1><<<grid, block, 0, s>>>(b, seed, eps, upd_seed, dev_scale);  \
-    else if constexpr (DT != kFP32) stage_kernel<DT, false, 2><<<grid, block, 0, s>>>(b, seed, eps, upd_seed, dev_scale); \
+    if (single_copy) stage_kernel<DT, true, 0><<<grid, block, 0, s>>>(one, seed, eps, 0, nullptr);                   \
+    else if (upd_mode == 0) stage_kernel<DT, false, 0><<<grid, block, 0, s>>>(one, seed, eps, 0, nullptr);           \
+    else if (upd_mode == 1) stage_kernel<DT, false, 1><<<grid, block, 0, s>>>(one, seed, eps, upd_seed, dev_scale);  \
+    else if constexpr (DT != kFP32) stage_kernel<DT, false, 2><<<grid, block, 0, s>>>(one, seed, eps, upd_seed, dev_scale); \
     return hipGetLastError();
     switch (dtype) {
     case kFP32: ZO_STAGE(kFP32)
