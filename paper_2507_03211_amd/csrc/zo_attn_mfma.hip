@@ -513,17 +513,23 @@ __global__ __launch_bounds__(256, kAttnPerCu<DH>) void attn_mfma_kernel(const ui
         }
 
         // Head sizes that ran on the plain kernel before this one took them keep its answer where a later token's value
-        // is not finite (64 and 128 have always multiplied it with zero here): 20 instructions per work item.
+        // is not finite (64 and 128 have always multiplied it with zero here): 20 instructions per work item.  And where the
+        // scores are so large that rounding the reference moves it by places: the key that set it has a probability of 2^kShift,
+        // so a normaliser below that means that they sank, below what fp16 holds from 2^29 on (scaled scores) and to nothing
+        // from 2^31.  (Upwards they overflow, and the row is not finite.)
+        float inv = 1.0f / l_run;
         if constexpr (kRedo) {
+            constexpr float least = kHalf ? 128.0f : 5.42101086e-20f;     // 2^(kShift - 4); 2^-64
+            if (!(l_run >= least)) inv = __builtin_nanf("");
             float probe = 0.0f;                                  // x times 0 is 0 for every finite x
 #pragma unroll
             for (int c = 0; c < CT; ++c)
 #pragma unroll
                 for (int i = 0; i < 16; ++i)
                     if (c * 32 + 8 * (i >> 2) < DH) probe = __builtin_fmaf(oacc[c][i], 0.0f, probe);
-            if (__builtin_amdgcn_ballot_w64(qrow < seq && !(probe == 0.0f)) != 0) again |= 1ull << (round & 63);
+            if (__builtin_amdgcn_ballot_w64(qrow < seq && !(probe == 0.0f && l_run >= least)) != 0) again |= 1ull << (round & 63);
         }
-        store_row(1.0f / l_run);
+        store_row(inv);
     }
     // The rows that came out not finite, once more the plain way, after all items: nothing of the loop above is live any
     // more, and a register that this needs is not missing there.  A lane finds its half of its row's state in what it has stored

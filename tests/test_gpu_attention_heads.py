@@ -178,3 +178,24 @@ def test_many_sequences_of_a_few_tokens(dtype, dh, n_seq, seq, heads, plain):
         flat = torch.empty(qkv.numel() + 1, device=DEV, dtype=qkv.dtype)
         off = flat[1:].view_as(qkv).copy_(qkv)
         assert np.array_equal(got, _run(off, n_seq, seq, heads, dh, dtype))
+
+
+# Scaled scores of 2^e and their neighbours a 64th apart: far enough that a row is the value of its largest key (or the mean of equal
+# ones), and exact in fp32: equal channels of 7 bits, so that every partial sum has 14.
+@pytest.mark.parametrize("dh", [80, 96, 112])
+@pytest.mark.parametrize("dtype,e", [(zi.FP16, e) for e in (16, 24, 28, 29, 30, 31, 32)] + [(zi.BF16, e) for e in (24, 29, 30, 31, 32, 33, 40, 60)])
+def test_scores_whose_reference_is_rounded_by_more_than_they_differ(dh, dtype, e):
+    n_seq, seq, heads = 2, 100, 3
+    sc = 1.4426950408889634 / dh ** 0.5
+    a = int(np.round((e - np.log2(sc * dh)) / 2))                          # 2^a per channel of q, 2^b (1 .. 2) per channel of k
+    b = int(np.round(e - np.log2(sc * dh))) - a
+    qkv = torch.randn(n_seq, seq, 3, heads, dh, device=DEV, generator=torch.Generator(device=DEV).manual_seed(dh + e))
+    j = torch.arange(n_seq * seq * heads, device=DEV).reshape(n_seq, seq, heads, 1)
+    qkv[:, :, 0] = 2.0 ** a
+    qkv[:, :, 1] = 2.0 ** b * (1 + (j * 37 % 64) / 64.0)
+    qkv = qkv.to(TDT[dtype]).reshape(n_seq * seq, 3 * heads * dh)
+    out = torch.empty(n_seq * seq, heads * dh, device=DEV, dtype=TDT[dtype])
+    zo_amd.zo_kernel_attention(qkv, out, dtype, n_seq, seq, heads, dh)
+    want = _oracle(qkv, n_seq, seq, heads, dh)
+    # e = 16: differences of 2^10 and more, so weights of 1 (of equal parts of it) throughout; one rounding of the output
+    assert np.max(np.abs(out.double().cpu().numpy().reshape(want.shape) - want)) < ULP[dtype] * (1 + np.abs(want).max())
