@@ -303,7 +303,10 @@ int zo_kernel_layernorm_pm(const void *resid, const void *g_plus, const void *g_
  * simply more sequences): qkv [n_seq * seq, 3 d] (q | k | v, heads contiguous inside each)
  * -> out [n_seq * seq, d], softmax(q k^T / sqrt(d_head)) v per (sequence, head).
  * The matrix path (16-bit types, d_head 64, 80, 96, 112, 128) wants qkv and out on 16-byte boundaries; anything else runs
- * on a slower kernel that keeps a row's scores in LDS, and a sequence too long for that is refused. */
+ * on a slower kernel that keeps a row's scores in LDS, and a sequence too long for that is refused.
+ * The matrix path exponentiates scaled scores (q . k log2(e) / sqrt(d_head)) against a rounded reference.  Heads of 64 and
+ * 128 hold while these stay below 2^26 (ZO_FP16) or 2^30 (ZO_BF16); beyond, the rounding outgrows the type, and rows can
+ * come out not finite or, in fp16, as zeros.  Heads of 80 to 112 work such rows again another way, whatever the score. */
 int zo_kernel_attention(const void *qkv, void *out, int dtype, int n_seq, int seq, int n_heads,
                         int d_head, void *stream);
 

@@ -182,20 +182,35 @@ def test_many_sequences_of_a_few_tokens(dtype, dh, n_seq, seq, heads, plain):
 
 # Scaled scores of 2^e and their neighbours a 64th apart: far enough that a row is the value of its largest key (or the mean of equal
 # ones), and exact in fp32: equal channels of 7 bits, so that every partial sum has 14.
-@pytest.mark.parametrize("dh", [80, 96, 112])
-@pytest.mark.parametrize("dtype,e", [(zi.FP16, e) for e in (16, 24, 28, 29, 30, 31, 32)] + [(zi.BF16, e) for e in (24, 29, 30, 31, 32, 33, 40, 60)])
-def test_scores_whose_reference_is_rounded_by_more_than_they_differ(dh, dtype, e):
-    n_seq, seq, heads = 2, 100, 3
+def _far(n_seq, seq, heads, dh, dtype, e, seed):
     sc = 1.4426950408889634 / dh ** 0.5
     a = int(np.round((e - np.log2(sc * dh)) / 2))                          # 2^a per channel of q, 2^b (1 .. 2) per channel of k
     b = int(np.round(e - np.log2(sc * dh))) - a
-    qkv = torch.randn(n_seq, seq, 3, heads, dh, device=DEV, generator=torch.Generator(device=DEV).manual_seed(dh + e))
+    qkv = torch.randn(n_seq, seq, 3, heads, dh, device=DEV, generator=torch.Generator(device=DEV).manual_seed(seed))
     j = torch.arange(n_seq * seq * heads, device=DEV).reshape(n_seq, seq, heads, 1)
     qkv[:, :, 0] = 2.0 ** a
     qkv[:, :, 1] = 2.0 ** b * (1 + (j * 37 % 64) / 64.0)
-    qkv = qkv.to(TDT[dtype]).reshape(n_seq * seq, 3 * heads * dh)
-    out = torch.empty(n_seq * seq, heads * dh, device=DEV, dtype=TDT[dtype])
-    zo_amd.zo_kernel_attention(qkv, out, dtype, n_seq, seq, heads, dh)
-    want = _oracle(qkv, n_seq, seq, heads, dh)
+    return qkv.to(TDT[dtype]).reshape(n_seq * seq, 3 * heads * dh)
+
+
+# Heads of 64 and 128: up to where the header says that they hold.
+@pytest.mark.parametrize("dh,dtype,e", [(dh, zi.FP16, e) for dh in (80, 96, 112) for e in (16, 24, 27, 28, 29, 30, 31, 32)] +
+                         [(dh, zi.BF16, e) for dh in (80, 96, 112) for e in (24, 29, 30, 31, 32, 33, 40, 60)] +
+                         [(dh, zi.FP16, e) for dh in (64, 128) for e in (16, 24, 25)] + [(dh, zi.BF16, e) for dh in (64, 128) for e in (24, 28, 29)])
+def test_scores_whose_reference_is_rounded_by_more_than_they_differ(dh, dtype, e):
+    qkv = _far(2, 100, 3, dh, dtype, e, dh + e)
+    want = _oracle(qkv, 2, 100, 3, dh)
     # e = 16: differences of 2^10 and more, so weights of 1 (of equal parts of it) throughout; one rounding of the output
-    assert np.max(np.abs(out.double().cpu().numpy().reshape(want.shape) - want)) < ULP[dtype] * (1 + np.abs(want).max())
+    assert np.max(np.abs(_run(qkv, 2, 100, 3, dh, dtype) - want)) < ULP[dtype] * (1 + np.abs(want).max())
+
+
+@pytest.mark.parametrize("dtype", [zi.BF16, zi.FP16])
+@pytest.mark.parametrize("dh", [80, 112])
+def test_such_sequences_among_others_over_several_rounds(dh, dtype):
+    n_seq, seq, heads = 24, 70, 40                                          # 120 items an XCD: a workgroup works two
+    qkv = _qkv(n_seq, seq, heads, dh, dtype, dh).reshape(n_seq, seq, -1)
+    qkv[3::5] = _far(n_seq, seq, heads, dh, dtype, 31, dh).reshape(n_seq, seq, -1)[3::5]
+    qkv = qkv.reshape(n_seq * seq, -1)
+    got, want = _run(qkv, n_seq, seq, heads, dh, dtype), _oracle(qkv, n_seq, seq, heads, dh)
+    # three roundings (probabilities, values' product, output) on the output's scale
+    assert np.max(np.abs(got - want)) < 3 * ULP[dtype] * (1 + np.abs(want).max())
