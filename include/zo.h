@@ -120,7 +120,8 @@ int zo_perturb(zo_model *m, uint64_t seed, float scale, int first_tensor, int n_
  *                 +eps (theta returns to within rounding).  ZO_RESIDENT only.
  *   dev_loss_pm   device, double[2], receives (l+, l-); may be NULL
  *   host_loss_pm  host, double[2]; if non-NULL the call waits for the result
- * A token id outside [0, vocab) makes both losses NaN. */
+ * A token id outside [0, vocab) makes both losses NaN.  For one batch and seq the losses are the same bits every time; those of
+ * another batch, or of the other mode, may differ by the rounding of sums whose order depends on how many rows run together. */
 int zo_dual_forward(zo_model *m, const int32_t *tokens, int batch, int seq, uint64_t seed,
                     float eps, int mode, double *dev_loss_pm, double *host_loss_pm);
 
@@ -282,7 +283,9 @@ int zo_kernel_stage_update_pm(void *theta, void *w_plus, void *w_minus, int dtyp
  *            1: y = relu(acc + b)
  *            2: resid += acc + b             (y = resid: fp32, or fp64 for ZO_FP32)
  *            3: y = acc                      (fp32 out, or fp64 for ZO_FP32; bias ignored)
- * 2-byte dtypes: n and k multiples of 8 and every buffer 16-byte aligned (ZO_EINVAL otherwise). */
+ * 2-byte dtypes: n and k multiples of 8 and every buffer 16-byte aligned (ZO_EINVAL otherwise).  They add the k terms of an
+ * element in an order that is fixed for a shape and device, but not the same for all shapes: with few rows four waves share
+ * them, so a row's last bits can depend on how many rows are in the call. */
 int zo_kernel_linear_pm(const void *x, const void *wt_plus, const void *wt_minus,
                         const void *b_plus, const void *b_minus, void *y,
                         int dtype, int m_half, int n, int k, int epilogue, void *stream);

@@ -732,6 +732,8 @@ __global__ __launch_bounds__(256, 2) void linear_mfma_small_kernel(
 // partial sums meet in LDS, in a fixed order.  For shapes whose tiles leave most CUs idle at 64 x 64: four times as many take part, a
 // CU loads half as much a slab, and the chain of slabs is a fourth as long.  What bounds it is a CU's loads: 32 KB of lines under way at
 // most, 55 B/ns from far memory and 110 from the L2.  Two stages are as fast as three (a second workgroup fits besides).
+// The other tilings add up a contraction slab by slab; here every fourth slab, then the four sums.  The error is no larger, but a row's last
+// bits depend on which tiling its launch takes, and so on how many rows and signs share the launch.
 // Both signs of m_half x n x k, us, operands far / near, 64 x 64 tiles -> here: 96 x 1024 x 4096 20.7 / 15.5 -> 12.2 / 7.1, 213 x 576 x
 // 2304 11.3 / 10.0 -> 7.0 / 5.4, 68 x 384 x 1536 8.6 / 7.6 -> 5.4 / 4.5, 213 x 576 x 576 5.6 / 4.9 -> 4.3 / 3.7.
 constexpr int kSplitStages = 2, kSplitBytes = 4 * kSplitStages * 64 * BK * 2;
@@ -935,10 +937,13 @@ template <int DT, int EPI> hipError_t launch_tile(Tile t, const Args &a)
     }
 }
 
-// Do the 32 x 32 tiles get a CU each?  From five slabs on, where each wave has one at least, they are then faster than any other
-// shape: 1.52 times in the geometric mean over 159 shapes (24 - 870 rows a sign, n 80 - 5120, k 320 - 14592, all epilogues), 1.19 at
-// least, 2.0 at most.  Two to four slabs would gain 0.3 - 0.6 us of a launch's 3.5; with 2.0 tiles a CU (250 x 1024 x 4096) the gain is
-// 1.14, with 3.2 (536 x 768 x 3072) 0.78.
+// Do the 32 x 32 tiles get a CU each, and five slabs at least?  They are then faster than any other shape: over 159 shapes (24 - 870 rows
+// a sign, n 80 - 5120, k 320 - 14592, all epilogues) 1.52 times in the geometric mean, 1.19 at least, operands far; over 30 others
+// far 1.57 (1.18 - 2.05), near 1.74 (1.20 - 2.49).
+// The line is short of where they stop gaining.  From one to two tiles a CU they gain 1.12 far, 1.18 near in the mean (39 shapes), up to
+// 1.26 and 1.33, but lose up to 8 and 12 % where a sign has few rows and many columns (28 x 4944 x 5248 28.1 -> 30.5 us, 25 x 4544 x 384
+// 4.7 -> 4.9); past two they lose (536 x 512 x 2048 12.7 -> 13.1, 642 x 400 x 9280 39.9 -> 47.3).  With two to four slabs they gain 1.15
+// (1.07 - 1.27, 0.3 - 0.6 us of a launch's 3.5; 30 shapes of up to a tile a CU).  Both are left to 64 x 64 tiles, with the bits they have there.
 bool one_small_tile_a_cu(int n_sign, int m_half, int n, int k)
 {
     const long tiles = (long)n_sign * ((m_half + 31) / 32) * ((n + 31) / 32);
