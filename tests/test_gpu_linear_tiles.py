@@ -1,5 +1,5 @@
 """The sign-batched linear layer over every tile shape its size rule picks (256 x 256, 256 x 192, 256 x 128, 192 x 128,
-128 x 128, 64 x 64): one row past a tile, ragged columns, contractions of one slab and up, each epilogue, both 16-bit types;
+128 x 128, 64 x 64, 32 x 32): one row past a tile, ragged columns, contractions of one slab and up, each epilogue, both 16-bit types;
 and the LM head over each of its tile heights and strip widths.  Every output element is compared."""
 import pytest
 import torch
@@ -19,12 +19,13 @@ SHAPES16 = [(3073, 4104, 192), (1537, 4104, 448),       # 256 x 256
             (641, 4104, 192), (1281, 2056, 192),        # 256 x 128
             (385, 5128, 256), (641, 3080, 256),         # 192 x 128
             (257, 5128, 320), (641, 1544, 320),         # 128 x 128
-            (1, 8, 64), (65, 72, 128), (257, 520, 192), (100, 1000, 1024)]   # 64 x 64
+            (1, 8, 64), (65, 72, 128), (257, 520, 192), (100, 1000, 1024),   # 64 x 64, the last 32 x 32
+            (257, 520, 704), (129, 1032, 1024)]                              # 64 x 64
 SHAPES32 = [(2561, 8200, 1024), (1025, 6152, 1024),     # 256 x 256; 128 x 128 and, without residual, 256 x 256
             (1281, 4104, 1024), (641, 5128, 2048),      # 192 x 128, 256 x 128
             (641, 3080, 768), (1281, 1544, 576),        # 192 x 128
             (385, 2568, 576), (641, 1544, 448),         # 64 x 64 and, without residual, 128 x 128
-            (3, 16, 64), (64, 64, 64), (130, 520, 320)] # 64 x 64
+            (3, 16, 64), (64, 64, 64), (130, 520, 320)] # 64 x 64, the last 32 x 32
 # LM head: rows a sign, d, vocabulary of each tile; its edges one row or 8 columns past where the rule allows it
 HEADS = [((256, 256), 193, 320, 20008), ((256, 256), 769, 192, 20232), ((192, 256), 257, 192, 17000), ((192, 256), 385, 256, 8200),
          ((128, 256), 100, 320, 17000), ((128, 256), 300, 256, 17000), ((128, 256), 1, 256, 20232), ((128, 128), 65, 512, 1000),
@@ -32,7 +33,7 @@ HEADS = [((256, 256), 193, 320, 20008), ((256, 256), 769, 192, 20232), ((192, 25
 # one row and 8 columns past whole tiles of the named shape: 16-bit outputs, fp32 outputs
 TILES = {(256, 256): [(1537, 4104, 448), (1537, 4104, 1024)], (256, 192): [(1281, 3080, 192), (1281, 3080, 2048)],
          (256, 128): [(1281, 2056, 192), (1025, 3080, 2048)], (192, 128): [(385, 5128, 256), (769, 2568, 768)],
-         (128, 128): [(257, 5128, 320), (513, 3080, 768)], (64, 64): [(257, 520, 192), (257, 520, 320)]}
+         (128, 128): [(257, 5128, 320), (513, 3080, 768)], (64, 64): [(257, 520, 704), (257, 520, 320)]}
 
 
 def _inputs(m_half, n, k, dtype, seed):
@@ -154,5 +155,16 @@ def test_lmhead_of_large_logits_with_full_mantissas(m_half, d, vocab, sign):
 @pytest.mark.parametrize("slabs", [1, 2, 3, 4, 5])
 def test_small_tile_of_few_slabs(m_half, n, slabs, epi, dtype):
     # 64 x 64 tiles: a ring of as many stages as there are slabs, up to four; rows of whole cache lines and others, whose
-    # 16-bit outputs of one or two slabs are stored another way
+    # 16-bit outputs of one or two slabs are stored another way; five slabs take 32 x 32 tiles
+    assert zo_amd.zo_kernel_linear_tile(m_half, n, 64 * slabs, epi) == ((64, 64) if slabs < 5 else (32, 32))
     test_linear_tiles(m_half, n, 64 * slabs, epi, dtype)
+
+
+@pytest.mark.parametrize("dtype", [zi.BF16, zi.FP16])
+@pytest.mark.parametrize("epi", [0, 1, 2, 3])
+@pytest.mark.parametrize("m_half,n,k", [(129, 1032, 320), (193, 776, 448), (257, 520, 576), (161, 1000, 1024)])
+def test_small_tile_whose_ring_comes_round(m_half, n, k, epi, dtype):
+    # 64 x 64 tiles of more slabs than their ring has stages: its first stage again once (5 slabs), all but one of them (7), two rounds
+    # and one (9), whole rounds (16); one row past a tile of 32 or 64, ragged columns
+    assert zo_amd.zo_kernel_linear_tile(m_half, n, k, epi) == (64, 64)
+    test_linear_tiles(m_half, n, k, epi, dtype)
