@@ -128,3 +128,14 @@ def test_the_plan_over_few_rounds_is_about_the_fastest(plans):
         shape = 2 if fill == items else 0 if slots == 32 * per_cu else 1
         # repeated measurements differ by 2 %; lines that hold for every number of tiles cost up to 5 % at some
         assert us[3 * (per_cu == full) + shape] <= 1.055 * min(us), (dh, seq, pairs)
+
+
+def test_the_gpu_tests_cases_take_the_plans_they_are_there_for(plans):
+    import test_gpu_attention_items as items
+    import test_gpu_attention_residency as residency
+    cases = items.CASES + residency.CASES
+    for case, (per_cu, slots, fill, _) in zip(cases, plans([(seq, heads, n_seq, 32, dh) for n_seq, seq, heads, dh, *_ in cases])):
+        n_seq, seq, heads, dh, want_cu, want = case
+        count = -(-n_seq * heads // 8) * -(-seq // 128)
+        kind = "all" if count <= 32 * per_cu else "one" if fill == count else "persistent" if slots == 32 * per_cu else "groups"
+        assert (per_cu, kind) == (want_cu, want), case

@@ -36,11 +36,14 @@ def _check(out, qkv, n_seq, seq, heads, dh, dtype):
     assert np.max(np.abs(out.double().cpu().numpy() - want)) < 3 * ULP[dtype] * (1 + np.abs(want).max())
 
 
-# 8 XCDs hold 96 workgroups each with heads of 64, 64 otherwise; items of 128 rows, (sequence, head) pairs dealt to the XCDs.  All pairs in
-# one group, but for the second (four rounds), the last two (1.6 rounds; two whole groups)
+# Items of 128 rows, (sequence, head) pairs dealt to 8 XCDs; more items than an XCD holds at once in all of them (test_attention_residency.py
+# asks for the plan): in groups of pairs, or all pairs in one group; the last one two whole groups
+CASES = [(14, 600, 16, 64, 3, "one"), (32, 331, 32, 64, 3, "groups"), (7, 300, 31, 128, 2, "one"), (6, 257, 45, 80, 2, "groups"), (3, 1300, 16, 128, 2, "one"),
+         (10, 600, 16, 128, 2, "groups"), (5, 1408, 16, 128, 2, "groups")]
+
+
 @pytest.mark.parametrize("dtype", [zi.BF16, zi.FP16])
-@pytest.mark.parametrize("n_seq,seq,heads,dh", [(10, 600, 16, 64), (32, 331, 32, 64), (7, 300, 31, 128), (4, 257, 45, 80), (3, 1300, 16, 128), (10, 600, 16, 128),
-                                               (5, 1408, 16, 128)])
+@pytest.mark.parametrize("n_seq,seq,heads,dh", [c[:4] for c in CASES])
 def test_a_workgroup_per_item_gives_the_bits_of_persistent_ones(dtype, n_seq, seq, heads, dh):
     qkv = _qkv(n_seq, seq, heads, dh, dtype, seq)
     out = _run(qkv, n_seq, seq, heads, dh, dtype)

@@ -1,5 +1,5 @@
-"""Causal attention, heads of 64 and 80 channels, on either side of the sizes where the number of workgroups a CU changes: every
-sequence has the bits it gets alone, where all of its items are under way at once, and those match the oracle."""
+"""Causal attention, heads of 64 and 80 channels, on either side of the sizes where the number of workgroups a CU or the way through the list
+changes: every sequence has the bits it gets alone, where all of its items are under way at once, and those match the oracle."""
 import pytest
 import torch
 
@@ -9,12 +9,16 @@ from test_gpu_attention_items import _check, _qkv, _run
 pytestmark = pytest.mark.gpu
 
 
-# 64: short sequences that fit at once with four workgroups a CU and just don't (one tile each), from 6 tiles on, one group over 1.5 rounds of 16
-# tiles; 80: all at once with three a CU, a second round that two a CU need too, rounds that favour three, 6 tiles over a little more than a
-# round, 10 tiles that two a CU hold in two rounds
+# sequences, tokens, heads, channels; the plan on 32 CUs an XCD (test_attention_residency.py asks for it): workgroups a CU, and "all" items at
+# once, "persistent" workgroups, a workgroup per item with the pairs in "groups" or in "one" group
+CASES = [(32, 70, 32, 64, 4, "all"), (33, 70, 32, 64, 3, "persistent"), (13, 1000, 8, 64, 3, "one"), (9, 641, 24, 64, 4, "one"), (12, 1921, 8, 64, 4, "one"),
+         (40, 700, 8, 64, 3, "persistent"), (33, 1000, 8, 64, 4, "persistent"), (46, 800, 8, 64, 3, "groups"), (67, 700, 8, 64, 4, "groups"),
+         (24, 70, 32, 80, 3, "all"), (25, 70, 32, 80, 2, "persistent"), (8, 300, 50, 80, 3, "persistent"), (9, 700, 16, 80, 3, "one"), (37, 600, 8, 80, 3, "groups"),
+         (4, 1211, 16, 80, 2, "one")]
+
+
 @pytest.mark.parametrize("dtype", [zi.BF16, zi.FP16])
-@pytest.mark.parametrize("n_seq,seq,heads,dh", [(32, 70, 32, 64), (33, 70, 32, 64), (9, 641, 24, 64), (12, 1921, 8, 64), (24, 70, 32, 80), (25, 70, 32, 80), (8, 300, 50, 80),
-                                               (9, 700, 16, 80), (4, 1211, 16, 80)])
+@pytest.mark.parametrize("n_seq,seq,heads,dh", [c[:4] for c in CASES])
 def test_either_side_of_the_line(dtype, n_seq, seq, heads, dh):
     qkv = _qkv(n_seq, seq, heads, dh, dtype, seq)
     out = _run(qkv, n_seq, seq, heads, dh, dtype)
