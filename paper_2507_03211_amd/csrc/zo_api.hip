@@ -307,7 +307,9 @@ Staged first_staged(zo_model *m) { return {m->ws + m->wsp.stage[0], m->ws + m->w
 // output is there; where that is small (few rows) or the model is large, groups are of one block.  Whole steps, one block a launch / here:
 // 3 layers of 384, 68 rows 196 -> 183 us, 12 of 768, 96 rows 827 -> 770, 16 x 512 rows 5154 -> 5124, 8 of 1024, 8 x 512 rows 3076 -> 3063.
 // The copies have to stay in the 256 MiB of the memory-side cache until the layers read them: two blocks of 1152 (122 MiB) 830 ->
-// 811 and 1437 -> 1427, but two of 1280 (150 MiB) 2497 -> 2535 and two of 1536 (216 MiB) 1434 -> 1551.
+// 811 and 1437 -> 1427, but two of 1280 (150 MiB) 2497 -> 2535 and two of 1536 (216 MiB) 1434 -> 1551.  The rows' own activations pass
+// through that cache too and do not move the line: 8 of 768 with 32768 rows a sign 14549 -> 14518, 8 of 1024 with 16384 10224 -> 10173,
+// 6 of 1152 with 16384 10093 -> 10085, with 8192 5498 -> 5481, with 4096 2990 -> 2982.
 constexpr int kStageGroup = 4;
 constexpr size_t kStageGroupBytes = 128u << 20;
 static_assert(4 + kStageGroup * kPerBlock <= kStageMaxDesc, "the embeddings, the final LayerNorm and a group in one launch");

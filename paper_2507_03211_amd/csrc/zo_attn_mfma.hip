@@ -139,9 +139,11 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // native vector: 
 // Workgroups a CU: four with 64 channels and three with 80, two with more.  A wave waits (for its item's first tiles, for LDS, for
 // its workgroup at a tile's barrier) more than it works, so a further workgroup is worth two K fragments less in flight (a ring of
 // two, 128 registers at 64 channels) and LDS rows without padding (80 channels: 50 KiB a workgroup, 162 registers).  us, a
-// workgroup less / so, all of it: 64 channels, 2048 tokens x 256 (head, sequence) pairs 189 / 174, 277 x 288 17.9 / 14.8; 80, 2048 x
-// 128 166 / 146, 847 x 124 41.7 / 35.4.  Bit for bit the same.  Registers spilled to memory cost more than the workgroup gains (138
-// registers held to 128: 277 x 288 16.5, 512 x 384 32 -> 37).
+// workgroup less / so, launches back to back: 64 channels, 2048 tokens x 256 (head, sequence) pairs 188 / 170, 277 x 288 17.9 / 14.8; 80,
+// 2048 x 128 164.5 / 148.9 (as single calls of a program 162.6 / 156.9), 847 x 128 44.9 / 37.7.  Bit for bit the same.  Registers spilled to
+// memory cost more than the workgroup gains (138 registers held to 128: 277 x 288 16.5, 512 x 384 32 -> 37).  Launches that keep three a CU
+// with 64 channels (zo_attn_items.h) run this instance too, held to three by LDS: one with a ring of four in 138 registers is no
+// faster there (46 sizes of 70 - 640 tokens: 1.001 of its time, 0.993 - 1.011).
 template <int DH> constexpr int kAttnPerCu = DH == 64 ? 4 : DH == 80 ? 3 : 2;
 template <int DT, int DH>
 __global__ __launch_bounds__(256, kAttnPerCu<DH>) void attn_mfma_kernel(const uint16_t *__restrict__ qkv, uint16_t *__restrict__ out, int seq,
@@ -165,13 +167,14 @@ __global__ __launch_bounds__(256, kAttnPerCu<DH>) void attn_mfma_kernel(const ui
     constexpr int KR = DH <= 80 ? 2 : KS % 4 == 0 ? 4 : KS;   // depth of the K fragment ring (it divides 2 KS: a fragment's slot is the same in every other unit)
     // K and V tiles, both [key][channel] as they sit in memory, 16-byte chunks XOR-swizzled per key so that
     // the MFMA fragment reads of K (32 keys, one chunk) and the transposing reads of V (4 keys x 32 bytes
-    // per 16 lanes) are free of conflicts on the 64-bank LDS.
+    // per 16 lanes) are free of conflicts on the 64-bank LDS (but for V's with 80 channels, below).
     // Three K and two V buffers: tiles arrive (global memory straight into LDS) while earlier ones are multiplied.
     __shared__ u32x4 ks3[3][TILE];
     __shared__ u32x4 vs2[2 * TILE + 4 * CT - CH];
     // (pitch 192 bytes: 4 consecutive rows start on 4 different quarters of the 64 banks, which is all the reads of V
     // need; K's 16 rows per read are told apart by the row bits above.  Pitch 160: 8 consecutive rows start on the 8 multiples of
-    // 8 banks, and K's other 8 rows have their chunks swapped in pairs)
+    // 8 banks, and K's other 8 rows have their chunks swapped in pairs; V's second 16 channels meet the first ones of the row three
+    // before on 8 banks, a third of the LDS cycles counted)
     auto kswz = [](int r) { return TIGHT ? ((r >> 3) & 1) : CH == 16 ? (r & 15) : CH == 12 ? ((r >> 2) & 3) : ((r >> 1) & 7); };
     auto vswz = [](int r) { return CH == 16 ? ((r & 3) << 2) : CH == 12 || TIGHT ? 0 : (((r >> 1) & 1) << 2); };
     auto in_row = [](int chunk) { return chunk < CHD ? chunk : chunk - 2; };

@@ -13,8 +13,9 @@ namespace zo {
 
 // ------------------------------------------------------------------ embedding
 // h[row, :] = E_sign[token] + Pos_sign[t];  target[row] = next token (or -1 at t = seq-1).
-// A wavefront a row, four elements a lane and access (d is a multiple of 8, and tables and stream lie on 16 bytes).  Memory bounds it: in a step, 16384 rows of 768, bf16, 28.9 us a workgroup a row and element by element, 22.3 so
-// (4.5 TB/s).
+// A wavefront a row, four elements a lane and access (d is a multiple of 8, and tables and stream lie on 16 bytes).  In a step, 16384
+// rows of 768, bf16, 28.9 us a workgroup a row and element by element, 22.3 so: 3.4 TB/s of what must reach memory (25 MB of token
+// rows, 50 MB of the stream; the position rows stay in the caches), rows scattered by the tokens.
 template <int DT>
 __global__ __launch_bounds__(256) void embed_kernel(const int32_t *__restrict__ tokens, const void *e_p, const void *e_m,
                                                     const void *pos_p, const void *pos_m, void *resid,
